@@ -1,0 +1,265 @@
+"""Workloads the library's speed is measured on.
+
+``listed()`` names the fixed cases, ``draw()`` gives further ones of the same
+ranges; ``prepare()`` makes what a program holds before the call (the loaded
+instance, device points, host literals), ``run()`` is one pass through the
+public entry points, ``work()`` the bytes and operations a pass cannot do
+without and ``exact()`` its result in 64 bits where it has one.
+
+A case's fields: ``call`` (eval, grad, solve, batch or request), ``kind`` of
+the random clauses (uniform: k literals each; mixed: 2 to 4; structured:
+2 + geometric lengths up to 12 over Zipf-distributed variables), ``n``
+variables, ``m`` clauses, ``k``, ``R`` restarts or points, and for solves
+``T`` steps and ``K``, the counting period.
+"""
+import math
+
+import numpy as np
+import torch
+
+import paper_2402_03640_amd as hm
+from paper_2402_03640_amd.autograd import maxsat_loss
+
+
+def _case(name, call, kind, n, m, k=3, R=1, T=0, K=1, weights=False, loss="unsat", optimizer="adam", lr=1e-4,
+          autotune=True, state=False, count=1):
+    return {"name": name, "call": call, "kind": kind, "n": n, "m": m, "k": k, "R": R, "T": T, "K": K,
+            "weights": weights, "loss": loss, "optimizer": optimizer, "lr": lr, "autotune": autotune,
+            "state": state, "count": count}
+
+
+def listed():
+    return [
+        # one point of a small formula: a caller's own search loop, where launches and waits are all the time
+        _case("eval-small", "eval", "uniform", 50, 215),
+        # loss, gradient and counts at 64 points of the benchmark formula: a caller's own optimizer
+        _case("eval-64-points", "eval", "uniform", 20000, 86000, R=64),
+        # the differentiable loss, forward and backward, inside a torch training step on dense 5-CNF
+        _case("grad-5cnf", "grad", "uniform", 12000, 204000, k=5, R=16),
+        # the small benchmark solve: latency of a step, counted every step
+        _case("solve-small", "solve", "uniform", 50, 215, T=1000),
+        # 16 restarts of a mid-small mixed formula, counted every step
+        _case("solve-mixed-16", "solve", "mixed", 1000, 4200, R=16, T=1000),
+        # the benchmark formula with one restart, as a serving request has it
+        _case("solve-one", "solve", "uniform", 20000, 86000, T=2000, K=50),
+        # the headline benchmark: 64 restarts together
+        _case("solve-64", "solve", "uniform", 20000, 86000, R=64, T=2000, K=50),
+        # the largest formula, skewed occurrences, one restart under the untimed schedule
+        _case("solve-structured", "solve", "structured", 500000, 2500000, T=200, K=50, autotune=False),
+        # the same with eight restarts (state past the last-level cache)
+        _case("solve-structured-8", "solve", "structured", 500000, 2500000, R=8, T=200, K=50),
+        # weighted MaxSAT with an odd restart count, a period that does not divide the steps, the state handed back
+        _case("solve-weighted-5", "solve", "mixed", 7919, 33413, R=5, T=390, K=20, weights=True, lr=1e-3, state=True),
+        # a server's group of one-restart requests of uneven size in one call
+        _case("batch-16", "batch", "uniform", 30000, 129000, T=1000, K=50, count=16),
+        # one request from host literals to result: the plan build, the upload and the solve
+        _case("request-4cnf", "request", "uniform", 30000, 255000, k=4, T=1000, K=50, autotune=False),
+    ]
+
+
+def _logint(rng, lo, hi):
+    return int(math.exp(rng.uniform(math.log(lo), math.log(hi + 1))))
+
+
+def draw(rng):
+    call = rng.choice(["eval", "grad", "solve", "solve", "solve", "batch", "request"])
+    kind = rng.choice(["uniform", "uniform", "mixed", "structured"])
+    k = rng.choice([3, 3, 4, 5])
+    n = _logint(rng, 50, 500000 if kind == "structured" else 60000)
+    if kind == "structured":
+        m = int(n * rng.uniform(4.0, 5.0))
+    elif kind == "mixed":
+        m = int(n * rng.uniform(3.5, 5.0))
+    else:
+        m = int(n * rng.uniform(3.5, 5.0) * 2 ** k / 8)
+    per = {"uniform": k, "mixed": 3, "structured": 3.5}[kind]
+    R = 1 if call in ("batch", "request") or rng.random() < 0.4 else _logint(rng, 2, 64)
+    while R > 1 and m * per * R > 6e7:
+        R = (R + 1) // 2
+    K = rng.choice([1, 10, 50, 50])
+    T = _logint(rng, 100, 2000)
+    # no more literal visits than the headline or the largest formula's solves
+    T = max(20, min(T, int(1.5e10 / (m * per * R + 2e6))))
+    count = 1
+    if call == "batch":
+        n = _logint(rng, 200, 60000)
+        m = int(n * (rng.uniform(3.5, 5.0) if kind != "uniform" else rng.uniform(3.5, 5.0) * 2 ** k / 8))
+        count = rng.randint(2, 16)
+        T = max(20, min(T, int(1.5e10 / (m * per * count + 2e6))))
+    solve = call in ("solve", "batch", "request")
+    return {"call": call, "kind": kind, "n": n, "m": m, "k": k, "R": R, "T": T if solve else 0,
+            "K": K if solve else 1, "weights": call == "solve" and rng.random() < 0.25,
+            "loss": "all" if rng.random() < 0.2 else "unsat",
+            "optimizer": "sgd" if solve and rng.random() < 0.1 else "adam", "lr": rng.choice([1e-4, 1e-3, 1e-2]),
+            "autotune": call == "solve" and R > 1, "state": call == "solve" and rng.random() < 0.3, "count": count}
+
+
+# ---- random formulas: DIMACS literals, every clause ended by 0 --------------------------------------
+
+def _pack(lengths, var, neg):
+    """Flat literal array from clause lengths and their variables (0-based) and signs, clause by clause."""
+    ends = np.cumsum(lengths + 1)
+    out = np.zeros(int(ends[-1]) if len(ends) else 0, dtype=np.int32)
+    keep = np.ones(out.size, dtype=bool)
+    keep[ends - 1] = False
+    out[keep] = (var + 1) * np.where(neg, -1, 1)
+    return out
+
+
+def _formula(rng, kind, n, m, k):
+    if kind == "uniform":
+        lengths = np.full(m, k, dtype=np.int64)
+    elif kind == "mixed":
+        lengths = rng.integers(2, 5, size=m)
+    else:
+        lengths = np.minimum(1 + rng.geometric(0.4, size=m), 12).astype(np.int64)
+    clause = np.repeat(np.arange(m), lengths)
+    if kind == "structured":
+        cdf = np.cumsum(np.arange(1, n + 1, dtype=np.float64) ** -1.1)
+        cdf /= cdf[-1]
+        perm = rng.permutation(n)
+
+        def vars_of(count):
+            return perm[np.minimum(np.searchsorted(cdf, rng.random(count), side="right"), n - 1)]
+    else:
+        def vars_of(count):
+            return rng.integers(0, n, size=count)
+    var = vars_of(clause.size)
+    todo = np.arange(clause.size)  # positions of clauses not yet known to hold distinct variables
+    while todo.size:
+        key = clause[todo] * n + var[todo]
+        key = np.sort(key)
+        bad = np.unique(key[1:][key[1:] == key[:-1]] // n)
+        if bad.size == 0:
+            break
+        hit = np.zeros(m, dtype=bool)
+        hit[bad] = True
+        todo = todo[hit[clause[todo]]]
+        var[todo] = vars_of(todo.size)  # a clause with a repeat is drawn again whole
+    neg = rng.random(clause.size) < 0.5
+    return lengths, clause, var, neg
+
+
+def _inputs(case, seed):
+    """Host inputs from the seed alone: the formula, its weights, the points."""
+    rng = np.random.default_rng([int(seed) & 0x7FFFFFFF, case["n"], case["m"], case["R"]])
+    f = _formula(rng, case["kind"], case["n"], case["m"], case["k"])
+    w = None
+    if case["weights"]:
+        w = rng.integers(1, 101, size=case["m"]).astype(np.int64)
+        w[rng.random(case["m"]) < 0.02] = 1 + int(w.sum())  # hard clauses
+    x = None
+    if case["call"] in ("eval", "grad"):
+        x = rng.uniform(-1.0, 1.0, size=(case["n"], case["R"])).astype(np.float32)
+    return f, w, x
+
+
+def _sizes(case, seed):
+    """Sizes of a batch's instances: log-uniform around n, as queued requests are."""
+    rng = np.random.default_rng([int(seed) & 0x7FFFFFFF, 77, case["count"]])
+    s = np.exp(rng.uniform(math.log(0.5), math.log(2.0), size=case["count"]))
+    return [(max(12, int(case["n"] * q)), max(1, int(case["m"] * q))) for q in s]
+
+
+def prepare(case, seed):
+    state = {"case": case, "seed": int(seed) & 0xFFFF}
+    loss = hm.LOSS_ALL if case["loss"] == "all" else hm.LOSS_UNSAT
+    state["solve"] = dict(steps=case["T"], eval_every=case["K"], lr=case["lr"], loss_mode=loss,
+                          optimizer=hm.SGD if case["optimizer"] == "sgd" else hm.ADAM)
+    state["loss"] = loss
+    if case["call"] == "batch":
+        state["cnfs"] = []
+        for i, (n, m) in enumerate(_sizes(case, seed)):
+            rng = np.random.default_rng([int(seed) & 0x7FFFFFFF, n, m, i])
+            lengths, _, var, neg = _formula(rng, case["kind"], n, m, case["k"])
+            state["cnfs"].append(hm.load_cnf(n, _pack(lengths, var, neg)))
+        return state
+    (lengths, _, var, neg), w, x = _inputs(case, seed)
+    lits = _pack(lengths, var, neg)
+    if case["call"] == "request":
+        state["lits"] = lits
+        return state
+    state["cnf"] = hm.load_cnf(case["n"], lits, weights=w)
+    if x is not None:
+        state["x"] = torch.from_numpy(x).cuda()
+        if case["call"] == "grad":
+            state["x"].requires_grad_(True)
+    return state
+
+
+def _outcome(r):
+    return {"cost": r.best_cost, "step": r.best_step, "assignment": r.best_assignment, "restart_best": r.restart_best,
+            "restart_step": r.restart_step, "loss": r.restart_loss, "x": r.x_final}
+
+
+def run(state):
+    case = state["case"]
+    if case["call"] == "eval":
+        loss, grad, unsat = hm.eval_relaxed(state["cnf"], state["x"], loss_mode=state["loss"])
+        return {"loss": loss, "grad": grad, "unsat": unsat}
+    if case["call"] == "grad":
+        x = state["x"]
+        x.grad = None
+        loss, unsat = maxsat_loss(state["cnf"], x, loss_mode=state["loss"])
+        loss.mean().backward()
+        return {"loss": loss.detach(), "grad": x.grad, "unsat": unsat}
+    if case["call"] == "batch":
+        cnfs = state["cnfs"]
+        outs = hm.solve_batch(cnfs, seeds=[state["seed"] + i for i in range(len(cnfs))], want_x=True, **state["solve"])
+        return [_outcome(r) for r in outs]
+    if case["call"] == "request":
+        with hm.load_cnf(case["n"], state["lits"]) as cnf:
+            return _outcome(hm.solve(cnf, seed=state["seed"], autotune=case["autotune"], want_x=True,
+                                     **state["solve"]))
+    r = hm.solve(state["cnf"], restarts=case["R"], seed=state["seed"], autotune=case["autotune"], want_x=True,
+                 want_state=case["state"], **state["solve"])
+    out = _outcome(r)
+    if case["state"]:
+        s = r.state
+        out["state"] = [s.x, s.best_assignment, s.best, s.best_step, s.step]
+        if s.m is not None:
+            out["state"] += [s.m, s.v]
+    return out
+
+
+def work(case):
+    per = {"uniform": case["k"], "mixed": 3.0, "structured": 3.5}[case["kind"]]
+    n, m, R = case["n"] * case["count"], case["m"] * case["count"], case["R"]
+    lits = per * m
+    # per literal and point: one addition into the clause score, one into the variable's sum;
+    # per variable and point: tanh, its derivative and the step, about 30 operations
+    one = R * (2.0 * lits + 3.0 * m + 30.0 * n)
+    read = 4.0 * (lits + m) + (8.0 * m if case["weights"] else 0.0)
+    if case["call"] in ("eval", "grad"):
+        return {"bytes": read + 8.0 * n * R + 16.0 * R, "flops": one}
+    # a solve reads the formula and writes the final points; what lies between need not leave the chip
+    return {"bytes": read + 5.0 * n * R, "flops": one * case["T"]}
+
+
+def exact(case, seed):
+    """Loss, gradient and count in 64 bits; a solve of many steps has no such value (its rounded points decide
+    which clauses count, so the steps part from a 64-bit run)."""
+    if case["call"] not in ("eval", "grad") or case["m"] * case["R"] > 4e7:
+        return None
+    (lengths, clause, var, neg), w, x = _inputs(case, seed)
+    n, m, R = case["n"], case["m"], case["R"]
+    cl, va = torch.from_numpy(clause), torch.from_numpy(var)
+    sg = torch.from_numpy(np.where(neg, -1.0, 1.0))
+    wt = torch.ones(m, dtype=torch.float64) if w is None else torch.from_numpy(w.astype(np.float64))
+    loss = torch.zeros(R, dtype=torch.float64)
+    unsat = torch.zeros(R, dtype=torch.int64)
+    grad = torch.zeros(n, R, dtype=torch.float64)
+    scale = 1.0 if case["call"] == "eval" else 1.0 / R  # the mean over the points
+    for r in range(R):
+        xr = torch.from_numpy(x[:, r].astype(np.float64))
+        t = torch.tanh(xr)
+        score = torch.zeros(m, dtype=torch.float64).index_add_(0, cl, sg * t[va])
+        true = ((xr[va] > 0) == (sg > 0)).to(torch.float64)
+        out = torch.zeros(m, dtype=torch.float64).index_add_(0, cl, true) == 0
+        mask = torch.ones(m, dtype=torch.float64) if case["loss"] == "all" else out.to(torch.float64)
+        loss[r] = (mask * wt * score * score).sum() / m
+        unsat[r] = int((out.to(torch.float64) * wt).sum()) if w is not None else int(out.sum())
+        a = 2.0 / m * mask * wt * score * scale
+        e = torch.exp(-2.0 * xr.abs())
+        grad[:, r] = torch.zeros(n, dtype=torch.float64).index_add_(0, va, sg * a[cl]) * (4.0 * e / (1.0 + e) ** 2)
+    return {"loss": loss, "grad": grad, "unsat": unsat}
