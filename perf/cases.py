@@ -154,9 +154,9 @@ def _inputs(case, seed):
     return f, w, x
 
 
-def _sizes(case, seed):
+def _sizes(case):
     """Sizes of a batch's instances: log-uniform around n, as queued requests are."""
-    rng = np.random.default_rng([int(seed) & 0x7FFFFFFF, 77, case["count"]])
+    rng = np.random.default_rng([case["n"], case["m"], case["count"]])
     s = np.exp(rng.uniform(math.log(0.5), math.log(2.0), size=case["count"]))
     return [(max(12, int(case["n"] * q)), max(1, int(case["m"] * q))) for q in s]
 
@@ -169,7 +169,7 @@ def prepare(case, seed):
     state["loss"] = loss
     if case["call"] == "batch":
         state["cnfs"] = []
-        for i, (n, m) in enumerate(_sizes(case, seed)):
+        for i, (n, m) in enumerate(_sizes(case)):
             rng = np.random.default_rng([int(seed) & 0x7FFFFFFF, n, m, i])
             lengths, _, var, neg = _formula(rng, case["kind"], n, m, case["k"])
             state["cnfs"].append(hm.load_cnf(n, _pack(lengths, var, neg)))
@@ -206,7 +206,9 @@ def run(state):
     if case["call"] == "batch":
         cnfs = state["cnfs"]
         outs = hm.solve_batch(cnfs, seeds=[state["seed"] + i for i in range(len(cnfs))], want_x=True, **state["solve"])
-        return [_outcome(r) for r in outs]
+        return {"cost": np.array([r.best_cost for r in outs]), "step": np.array([r.best_step for r in outs]),
+                "loss": np.array([r.final_loss for r in outs]),
+                "assignment": np.concatenate([r.best_assignment for r in outs]), "x": [r.x_final for r in outs]}
     if case["call"] == "request":
         with hm.load_cnf(case["n"], state["lits"]) as cnf:
             return _outcome(hm.solve(cnf, seed=state["seed"], autotune=case["autotune"], want_x=True,
