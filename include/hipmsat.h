@@ -166,7 +166,11 @@ typedef struct {
                             restart count, optimizer and loss mode, and keep the fastest
                             (small instances skip the timing); 0 = take the resident solver
                             (255) when the state fits it and nnz <= 2^15 (2^16 with K = 1),
-                            else a fixed tiled schedule for R */
+                            else a fixed tiled schedule for R.  Either way a solve of 64 steps
+                            or more that the cluster solver (254: a few workgroups of one XCD
+                            per restart, unsat-masked loss, clauses of at most five literals,
+                            at most about 32000 variables, no split rows) can run and is known
+                            to run faster takes it without timing */
     double time_limit_s; /* > 0: stop at a K-step boundary once exceeded (not reproducible) */
     const float* x0;     /* DEVICE [n][R] initial values, or NULL for SplitMix64 U(-1,1) */
     void* stream;        /* hipStream_t */

@@ -27,8 +27,11 @@ ADAM, SGD = 0, 1
 LOSS_UNSAT, LOSS_ALL = 0, 1
 
 # schedule id of the resident solver (whole loop in one workgroup per restart);
-# other ids are a kernel table index | rows per work unit << 8
+# ids other than this and the next are a kernel table index | rows per work unit << 8
 RESIDENT = 255
+# schedule id of the cluster solver (whole loop in several workgroups of one
+# XCD per restart); it takes the solves it was measured to be faster on
+CLUSTER = 254
 
 
 class HipMsatError(RuntimeError):

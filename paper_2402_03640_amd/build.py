@@ -65,6 +65,8 @@ def build(verbose: bool = False, sanitize: bool = False) -> str:
                                os.path.join(BUILD, "hipmsat.o")],
         [HIPCC] + HIP_FLAGS + ["-c", os.path.join(CSRC, "small.hip"), "-o",
                                os.path.join(BUILD, "small.o")],
+        [HIPCC] + HIP_FLAGS + ["-c", os.path.join(CSRC, "cluster.hip"), "-o",
+                               os.path.join(BUILD, "cluster.o")],
     ]
     if not sanitize:
         jobs.append([HIPCC] + HIP_FLAGS + ["-shared", os.path.join(CSRC, "probe.hip"), "-o", PROBE_OUT + ".tmp"])
@@ -77,7 +79,8 @@ def build(verbose: bool = False, sanitize: bool = False) -> str:
         san_link = ["-L" + rt, "-Wl,-rpath," + rt, "-lasan", "-lubsan"]
     outs.append(_run([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp,
                       os.path.join(bdir, "plan.o"), os.path.join(BUILD, "kernels.o"),
-                      os.path.join(BUILD, "hipmsat.o"), os.path.join(BUILD, "small.o")] + san_link))
+                      os.path.join(BUILD, "hipmsat.o"), os.path.join(BUILD, "small.o"),
+                      os.path.join(BUILD, "cluster.o")] + san_link))
     os.replace(tmp, out)
     if not sanitize:
         os.replace(PROBE_OUT + ".tmp", PROBE_OUT)

@@ -1,0 +1,107 @@
+// Cluster solver: the whole Algorithm 1 loop of one (instance, restart) runs
+// in C workgroups on the CUs of one XCD, with the relaxed values of every
+// variable in each workgroup's LDS.  Used where the state of an instance fits
+// LDS but one workgroup is too slow and the tiled kernels are bound by launch
+// latency or by the fabric traffic of their gathers.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "kernels.hpp"
+#include "plan.hpp"
+
+namespace hms {
+
+constexpr int kXcds = 8;              // XCDs of the GPU, each with its own L2
+constexpr int kXcdCus = 32;           // CUs per XCD: the most workgroups a cluster can have
+constexpr int kClusterThreads = 1024;
+constexpr int kClusterMaxK = 5;       // longest clause
+constexpr int kClusterMaxPos = 32768; // LDS slots a 15-bit literal field can name
+constexpr int32_t kClusterMaxT = 1 << 20;
+
+// Shape of a cluster solve of an instance.
+struct ClusterShape {
+    int32_t C = 0;         // workgroups per restart (a power of two)
+    int32_t NO = 0;        // other literals per occurrence record (2, 3 or 4)
+    int32_t slice = 0;     // variables per workgroup, padded to whole tiles
+    int32_t live_tiles = 0;  // clause tiles before the tautological ones
+    size_t lds = 0;        // dynamic LDS per workgroup
+    int32_t per_launch = 0;  // restarts one launch holds
+};
+
+// One instance of a cluster launch (device-visible).
+struct ClusterDesc {
+    const TileDesc* c_tile;
+    const uint32_t* c_ent;
+    const TileDesc* v_tile;
+    const uint32_t* v_ent;
+    const int32_t* var_old;
+    const int64_t* c_w;   // weight of each clause row, or null
+    // built by launch_cluster_build
+    uint32_t* counts;     // [n_act] occurrences per variable: positive | negative << 16
+    int32_t* bins;        // [kClusterBins] variables per list length, then the first rank of each
+    int32_t* slot;        // [n_act] LDS slot of a variable
+    int32_t* var;         // [C * slice] variable of an LDS slot, -1: none
+    int2* tile;           // [v_tiles] first record block, list length
+    uint32_t* rec;        // occurrence records
+    float* wrec;          // weighted: clause weight per record
+    uint32_t* cslot;      // [c_ent] clause entries with LDS slots in place of variables
+    float2* scal;         // Adam scalars of each step of this launch
+    int32_t n, n_act, c_tiles, v_tiles, C, log2C, NO, slice;
+    int64_t c_ent_n;
+    int32_t R, T, K, opt;
+    int64_t w_empty, best0;
+    float two_over_m, lr, b1, b2, eps, omb1, omb2;
+    double inv_m;
+    uint64_t seed;
+    const float* x0;      // caller order [n][R] or null
+    const float* m0;
+    const float* v0;
+    int32_t step0, resume;
+    uint8_t* best_a;      // [R][n] caller order
+    int64_t* best;        // [R]
+    int32_t* best_step;   // [R]
+    double* final_loss;   // [R]
+    float* x_final;       // caller order [n][R] or null
+    float* m_final;
+    float* v_final;
+    TracePoint* trace;    // [trace_cap][R] or null
+    int32_t trace_cap, pad;
+};
+
+// One cluster of a launch: restart r of desc, its exchange buffers, and the
+// control words of its registration (arrived count; 0 undecided, 1 go, 2 void).
+struct ClusterGroup {
+    const ClusterDesc* desc;
+    float* tbuf;       // [2][C * slice] signed tanh, by LDS slot
+    uint64_t* flags;   // [C] 128-byte lines, by step parity: step number | partial count << 32
+    double* losses;    // [2][C] partial losses, by step parity
+    int32_t* ctl;      // [0] arrived, [1] decision, [2] a bounded wait ran out
+    int32_t r, C;
+};
+
+struct ClusterLaunch {
+    const ClusterGroup* groups;  // device; clusters of XCD x are [off[x], off[x + 1])
+    int32_t* tickets;            // device [kXcds], zero
+    int32_t off[kXcds + 1];
+    int32_t shared_off;          // LDS offset of the workgroup variables (set by launch_cluster)
+};
+
+// Whether the instance can run as a cluster solve of R restarts, and how.
+bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& sh);
+constexpr int kClusterBins = 512;  // list lengths (rows kept whole have at most kSplitDense entries)
+// Words of a record block (8 records of each list for 64 rows: column bits,
+// then the records) and the most blocks of an instance with `cols`
+// variable-side columns in `tiles` tiles.
+constexpr int cluster_block_words(int NO) { return 128 + 1024 * (NO <= 2 ? 1 : 2); }
+inline size_t cluster_blocks(size_t cols, int32_t tiles) { return cols / 8 + (size_t)tiles; }
+
+// Variable order, records and clause slots of an instance, from its device
+// plan, and the Adam scalars of steps step0 .. step0 + T - 1.  D.bins is zero.
+hipError_t launch_cluster_build(const ClusterDesc& D, double lr, double b1, double b2, hipStream_t s);
+hipError_t launch_cluster(const ClusterLaunch& L, int32_t NO, bool weighted, size_t lds, size_t lds_cap,
+                          hipStream_t s);
+
+}  // namespace hms

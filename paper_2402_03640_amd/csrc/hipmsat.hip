@@ -14,6 +14,7 @@
 #include <tuple>
 #include <vector>
 
+#include "cluster.hpp"
 #include "hipmsat.h"
 #include "kernels.hpp"
 #include "plan.hpp"
@@ -733,7 +734,11 @@ struct Events {
 bool resident_ok(const hms_cnf* cnf, const hms_solve_params* p);
 bool resident_preferred(const hms_cnf* cnf, const hms_solve_params* p);
 hms_status time_resident(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms);
+hms_status time_cluster(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms);
+bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p);
+bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p);
 constexpr int32_t kResidentId = 0xff;
+constexpr int32_t kClusterId = 0xfe;
 constexpr int64_t kResidentNnz = 1 << 15;  // largest instance the untimed choice sends to the resident solver
 
 uint64_t tune_key(const hms_solve_params* p) {
@@ -909,7 +914,9 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, in
     std::vector<int32_t> cands;
     for (auto& kv : picks) cands.push_back(kv.first | (kv.second.Uf << 8) | (kv.second.Ub << 16));
     if (resident_ok(cnf, p)) cands.push_back(kResidentId);
+    if (cluster_ok(cnf, p)) cands.push_back(kClusterId);
     auto time_code = [&](int32_t code, double& ms) {
+        if (code == kClusterId) return time_cluster(cnf, p, iters, ms);
         return code == kResidentId ? time_resident(cnf, p, iters, ms) : time_steps(cnf, p, code, iters, ms);
     };
     std::vector<std::pair<double, int32_t>> timed;
@@ -925,7 +932,9 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, in
     std::sort(timed.begin(), timed.end());
     const int untimed = auto_schedule(p->restarts, p->loss_mode, cnf->plan.nnz, cnf->plan.n_act);
     for (size_t k = 0; k < timed.size(); ++k) {
-        if (k >= 3 && (timed[k].second == kResidentId || (timed[k].second & 0xff) != untimed)) continue;
+        if (k >= 3 && (timed[k].second == kResidentId || timed[k].second == kClusterId ||
+                       (timed[k].second & 0xff) != untimed))
+            continue;
         for (int rep = 0; rep < 2; ++rep) {
             double ms = 0;
             hms_status rc = time_code(timed[k].second, ms);
@@ -938,7 +947,7 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, in
             best_ms = tc.first;
             best = tc.second;
         }
-    if (best != kResidentId && ((best >> 16) & 0xff) == ((best >> 8) & 0xff)) best &= 0xffff;  // canonical id
+    if (best != kResidentId && best != kClusterId && ((best >> 16) & 0xff) == ((best >> 8) & 0xff)) best &= 0xffff;  // canonical id
     {
         std::lock_guard<std::mutex> lk(cnf->tune_mu);
         cnf->tuned[tune_key(p)] = best;
@@ -952,20 +961,29 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, in
 hms_status resolve_schedule(const hms_cnf* cnf, const hms_solve_params* p, int32_t& code) {
     code = p->schedule;
     if (code != 0) return HMS_OK;
+    // the resident and the cluster solver cannot honour a time limit or a
+    // cancel flag: a solve that asks for one takes the tiled choice below
+    // instead (as one whose size class was tuned on an instance that fits them
+    // when it does not)
+    auto runs = [&](int32_t c) {
+        return c == kResidentId ? resident_ok(cnf, p) : c == kClusterId ? cluster_ok(cnf, p) : true;
+    };
     {
         std::lock_guard<std::mutex> lk(cnf->tune_mu);
         auto it = cnf->tuned.find(tune_key(p));
-        // the resident solver cannot honour a time limit or a cancel flag:
-        // a solve that asks for one takes the tiled choice below instead
-        if (it != cnf->tuned.end() && (it->second != kResidentId || resident_ok(cnf, p))) {
+        if (it != cnf->tuned.end() && runs(it->second)) {
             code = it->second;
             return HMS_OK;
         }
     }
+    if (cluster_preferred(cnf, p)) {  // no timing needed: ahead of every other schedule where it runs
+        code = kClusterId;
+        return HMS_OK;
+    }
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(class_key(cnf, p));
-        if (it != g_tuned.end() && (it->second != kResidentId || resident_ok(cnf, p))) {
+        if (it != g_tuned.end() && runs(it->second)) {
             code = it->second;
             return HMS_OK;
         }
@@ -1198,6 +1216,299 @@ hms_status time_resident(const hms_cnf* cnf, const hms_solve_params* p0, int32_t
     return HMS_OK;
 }
 
+// ---- cluster path (C workgroups of one XCD per restart) ---------------------
+size_t cluster_lds_cap(int dev) {
+    static std::atomic<size_t> cached[64] = {};
+    if (dev >= 0 && dev < 64) {
+        const size_t c = cached[dev].load(std::memory_order_relaxed);
+        if (c) return c;
+    }
+    int v = 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) v = 65536;
+    const size_t lim = (size_t)v;
+    if (dev >= 0 && dev < 64) cached[dev].store(lim, std::memory_order_relaxed);
+    return lim;
+}
+
+// Whole GPUs only: every XCD with all its CUs.
+bool cluster_device(int dev) {
+    static std::atomic<int> cached[64] = {};  // 0 unknown, 1 yes, 2 no
+    if (dev < 0 || dev >= 64) return false;
+    int c = cached[dev].load(std::memory_order_relaxed);
+    if (c == 0) {
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
+        c = cus == hms::kXcds * hms::kXcdCus ? 1 : 2;
+        cached[dev].store(c, std::memory_order_relaxed);
+    }
+    return c == 1;
+}
+
+bool cluster_fits(const hms_cnf* cnf, const hms_solve_params* p, hms::ClusterShape& sh) {
+    // what the tiled set-up refuses is left to it
+    if ((p->optimizer != HMS_ADAM && p->optimizer != HMS_SGD) || !std::isfinite(p->lr) || !std::isfinite(p->beta1) ||
+        !std::isfinite(p->beta2) || !std::isfinite(p->eps))
+        return false;
+    return p->loss_mode == HMS_LOSS_UNSAT && p->time_limit_s <= 0 && p->cancel == nullptr && p->restarts >= 1 &&
+           p->steps >= 0 && p->eval_every >= 1 && p->steps <= hms::kClusterMaxT && cluster_device(cnf->device) &&
+           hms::cluster_shape(cnf->plan, p->restarts, cluster_lds_cap(cnf->device), sh);
+}
+
+bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p) {
+    hms::ClusterShape sh;
+    return cluster_fits(cnf, p, sh);
+}
+
+// Without timing, the cluster solver is taken wherever it runs and was the
+// faster one, us per step on uniform 3-, 4-, 5-CNF and mixed formulas of 400 to
+// 28000 variables, 1 to 100 restarts, against the tuned tiled or resident
+// schedule:
+//   - from 2^14 nonzeros up (2^15 where clauses have five literals): below, the
+//     resident solver's single workgroup needs no exchange (5160 nonzeros: 2.4
+//     against 2.9; 12900: 3.0 against 2.8; 34400 in 5-CNF: 9.1 against 8.6);
+//   - with one restart only one XCD works, and the others' share of the
+//     tiled kernels wins again past 2^21 record terms (nonzeros times other
+//     literals per clause; 3-CNF n = 28000: 4.6 against 7.1; 4-CNF n = 16000:
+//     7.5 against 8.8, n = 28000: 11.2 against 10.4);
+//   - from 64 steps on: building the records costs 40 to 250 us, about what
+//     60 steps gain.
+bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p) {
+    hms::ClusterShape sh;
+    if (p->steps < 64 || !cluster_fits(cnf, p, sh)) return false;
+    const int64_t nnz = cnf->plan.nnz;
+    if (nnz <= (int64_t(1) << (sh.NO >= 4 ? 15 : 14))) return false;
+    return p->restarts > 1 || nnz * sh.NO <= (int64_t(1) << 21);
+}
+
+// One cluster launch at a time on a device: two that each hold part of an XCD
+// would wait for each other until their registrations run out.
+std::mutex g_cluster_mu[64];
+
+// Runs the solve as clusters; *ran = false (and HMS_OK) when the device was
+// taken by another cluster solve or a cluster could not assemble: nothing has
+// been written then and the caller takes the tiled kernels.
+hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solve_result* res, bool& ran) {
+    ran = false;
+    const hms::HostPlan& P = cnf->plan;
+    hms::ClusterShape sh;
+    if (!cluster_fits(cnf, p, sh)) return fail(HMS_ERR_ARG, "the cluster schedule does not fit this solve");
+    std::unique_lock<std::mutex> lk(g_cluster_mu[cnf->device], std::try_to_lock);
+    if (!lk.owns_lock()) return HMS_OK;
+    const int32_t R = p->restarts;
+    const bool adam = p->optimizer == HMS_ADAM;
+    hipStream_t s = (hipStream_t)p->stream;
+    const hms_solve_state* rs = p->resume;
+    hms_solve_state* so = res->state;
+    // host destinations and sources of the copies below: declared before the
+    // guard that waits for the stream
+    std::vector<int64_t> best(R);
+    std::vector<int32_t> bstep(R);
+    std::vector<double> closs(R);
+    const int32_t launches = (R + sh.per_launch - 1) / sh.per_launch;
+    const int32_t clusters = std::min(R, sh.per_launch);
+    std::vector<hms::ClusterGroup> groups(R);
+    std::vector<int32_t> ctl((size_t)R * 4);
+    Layout lay;
+    const size_t o_desc = lay.add(sizeof(hms::ClusterDesc));
+    const size_t o_groups = lay.add(sizeof(hms::ClusterGroup) * R);
+    const SmallOut out = layout_small_out(P, R, lay);
+    const size_t o_trace = res->trace ? lay.add((size_t)res->trace_cap * R * sizeof(hms::TracePoint)) : 0;
+    const size_t blocks = hms::cluster_blocks(P.v_ent.size() / hms::kTile, P.v_tiles);
+    const size_t o_counts = lay.add((size_t)P.n_act * 4);
+    const size_t o_slot = lay.add((size_t)P.n_act * 4);
+    const size_t o_var = lay.add((size_t)sh.C * sh.slice * 4);
+    const size_t o_tile = lay.add((size_t)P.v_tiles * sizeof(int2));
+    const size_t o_rec = lay.add(blocks * hms::cluster_block_words(sh.NO) * 4);
+    const size_t o_wrec = P.weighted ? lay.add(blocks * 1024 * 4) : 0;
+    const size_t o_cslot = lay.add(P.c_ent.size() * 4);
+    const size_t o_scal = lay.add((size_t)std::max(p->steps, 1) * sizeof(float2));
+    const size_t line = 128;
+    const size_t tb_bytes = (size_t)2 * sh.C * sh.slice * 4;
+    const size_t o_tbuf = lay.add(tb_bytes * clusters);
+    const size_t o_loss = lay.add((size_t)2 * sh.C * 8 * clusters);
+    // zeroed before the launches: flags, control words and tickets of each
+    const size_t o_zero = lay.add(0);
+    const size_t o_flags = lay.add(line * sh.C * R);
+    const size_t o_ctl = lay.add((size_t)R * 16);
+    const size_t o_tick = lay.add((size_t)launches * hms::kXcds * 4);
+    const size_t o_bins = lay.add(hms::kClusterBins * 4);
+    const size_t zero_bytes = lay.off - o_zero;
+    Arena A;
+    A.s = s;
+    HIPTRY(hipMallocAsync((void**)&A.base, lay.off, s));
+    hms::ClusterDesc D{};
+    D.c_tile = cnf->c_tile;
+    D.c_ent = cnf->c_ent;
+    D.v_tile = cnf->v_tile;
+    D.v_ent = cnf->v_ent;
+    D.var_old = cnf->var_old;
+    D.c_w = cnf->c_w;
+    D.counts = A.at<uint32_t>(o_counts);
+    D.bins = A.at<int32_t>(o_bins);
+    D.slot = A.at<int32_t>(o_slot);
+    D.var = A.at<int32_t>(o_var);
+    D.tile = A.at<int2>(o_tile);
+    D.cslot = A.at<uint32_t>(o_cslot);
+    D.c_ent_n = (int64_t)P.c_ent.size();
+    D.rec = A.at<uint32_t>(o_rec);
+    D.wrec = P.weighted ? A.at<float>(o_wrec) : nullptr;
+    D.scal = A.at<float2>(o_scal);
+    D.n = P.n;
+    D.n_act = P.n_act;
+    D.c_tiles = P.c_tiles;
+    D.v_tiles = P.v_tiles;
+    D.C = sh.C;
+    D.log2C = ilog2(sh.C);
+    D.NO = sh.NO;
+    D.slice = sh.slice;
+    D.R = R;
+    D.T = p->steps;
+    D.K = p->eval_every;
+    D.opt = adam ? hms::kAdam : hms::kSgd;
+    D.w_empty = P.w_empty;
+    D.best0 = P.w_total;
+    D.two_over_m = P.m > 0 ? (float)(2.0 / (double)P.m) : 0.0f;
+    D.inv_m = P.m > 0 ? 1.0 / (double)P.m : 0.0;
+    D.lr = p->lr;
+    D.b1 = p->beta1;
+    D.b2 = p->beta2;
+    D.eps = p->eps;
+    D.omb1 = 1.0f - p->beta1;
+    D.omb2 = 1.0f - p->beta2;
+    D.seed = p->seed;
+    D.x0 = p->x0;
+    D.best_a = A.at<uint8_t>(out.o_best_a);
+    D.best = A.at<int64_t>(out.o_best);
+    D.best_step = A.at<int32_t>(out.o_step);
+    D.final_loss = A.at<double>(out.o_loss);
+    D.x_final = res->x_final ? res->x_final : (so ? so->x : nullptr);
+    if (so && adam) {
+        D.m_final = so->m;
+        D.v_final = so->v;
+    }
+    if (res->trace) {
+        D.trace = A.at<hms::TracePoint>(o_trace);
+        D.trace_cap = res->trace_cap;
+    }
+    if (rs) {
+        D.x0 = rs->x;
+        D.m0 = adam ? rs->m : nullptr;
+        D.v0 = adam ? rs->v : nullptr;
+        D.step0 = rs->step;
+        D.resume = 1;
+    }
+    // restart r of a launch on XCD r % 8; the groups of a launch lie XCD by XCD
+    std::vector<hms::ClusterLaunch> L(launches);
+    int32_t g = 0;
+    for (int32_t k = 0; k < launches; ++k) {
+        const int32_t r0 = k * sh.per_launch;
+        const int32_t cnt = std::min(sh.per_launch, R - r0);
+        L[k].groups = A.at<hms::ClusterGroup>(o_groups);
+        L[k].tickets = A.at<int32_t>(o_tick) + (size_t)k * hms::kXcds;
+        for (int32_t x = 0; x < hms::kXcds; ++x) {
+            L[k].off[x] = g;
+            for (int32_t i = x; i < cnt; i += hms::kXcds, ++g) {
+                hms::ClusterGroup& q = groups[g];
+                q.desc = A.at<hms::ClusterDesc>(o_desc);
+                q.tbuf = A.at<float>(o_tbuf + tb_bytes * i);
+                q.losses = A.at<double>(o_loss) + (size_t)2 * sh.C * i;
+                q.flags = A.at<uint64_t>(o_flags + line * sh.C * g);
+                q.ctl = A.at<int32_t>(o_ctl) + (size_t)g * 4;
+                q.r = r0 + i;
+                q.C = sh.C;
+            }
+        }
+        L[k].off[hms::kXcds] = g;
+    }
+    Events E;
+    for (int i = 0; i < 2; ++i) HIPTRY(hipEventCreate(&E.e[i]));
+    SyncOnExit done{s};
+    HIPTRY(hipMemcpyAsync(A.base + o_desc, &D, sizeof(D), hipMemcpyHostToDevice, s));
+    HIPTRY(hipMemcpyAsync(A.base + o_groups, groups.data(), sizeof(hms::ClusterGroup) * R, hipMemcpyHostToDevice, s));
+    HIPTRY(hipMemsetAsync(A.base + o_zero, 0, zero_bytes, s));
+    if (rs) {
+        // the resumed best enters through the output arrays the kernel updates
+        HIPTRY(hipMemcpyAsync(D.best, rs->best, (size_t)R * 8, hipMemcpyHostToDevice, s));
+        HIPTRY(hipMemcpyAsync(D.best_step, rs->best_step, (size_t)R * 4, hipMemcpyHostToDevice, s));
+        if (P.n > 0)
+            HIPTRY(hipMemcpyAsync(D.best_a, rs->best_assignment, (size_t)R * P.n, hipMemcpyDeviceToDevice, s));
+    }
+    HIPTRY(hipEventRecord(E.e[0], s));
+    HIPTRY(hms::launch_cluster_build(D, (double)p->lr, (double)p->beta1, (double)p->beta2, s));
+    for (const auto& l : L)
+        HIPTRY(hms::launch_cluster(l, sh.NO, P.weighted, sh.lds, cluster_lds_cap(cnf->device), s));
+    HIPTRY(hipEventRecord(E.e[1], s));
+    HIPTRY(hipMemcpyAsync(best.data(), D.best, R * 8, hipMemcpyDeviceToHost, s));
+    HIPTRY(hipMemcpyAsync(bstep.data(), D.best_step, R * 4, hipMemcpyDeviceToHost, s));
+    HIPTRY(hipMemcpyAsync(closs.data(), D.final_loss, R * 8, hipMemcpyDeviceToHost, s));
+    HIPTRY(hipMemcpyAsync(ctl.data(), A.base + o_ctl, (size_t)R * 16, hipMemcpyDeviceToHost, s));
+    HIPTRY(hipStreamSynchronize(s));
+    for (int32_t i = 0; i < R; ++i)
+        if (ctl[(size_t)i * 4 + 1] != 1 || ctl[(size_t)i * 4 + 2] != 0) return HMS_OK;  // not all assembled
+    ran = true;
+    int32_t br = 0;
+    for (int32_t r = 1; r < R; ++r)
+        if (best[r] < best[br]) br = r;
+    if (res->best_assignment && P.n > 0)
+        HIPTRY(hipMemcpyAsync(res->best_assignment, D.best_a + (size_t)br * P.n, P.n, hipMemcpyDeviceToHost, s));
+    if (so && P.n > 0) {
+        if (res->x_final && so->x != res->x_final)
+            HIPTRY(hipMemcpyAsync(so->x, res->x_final, (size_t)P.n * R * 4, hipMemcpyDeviceToDevice, s));
+        HIPTRY(hipMemcpyAsync(so->best_assignment, D.best_a, (size_t)R * P.n, hipMemcpyDeviceToDevice, s));
+    }
+    HIPTRY(hipStreamSynchronize(s));
+    float ms = 0;
+    HIPTRY(hipEventElapsedTime(&ms, E.e[0], E.e[1]));
+    res->best_cost = best[br];
+    res->best_restart = br;
+    res->best_step = bstep[br];
+    res->steps_done = p->steps;
+    res->schedule = kClusterId;
+    res->final_loss = closs[br];
+    res->device_ms = ms;
+    if (res->restart_best) std::memcpy(res->restart_best, best.data(), R * 8);
+    if (res->restart_step) std::memcpy(res->restart_step, bstep.data(), R * 4);
+    if (res->restart_loss) std::memcpy(res->restart_loss, closs.data(), R * 8);
+    if (so) {
+        std::memcpy(so->best, best.data(), R * 8);
+        std::memcpy(so->best_step, bstep.data(), R * 4);
+        so->step = (rs ? rs->step : 0) + p->steps;
+    }
+    if (res->trace) {
+        const int32_t s0 = rs ? rs->step : 0;
+        if (hms_status rt = read_trace(D.trace, R, p->eval_every, s0, s0 + p->steps, s, res)) return rt;
+    }
+    for (int32_t r = 0; r < R; ++r)
+        if (!std::isfinite(closs[r])) return fail(HMS_ERR_NONFINITE, "the loss at the final iterate is not finite");
+    return HMS_OK;
+}
+
+// Device time per step of the cluster solver, by the difference of a short
+// and a three times longer solve (as time_resident); a device taken by
+// another cluster solve leaves it untimed (never the fastest).
+hms_status time_cluster(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms) {
+    hms_solve_params p = *p0;
+    p.eval_every = std::max(p0->eval_every, 1);
+    p.x0 = nullptr;
+    p.resume = nullptr;
+    const int32_t S = std::max(iters, 16) * 4;
+    double t[3] = {0, 0, 0};
+    for (int k = 0; k < 3; ++k) {
+        p.steps = k == 2 ? 3 * S : S;
+        hms_solve_result r{};
+        bool ran = false;
+        hms_status rc = solve_cluster(cnf, &p, &r, ran);
+        if (rc) return rc;
+        if (!ran) {
+            ms = 1e30;
+            return HMS_OK;
+        }
+        t[k] = r.device_ms;
+    }
+    ms = std::max(t[2] - t[1], 0.0) / (2.0 * S);
+    return HMS_OK;
+}
+
 // The count at x_T (always taken) and the snapshot of the best assignment.
 hipError_t count_final(const hms_cnf* cnf, const SolveSetup& Z, hipStream_t s) {
     const Shape& sh = Z.sh;
@@ -1421,6 +1732,12 @@ hms_status hms_solve(const hms_cnf* cnf, const hms_solve_params* p, hms_solve_re
             return fail(HMS_ERR_ARG, "restarts >= 1, steps >= 0 and eval_every >= 1 required");
         return solve_resident(cnf, p, res);
     }
+    if (p->schedule == kClusterId) {
+        bool ran = false;
+        rc0 = solve_cluster(cnf, p, res, ran);
+        if (rc0 || ran) return rc0;
+        pr.schedule = 0;  // the untimed tiled choice
+    }
     SolveSetup Z;
     rc0 = setup_solve(cnf, p, Z);
     if (rc0) return rc0;
@@ -1547,6 +1864,15 @@ hms_status hms_time_kernels(const hms_cnf* cnf, const hms_solve_params* p, int32
         if (!resident_ok(cnf, p)) return fail(HMS_ERR_ARG, "the resident schedule does not fit this instance");
         double ms = 0;
         hms_status rc = time_resident(cnf, p, iters, ms);
+        if (rc) return rc;
+        if (fwd_ms) *fwd_ms = 0.0;
+        if (bwd_ms) *bwd_ms = 0.0;
+        if (step_ms) *step_ms = ms;
+        return HMS_OK;
+    }
+    if (p->schedule == kClusterId) {
+        double ms = 0;
+        hms_status rc = time_cluster(cnf, p, iters, ms);
         if (rc) return rc;
         if (fwd_ms) *fwd_ms = 0.0;
         if (bwd_ms) *bwd_ms = 0.0;
@@ -1765,7 +2091,7 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
             if (p.schedule == kResidentId) p.schedule = 0;
             int32_t code = 0;
             hms_status st = resolve_schedule(cnfs[g[k0]], &p, code);
-            if (!st && code == kResidentId) code = 0;
+            if (!st && (code == kResidentId || code == kClusterId)) code = 0;
             // one explicit schedule for the whole group (the automatic choice
             // depends on the instance)
             Shape sh0;
