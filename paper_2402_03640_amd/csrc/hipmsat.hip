@@ -134,13 +134,18 @@ int auto_schedule(int32_t R, int loss_mode, int64_t nnz = 0, int32_t n_act = 0) 
         // while the rows are few, two beyond
         return n_act <= (1 << 14) ? 39 : 38;
     }
-    if (R <= 2) return 2;
-    if (R <= 4) return 3;
-    if (R <= 8) return 5;
+    // several restarts, forward + backward us timed over every entry on 3-CNF
+    // n = 20000 m = 86000 and 5-CNF n = 12000 m = 204000 (unmasked): up to eight
+    // the long backward batches at four lanes per row (8 restarts 10.6 and 23.5,
+    // entry 5: 10.4 and 24.8); then four restarts per lane, 16 or 32 restarts
+    // per group (16: 13.1 and 28.0, entry 4 13.4 and 29.6; 32: 16.6 and 35.1,
+    // entry 10 21.3 and 50; 64: 25.6 and 53.8, entry 15 27.4 and 60.6), two
+    // per lane (32: 18.5 and 40.2), else one restart per lane, 16 per group
+    // (32: 19.8 and 40.4)
+    if (R <= 8) return 39;
+    if (R % 4 == 0) return R <= 16 ? 33 : 34;
     if (R <= 16) return 4;
-    if (R <= 32) return 10;
-    if (R % 4 == 0) return 15;
-    return 14;
+    return R % 2 == 0 ? 35 : 6;
 }
 
 struct Shape {
@@ -178,7 +183,17 @@ hms_status make_shape(const hms::HostPlan& P, int32_t R, int32_t req, int loss_m
     sh.mask = c.mask;
     sh.slot = c.slot;
     if (R % sh.V != 0) return fail(HMS_ERR_ARG, "schedule vector width does not divide the restart count");
-    if (U == 0) U = hms::default_rows_per_unit(sh.sched);
+    if (U == 0) {
+        U = hms::default_rows_per_unit(sh.sched);
+        if (Ub == 0) Ub = U;
+        // the automatic choice gives a forward wavefront more rows once the
+        // wavefronts pass what the chip holds: each writes its count and
+        // loss partials, 16 bytes per restart (64 restarts at n = 20000: 4 rows
+        // per unit wrote 22 MB of them, the counting forward 18.3 us)
+        const int64_t groups = (R + sh.P * sh.V - 1) / (sh.P * sh.V);
+        if (idx == 0 && c.nt == 1 && !sh.mask)
+            while (U < hms::kTile && (int64_t)P.c_tiles * (hms::kTile / U) * groups > 8192) U *= 2;
+    }
     if (Ub == 0) Ub = U;
     const int per_pass = (64 / sh.P) * sh.UR;
     if (U % per_pass != 0 || hms::kTile % U != 0 || (sh.mask && U < 32) || Ub % per_pass != 0 || hms::kTile % Ub != 0)
@@ -386,7 +401,6 @@ Launch make_launch(const hms_cnf* C, const Shape& sh, const State& S, int opt, i
     b.m = S.m;
     b.v = S.v;
     b.t = S.t;
-    b.g_out = S.g;
     b.best_a = S.best_a;
     b.improved = S.improved;
     b.st = S.st;
@@ -397,6 +411,7 @@ Launch make_launch(const hms_cnf* C, const Shape& sh, const State& S, int opt, i
     b.omb1 = 1.0f - b1;
     b.omb2 = 1.0f - b2;
     b.seg_first = C->seg_first;
+    b.var_old = C->var_old;
     hms::ReduceArgs& r = L.ra;
     r.cnt_part = S.cnt_part;
     r.loss_part = S.loss_part;
@@ -432,6 +447,53 @@ hipError_t enqueue_step(const Launch& L, bool eval, hipStream_t s) {
     if (e != hipSuccess) return e;
     return hms::launch_combine(L.opt, b, s);
 }
+
+// Pinned host memory that the last kernel of a call writes its few results
+// into, so the caller waits once instead of copying each from the device.  The
+// free list is shared by all threads and holds at most kPinnedKeep pieces; a
+// piece is in use from here until the call that took it has waited for its
+// stream.  Allocation failing is no error: the caller copies instead.
+constexpr size_t kPinnedBytes = 8192;
+constexpr size_t kPinnedKeep = 64;
+std::mutex g_pinned_mu;
+std::vector<void*> g_pinned;
+
+struct Pinned {
+    char* p = nullptr;
+    hipStream_t s = nullptr;
+    bool waited = false;  // the stream has drained since the last launch that writes here
+    Pinned(size_t bytes, hipStream_t stream) : s(stream) {
+        if (bytes > kPinnedBytes) return;
+        {
+            std::lock_guard<std::mutex> lk(g_pinned_mu);
+            if (!g_pinned.empty()) {
+                p = static_cast<char*>(g_pinned.back());
+                g_pinned.pop_back();
+                return;
+            }
+        }
+        void* q = nullptr;
+        if (hipHostMalloc(&q, kPinnedBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        p = static_cast<char*>(q);
+    }
+    ~Pinned() {
+        if (!p) return;
+        if (!waited) (void)hipStreamSynchronize(s);
+        {
+            std::lock_guard<std::mutex> lk(g_pinned_mu);
+            if (g_pinned.size() < kPinnedKeep) {
+                g_pinned.push_back(p);
+                return;
+            }
+        }
+        (void)hipHostFree(p);
+    }
+    Pinned(const Pinned&) = delete;
+    Pinned& operator=(const Pinned&) = delete;
+};
 
 hms_status check_cnf(const hms_cnf* C) {
     if (!C) return fail(HMS_ERR_ARG, "null instance handle");
@@ -2185,6 +2247,15 @@ hms_status scratch_on(int dev, char*& ptr) {
     return HMS_OK;
 }
 
+// Gradients between the caller's arrays; vector access where rows of R floats
+// start 16-byte aligned for every vector width that divides R.
+void set_grad(hms::BwdArgs& b, const float* x, const float* scale, float* grad) {
+    b.x_in = x;
+    b.scale = scale;
+    b.grad_out = grad;
+    b.wide = (((uintptr_t)x | (uintptr_t)grad) & 15) == 0 ? 1 : 0;
+}
+
 // One evaluation of the relaxed objective (hms_eval_relaxed).  With `fixed`
 // the workspace is that device memory (cap bytes) and loss / unsat are
 // DEVICE outputs, so nothing is allocated and nothing waits; otherwise the
@@ -2202,44 +2273,99 @@ hms_status eval_relaxed_impl(const hms_cnf* cnf, const float* x, int32_t R, int3
     // pays for them) and they would take workspace
     hms_status rc = make_shape(P, R, 0, loss_mode, sh, true, false);
     if (rc) return rc;
-    const bool want_g = grad != nullptr;
+    const bool want_g = grad != nullptr && P.n > 0;
     Layout lay;
     size_t off[kOffN];
     layout_state(P, sh, false, want_g, false, lay, off);
+    if (fixed && lay.off > cap)
+        return fail(HMS_ERR_TOO_LARGE, "this evaluation needs " + std::to_string(lay.off) +
+                                           " bytes of workspace, more than the " + std::to_string(cap) +
+                                           " of the allocation-free variant");
+    // results: straight to the caller's device arrays, or to host memory the
+    // kernels can write
+    Pinned host(fixed || !(loss || unsat) ? kPinnedBytes + 1 : (size_t)R * 16, s);
+    double* d_loss = fixed ? loss : reinterpret_cast<double*>(host.p);
+    int64_t* d_unsat = fixed ? unsat : reinterpret_cast<int64_t*>(host.p ? host.p + (size_t)R * 8 : nullptr);
+    auto finish = [&]() -> hms_status {  // host outputs, once the pinned memory is written
+        HIPTRY(hipStreamSynchronize(s));
+        host.waited = true;
+        if (loss) std::memcpy(loss, d_loss, (size_t)R * 8);
+        if (unsat) std::memcpy(unsat, d_unsat, (size_t)R * 8);
+        return HMS_OK;
+    };
+    // small instances: one launch, one workgroup per point, nothing allocated
+    const bool partly = want_g && grad != x && grad < x + (size_t)P.n * R && x < grad + (size_t)P.n * R;
+    if (!partly && (fixed || host.p || !(loss || unsat)) && hms::eval_small_ok(P, lds_limit(cnf->device))) {
+        hms::EvalSmall E{};
+        E.c_tile = cnf->c_tile;
+        E.c_ent = cnf->c_ent;
+        E.v_tile = cnf->v_tile;
+        E.v_ent = cnf->v_ent;
+        E.seg_first = cnf->seg_first;
+        E.var_old = cnf->var_old;
+        E.c_w = cnf->c_w;
+        E.n = P.n;
+        E.n_act = P.n_act;
+        E.n_heavy = P.n_heavy;
+        E.c_tiles = P.c_tiles;
+        E.v_tiles = P.v_tiles;
+        E.seg_tiles = P.seg_tiles;
+        E.seg_rows = P.seg_rows;
+        E.R = R;
+        E.all_mode = loss_mode == HMS_LOSS_ALL;
+        E.two_over_m = P.m > 0 ? (float)(2.0 / (double)P.m) : 0.0f;
+        E.inv_m = P.m > 0 ? 1.0 / (double)P.m : 0.0;
+        E.w_empty = P.w_empty;
+        E.x = x;
+        E.loss = d_loss;
+        E.unsat = d_unsat;
+        E.grad = want_g ? grad : nullptr;
+        HIPTRY(hms::launch_eval_small(E, P, lds_limit(cnf->device), s));
+        return host.p ? finish() : HMS_OK;
+    }
     Arena A;
     A.s = s;
     if (fixed) {
-        if (lay.off > cap)
-            return fail(HMS_ERR_TOO_LARGE, "this evaluation needs " + std::to_string(lay.off) +
-                                               " bytes of workspace, more than the " + std::to_string(cap) +
-                                               " of the allocation-free variant");
         A.base = fixed;
         A.owns = false;
     } else {
         HIPTRY(hipMallocAsync((void**)&A.base, lay.off, s));
     }
-    // host outputs are written by queued copies: an early return waits (the
-    // allocation-free variant has device outputs only and never waits)
-    SyncOnExit outs_done{s, fixed == nullptr};
+    // host outputs are written by queued copies or kernels: an early return
+    // waits (the allocation-free variant has device outputs only and never waits)
+    SyncOnExit outs_done{s, fixed == nullptr && !host.p};
     // every piece the kernels read is written first (init kernel, forward
     // pass), so a reused workspace needs no clearing
     State S = bind_state(A, off, false, want_g, false);
     hms::InitArgs ia = make_init(cnf, sh, S);
     ia.x0 = x;
-    HIPTRY(hms::launch_init(ia, s));
+    if (want_g && !partly) {
+        ia.grad_zero = grad;
+        ia.n_act = P.n_act;
+    }
     Launch L = make_launch(cnf, sh, S, hms::kGrad, loss_mode, 0.f, 0.9f, 0.999f, 1e-8f);
     L.ra.track = 0;
+    if (d_loss) L.ra.cur_loss = d_loss;
+    if (d_unsat) L.ra.cur_count = d_unsat;
+    float* g = grad;
+    if (partly) g = S.g;  // the gradients would overwrite points still to be read: by way of the workspace
+    L.fa.st = nullptr;    // no optimizer step follows
+    HIPTRY(hms::launch_points(ia, s));
     HIPTRY(hms::launch_fwd(sh.sched, true, L.fa, sh.fwd_blocks, s));
     HIPTRY(hms::launch_reduce(L.ra, s));
     if (want_g) {
+        if (partly) HIPTRY(hms::launch_grad_zero(P.n, P.n_act, R, cnf->var_old, nullptr, g, s));
+        set_grad(L.ba, x, nullptr, g);
         HIPTRY(hms::launch_bwd(sh.sched, hms::kGrad, L.ba, sh.bwd_blocks, s));
         HIPTRY(hms::launch_combine(hms::kGrad, L.ba, s));
-        HIPTRY(hms::launch_scatter(P.n, P.n_act, sh.B, cnf->var_old, S.g, grad, s));
+        if (partly) HIPTRY(hipMemcpyAsync(grad, g, (size_t)P.n * R * 4, hipMemcpyDeviceToDevice, s));
     }
-    const hipMemcpyKind kind = fixed ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    if (loss) HIPTRY(hipMemcpyAsync(loss, S.cur_loss, (size_t)R * 8, kind, s));
-    if (unsat) HIPTRY(hipMemcpyAsync(unsat, S.cur_count, (size_t)R * 8, kind, s));
-    if (!fixed && (loss || unsat)) HIPTRY(hipStreamSynchronize(s));
+    if (host.p) return finish();
+    if (!fixed) {
+        if (loss) HIPTRY(hipMemcpyAsync(loss, S.cur_loss, (size_t)R * 8, hipMemcpyDeviceToHost, s));
+        if (unsat) HIPTRY(hipMemcpyAsync(unsat, S.cur_count, (size_t)R * 8, hipMemcpyDeviceToHost, s));
+        if (loss || unsat) HIPTRY(hipStreamSynchronize(s));
+    }
     return HMS_OK;
 }
 
@@ -2305,13 +2431,14 @@ hms_status hms_forward(const hms_cnf* cnf, const float* x, int32_t R, int32_t lo
     if (adjoint) S.a = static_cast<float*>(adjoint);
     hms::InitArgs ia = make_init(cnf, sh, S);
     ia.x0 = x;
-    HIPTRY(hms::launch_init(ia, s));
+    HIPTRY(hms::launch_points(ia, s));
     Launch L = make_launch(cnf, sh, S, hms::kGrad, loss_mode, 0.f, 0.9f, 0.999f, 1e-8f);
     L.ra.track = 0;
+    L.fa.st = nullptr;
+    L.ra.cur_loss = loss;
+    if (unsat) L.ra.cur_count = unsat;
     HIPTRY(hms::launch_fwd(sh.sched, true, L.fa, sh.fwd_blocks, s));
     HIPTRY(hms::launch_reduce(L.ra, s));
-    HIPTRY(hipMemcpyAsync(loss, S.cur_loss, (size_t)R * 8, hipMemcpyDeviceToDevice, s));
-    if (unsat) HIPTRY(hipMemcpyAsync(unsat, S.cur_count, (size_t)R * 8, hipMemcpyDeviceToDevice, s));
     return HMS_OK;
 }
 
@@ -2334,15 +2461,22 @@ hms_status hms_backward(const hms_cnf* cnf, const float* x, int32_t R, int32_t l
     HIPTRY(hipMallocAsync((void**)&A.base, lay.off, s));
     State S = bind_state(A, off, false, true, false);
     if (adjoint) S.a = const_cast<float*>(static_cast<const float*>(adjoint));
-    hms::InitArgs ia = make_init(cnf, sh, S);
-    ia.x0 = x;
-    if (adjoint) ia.a = nullptr;  // the saved adjoint is read-only here
-    HIPTRY(hms::launch_init(ia, s));
     Launch L = make_launch(cnf, sh, S, hms::kGrad, loss_mode, 0.f, 0.9f, 0.999f, 1e-8f);
-    if (!adjoint) HIPTRY(hms::launch_fwd(sh.sched, false, L.fa, sh.fwd_blocks, s));  // recompute the scores
+    if (!adjoint) {  // recompute the scores
+        hms::InitArgs ia = make_init(cnf, sh, S);
+        ia.x0 = x;
+        L.fa.st = nullptr;
+        HIPTRY(hms::launch_points(ia, s));
+        HIPTRY(hms::launch_fwd(sh.sched, false, L.fa, sh.fwd_blocks, s));
+    }
+    // gradients that would overwrite points still to be read go by way of the workspace
+    const bool partly = grad_x != x && grad_x < x + (size_t)P.n * R && x < grad_x + (size_t)P.n * R;
+    float* g = partly ? S.g : grad_x;
+    HIPTRY(hms::launch_grad_zero(P.n, P.n_act, R, cnf->var_old, grad_loss, g, s));
+    set_grad(L.ba, x, grad_loss, g);
     HIPTRY(hms::launch_bwd(sh.sched, hms::kGrad, L.ba, sh.bwd_blocks, s));
     HIPTRY(hms::launch_combine(hms::kGrad, L.ba, s));
-    HIPTRY(hms::launch_scatter(P.n, P.n_act, sh.B, cnf->var_old, S.g, grad_x, s, grad_loss));
+    if (partly) HIPTRY(hipMemcpyAsync(grad_x, g, (size_t)P.n * R * 4, hipMemcpyDeviceToDevice, s));
     return HMS_OK;
 }
 

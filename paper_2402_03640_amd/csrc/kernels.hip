@@ -291,14 +291,27 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& A, const int bx) {
         }
     }
     if (EVAL) {
+        // without weights a wavefront's count fits 32 bits: half the exchanges
+        if (A.w == nullptr) {
+            int c32[V];
 #pragma unroll
-        for (int off = P; off < 64; off <<= 1) {
+            for (int k = 0; k < V; ++k) c32[k] = (int)cnt[k];
 #pragma unroll
-            for (int k = 0; k < V; ++k) {
-                cnt[k] += __shfl_xor(cnt[k], off);
-                los[k] += __shfl_xor(los[k], off);
-            }
+            for (int off = P; off < 64; off <<= 1)
+#pragma unroll
+                for (int k = 0; k < V; ++k) c32[k] += __shfl_xor(c32[k], off);
+#pragma unroll
+            for (int k = 0; k < V; ++k) cnt[k] = c32[k];
+        } else {
+#pragma unroll
+            for (int off = P; off < 64; off <<= 1)
+#pragma unroll
+                for (int k = 0; k < V; ++k) cnt[k] += __shfl_xor(cnt[k], off);
         }
+#pragma unroll
+        for (int off = P; off < 64; off <<= 1)
+#pragma unroll
+            for (int k = 0; k < V; ++k) los[k] += __shfl_xor(los[k], off);
         if (s == 0 && ract) {
 #pragma unroll
             for (int k = 0; k < V; ++k) {
@@ -569,8 +582,19 @@ struct VarState {
 // Loads of the epilogue's inputs, issued before the transposed sum so they
 // overlap its gathers.
 template <int V, int OPT>
-__device__ __forceinline__ VarState<V, OPT> var_load(const BwdArgs& A, size_t base) {
+__device__ __forceinline__ VarState<V, OPT> var_load(const BwdArgs& A, size_t base, int var, int r0) {
     VarState<V, OPT> st;
+    if constexpr (OPT == kGrad) {
+        // row `var` of the caller's points, one run of R floats
+        const float* p = A.x_in + (size_t)A.var_old[var] * A.B.R + r0;
+        if (V == 1 || A.wide) {
+            st.x = ldv<V>(p);
+        } else {
+#pragma unroll
+            for (int k = 0; k < V; ++k) st.x.v[k] = p[k];
+        }
+        return st;
+    }
     st.x = ldv<V>(A.x + base);
     if constexpr (OPT == kAdam) {
         st.m = ldv<V>(A.m + base);
@@ -580,7 +604,7 @@ __device__ __forceinline__ VarState<V, OPT> var_load(const BwdArgs& A, size_t ba
 }
 
 template <int V, int OPT>
-__device__ __forceinline__ void var_epilogue(const BwdArgs& A, size_t base, int r0, const double (&G)[V],
+__device__ __forceinline__ void var_epilogue(const BwdArgs& A, size_t base, int var, int r0, const double (&G)[V],
                                              VarState<V, OPT> st) {
     VecF<V>& xv = st.x;
     if (A.eval) {
@@ -594,8 +618,14 @@ __device__ __forceinline__ void var_epilogue(const BwdArgs& A, size_t base, int 
     if constexpr (OPT == kGrad) {
         VecF<V> gv;
 #pragma unroll
-        for (int k = 0; k < V; ++k) gv.v[k] = g[k];
-        stv<V>(A.g_out + base, gv);
+        for (int k = 0; k < V; ++k) gv.v[k] = A.scale != nullptr ? A.scale[r0 + k] * g[k] : g[k];
+        float* p = A.grad_out + (size_t)A.var_old[var] * A.B.R + r0;
+        if (V == 1 || A.wide) {
+            stv<V>(p, gv);
+        } else {
+#pragma unroll
+            for (int k = 0; k < V; ++k) p[k] = gv.v[k];
+        }
         return;
     } else if constexpr (OPT == kSgd) {
         VecF<V> tv;
@@ -626,8 +656,8 @@ __device__ __forceinline__ void var_epilogue(const BwdArgs& A, size_t base, int 
 }
 
 template <int V, int OPT>
-__device__ __forceinline__ void var_epilogue(const BwdArgs& A, size_t base, int r0, const double (&G)[V]) {
-    var_epilogue<V, OPT>(A, base, r0, G, var_load<V, OPT>(A, base));
+__device__ __forceinline__ void var_epilogue(const BwdArgs& A, size_t base, int var, int r0, const double (&G)[V]) {
+    var_epilogue<V, OPT>(A, base, var, r0, G, var_load<V, OPT>(A, base, var, r0));
 }
 
 // ---------------------------------------------------------------------------
@@ -681,9 +711,10 @@ __device__ __forceinline__ void bwd_body(const BwdArgs& A, const int bx) {
         if (kEarly && !segtile) {
 #pragma unroll
             for (int j = 0; j < UR; ++j)
-                if (rowin0 + j < (int)d.nreal)
-                    st[j] = var_load<V, OPT>(
-                        A, xbase + (size_t)(A.n_heavy + (tile * kTile + rowin0 + j - A.seg_tiles * kTile)) * B.G + rl);
+                if (rowin0 + j < (int)d.nreal) {
+                    const int var = A.n_heavy + (tile * kTile + rowin0 + j - A.seg_tiles * kTile);
+                    st[j] = var_load<V, OPT>(A, xbase + (size_t)var * B.G + rl, var, r0);
+                }
         }
         // batches of CB columns, then one batch of the last d.len % CB: all
         // entry loads, then all gathers, then the sums in column order (no
@@ -768,9 +799,9 @@ __device__ __forceinline__ void bwd_body(const BwdArgs& A, const int bx) {
             } else {
                 const int var = A.n_heavy + (row - A.seg_tiles * kTile);
                 if constexpr (kEarly)
-                    var_epilogue<V, OPT>(A, xbase + (size_t)var * B.G + rl, r0, G[j], st[j]);
+                    var_epilogue<V, OPT>(A, xbase + (size_t)var * B.G + rl, var, r0, G[j], st[j]);
                 else
-                    var_epilogue<V, OPT>(A, xbase + (size_t)var * B.G + rl, r0, G[j]);
+                    var_epilogue<V, OPT>(A, xbase + (size_t)var * B.G + rl, var, r0, G[j]);
             }
         }
     }
@@ -834,7 +865,7 @@ __device__ __forceinline__ void combine_body(const BwdArgs& A, const int bx, dou
         r = w % B.R;
     }
     const size_t base = ((size_t)(r / B.G) * B.rows_x + h) * B.G + r % B.G;
-    const VarState<1, OPT> st = var_load<1, OPT>(A, base);
+    const VarState<1, OPT> st = var_load<1, OPT>(A, base, h, r);
     const double* sg = A.seg_part + (size_t)(r / B.G) * B.rows_seg * B.G + r % B.G;
     const int p0 = A.seg_first[h];
     const int p1 = A.seg_first[h + 1];
@@ -856,7 +887,7 @@ __device__ __forceinline__ void combine_body(const BwdArgs& A, const int bx, dou
     for (int off = 32; off >= 1; off >>= 1) u = u + __shfl_down(u, off);
     if (lane != 0) return;
     double G[1] = {u};
-    var_epilogue<1, OPT>(A, base, r, G, st);
+    var_epilogue<1, OPT>(A, base, h, r, G, st);
 }
 
 template <int OPT>
@@ -1060,6 +1091,44 @@ __global__ __launch_bounds__(256) void k_init(InitArgs A) {
         A.st->step_size = 0.0f;
         A.st->inv_sqrt_bc2 = 1.0f;
     }
+}
+
+// t at the caller's points, V restarts per thread (the scalar form of k_init
+// spent 7.9 us on 20000 x 64 values: one value and one 64-bit division a thread).
+template <int V>
+__global__ __launch_bounds__(256) void k_points(InitArgs A) {
+    const Blocking B = A.B;
+    const uint32_t per = (uint32_t)B.R / V;
+    const uint64_t idx = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint64_t total = (uint64_t)A.n * per;
+    if (idx < total) {
+        // 32-bit division wherever the index allows
+        const uint32_t i = total <= 0xffffffffull ? (uint32_t)idx / per : (uint32_t)(idx / per);
+        const uint32_t r = (uint32_t)(idx - (uint64_t)i * per) * V;
+        const size_t o = (size_t)A.var_old[i] * B.R + r;
+        const VecF<V> x = ldv<V>(A.x0 + o);
+        VecF<V> t;
+#pragma unroll
+        for (int k = 0; k < V; ++k) t.v[k] = signed_tanh(x.v[k]);
+        stv<V>(A.t + boff(B, B.rows_x, (int)i, (int)r), t);
+        if (A.grad_zero != nullptr && (int32_t)i >= A.n_act)
+#pragma unroll
+            for (int k = 0; k < V; ++k) A.grad_zero[o + k] = 0.0f;
+    }
+    if (idx < (uint64_t)B.R) {
+        const int r = (int)idx;
+        A.t[boff(B, B.rows_x, A.n, r)] = -0.0f;
+        A.a[boff(B, B.rows_a, A.a_zero_row, r)] = 0.0f;
+    }
+    if (idx < (uint64_t)A.umask_words) A.umask[idx] = 0u;
+}
+
+__global__ __launch_bounds__(256) void k_grad_zero(int32_t n, int32_t n_act, int32_t R, const int32_t* var_old,
+                                                   const float* scale, float* grad) {
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (int64_t)(n - n_act) * R) return;
+    const int32_t r = (int32_t)(idx % R);
+    grad[(size_t)var_old[n_act + (int32_t)(idx / R)] * R + r] = scale != nullptr ? scale[r] * 0.0f : 0.0f;
 }
 
 __global__ __launch_bounds__(256) void k_slot_fill(uint32_t* __restrict__ p, int64_t n) {
@@ -1353,6 +1422,27 @@ hipError_t launch_build_slots(const SlotArgs& A, hipStream_t s) {
     if (e != hipSuccess || A.v_tiles == 0) return e;
     const int64_t rows = (int64_t)A.v_tiles * kTile;
     hipLaunchKernelGGL(k_slots, dim3((int)((rows + 255) / 256)), dim3(256), 0, s, A);
+    return hipGetLastError();
+}
+
+hipError_t launch_points(const InitArgs& A, hipStream_t s) {
+    const bool wide = A.B.R % 4 == 0 && A.B.G % 4 == 0 && ((uintptr_t)A.x0 & 15) == 0;
+    int64_t total = (int64_t)A.n * (wide ? A.B.R / 4 : A.B.R);
+    total = std::max<int64_t>(std::max<int64_t>(total, A.B.R), std::max(A.umask_words, 1));
+    const dim3 grid((uint32_t)((total + 255) / 256));
+    if (wide)
+        hipLaunchKernelGGL((k_points<4>), grid, dim3(256), 0, s, A);
+    else
+        hipLaunchKernelGGL((k_points<1>), grid, dim3(256), 0, s, A);
+    return hipGetLastError();
+}
+
+hipError_t launch_grad_zero(int32_t n, int32_t n_act, int32_t R, const int32_t* var_old, const float* scale,
+                            float* grad, hipStream_t s) {
+    const int64_t total = (int64_t)(n - n_act) * R;
+    if (total == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_grad_zero, dim3((int)((total + 255) / 256)), dim3(256), 0, s, n, n_act, R, var_old, scale,
+                       grad);
     return hipGetLastError();
 }
 

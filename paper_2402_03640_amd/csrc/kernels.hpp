@@ -90,12 +90,19 @@ struct BwdArgs {
     float* m;
     float* v;
     float* t;
-    float* g_out;
     uint8_t* best_a;
     const int32_t* improved;
     StepState* st;
     float lr, b1, b2, eps, omb1, omb2;
     const int32_t* seg_first;
+    // gradients straight between the caller's arrays ([n][R], caller variable
+    // order): x is read from x_in and scale[r] * g (scale null: g) written to
+    // grad_out, so no blocked copy of either is made
+    const float* x_in;
+    const float* scale;
+    float* grad_out;
+    const int32_t* var_old;
+    int32_t wide;         // both arrays allow vector access (16-byte aligned)
 };
 
 // One counted iterate of one restart: the trajectory record of a solve.
@@ -147,6 +154,8 @@ struct InitArgs {
     float* vv;
     float* a;
     uint32_t* umask;
+    float* grad_zero;         // launch_points: gradients of the variables in no clause (rows n_act on), or null
+    int32_t n_act;
     float* contrib;           // slot schedules: zeroed (contrib_n floats), else null
     int64_t contrib_n;
     uint8_t* best_a;
@@ -216,6 +225,14 @@ struct SlotArgs {
 hipError_t launch_build_slots(const SlotArgs& A, hipStream_t s);
 
 hipError_t launch_init(const InitArgs& A, hipStream_t s);
+// The start of one evaluation at the caller's points: t of every variable and
+// the constant rows (what launch_init does, without x, moments or bests), and
+// 0 into the gradients of variables in no clause when A.grad_zero is set.
+// Four restarts per thread where R, G and the points' alignment allow.
+hipError_t launch_points(const InitArgs& A, hipStream_t s);
+// grad[var_old[i]][r] = scale[r] * 0 for the variables in no clause.
+hipError_t launch_grad_zero(int32_t n, int32_t n_act, int32_t R, const int32_t* var_old, const float* scale,
+                            float* grad, hipStream_t s);
 hipError_t launch_snapshot(int32_t n_act, const Blocking& B, const float* x, const int32_t* improved,
                            uint8_t* best_a, hipStream_t s);
 hipError_t launch_extract(int32_t n, const Blocking& B, int32_t r, const int32_t* var_old, const uint8_t* best_a,

@@ -465,7 +465,135 @@ __global__ __launch_bounds__(NW * 64) void k_small(const SmallDesc* __restrict__
         }
 }
 
+// One evaluation per workgroup (see EvalSmall).  Bound by latency: the chain is
+// x -> t -> barrier -> clause rows -> barrier -> variable rows, each phase a few
+// dependent reads, against seven launches and two copies of the tiled
+// evaluation.  Same arithmetic and order as the tiled kernels.
+template <int NW>
+__global__ __launch_bounds__(NW * 64) void k_eval_small(EvalSmall E) {
+    constexpr int kThreads = NW * 64;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int64_t red_c[NW];
+    __shared__ double red_l[NW];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int r = blockIdx.x;
+    const int n = E.n;
+    const int crows = E.c_tiles * kTile;
+    const int vrows = E.v_tiles * kTile;
+    float* lt = reinterpret_cast<float*>(smem);
+    float* la = lt + n + 1;
+    double* seg = reinterpret_cast<double*>(smem + align8((size_t)(n + 1 + crows + 1) * 4));
+    for (int i = tid; i < n; i += kThreads) {
+        const size_t e = (size_t)E.var_old[i] * E.R + r;
+        lt[i] = signed_tanh(E.x[e]);
+        if (E.grad != nullptr && i >= E.n_act) E.grad[e] = 0.0f;
+    }
+    if (tid == 0) {
+        lt[n] = -0.0f;
+        la[crows] = 0.0f;
+    }
+    __syncthreads();
+    int64_t cnt = 0;
+    double los = 0.0;
+    for (int row = tid; row < crows; row += kThreads) {
+        const int tile = row >> 6;
+        const int rowin = row & 63;
+        const TileDesc d = ldtile(E.c_tile + __builtin_amdgcn_readfirstlane(tile));
+        const uint32_t* e = E.c_ent + (size_t)d.base + rowin;
+        float f = 0.0f;
+        uint32_t allf = ~0u;
+        if (d.len <= 16) {
+#pragma unroll 4
+            for (uint32_t c = 0; c < d.len; ++c) {
+                const uint32_t en = e[(size_t)c * kTile];
+                const uint32_t b = __float_as_uint(lt[en & kIdx]) ^ (en & kSign);
+                f = f + __uint_as_float(b);
+                allf &= b;
+            }
+        } else {
+            double fd = 0.0;
+#pragma unroll 4
+            for (uint32_t c = 0; c < d.len; ++c) {
+                const uint32_t en = e[(size_t)c * kTile];
+                const uint32_t b = __float_as_uint(lt[en & kIdx]) ^ (en & kSign);
+                fd = fd + (double)__uint_as_float(b);
+                allf &= b;
+            }
+            f = (float)fd;
+        }
+        const bool real = rowin < (int)d.nreal;
+        const int64_t wj = (E.c_w != nullptr && real) ? E.c_w[row] : 1;
+        const bool unsat = real && (d.flags & 1u) == 0 && (allf >> 31) != 0;
+        const bool mu = real && (E.all_mode ? true : unsat);
+        la[row] = mu ? (f * (float)wj) * E.two_over_m : 0.0f;
+        cnt += unsat ? wj : 0;
+        los += mu ? ((double)f * (double)f) * (double)wj : 0.0;
+    }
+    for (int o = 32; o >= 1; o >>= 1) {
+        cnt += __shfl_xor(cnt, o);
+        los += __shfl_xor(los, o);
+    }
+    if (lane == 0) {
+        red_c[wave] = cnt;
+        red_l[wave] = los;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int64_t c = E.w_empty;
+        double l = 0.0;
+        for (int w = 0; w < NW; ++w) {
+            c += red_c[w];
+            l = l + red_l[w];
+        }
+        if (E.unsat != nullptr) E.unsat[r] = c;
+        if (E.loss != nullptr) E.loss[r] = l * E.inv_m;
+    }
+    if (E.grad == nullptr) return;
+    for (int row = tid; row < vrows; row += kThreads) {
+        const int tile = __builtin_amdgcn_readfirstlane(row >> 6);
+        const int rowin = row & 63;
+        const TileDesc d = ldtile(E.v_tile + tile);
+        if (rowin >= (int)d.nreal) continue;
+        const uint32_t* e = E.v_ent + (size_t)d.base + rowin;
+        double G = 0.0;
+#pragma unroll 8
+        for (uint32_t c = 0; c < d.len; ++c) {
+            const uint32_t en = e[(size_t)c * kTile];
+            G = G + (double)__uint_as_float(__float_as_uint(la[en & kIdx]) ^ (en & kSign));
+        }
+        if (tile < E.seg_tiles) {
+            seg[row] = G;
+        } else {
+            const size_t at = (size_t)E.var_old[E.n_heavy + (row - E.seg_tiles * kTile)] * E.R + r;
+            E.grad[at] = grad_of(E.x[at], G);
+        }
+    }
+    if (E.n_heavy == 0) return;
+    __syncthreads();
+    for (int h = wave; h < E.n_heavy; h += NW) {
+        double u = 0.0;
+        const int p1 = E.seg_first[h + 1];
+        for (int p = E.seg_first[h] + lane; p < p1; p += 64) u = u + seg[p];
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) u = u + __shfl_down(u, o);
+        if (lane == 0) {
+            const size_t at = (size_t)E.var_old[h] * E.R + r;
+            E.grad[at] = grad_of(E.x[at], u);
+        }
+    }
+}
+
+size_t eval_small_lds(const HostPlan& P) {
+    return align8((size_t)(P.n + 1 + P.c_tiles * kTile + 1) * 4) + (size_t)P.seg_rows * 8;
+}
+
 }  // namespace
+
+bool eval_small_ok(const HostPlan& P, size_t lds_cap) {
+    return P.nnz <= (1 << 16) && P.n_heavy_wide == 0 && eval_small_lds(P) <= lds_cap;
+}
 
 size_t small_lds_bytes(const HostPlan& P) {
     size_t b = (size_t)(P.n + 1) * 4 + (size_t)(P.c_tiles * kTile + 1) * 4 + (size_t)P.n * 12;
@@ -527,6 +655,25 @@ hipError_t launch_small_as(const SmallDesc* d_descs, int32_t n_desc, int32_t blo
     return hipGetLastError();
 }
 
+template <int NW>
+hipError_t launch_eval_as(const EvalSmall& E, size_t lds, size_t lds_cap, hipStream_t s) {
+    if (lds > lds_cap) return hipErrorInvalidValue;
+    static std::atomic<uint64_t> set_on{0};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev >= 0 && dev < 64 ? uint64_t(1) << dev : 0;
+    if (!bit || !(set_on.load(std::memory_order_acquire) & bit)) {
+        std::lock_guard<std::mutex> lk(g_attr_mu);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_eval_small<NW>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_cap);
+        if (e != hipSuccess) return e;
+        set_on.fetch_or(bit, std::memory_order_release);
+    }
+    hipLaunchKernelGGL((k_eval_small<NW>), dim3(E.R), dim3(NW * 64), lds, s, E);
+    return hipGetLastError();
+}
+
 template <int NW, int RF, int FE>
 hipError_t launch_small_nw(const SmallDesc* d_descs, int32_t n_desc, int32_t blocks, size_t lds_bytes, size_t lds_cap,
                            int32_t stage, hipStream_t s) {
@@ -559,6 +706,13 @@ bool small_reg_ok(const HostPlan& P, int32_t launch_rows) {
             if (d.len > (uint32_t)kRegB) return false;
     }
     return true;
+}
+
+hipError_t launch_eval_small(const EvalSmall& E, const HostPlan& P, size_t lds_cap, hipStream_t s) {
+    if (E.R < 1) return hipErrorInvalidValue;
+    const size_t lds = eval_small_lds(P);
+    if (std::max(P.c_tiles, P.v_tiles) * kTile <= kSmallRows4) return launch_eval_as<4>(E, lds, lds_cap, s);
+    return launch_eval_as<16>(E, lds, lds_cap, s);
 }
 
 hipError_t launch_small(const SmallDesc* d_descs, int32_t n_desc, int32_t blocks, size_t lds_bytes, size_t lds_cap,

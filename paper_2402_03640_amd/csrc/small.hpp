@@ -53,6 +53,33 @@ struct SmallDesc {
     int32_t trace_cap;
 };
 
+// One evaluation (loss, count, gradient) of each of R points in one launch, a
+// workgroup per point with t and the adjoint in LDS.  The points and gradients
+// are the caller's arrays ([n][R], caller variable order); each output may be
+// null.
+struct EvalSmall {
+    const TileDesc* c_tile;
+    const uint32_t* c_ent;
+    const TileDesc* v_tile;
+    const uint32_t* v_ent;
+    const int32_t* seg_first;
+    const int32_t* var_old;
+    const int64_t* c_w;   // weight of each clause row, or null
+    int32_t n, n_act, n_heavy, c_tiles, v_tiles, seg_tiles, seg_rows, R, all_mode;
+    float two_over_m;
+    double inv_m;
+    int64_t w_empty;
+    const float* x;
+    double* loss;         // [R]
+    int64_t* unsat;       // [R]
+    float* grad;
+};
+// Instances it takes: those that fit its LDS, up to 2^16 nonzeros (one
+// workgroup then takes at most about what the launches of the tiled
+// evaluation do) and no variable wider than the 64-slot combine.
+bool eval_small_ok(const HostPlan& P, size_t lds_cap);
+hipError_t launch_eval_small(const EvalSmall& E, const HostPlan& P, size_t lds_cap, hipStream_t s);
+
 // LDS bytes the resident solver needs for an instance's state (per workgroup).
 size_t small_lds_bytes(const HostPlan& P);
 // State plus the plan sides that also fit within `limit` bytes (clause side
