@@ -49,6 +49,8 @@ constexpr int kWaves = kClusterThreads / 64;
 constexpr int kFlagStride = 16;          // u64 per flag: one 128-byte line
 constexpr uint64_t kRegisterTicks = 2000000;  // wall-clock ticks (100 MHz) a cluster waits to fill: 20 ms
 constexpr int kSpinLimit = 1 << 21;      // polls of one flag, about a second
+constexpr int kOneSlots = 4096;           // LDS slots up to which t is exchanged as {t, step} words
+constexpr uint32_t kAltByte = 0x20000;   // second copy of t in LDS (a bit past every record offset)
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -65,8 +67,9 @@ __host__ __device__ __forceinline__ size_t up16(size_t b) { return (b + 15) & ~s
 struct Shared {
     const ClusterGroup* group;
     int member, dead;
-    unsigned long long cnt[2], tot[2];
+    unsigned long long cnt[2], tot[4];
     double los[kWaves];
+    unsigned long long wcnt[kWaves];
 };
 
 // LDS of a workgroup: t of all variables and two constants, own x, m, v, own
@@ -277,11 +280,6 @@ __global__ __launch_bounds__(256) void k_cluster_scalars(float2* scal, int32_t s
     scal[k] = make_float2(ss, ib2);
 }
 
-template <int N>
-struct Cols {
-    static constexpr int value = N;
-};
-
 // A wave-uniform pointer, and a structure behind one, in scalar registers.
 template <typename T>
 __device__ __forceinline__ T* uniform(T* p) {
@@ -289,6 +287,13 @@ __device__ __forceinline__ T* uniform(T* p) {
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
     return (T*)(((uint64_t)hi << 32) | lo);
+}
+// The same pointer, opaque to the compiler: what is loaded through it is loaded
+// there and then, not ahead of a loop.
+template <typename T>
+__device__ __forceinline__ const T* launder(const T* p) {
+    asm volatile("" : "+s"(p));
+    return p;
 }
 template <typename T>
 __device__ __forceinline__ T load_uniform(const T* p) {
@@ -307,10 +312,320 @@ __device__ __forceinline__ T load_uniform(const T* p) {
 // counts).
 __device__ __attribute__((noinline)) float signed_tanh_call(float x) { return signed_tanh(x); }
 
+// One record block of the list that counts (neg: x rounds to true).
+template <int NO, bool WT>
+struct RecordBlock {
+    static constexpr int W = NO <= 2 ? 1 : 2;
+    uint32_t w[8 * W];
+    float wf[WT ? 8 : 1];
+    uint32_t bits;
+    __device__ __forceinline__ void load(const HMS_GLOBAL uint32_t* rec, const HMS_GLOBAL float* wrec, int block,
+                                         bool neg, int lane) {
+        const HMS_GLOBAL uint32_t* bp = rec + (size_t)block * cluster_block_words(NO);
+        bits = bp[(neg ? 64 : 0) + lane];
+        const HMS_GLOBAL u32x4* qp = (const HMS_GLOBAL u32x4*)(bp + 128) + ((neg ? 128 * W : 0) + lane);
+#pragma unroll
+        for (int k = 0; k < 2 * W; ++k) {
+            const u32x4 v = qp[k * 64];
+            w[4 * k] = v.x;
+            w[4 * k + 1] = v.y;
+            w[4 * k + 2] = v.z;
+            w[4 * k + 3] = v.w;
+        }
+        if constexpr (WT) {
+            const HMS_GLOBAL f32x4* fp = (const HMS_GLOBAL f32x4*)(wrec + (size_t)block * 1024) + ((neg ? 128 : 0) + lane);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const f32x4 v = fp[k * 64];
+                wf[4 * k] = v.x;
+                wf[4 * k + 1] = v.y;
+                wf[4 * k + 2] = v.z;
+                wf[4 * k + 3] = v.w;
+            }
+        }
+    }
+};
+
+// Adds records OFF .. OFF + N - 1 of a block to the row's sum of magnitudes.
+// t sits at LDS byte `at` (a power of two past every offset, or 0).
+template <int N, int OFF, int NO, bool WT>
+__device__ __forceinline__ void sum_records(const unsigned char* smem, const uint32_t at, const RecordBlock<NO, WT>& b,
+                                            const float to, const float tom, double& Gm) {
+    constexpr int W = RecordBlock<NO, WT>::W;
+    float t[N][NO];
+#pragma unroll
+    for (int c = 0; c < N; ++c)
+#pragma unroll
+        for (int j = 0; j < NO; ++j) {
+            const uint32_t w = b.w[(OFF + c) * W + (j >> 1)];
+            t[c][j] = *reinterpret_cast<const float*>(smem + (((j & 1 ? w >> 15 : w) & 0x1fffcu) | at));
+        }
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        // sign bit set in lanes whose clause is unsatisfied: the own literal is
+        // false on this list, and so is every other
+        uint32_t fl = ~0u;
+#pragma unroll
+        for (int j = 0; j < NO; ++j)
+            fl &= __float_as_uint(t[c][j]) ^ (b.w[(OFF + c) * W + (j >> 1)] << (j & 1 ? 30 : 31));
+        // magnitudes in clause order: z is the own term until its place is reached
+        uint32_t z = __float_as_uint(to);
+        float f = fabsf(t[c][0]);
+#pragma unroll
+        for (int j = 2; j <= NO; ++j) {
+            uint32_t after;  // all ones where the own literal comes after literal j
+            asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(after) : "v"(b.bits), "n"(OFF + c + 8 * (j - 2)));
+            const uint32_t oj = __float_as_uint(t[c][j - 1]);
+            uint32_t take;
+            asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(take) : "v"(after), "v"(oj), "v"(z));
+            asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(z) : "v"(after), "v"(z), "v"(oj));
+            f = f + fabsf(__uint_as_float(take));
+        }
+        f = f + fabsf(__uint_as_float(z));
+        if constexpr (WT) f = f * b.wf[OFF + c];
+        uint32_t a = __float_as_uint(f * tom) & (uint32_t)((int)fl >> 31);
+        asm("" : "+v"(a));  // the mask stays on the 32-bit value
+        Gm = Gm + (double)__uint_as_float(a);
+    }
+}
+
+// The first `left` records of a block (1 to 8; whole pairs, the rest is inert),
+// up to 16 gathers together.
+template <int NO, bool WT>
+__device__ __forceinline__ void sum_block(const unsigned char* smem, const uint32_t at, const RecordBlock<NO, WT>& b,
+                                          const int left, const float to, const float tom, double& Gm) {
+    if constexpr (NO == 2) {
+        if (left > 6) sum_records<8, 0>(smem, at, b, to, tom, Gm);
+        else if (left > 4) sum_records<6, 0>(smem, at, b, to, tom, Gm);
+        else if (left > 2) sum_records<4, 0>(smem, at, b, to, tom, Gm);
+        else sum_records<2, 0>(smem, at, b, to, tom, Gm);
+    } else {
+        if (left > 2) sum_records<4, 0>(smem, at, b, to, tom, Gm);
+        else sum_records<2, 0>(smem, at, b, to, tom, Gm);
+        if (left > 6) sum_records<4, 4>(smem, at, b, to, tom, Gm);
+        else if (left > 4) sum_records<2, 4>(smem, at, b, to, tom, Gm);
+    }
+}
+
+// The sum over the wavefront, in every lane.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);   // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);   // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);   // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);   // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// One row's part in the count and the loss.
+template <bool WT>
+__device__ __forceinline__ void count_row(const bool unsat, const float f, const HMS_GLOBAL int64_t* c_w,
+                                          const size_t row, const bool want_loss, unsigned long long& cnt, double& los) {
+    if constexpr (WT) {
+        const int64_t w = unsat ? c_w[row] : 0;
+        cnt += (unsigned long long)w;
+        if (want_loss && unsat) los += ((double)f * (double)f) * (double)w;
+    } else {
+        cnt += (unsigned long long)__popcll(__ballot(unsat));
+        if (want_loss && unsat) los += (double)f * (double)f;
+    }
+}
+
+// Unsatisfied weight of clause tiles ct0, ct0 + stride, ...; the loss terms are
+// added to los.  Both are the wavefront's sums.
+template <bool WT>
+__device__ __forceinline__ unsigned long long count_clauses(const unsigned char* smem, const uint32_t at,
+                                                            const TileDesc* c_tile, const HMS_GLOBAL uint32_t* cslot,
+                                                            const HMS_GLOBAL int64_t* c_w, const int c_tiles,
+                                                            const int ct0, const int stride, const int lane,
+                                                            const bool want_loss, double& los) {
+    unsigned long long cnt = 0;
+    double l = 0.0;
+    for (int ct = ct0; ct < c_tiles; ct += stride) {
+        const TileDesc d = ldtile(c_tile + ct);
+        if (d.flags & 1u) continue;  // tautologies are never unsatisfied
+        float f = 0.0f;
+        uint32_t all = ~0u;
+#pragma unroll 5
+        for (uint32_t c = 0; c < d.len; ++c) {
+            const uint32_t en = cslot[(size_t)d.base + (size_t)c * kTile + lane];
+            const uint32_t b = *reinterpret_cast<const uint32_t*>(smem + (((en & kIdx) << 2) | at)) ^ (en & kSign);
+            f = f + __uint_as_float(b);
+            all &= b;
+        }
+        count_row<WT>(lane < (int)d.nreal && (all >> 31) != 0, f, c_w, (size_t)ct * kTile + lane, want_loss, cnt, l);
+    }
+    if constexpr (WT)
+        for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o);
+    if (want_loss) {
+        for (int o = 32; o >= 1; o >>= 1) l += __shfl_xor(l, o);
+        los += l;
+    }
+    return cnt;
+}
+
+// One clause tile's entries in registers (clauses of at most kClusterMaxK
+// literals), for a wavefront that counts it every time.
+struct ClauseCache {
+    uint32_t en[kClusterMaxK];
+    int len = 0, tile = 0;
+    bool real = false;
+    __device__ __forceinline__ void load(const TileDesc* c_tile, const HMS_GLOBAL uint32_t* cslot, const int ct,
+                                         const int c_tiles, const int lane) {
+        if (ct >= c_tiles) return;
+        const TileDesc d = ldtile(c_tile + ct);
+        if (d.flags & 1u) return;
+        tile = ct;
+        len = (int)d.len;
+        real = lane < (int)d.nreal;
+#pragma unroll
+        for (int c = 0; c < kClusterMaxK; ++c)
+            if (c < len) en[c] = cslot[(size_t)d.base + (size_t)c * kTile + lane];
+    }
+    template <bool WT>
+    __device__ __forceinline__ unsigned long long count(const unsigned char* smem, const uint32_t at,
+                                                        const HMS_GLOBAL int64_t* c_w, const bool want_loss, double& los,
+                                                        const int lane) const {
+        los = 0.0;
+        unsigned long long cnt = 0;
+        if (len == 0) return 0;
+        float f = 0.0f;
+        uint32_t all = ~0u, b[kClusterMaxK];
+#pragma unroll
+        for (int c = 0; c < kClusterMaxK; ++c)
+            if (c < len)
+                b[c] = *reinterpret_cast<const uint32_t*>(smem + (((en[c] & kIdx) << 2) | at)) ^ (en[c] & kSign);
+#pragma unroll
+        for (int c = 0; c < kClusterMaxK; ++c)
+            if (c < len) {
+                f = f + __uint_as_float(b[c]);
+                all &= b[c];
+            }
+        count_row<WT>(real && (all >> 31) != 0, f, c_w, (size_t)tile * kTile + lane, want_loss, cnt, los);
+        if constexpr (WT)
+            for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o);
+        if (want_loss)
+            for (int o = 32; o >= 1; o >>= 1) los += __shfl_xor(los, o);
+        return cnt;
+    }
+};
+
+// The flag exchange, after the workgroup's flag is out: a wavefront waits for
+// its one or two peers (one per lane), then copies its part of their slices
+// into LDS (16 / C wavefronts per peer, two whole slices each with 32
+// workgroups).
+__device__ __forceinline__ void collect(const ClusterGroup& G, Shared& sh, unsigned char* smem, HMS_GLOBAL float* tb,
+                                        const int member, const int C, const int log2C, const int slice,
+                                        const int wave, const int lane, const int step, const bool eval,
+                                        const bool last) {
+    const int par = step & 1;
+    const int parts = C <= kWaves ? kWaves >> log2C : 1;
+    const int rounds = C <= kWaves ? 1 : C / kWaves;
+    const int pw = rounds == 1 ? wave / parts : wave;
+    const int part = rounds == 1 ? wave % parts : 0;
+    const int peer0 = (pw + member) & (C - 1);
+    const int peer1 = rounds == 1 ? peer0 : (pw + kWaves + member) & (C - 1);
+    const HMS_GLOBAL uint64_t* fl =
+        (const HMS_GLOBAL uint64_t*)G.flags + (size_t)(lane & 1 ? peer1 : peer0) * kFlagStride + par;
+    uint64_t f = 0;
+    bool ok = lane >= 2;
+    for (int spins = 0; spins <= kSpinLimit; ++spins) {
+        if (!ok) {
+            f = __hip_atomic_load(fl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ok = (uint32_t)f == (uint32_t)(step + 1);
+        }
+        if (__ballot(!ok) == 0) break;
+    }
+    if (__ballot(!ok) != 0) sh.dead = 1;
+    if (eval && part == 0 && lane < rounds) atomicAdd(&sh.tot[par], (unsigned long long)(f >> 32));
+    if (last) return;
+    // device-scope loads: from the L2, never from this CU's L1
+    const int P = C * slice;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)tb, 0, P * 4, 0x00020000);
+    const int s4 = slice / 4;
+    u32x4* dst = reinterpret_cast<u32x4*>(smem);
+    const int stride = parts * 64;
+    const int n4 = rounds * s4;  // 16-byte pieces of both slices
+    for (int i0 = part * 64; i0 < n4; i0 += 6 * stride) {
+        u32x4 v[6];
+        int at[6];
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            const int i = i0 + j * stride + lane;
+            at[j] = i < s4 ? peer0 * s4 + i : peer1 * s4 + (i - s4);
+            if (i < n4) v[j] = __builtin_amdgcn_raw_buffer_load_b128(rs, at[j] * 16, 0, 16);
+        }
+#pragma unroll
+        for (int j = 0; j < 6; ++j)
+            if (i0 + j * stride + lane < n4) dst[at[j]] = v[j];
+    }
+}
+
+// Initial value of variable v (o: its place in the caller's order).
+__device__ __forceinline__ float start_x(const ClusterDesc& D, const int r, const int v, int& o) {
+    o = D.var_old[v];
+    if (D.x0 != nullptr) return D.x0[(size_t)o * D.R + r];
+    const uint64_t z = splitmix64(D.seed + (uint64_t)r, (uint64_t)o + 1);
+    return 2.0f * ((float)(z >> 40) * (1.0f / 16777216.0f)) - 1.0f;
+}
+
+// Variables in no clause keep their start (all threads of one workgroup).
+__device__ __forceinline__ void keep_inactive(const ClusterDesc& D, const int r, const int tid, uint8_t* best_a) {
+    for (int v = D.n_act + tid; v < D.n; v += kClusterThreads) {
+        int o;
+        const float x = start_x(D, r, v, o);
+        const size_t e = (size_t)o * D.R + r;
+        if (!D.resume) best_a[o] = x > 0.0f ? 1 : 0;
+        if (D.x_final != nullptr) D.x_final[e] = x;
+        if (D.m_final != nullptr) {
+            D.m_final[e] = D.m0 != nullptr ? D.m0[e] : 0.0f;
+            D.v_final[e] = D.v0 != nullptr ? D.v0[e] : 0.0f;
+        }
+    }
+}
+
+// Registration of a workgroup (one thread): its place on its XCD, then the
+// wait until the whole cluster has arrived.  sh.group is null when there is
+// nothing to do: no cluster left for this ticket, or one that did not fill.
+__device__ void enroll(const ClusterLaunch& A, Shared& sh) {
+    const int x = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kXcds - 1);  // XCC_ID
+    int tk = __hip_atomic_fetch_add(A.tickets + x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const ClusterGroup* g = nullptr;
+    for (int i = A.off[x]; i < A.off[x + 1]; ++i) {
+        if (tk < A.groups[i].C) {
+            g = A.groups + i;
+            break;
+        }
+        tk -= A.groups[i].C;
+    }
+    if (g != nullptr) {
+        int32_t* ctl = g->ctl;
+        const int before = __hip_atomic_fetch_add(ctl, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int expect = 0;
+        if (before == g->C - 1)
+            __hip_atomic_compare_exchange_strong(ctl + 1, &expect, 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t t0 = wall_clock64();
+        int go = 0;
+        while ((go = __hip_atomic_load(ctl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
+            if (wall_clock64() - t0 > kRegisterTicks) {
+                expect = 0;
+                __hip_atomic_compare_exchange_strong(ctl + 1, &expect, 2, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (go != 1) g = nullptr;
+    }
+    sh.group = g;
+    sh.member = tk;
+    sh.dead = 0;
+    sh.cnt[0] = sh.cnt[1] = sh.tot[0] = sh.tot[1] = sh.tot[2] = sh.tot[3] = 0;
+}
+
 template <int NO, bool WT>
 __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     constexpr int W = NO <= 2 ? 1 : 2;
-    constexpr int BW = cluster_block_words(NO);
     extern __shared__ __align__(16) unsigned char smem[];
     Shared& sh = *reinterpret_cast<Shared*>(smem + A.shared_off);
 
@@ -318,41 +633,7 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // ---- registration ---------------------------------------------------------
-    if (tid == 0) {
-        const int x = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kXcds - 1);  // XCC_ID
-        int tk = __hip_atomic_fetch_add(A.tickets + x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const ClusterGroup* g = nullptr;
-        for (int i = A.off[x]; i < A.off[x + 1]; ++i) {
-            if (tk < A.groups[i].C) {
-                g = A.groups + i;
-                break;
-            }
-            tk -= A.groups[i].C;
-        }
-        if (g != nullptr) {
-            int32_t* ctl = g->ctl;
-            const int before = __hip_atomic_fetch_add(ctl, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int expect = 0;
-            if (before == g->C - 1)
-                __hip_atomic_compare_exchange_strong(ctl + 1, &expect, 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
-            const uint64_t t0 = wall_clock64();
-            int go = 0;
-            while ((go = __hip_atomic_load(ctl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
-                if (wall_clock64() - t0 > kRegisterTicks) {
-                    expect = 0;
-                    __hip_atomic_compare_exchange_strong(ctl + 1, &expect, 2, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
-            if (go != 1) g = nullptr;
-        }
-        sh.group = g;
-        sh.member = tk;
-        sh.dead = 0;
-        sh.cnt[0] = sh.cnt[1] = sh.tot[0] = sh.tot[1] = 0;
-    }
+    if (tid == 0) enroll(A, sh);
     __syncthreads();
     const ClusterGroup* gp = uniform(sh.group);
     if (gp == nullptr) return;
@@ -376,16 +657,10 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     uint8_t* best_a = D.best_a + (size_t)r * n;
 
     // ---- initial point ----------------------------------------------------------
-    auto initial = [&](int v, int& o) {
-        o = D.var_old[v];
-        if (D.x0 != nullptr) return D.x0[(size_t)o * D.R + r];
-        const uint64_t z = splitmix64(D.seed + (uint64_t)r, (uint64_t)o + 1);
-        return 2.0f * ((float)(z >> 40) * (1.0f / 16777216.0f)) - 1.0f;
-    };
     for (int i = tid; i < P; i += kClusterThreads) {
         const int v = D.var[i];
         int o = 0;
-        const float x = v >= 0 ? initial(v, o) : 0.0f;
+        const float x = v >= 0 ? start_x(D, r, v, o) : 0.0f;
         lt[i] = signed_tanh(x);
         const int l = i - member * slice;
         if (l >= 0 && l < slice) {
@@ -398,19 +673,7 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
         lt[P] = -0.0f;     // a literal that is false
         lt[P + 1] = 0.0f;  // a literal that is true
     }
-    // inactive variables keep their start
-    if (member == 0)
-        for (int v = n_act + tid; v < n; v += kClusterThreads) {
-            int o;
-            const float x = initial(v, o);
-            const size_t e = (size_t)o * D.R + r;
-            if (!D.resume) best_a[o] = x > 0.0f ? 1 : 0;
-            if (D.x_final != nullptr) D.x_final[e] = x;
-            if (D.m_final != nullptr) {
-                D.m_final[e] = D.m0 != nullptr ? D.m0[e] : 0.0f;
-                D.v_final[e] = D.v0 != nullptr ? D.v0[e] : 0.0f;
-            }
-        }
+    if (member == 0) keep_inactive(D, r, tid, best_a);
     __syncthreads();
     const int32_t* my_var = D.var + member * slice;  // own variables, by own slot
     for (int q = wave; q < ntl; q += kWaves) {
@@ -437,90 +700,16 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     const uint32_t* scal = reinterpret_cast<const uint32_t*>(D.scal);
     const int64_t w_empty = D.w_empty;
 
-    // copies: wavefront w takes part `part` of `parts` of a peer's slice
-    // (two whole slices with 32 workgroups)
-    const int parts = C <= kWaves ? kWaves >> log2C : 1;
-    const int rounds = C <= kWaves ? 1 : C / kWaves;
-
     // own tiles of this wavefront
     const int my_tiles = ntl > wave ? (ntl - 1 - wave) / kWaves + 1 : 0;
     auto own_tile = [&](int i) { return i * kWaves + wave; };
-    // one record block of the list that counts (neg: x rounds to true), loaded
-    // one block ahead
-    struct Block {
-        uint32_t w[8 * W];
-        float wf[WT ? 8 : 1];
-        uint32_t bits;
-    };
-    auto fetch = [&](Block& b, int block, bool neg) {
-        const HMS_GLOBAL uint32_t* bp = rec + (size_t)block * BW;
-        b.bits = bp[(neg ? 64 : 0) + lane];
-        const HMS_GLOBAL u32x4* qp = (const HMS_GLOBAL u32x4*)(bp + 128) + ((neg ? 128 * W : 0) + lane);
-#pragma unroll
-        for (int k = 0; k < 2 * W; ++k) {
-            const u32x4 v = qp[k * 64];
-            b.w[4 * k] = v.x;
-            b.w[4 * k + 1] = v.y;
-            b.w[4 * k + 2] = v.z;
-            b.w[4 * k + 3] = v.w;
-        }
-        if constexpr (WT) {
-            const HMS_GLOBAL f32x4* fp = (const HMS_GLOBAL f32x4*)(wrec + (size_t)block * 1024) + ((neg ? 128 : 0) + lane);
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const f32x4 v = fp[k * 64];
-                b.wf[4 * k] = v.x;
-                b.wf[4 * k + 1] = v.y;
-                b.wf[4 * k + 2] = v.z;
-                b.wf[4 * k + 3] = v.w;
-            }
-        }
-    };
-    // records OFF .. OFF + N - 1 of a block
-    auto sum_records = [&](auto nc, auto oc, const Block& b, const float to, double& Gm) {
-        constexpr int N = decltype(nc)::value, OFF = decltype(oc)::value;
-        float t[N][NO];
-#pragma unroll
-        for (int c = 0; c < N; ++c)
-#pragma unroll
-            for (int j = 0; j < NO; ++j) {
-                const uint32_t w = b.w[(OFF + c) * W + (j >> 1)];
-                t[c][j] = *reinterpret_cast<const float*>(smem + ((j & 1 ? w >> 15 : w) & 0x1fffcu));
-            }
-#pragma unroll
-        for (int c = 0; c < N; ++c) {
-            // sign bit set in lanes whose clause is unsatisfied: the own literal
-            // is false on this list, and so is every other
-            uint32_t fl = ~0u;
-#pragma unroll
-            for (int j = 0; j < NO; ++j)
-                fl &= __float_as_uint(t[c][j]) ^ (b.w[(OFF + c) * W + (j >> 1)] << (j & 1 ? 30 : 31));
-            // magnitudes in clause order: z is the own term until its place is reached
-            uint32_t z = __float_as_uint(to);
-            float f = fabsf(t[c][0]);
-#pragma unroll
-            for (int j = 2; j <= NO; ++j) {
-                uint32_t after;  // all ones where the own literal comes after literal j
-                asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(after) : "v"(b.bits), "n"(OFF + c + 8 * (j - 2)));
-                const uint32_t oj = __float_as_uint(t[c][j - 1]);
-                uint32_t take;
-                asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(take) : "v"(after), "v"(oj), "v"(z));
-                asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(z) : "v"(after), "v"(z), "v"(oj));
-                f = f + fabsf(__uint_as_float(take));
-            }
-            f = f + fabsf(__uint_as_float(z));
-            if constexpr (WT) f = f * b.wf[OFF + c];
-            uint32_t a = __float_as_uint(f * tom) & (uint32_t)((int)fl >> 31);
-            asm("" : "+v"(a));  // the mask stays on the 32-bit value
-            Gm = Gm + (double)__uint_as_float(a);
-        }
-    };
+    RecordBlock<NO, WT> nx;  // the next record block, loaded one block ahead
+    auto fetch = [&](RecordBlock<NO, WT>& b, int block, bool neg) { b.load(rec, wrec, block, neg, lane); };
     auto tile_info = [&](int i) {
         const uint32_t* p = reinterpret_cast<const uint32_t*>(tiles + (own_tile(i) * C + member));
         return make_int2((int)ldc(p), (int)ldc(p + 1));
     };
     int2 tn = make_int2(0, 0);
-    Block nx;
     if (my_tiles > 0) {
         tn = tile_info(0);
         fetch(nx, __builtin_amdgcn_readfirstlane(tn.x), lx[own_tile(0) * 64 + lane] > 0.0f);
@@ -534,40 +723,16 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
         const bool want_loss = last || (eval && D.trace != nullptr);
         const int par = step & 1;
         HMS_GLOBAL float* tb = (HMS_GLOBAL float*)G.tbuf + (size_t)par * P;
-        // ---- count and loss of this iterate: the clause tiles, dealt out over
-        // the cluster's wavefronts from the last one on (the variable tiles
-        // start at the first)
+        // ---- count and loss of this iterate ------------------------------------
         if (eval) {
-            unsigned long long cnt = 0;
+            // the clause tiles are dealt out from the last wavefront on (the
+            // variable tiles start at the first)
             double los = 0.0;
-            for (int ct = (kWaves - 1 - wave) * C + member; ct < c_tiles; ct += kWaves * C) {
-                const TileDesc d = ldtile(c_tile + ct);
-                if (d.flags & 1u) continue;  // tautologies are never unsatisfied
-                float f = 0.0f;
-                uint32_t all = ~0u;
-                for (uint32_t c = 0; c < d.len; ++c) {
-                    const uint32_t en = cslot[(size_t)d.base + (size_t)c * kTile + lane];
-                    const uint32_t b = __float_as_uint(lt[en & kIdx]) ^ (en & kSign);
-                    f = f + __uint_as_float(b);
-                    all &= b;
-                }
-                const bool unsat = lane < (int)d.nreal && (all >> 31) != 0;
-                if constexpr (WT) {
-                    const int64_t w = unsat ? c_w[(size_t)ct * kTile + lane] : 0;
-                    cnt += (unsigned long long)w;
-                    if (want_loss && unsat) los += ((double)f * (double)f) * (double)w;
-                } else {
-                    cnt += (unsigned long long)__popcll(__ballot(unsat));
-                    if (want_loss && unsat) los += (double)f * (double)f;
-                }
-            }
-            if constexpr (WT)
-                for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o);
+            const unsigned long long cnt = count_clauses<WT>(smem, 0u, c_tile, cslot, c_w, c_tiles,
+                                                             (kWaves - 1 - wave) * C + member, kWaves * C, lane,
+                                                             want_loss, los);
             if (lane == 0 && cnt != 0) atomicAdd(&sh.cnt[par], cnt);
-            if (want_loss) {
-                for (int o = 32; o >= 1; o >>= 1) los += __shfl_xor(los, o);
-                if (lane == 0) sh.los[wave] = los;
-            }
+            if (want_loss && lane == 0) sh.los[wave] = los;
         }
         // ---- transposed sums and optimizer step of the own variables --------
         float2 sc = make_float2(0.0f, 1.0f);
@@ -591,25 +756,14 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
                 if (more) tn = tile_info(i + 1);
                 const float xn = lx[own_tile(more ? i + 1 : i) * 64 + lane];
                 for (int k = 0; k < len; k += 8) {
-                    Block b = nx;
+                    RecordBlock<NO, WT> b = nx;
 #pragma unroll
                     for (int j = 0; j < 8 * W; ++j) asm volatile("" : "+v"(b.w[j]));
                     asm volatile("" : "+v"(b.bits));
                     const int left = len - k;
                     if (left > 8) fetch(nx, tb0 + (k >> 3) + 1, xo > 0.0f);
                     else if (more) fetch(nx, __builtin_amdgcn_readfirstlane(tn.x), xn > 0.0f);
-                    // up to 16 gathers go out together
-                    if constexpr (NO == 2) {
-                        if (left > 6) sum_records(Cols<8>{}, Cols<0>{}, b, to, Gm);
-                        else if (left > 4) sum_records(Cols<6>{}, Cols<0>{}, b, to, Gm);
-                        else if (left > 2) sum_records(Cols<4>{}, Cols<0>{}, b, to, Gm);
-                        else sum_records(Cols<2>{}, Cols<0>{}, b, to, Gm);
-                    } else {
-                        if (left > 2) sum_records(Cols<4>{}, Cols<0>{}, b, to, Gm);
-                        else sum_records(Cols<2>{}, Cols<0>{}, b, to, Gm);
-                        if (left > 6) sum_records(Cols<4>{}, Cols<4>{}, b, to, Gm);
-                        else if (left > 4) sum_records(Cols<2>{}, Cols<4>{}, b, to, Gm);
-                    }
+                    sum_block(smem, 0u, b, left, to, tom, Gm);
                 }
                 // a positive literal in the loss adds -a, a negative one +a (0.0 - 0.0 keeps an empty sum +0)
                 const double Gs = xo > 0.0f ? Gm : 0.0 - Gm;
@@ -652,48 +806,7 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
             sh.tot[par ^ 1] = 0;
         }
         // ---- every workgroup's new t (and count) ------------------------------
-        // a wavefront waits for its one or two peers (one per lane), then
-        // copies its part of their slices
-        {
-            const int pw = rounds == 1 ? wave / parts : wave;
-            const int part = rounds == 1 ? wave % parts : 0;
-            const int peer0 = (pw + member) & (C - 1);
-            const int peer1 = rounds == 1 ? peer0 : (pw + kWaves + member) & (C - 1);
-            const HMS_GLOBAL uint64_t* fl =
-                (const HMS_GLOBAL uint64_t*)G.flags + (size_t)(lane & 1 ? peer1 : peer0) * kFlagStride + par;
-            uint64_t f = 0;
-            bool ok = lane >= 2;
-            for (int spins = 0; spins <= kSpinLimit; ++spins) {
-                if (!ok) {
-                    f = __hip_atomic_load(fl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    ok = (uint32_t)f == (uint32_t)(step + 1);
-                }
-                if (__ballot(!ok) == 0) break;
-            }
-            if (__ballot(!ok) != 0) sh.dead = 1;
-            if (eval && part == 0 && lane < rounds) atomicAdd(&sh.tot[par], (unsigned long long)(f >> 32));
-            if (!last) {
-                // device-scope loads: from the L2, never from this CU's L1
-                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)tb, 0, P * 4, 0x00020000);
-                const int s4 = slice / 4;
-                u32x4* dst = reinterpret_cast<u32x4*>(lt);
-                const int stride = parts * 64;
-                const int n4 = rounds * s4;  // 16-byte pieces of both slices
-                for (int i0 = part * 64; i0 < n4; i0 += 6 * stride) {
-                    u32x4 v[6];
-                    int at[6];
-#pragma unroll
-                    for (int j = 0; j < 6; ++j) {
-                        const int i = i0 + j * stride + lane;
-                        at[j] = i < s4 ? peer0 * s4 + i : peer1 * s4 + (i - s4);
-                        if (i < n4) v[j] = __builtin_amdgcn_raw_buffer_load_b128(rs, at[j] * 16, 0, 16);
-                    }
-#pragma unroll
-                    for (int j = 0; j < 6; ++j)
-                        if (i0 + j * stride + lane < n4) dst[at[j]] = v[j];
-                }
-            }
-        }
+        collect(G, sh, smem, tb, member, C, log2C, slice, wave, lane, step, eval, last);
         __syncthreads();
         if (__builtin_amdgcn_readfirstlane(sh.dead)) break;
         if (eval) {
@@ -743,30 +856,416 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     }
 }
 
+// At most one variable tile per wavefront: x, m, v and the records of the list
+// in use stay in registers (the records are loaded again when a variable's
+// rounding turns), and what the next step needs of x alone (sech^2) is taken
+// while the exchange is under way.  A step is one chain of latencies, so every
+// link counts.
+//
+// EX (up to kOneSlots LDS slots): t goes out as 64-bit words {t, step} and every
+// thread polls the slots it copies, so there is no flag to wait for: the
+// workgroup barrier before it, the wait for the stores' acknowledgement and one
+// round trip through the L2 go.  t is held twice in LDS (a slow wavefront still
+// gathers the old values while others fill in the new), the second copy at byte
+// kAltByte.  The lower half of the wavefronts holds the variable tiles and
+// copies t; those without a tile count, their clause tiles' entries in
+// registers, and publish {step, count} per wavefront, which the upper half
+// collects one step later, when it has long arrived; the best is brought up to
+// date then.  Collected counts are summed over lanes before they go to LDS (64
+// atomics on one address held the barrier for 1.1 us).  Counts and losses are
+// kept for four steps: a workgroup may be one step ahead of another that still
+// collects the step before.
+//
+// us a step, against the flag exchange, the form for many tiles and the
+// resident solver: mixed n = 1000, 16 restarts 2.74 counting every step and 2.65
+// every 50 (3.49 and 2.87; 3.68 and 3.44; 3.63 and 3.09); 3-CNF n = 4000, one
+// restart 2.56 (2.79; 3.40; -).  More wavefronts for t and fewer for the count
+// lose with a count every step (4.7 with half of the wavefronts counting).
+template <int NO, bool WT, bool EX>
+__global__ __launch_bounds__(kClusterThreads) void k_cluster_one(ClusterLaunch A) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    Shared& sh = *reinterpret_cast<Shared*>(smem + A.shared_off);
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid == 0) enroll(A, sh);
+    __syncthreads();
+    const ClusterGroup* gp = uniform(sh.group);
+    if (gp == nullptr) return;
+    const ClusterGroup G = load_uniform(gp);
+    const ClusterDesc* dp = G.desc;
+    const int member = __builtin_amdgcn_readfirstlane(sh.member);
+    const int C = G.C;
+    const int r = G.r;
+    int P, slice;
+    bool mine, own_bit = false;
+    int var = -1, o = 0, best_step;
+    float x = 0.0f, m = 0.0f, v = 0.0f;
+    int64_t best;
+    RecordBlock<NO, WT> b0, b1;
+    int len = 0, block0 = 0;
+    ClauseCache cache;
+    float tom, lr;
+    AdamCoef co;
+    int T, K, opt, kc;
+    const uint32_t* scal;
+    const HMS_GLOBAL int64_t* c_w;
+    // EX: the slots this thread copies (bit j: slot tid + 512 j is a real
+    // tile's) and whether it collects a count word
+    constexpr int kHalf = kClusterThreads / 2;
+    constexpr int NP = kOneSlots / kHalf;
+    int CW;  // counting wavefronts, those without a tile (the last CW)
+    uint32_t todo_t = 0;
+    bool todo_c = false, counting;
+    {
+    const ClusterDesc D = load_uniform(launder(dp));
+    slice = D.slice;
+    P = C * slice;
+    CW = kWaves - slice / 64;
+    mine = wave * C + member < D.v_tiles;  // this wavefront's tile
+    float* lt = reinterpret_cast<float*>(smem);
+    uint8_t* best_a = D.best_a + (size_t)r * D.n;
+
+    // ---- initial point ----------------------------------------------------------
+    for (int i = tid; i < P; i += kClusterThreads) {
+        const int v = D.var[i];
+        int o;
+        lt[i] = v >= 0 ? signed_tanh(start_x(D, r, v, o)) : 0.0f;
+    }
+    if (tid == 0)
+        for (int k = 0; k < (EX ? 2 : 1); ++k) {
+            float* p = reinterpret_cast<float*>(smem + (k ? kAltByte : 0u));
+            p[P] = -0.0f;     // a literal that is false
+            p[P + 1] = 0.0f;  // a literal that is true
+        }
+    if (member == 0) keep_inactive(D, r, tid, best_a);
+    if (mine) var = D.var[member * slice + wave * 64 + lane];
+    if (var >= 0) {
+        x = start_x(D, r, var, o);
+        const size_t e = (size_t)o * D.R + r;
+        if (D.m0 != nullptr) m = D.m0[e];
+        if (D.v0 != nullptr) v = D.v0[e];
+        own_bit = D.resume ? best_a[o] != 0 : x > 0.0f;
+    }
+    best = D.resume ? D.best[r] : D.best0;
+    best_step = D.resume ? D.best_step[r] : -1;
+    co = AdamCoef{D.b1, D.b2, D.eps, D.omb1, D.omb2};
+    tom = D.two_over_m;
+    lr = D.lr;
+    T = D.T;
+    K = D.K;
+    opt = D.opt;
+    kc = D.step0 % K;
+    scal = reinterpret_cast<const uint32_t*>(D.scal);
+    c_w = (const HMS_GLOBAL int64_t*)D.c_w;
+    if (mine) {
+        const uint32_t* p = reinterpret_cast<const uint32_t*>(D.tile + (wave * C + member));
+        block0 = __builtin_amdgcn_readfirstlane((int)ldc(p));
+        len = __builtin_amdgcn_readfirstlane((int)ldc(p + 1));
+        const HMS_GLOBAL uint32_t* rec = (const HMS_GLOBAL uint32_t*)D.rec;
+        const HMS_GLOBAL float* wrec = (const HMS_GLOBAL float*)D.wrec;
+        b0.load(rec, wrec, block0, x > 0.0f, lane);
+        if (len > 8) b1.load(rec, wrec, block0 + 1, x > 0.0f, lane);
+    }
+    if constexpr (EX) {
+        if (tid < kHalf) {
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                const int i = tid + j * kHalf;
+                if (i < P && (i % slice) / 64 * C + i / slice < D.v_tiles) todo_t |= 1u << j;
+            }
+        }
+        // word i: workgroup i / CW, its wavefront kWaves - 1 - i % CW.  Published
+        // as far as there are clause tiles, the last wavefront's always (the
+        // loss goes before it)
+        const int i = tid - kHalf;
+        todo_c = i >= 0 && i < CW * C && (i % CW == 0 || i % CW * C + i / CW < D.c_tiles);
+    }
+    counting = !EX || (wave >= kWaves - CW && (wave == kWaves - 1 || (kWaves - 1 - wave) * C + member < D.c_tiles));
+    if (EX && counting)
+        cache.load(D.c_tile, (const HMS_GLOBAL uint32_t*)D.cslot, (kWaves - 1 - wave) * C + member, D.c_tiles, lane);
+    }
+    // from here on what only some steps need is read again where it is needed:
+    // kept, it would fill the scalar registers and spill
+    const int np = (P + kHalf - 1) / kHalf;
+    HMS_GLOBAL uint64_t* words = (HMS_GLOBAL uint64_t*)G.tbuf;   // [2][P]
+    HMS_GLOBAL uint64_t* counts = (HMS_GLOBAL uint64_t*)G.flags; // [4][CW C]
+    float to = signed_tanh(x);
+    float s2 = sech2f(x);
+    bool neg = x > 0.0f;
+    bool pend = false, pend_was = false;  // the step before was counted; the rounding it had
+    // this thread's count word of iterate `it`, when it has arrived
+    auto count_of = [&](int it, uint32_t& got, bool& left) {
+        if (!left) return;
+        const uint64_t c = __hip_atomic_load(counts + (it & 3) * CW * C + tid - kHalf, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        if ((uint32_t)c != (uint32_t)(it + 1)) return;
+        got = (uint32_t)(c >> 32);
+        left = false;
+    };
+    auto add_counts = [&](uint32_t got, unsigned long long* tot) {
+        const unsigned long long sum =
+            WT ? ((unsigned long long)wave_sum(got >> 16) << 16) + wave_sum(got & 0xffffu) : wave_sum(got);
+        if (lane == 0 && sum != 0) atomicAdd(tot, sum);
+    };
+    // the outcome of iterate `it`, counted in full
+    auto outcome = [&](int it, bool bit, unsigned long long total, int lpar) {
+        const ClusterDesc* d = launder(dp);
+        const int64_t c = load_uniform(&d->w_empty) + (int64_t)total;
+        if (c < best) {
+            best = c;
+            best_step = load_uniform(&d->step0) + it;
+            own_bit = bit;
+        }
+        if (member != 0) return;
+        TracePoint* trace = load_uniform(&d->trace);
+        if ((it == T || trace != nullptr) && tid == 0) {
+            double* losses = load_uniform(&launder(gp)->losses);
+            double ls = 0.0;
+            for (int p = 0; p < C; ++p)
+                ls = ls + __hip_atomic_load(losses + lpar * C + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ls = ls * load_uniform(&d->inv_m);
+            if (it == T) load_uniform(&d->final_loss)[r] = ls;
+            if (trace != nullptr) {
+                const int64_t s0 = load_uniform(&d->step0);
+                const int64_t gs = s0 + it;
+                const int64_t row = ((gs + K - 1) / K - (s0 + K - 1) / K) % load_uniform(&d->trace_cap);
+                trace[(size_t)row * load_uniform(&d->R) + r] = TracePoint{(int32_t)gs, 0, c, ls};
+            }
+        }
+    };
+    const bool traced = load_uniform(&launder(dp)->trace) != nullptr;
+    __syncthreads();
+
+    for (int step = 0; step <= T; ++step) {
+        const bool last = step == T;
+        const bool eval = kc == 0 || last;
+        if (++kc == K) kc = 0;
+        const bool want_loss = last || (eval && traced);
+        const int par = step & 1;
+        const uint32_t at = EX && par ? kAltByte : 0u;
+        const uint32_t epoch = (uint32_t)(step + 1);
+        HMS_GLOBAL float* tb = (HMS_GLOBAL float*)G.tbuf + (size_t)par * P;
+        if (eval && counting) {
+            double los = 0.0;
+            unsigned long long cnt = 0;
+            const int first = (kWaves - 1 - wave) * C + member;
+            if constexpr (EX) cnt = cache.count<WT>(smem, at, c_w, want_loss, los, lane);
+            const ClusterDesc* d = launder(dp);
+            const int c_tiles = load_uniform(&d->c_tiles);
+            if (!EX || first + CW * C < c_tiles)
+                cnt += count_clauses<WT>(smem, at, load_uniform(&d->c_tile),
+                                         (const HMS_GLOBAL uint32_t*)load_uniform(&d->cslot), c_w, c_tiles,
+                                         EX ? first + CW * C : first, (EX ? CW : kWaves) * C, lane, want_loss, los);
+            if (lane == 0) {
+                if constexpr (EX) {
+                    if (want_loss) {
+                        sh.los[wave] = los;
+                        sh.wcnt[wave] = cnt;
+                    } else {
+                        __hip_atomic_store(counts + ((step & 3) * C + member) * CW + (kWaves - 1 - wave),
+                                           (uint64_t)epoch | ((uint64_t)cnt << 32), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                } else {
+                    if (cnt != 0) atomicAdd(&sh.cnt[par], cnt);
+                    if (want_loss) sh.los[wave] = los;
+                }
+            }
+        }
+        const bool was = x > 0.0f;
+        if (mine && !last) {
+            float2 sc = make_float2(0.0f, 1.0f);
+            if (opt != kSgd)
+                sc = make_float2(__uint_as_float(ldc(scal + 2 * step)), __uint_as_float(ldc(scal + 2 * step + 1)));
+            double Gm = 0.0;
+            sum_block(smem, at, b0, len, to, tom, Gm);
+            if (len > 8) sum_block(smem, at, b1, len - 8, to, tom, Gm);
+            for (int k = 16; k < len; k += 8) {
+                RecordBlock<NO, WT> b;
+                const ClusterDesc* d = launder(dp);
+                b.load((const HMS_GLOBAL uint32_t*)load_uniform(&d->rec), (const HMS_GLOBAL float*)load_uniform(&d->wrec),
+                       block0 + (k >> 3), neg, lane);
+                sum_block(smem, at, b, len - k, to, tom, Gm);
+            }
+            // a positive literal in the loss adds -a, a negative one +a (0.0 - 0.0 keeps an empty sum +0)
+            const double Gs = was ? Gm : 0.0 - Gm;
+            const float g = (float)((double)s2 * Gs);
+            if (opt == kSgd) x = x - lr * g;
+            else adam_update(x, m, v, g, sc.x, sc.y, co);
+            to = signed_tanh_call(x);
+            const int slot = member * slice + wave * 64 + lane;
+            if constexpr (EX)
+                __hip_atomic_store(words + (size_t)par * P + slot, (uint64_t)__float_as_uint(to) | ((uint64_t)epoch << 32),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            else
+                __hip_atomic_store(tb + slot, to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            // the next step's share that needs x alone
+            neg = x > 0.0f;
+            if (__ballot(neg != was) != 0) {
+                const ClusterDesc* d = launder(dp);
+                const HMS_GLOBAL uint32_t* rec = (const HMS_GLOBAL uint32_t*)load_uniform(&d->rec);
+                const HMS_GLOBAL float* wrec = (const HMS_GLOBAL float*)load_uniform(&d->wrec);
+                b0.load(rec, wrec, block0, neg, lane);
+                if (len > 8) b1.load(rec, wrec, block0 + 1, neg, lane);
+            }
+            s2 = sech2f(x);
+        }
+        if constexpr (EX) {
+            if (want_loss) {
+                // all partial losses before the counts that stand for them
+                __syncthreads();
+                if (wave == kWaves - 1 && lane == 0) {
+                    const int c_tiles = load_uniform(&launder(dp)->c_tiles);
+                    double* losses = load_uniform(&launder(gp)->losses);
+                    double ls = 0.0;
+                    for (int w = 0; w < CW; ++w)
+                        if (w == 0 || w * C + member < c_tiles) ls = ls + sh.los[kWaves - 1 - w];
+                    __hip_atomic_store(losses + (step & 3) * C + member, ls, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                    __builtin_amdgcn_s_waitcnt(0);
+                    for (int w = 0; w < CW; ++w)
+                        if (w == 0 || w * C + member < c_tiles)
+                            __hip_atomic_store(counts + ((step & 3) * C + member) * CW + w,
+                                               (uint64_t)epoch | ((uint64_t)sh.wcnt[kWaves - 1 - w] << 32),
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            }
+            int spins = 0;
+            if (wave < kWaves / 2) {
+                // the new t of every slot, into the next step's copy
+                uint32_t left = last ? 0u : todo_t;
+                unsigned char* next = smem + (par ? 0u : kAltByte) + 4 * tid;
+                const HMS_GLOBAL uint64_t* from = words + (size_t)par * P + tid;
+                while (__ballot(left != 0) != 0) {
+                    uint64_t w[NP];
+#pragma unroll
+                    for (int j = 0; j < NP; ++j)
+                        if (j < np) {
+                            if (left & (1u << j))
+                                w[j] = __hip_atomic_load(from + j * kHalf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        }
+#pragma unroll
+                    for (int j = 0; j < NP; ++j)
+                        if (j < np) {
+                            if ((left & (1u << j)) && (uint32_t)(w[j] >> 32) == epoch) {
+                                *reinterpret_cast<uint32_t*>(next + 4 * j * kHalf) = (uint32_t)w[j];
+                                left &= ~(1u << j);
+                            }
+                        }
+                    if (++spins > kSpinLimit) {
+                        sh.dead = 1;
+                        break;
+                    }
+                }
+            } else {
+                // the counts of the step before (and, at the end, of this one)
+                bool left_p = pend && todo_c, left_c = last && todo_c;
+                uint32_t got_p = 0, got_c = 0;
+                while (__ballot(left_p || left_c) != 0) {
+                    count_of(step - 1, got_p, left_p);
+                    count_of(step, got_c, left_c);
+                    if (++spins > kSpinLimit) {
+                        sh.dead = 1;
+                        break;
+                    }
+                }
+                if (tid - kHalf < (CW * C + 63 & ~63)) {
+                    if (pend) add_counts(got_p, &sh.tot[step % 3]);
+                    if (last) add_counts(got_c, &sh.tot[3]);
+                }
+            }
+        } else {
+            // own stores have reached the L2, then the flag
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            if (tid == 0) {
+                if (want_loss) {
+                    double ls = 0.0;
+                    for (int w = 0; w < kWaves; ++w) ls = ls + sh.los[w];
+                    __hip_atomic_store(load_uniform(&launder(gp)->losses) + par * C + member, ls, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    __builtin_amdgcn_s_waitcnt(0);
+                }
+                __hip_atomic_store((HMS_GLOBAL uint64_t*)G.flags + (size_t)member * kFlagStride + par,
+                                   (uint64_t)epoch | ((uint64_t)sh.cnt[par] << 32), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+                sh.cnt[par ^ 1] = 0;
+                sh.tot[par ^ 1] = 0;
+            }
+            collect(G, sh, smem, tb, member, C, __builtin_ctz(C), slice, wave, lane, step, eval, last);
+        }
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(sh.dead)) break;
+        if constexpr (EX) {
+            // three totals in turn; the one cleared here was last read before
+            // this barrier and is next added to after the next one
+            if (tid == 0) sh.tot[(step + 2) % 3] = 0;
+            if (pend) outcome(step - 1, pend_was, sh.tot[step % 3], (step - 1) & 3);
+            if (last) outcome(step, was, sh.tot[3], step & 3);
+            pend = eval;
+            pend_was = was;
+        } else if (eval) {
+            outcome(step, was, sh.tot[par], par);
+        }
+    }
+    if (__builtin_amdgcn_readfirstlane(sh.dead)) {
+        if (tid == 0) __hip_atomic_store(load_uniform(&launder(gp)->ctl) + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+    const ClusterDesc D = load_uniform(launder(dp));
+    if (var >= 0) {
+        const size_t e = (size_t)o * D.R + r;
+        D.best_a[(size_t)r * D.n + o] = own_bit ? 1 : 0;
+        if (D.x_final != nullptr) D.x_final[e] = x;
+        if (D.m_final != nullptr) {
+            D.m_final[e] = m;
+            D.v_final[e] = v;
+        }
+    }
+    if (member == 0 && tid == 0) {
+        D.best[r] = best;
+        D.best_step[r] = best_step;
+    }
+}
+
 std::mutex g_cluster_attr_mu;
 
-template <int NO, bool WT>
-hipError_t launch_as(ClusterLaunch L, size_t lds, size_t lds_cap, hipStream_t s) {
+template <typename Kernel>
+hipError_t launch_as(Kernel kernel, ClusterLaunch L, size_t lds, size_t lds_cap, hipStream_t s,
+                     std::atomic<uint64_t>& set_on) {
     L.shared_off = (int32_t)(lds - sizeof(Shared));
-    static std::atomic<uint64_t> set_on{0};  // bit d: attribute set on device d
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     const uint64_t bit = dev >= 0 && dev < 64 ? uint64_t(1) << dev : 0;
     if (!bit || !(set_on.load(std::memory_order_acquire) & bit)) {
         std::lock_guard<std::mutex> lk(g_cluster_attr_mu);
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cluster<NO, WT>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_cap);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds_cap);
         if (e != hipSuccess) return e;
         set_on.fetch_or(bit, std::memory_order_release);
     }
     // one workgroup per CU: they are dealt round-robin over the XCDs, so every
     // XCD gets kXcdCus tickets; the surplus exits at once
-    hipLaunchKernelGGL((k_cluster<NO, WT>), dim3(kXcds * kXcdCus), dim3(kClusterThreads), lds, s, L);
+    hipLaunchKernelGGL(kernel, dim3(kXcds * kXcdCus), dim3(kClusterThreads), lds, s, L);
     return hipGetLastError();
 }
 
+template <int NO, bool WT>
+hipError_t launch_mode(const ClusterLaunch& L, const ClusterShape& sh, size_t lds_cap, hipStream_t s) {
+    static std::atomic<uint64_t> set_on[3];  // bit d: the kernel's attribute is set on device d
+    switch (sh.mode) {
+        case kClusterMany: return launch_as(k_cluster<NO, WT>, L, sh.lds, lds_cap, s, set_on[0]);
+        case kClusterOne: return launch_as(k_cluster_one<NO, WT, false>, L, sh.lds, lds_cap, s, set_on[1]);
+        default: return launch_as(k_cluster_one<NO, WT, true>, L, sh.lds, lds_cap, s, set_on[2]);
+    }
+}
+
 }  // namespace
+
+size_t one_lds_bytes(int32_t C, int32_t slice, bool ex) {
+    return (ex ? kAltByte : 0) + t_bytes(C, slice) + sizeof(Shared);
+}
 
 bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& sh) {
     if (P.n_heavy != 0 || P.v_tiles < 2 || P.w_total >= (int64_t(1) << 32)) return false;
@@ -779,6 +1278,27 @@ bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& s
     int32_t C = kXcdCus;
     while (C > 2 && (int64_t)kXcds * (kXcdCus / C) < R) C /= 2;
     while (C > 2 && C > P.v_tiles) C /= 2;
+    // at most one tile per wavefront: the fewest workgroups that leave each of
+    // their four SIMDs one tile, half as many tiles where t goes in words (n =
+    // 4000, 3-CNF, one restart: 2.33 us a step at one, 2.31 at two, 2.39 at
+    // four, 2.94 at sixteen tiles)
+    if (P.v_tiles <= kWaves * C) {
+        const int per = P.v_tiles * kTile <= kOneSlots ? 2 : 4;  // tiles per workgroup
+        int32_t c1 = 2;
+        while (c1 < C && P.v_tiles > per * c1) c1 *= 2;
+        const int32_t slice = (P.v_tiles + c1 - 1) / c1 * kTile;
+        const bool words = c1 * slice <= kOneSlots && slice / kTile <= kWaves / 2;
+        const size_t lds = one_lds_bytes(c1, slice, words);
+        if (lds <= lds_cap && c1 * slice + 2 <= kClusterMaxPos) {
+            sh.C = c1;
+            sh.slice = slice;
+            sh.lds = lds;
+            sh.mode = words ? kClusterOneWords : kClusterOne;
+            sh.per_launch = kXcds * (kXcdCus / c1);
+            return true;
+        }
+    }
+    sh.mode = kClusterMany;
     for (;; C *= 2) {
         if (C > kXcdCus) return false;
         sh.slice = (P.v_tiles + C - 1) / C * kTile;
@@ -802,13 +1322,13 @@ hipError_t launch_cluster_build(const ClusterDesc& D, double lr, double b1, doub
     return hipGetLastError();
 }
 
-hipError_t launch_cluster(const ClusterLaunch& L, int32_t NO, bool weighted, size_t lds, size_t lds_cap,
+hipError_t launch_cluster(const ClusterLaunch& L, const ClusterShape& sh, bool weighted, size_t lds_cap,
                           hipStream_t s) {
-    if (lds > lds_cap) return hipErrorInvalidValue;
-    switch (NO) {
-        case 2: return weighted ? launch_as<2, true>(L, lds, lds_cap, s) : launch_as<2, false>(L, lds, lds_cap, s);
-        case 3: return weighted ? launch_as<3, true>(L, lds, lds_cap, s) : launch_as<3, false>(L, lds, lds_cap, s);
-        case 4: return weighted ? launch_as<4, true>(L, lds, lds_cap, s) : launch_as<4, false>(L, lds, lds_cap, s);
+    if (sh.lds > lds_cap) return hipErrorInvalidValue;
+    switch (sh.NO) {
+        case 2: return weighted ? launch_mode<2, true>(L, sh, lds_cap, s) : launch_mode<2, false>(L, sh, lds_cap, s);
+        case 3: return weighted ? launch_mode<3, true>(L, sh, lds_cap, s) : launch_mode<3, false>(L, sh, lds_cap, s);
+        case 4: return weighted ? launch_mode<4, true>(L, sh, lds_cap, s) : launch_mode<4, false>(L, sh, lds_cap, s);
         default: return hipErrorInvalidValue;
     }
 }

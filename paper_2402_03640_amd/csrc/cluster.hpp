@@ -21,8 +21,14 @@ constexpr int kClusterMaxK = 5;       // longest clause
 constexpr int kClusterMaxPos = 32768; // LDS slots a 15-bit literal field can name
 constexpr int32_t kClusterMaxT = 1 << 20;
 
+// How a cluster's wavefronts hold their tiles: several each (state in LDS), or
+// at most one (state in registers), the latter exchanging t behind flags or,
+// for few variables, as words that carry their step.
+enum ClusterMode : int32_t { kClusterMany = 0, kClusterOne = 1, kClusterOneWords = 2 };
+
 // Shape of a cluster solve of an instance.
 struct ClusterShape {
+    int32_t mode = kClusterMany;
     int32_t C = 0;         // workgroups per restart (a power of two)
     int32_t NO = 0;        // other literals per occurrence record (2, 3 or 4)
     int32_t slice = 0;     // variables per workgroup, padded to whole tiles
@@ -75,9 +81,12 @@ struct ClusterDesc {
 // control words of its registration (arrived count; 0 undecided, 1 go, 2 void).
 struct ClusterGroup {
     const ClusterDesc* desc;
-    float* tbuf;       // [2][C * slice] signed tanh, by LDS slot
+    float* tbuf;       // [2][C * slice] signed tanh, by LDS slot (kClusterOneWords: 64-bit words
+                       // {t, step}, zero before the launch)
     uint64_t* flags;   // [C] 128-byte lines, by step parity: step number | partial count << 32
-    double* losses;    // [2][C] partial losses, by step parity
+                       // (kClusterOneWords: [4][8 C], by step, one word per counting wavefront);
+                       // zero before the launch
+    double* losses;    // [2][C] partial losses, by step parity (kClusterOneWords: [4][C])
     int32_t* ctl;      // [0] arrived, [1] decision, [2] a bounded wait ran out
     int32_t r, C;
 };
@@ -101,7 +110,12 @@ inline size_t cluster_blocks(size_t cols, int32_t tiles) { return cols / 8 + (si
 // Variable order, records and clause slots of an instance, from its device
 // plan, and the Adam scalars of steps step0 .. step0 + T - 1.  D.bins is zero.
 hipError_t launch_cluster_build(const ClusterDesc& D, double lr, double b1, double b2, hipStream_t s);
-hipError_t launch_cluster(const ClusterLaunch& L, int32_t NO, bool weighted, size_t lds, size_t lds_cap,
+// Bytes of one cluster's exchange buffer and flags.
+inline size_t cluster_tbuf_bytes(const ClusterShape& sh) {
+    return (size_t)2 * sh.C * sh.slice * (sh.mode == kClusterOneWords ? 8 : 4);
+}
+inline size_t cluster_flag_bytes(const ClusterShape& sh) { return (size_t)sh.C * 512; }
+hipError_t launch_cluster(const ClusterLaunch& L, const ClusterShape& sh, bool weighted, size_t lds_cap,
                           hipStream_t s);
 
 }  // namespace hms

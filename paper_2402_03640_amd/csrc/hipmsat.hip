@@ -1322,23 +1322,31 @@ bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p) {
 }
 
 // Without timing, the cluster solver is taken wherever it runs and was the
-// faster one, us per step on uniform 3-, 4-, 5-CNF and mixed formulas of 400 to
-// 28000 variables, 1 to 100 restarts, against the tuned tiled or resident
+// faster one, us per step on uniform 3-, 4-, 5-CNF and mixed formulas of 150 to
+// 28000 variables, 1 to 256 restarts, against the resident or the tuned tiled
 // schedule:
-//   - from 2^14 nonzeros up (2^15 where clauses have five literals): below, the
-//     resident solver's single workgroup needs no exchange (5160 nonzeros: 2.4
-//     against 2.9; 12900: 3.0 against 2.8; 34400 in 5-CNF: 9.1 against 8.6);
+//   - from 5, 7 and 24 thousand nonzeros up with at most three, four and five
+//     literals per clause: below, the resident solver's single workgroup needs
+//     no exchange (counted every step / every 50; resident against clusters:
+//     3-CNF 3870 nonzeros 2.8 / 2.4 against 2.4 / 2.3, 5805: 3.2 / 2.6 against
+//     2.4 / 2.3, 12900: 3.6 / 3.1 against 2.5 / 2.3; mixed 5644: 3.0 / 2.5
+//     against 3.0 / 2.9, 7566: 3.2 / 2.7 against 2.6 / 2.5; 5-CNF 12900: 5.8 /
+//     5.3 against 7.9 / 7.8, 25800: 9.4 / 8.7 against 7.7 / 7.7);
+//   - as long as the resident solver is the other choice, only with all
+//     restarts in one launch (256 restarts: 2.7 against 4.7 at 5805 nonzeros,
+//     6.1 against 9.5 at 20640);
 //   - with one restart only one XCD works, and the others' share of the
 //     tiled kernels wins again past 2^21 record terms (nonzeros times other
 //     literals per clause; 3-CNF n = 28000: 4.6 against 7.1; 4-CNF n = 16000:
 //     7.5 against 8.8, n = 28000: 11.2 against 10.4);
-//   - from 64 steps on: building the records costs 40 to 250 us, about what
-//     60 steps gain.
+//   - from 64 steps on (256 up to 2^14 nonzeros, where a step gains least):
+//     building the records costs 40 to 250 us, about what so many steps gain.
 bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p) {
     hms::ClusterShape sh;
-    if (p->steps < 64 || !cluster_fits(cnf, p, sh)) return false;
     const int64_t nnz = cnf->plan.nnz;
-    if (nnz <= (int64_t(1) << (sh.NO >= 4 ? 15 : 14))) return false;
+    if (p->steps < (nnz <= (int64_t(1) << 14) ? 256 : 64) || !cluster_fits(cnf, p, sh)) return false;
+    if (nnz < 1000 * (sh.NO >= 4 ? 24 : sh.NO == 3 ? 7 : 5)) return false;
+    if (nnz <= kResidentNnz && p->restarts > sh.per_launch) return false;
     return p->restarts > 1 || nnz * sh.NO <= (int64_t(1) << 21);
 }
 
@@ -1354,6 +1362,16 @@ hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solv
     const hms::HostPlan& P = cnf->plan;
     hms::ClusterShape sh;
     if (!cluster_fits(cnf, p, sh)) return fail(HMS_ERR_ARG, "the cluster schedule does not fit this solve");
+    // outputs over inputs: a solve whose clusters did not assemble would have
+    // to start again from overwritten values
+    const size_t nR = (size_t)P.n * p->restarts;
+    const float* const ins[] = {p->x0, p->resume ? p->resume->x : nullptr, p->resume ? p->resume->m : nullptr,
+                                p->resume ? p->resume->v : nullptr};
+    const float* const outs[] = {res->x_final, res->state ? res->state->x : nullptr,
+                                 res->state ? res->state->m : nullptr, res->state ? res->state->v : nullptr};
+    for (const float* i : ins)
+        for (const float* o : outs)
+            if (i && o && i < o + nR && o < i + nR) return HMS_OK;
     std::unique_lock<std::mutex> lk(g_cluster_mu[cnf->device], std::try_to_lock);
     if (!lk.owns_lock()) return HMS_OK;
     const int32_t R = p->restarts;
@@ -1384,13 +1402,17 @@ hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solv
     const size_t o_wrec = P.weighted ? lay.add(blocks * 1024 * 4) : 0;
     const size_t o_cslot = lay.add(P.c_ent.size() * 4);
     const size_t o_scal = lay.add((size_t)std::max(p->steps, 1) * sizeof(float2));
-    const size_t line = 128;
-    const size_t tb_bytes = (size_t)2 * sh.C * sh.slice * 4;
-    const size_t o_tbuf = lay.add(tb_bytes * clusters);
-    const size_t o_loss = lay.add((size_t)2 * sh.C * 8 * clusters);
+    const size_t tb_bytes = hms::cluster_tbuf_bytes(sh);
+    const size_t fl_bytes = hms::cluster_flag_bytes(sh);
+    // words that carry their step start at zero in every launch; plain t is
+    // written before it is read, so later launches reuse the first one's
+    const bool words = sh.mode == hms::kClusterOneWords;
+    const size_t o_tbuf0 = words ? 0 : lay.add(tb_bytes * clusters);
+    const size_t o_loss = lay.add((size_t)4 * sh.C * 8 * clusters);
     // zeroed before the launches: flags, control words and tickets of each
     const size_t o_zero = lay.add(0);
-    const size_t o_flags = lay.add(line * sh.C * R);
+    const size_t o_tbuf = words ? lay.add(tb_bytes * R) : o_tbuf0;
+    const size_t o_flags = lay.add(fl_bytes * R);
     const size_t o_ctl = lay.add((size_t)R * 16);
     const size_t o_tick = lay.add((size_t)launches * hms::kXcds * 4);
     const size_t o_bins = lay.add(hms::kClusterBins * 4);
@@ -1472,9 +1494,9 @@ hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solv
             for (int32_t i = x; i < cnt; i += hms::kXcds, ++g) {
                 hms::ClusterGroup& q = groups[g];
                 q.desc = A.at<hms::ClusterDesc>(o_desc);
-                q.tbuf = A.at<float>(o_tbuf + tb_bytes * i);
-                q.losses = A.at<double>(o_loss) + (size_t)2 * sh.C * i;
-                q.flags = A.at<uint64_t>(o_flags + line * sh.C * g);
+                q.tbuf = A.at<float>(o_tbuf + tb_bytes * (words ? r0 + i : i));
+                q.losses = A.at<double>(o_loss) + (size_t)4 * sh.C * i;
+                q.flags = A.at<uint64_t>(o_flags + fl_bytes * g);
                 q.ctl = A.at<int32_t>(o_ctl) + (size_t)g * 4;
                 q.r = r0 + i;
                 q.C = sh.C;
@@ -1498,7 +1520,7 @@ hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solv
     HIPTRY(hipEventRecord(E.e[0], s));
     HIPTRY(hms::launch_cluster_build(D, (double)p->lr, (double)p->beta1, (double)p->beta2, s));
     for (const auto& l : L)
-        HIPTRY(hms::launch_cluster(l, sh.NO, P.weighted, sh.lds, cluster_lds_cap(cnf->device), s));
+        HIPTRY(hms::launch_cluster(l, sh, P.weighted, cluster_lds_cap(cnf->device), s));
     HIPTRY(hipEventRecord(E.e[1], s));
     HIPTRY(hipMemcpyAsync(best.data(), D.best, R * 8, hipMemcpyDeviceToHost, s));
     HIPTRY(hipMemcpyAsync(bstep.data(), D.best_step, R * 4, hipMemcpyDeviceToHost, s));

@@ -57,12 +57,14 @@ def _ragged(n, m, seed, kmax=5, spread=None):
 # tile and list edges: 65 and 129 variables (one row in the last tile), lists
 # of 7 to 17 records (a record block holds 8), one workgroup more than tiles
 # allow; 1, 8, 9, 17, 33, 65 restarts (workgroups per restart 32 down to 4,
-# and a second launch)
+# and a second launch); 4096 and 4097 variables (t exchanged in words that carry
+# their step, and behind flags), one tile per wavefront and several
 CASES = [("uniform", 65, 300, 3, 1), ("uniform", 129, 520, 3, 9), ("uniform", 1000, 4200, 3, 17),
          ("uniform", 640, 2752, 4, 8), ("uniform", 300, 4000, 5, 33), ("mixed", 1000, 4200, 4, 65),
          ("uniform", 5000, 21500, 3, 2), ("two", 2000, 5000, 2, 3), ("ragged", 700, 3000, 5, 5),
          ("ragged3", 2500, 9000, 3, 4), ("sparse", 4000, 3000, 4, 2), ("uniform", 20000, 86000, 3, 64),
-         ("uniform", 30000, 129000, 3, 18)]
+         ("uniform", 30000, 129000, 3, 18), ("uniform", 4096, 17600, 3, 1), ("uniform", 4097, 17600, 3, 1),
+         ("mixed", 2050, 8600, 4, 16), ("uniform", 8200, 35000, 3, 9)]
 
 
 def _formula(kind, n, m, k, seed):
