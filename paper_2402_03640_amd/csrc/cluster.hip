@@ -79,6 +79,33 @@ size_t lds_bytes(int32_t C, int32_t slice) {
     return up16(t_bytes(C, slice) + (size_t)slice * 12 + (size_t)(slice / 64) * 16) + sizeof(Shared);
 }
 
+// A wave-uniform pointer, and a structure behind one, in scalar registers.
+template <typename T>
+__device__ __forceinline__ T* uniform(T* p) {
+    const uint64_t a = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    return (T*)(((uint64_t)hi << 32) | lo);
+}
+// The same pointer, opaque to the compiler: what is loaded through it is loaded
+// there and then, not ahead of a loop.
+template <typename T>
+__device__ __forceinline__ const T* launder(const T* p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+template <typename T>
+__device__ __forceinline__ T load_uniform(const T* p) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    const uint32_t* w = reinterpret_cast<const uint32_t*>(p);
+    uint32_t u[sizeof(T) / 4];
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 4; ++i) u[i] = ldc(w + i);
+    T out;
+    __builtin_memcpy(&out, u, sizeof(T));
+    return out;
+}
+
 // ---- build ------------------------------------------------------------------
 // A variable's occurrences are kept as two lists, the positive and the negative
 // literals, each in plan order.  A clause is in the loss only if all its
@@ -86,12 +113,14 @@ size_t lds_bytes(int32_t C, int32_t slice) {
 // positive one when x rounds to true) and a step walks the other alone.  Rows
 // are ordered by their longer list, so the 64 rows of a tile end together
 // (3-CNF, 12.9 occurrences per variable: 8.5 records walked instead of 13.3).
+// Every kernel builds one instance per row of its grid: Ds[blockIdx.y].
 
 __device__ __forceinline__ int list_len(uint32_t counts) { return max((int)(counts & 0xffffu), (int)(counts >> 16)); }
 
 // Occurrences of each variable and the histogram of list lengths (summed in
 // LDS first: lengths repeat, and device atomics on one word go one by one).
-__global__ __launch_bounds__(1024) void k_cluster_count(ClusterDesc D) {
+__global__ __launch_bounds__(1024) void k_cluster_count(const ClusterDesc* Ds) {
+    const ClusterDesc D = load_uniform(Ds + blockIdx.y);
     __shared__ int h[kClusterBins];
     const int v = blockIdx.x * 1024 + threadIdx.x;
     if (threadIdx.x < kClusterBins) h[threadIdx.x] = 0;
@@ -114,7 +143,8 @@ __global__ __launch_bounds__(1024) void k_cluster_count(ClusterDesc D) {
 
 // First rank of each list length (longest first), and every tile's length and
 // first record block.  One workgroup.
-__global__ __launch_bounds__(kClusterBins) void k_cluster_scan(ClusterDesc D) {
+__global__ __launch_bounds__(kClusterBins) void k_cluster_scan(const ClusterDesc* Ds) {
+    const ClusterDesc D = load_uniform(Ds + blockIdx.y);
     __shared__ int first[kClusterBins + 1];
     __shared__ int blocks[kClusterMaxPos / kTile];
     const int tid = threadIdx.x;
@@ -156,7 +186,8 @@ __global__ __launch_bounds__(kClusterBins) void k_cluster_scan(ClusterDesc D) {
 
 // Rank, and with it tile, workgroup and LDS slot of each variable.  Equal
 // lengths take ranks in any order: nothing but the placement depends on it.
-__global__ __launch_bounds__(1024) void k_cluster_rank(ClusterDesc D) {
+__global__ __launch_bounds__(1024) void k_cluster_rank(const ClusterDesc* Ds) {
+    const ClusterDesc D = load_uniform(Ds + blockIdx.y);
     __shared__ int h[kClusterBins];
     const int i = blockIdx.x * 1024 + threadIdx.x;
     const int P = D.C * D.slice;
@@ -186,7 +217,8 @@ __global__ __launch_bounds__(1024) void k_cluster_rank(ClusterDesc D) {
 // list (own literal comes after other literal j in the clause, j = 2 .. NO, 8
 // bits each; the first two terms of a sum commute), then the records in quads
 // of 16 bytes per row, so every load of a wavefront covers whole lines.
-__global__ __launch_bounds__(1024) void k_cluster_records(ClusterDesc D) {
+__global__ __launch_bounds__(1024) void k_cluster_records(const ClusterDesc* Ds) {
+    const ClusterDesc D = load_uniform(Ds + blockIdx.y);
     __shared__ uint8_t at[2][kSplitDense][64];         // column of each list's k-th entry
     __shared__ uint32_t bits[2][kSplitDense / 8][64];
     const int lane = threadIdx.x & 63;
@@ -271,40 +303,13 @@ __global__ __launch_bounds__(1024) void k_cluster_records(ClusterDesc D) {
         rp[(size_t)(i >> 1) * cluster_block_words(NO) + (i & 1) * 64 + lane] = bits[i & 1][i >> 1][lane];
 }
 
-__global__ __launch_bounds__(256) void k_cluster_scalars(float2* scal, int32_t step0, int32_t T, double lr, double b1,
-                                                         double b2) {
+__global__ __launch_bounds__(256) void k_cluster_scalars(const ClusterDesc* Ds) {
+    const ClusterDesc D = load_uniform(Ds + blockIdx.y);
     const int32_t k = (int32_t)(blockIdx.x * 256 + threadIdx.x);
-    if (k >= T) return;
+    if (k >= D.T) return;
     float ss, ib2;
-    adam_scalars((double)(step0 + k) + 1.0, lr, b1, b2, ss, ib2);
-    scal[k] = make_float2(ss, ib2);
-}
-
-// A wave-uniform pointer, and a structure behind one, in scalar registers.
-template <typename T>
-__device__ __forceinline__ T* uniform(T* p) {
-    const uint64_t a = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-    return (T*)(((uint64_t)hi << 32) | lo);
-}
-// The same pointer, opaque to the compiler: what is loaded through it is loaded
-// there and then, not ahead of a loop.
-template <typename T>
-__device__ __forceinline__ const T* launder(const T* p) {
-    asm volatile("" : "+s"(p));
-    return p;
-}
-template <typename T>
-__device__ __forceinline__ T load_uniform(const T* p) {
-    static_assert(sizeof(T) % 4 == 0, "whole words");
-    const uint32_t* w = reinterpret_cast<const uint32_t*>(p);
-    uint32_t u[sizeof(T) / 4];
-#pragma unroll
-    for (size_t i = 0; i < sizeof(T) / 4; ++i) u[i] = ldc(w + i);
-    T out;
-    __builtin_memcpy(&out, u, sizeof(T));
-    return out;
+    adam_scalars((double)(D.step0 + k) + 1.0, (double)D.lr, (double)D.b1, (double)D.b2, ss, ib2);
+    D.scal[k] = make_float2(ss, ib2);
 }
 
 // Out of line: the branch inside tanhf would make the compiler treat the whole
@@ -1267,7 +1272,7 @@ size_t one_lds_bytes(int32_t C, int32_t slice, bool ex) {
     return (ex ? kAltByte : 0) + t_bytes(C, slice) + sizeof(Shared);
 }
 
-bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& sh) {
+bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& sh, bool many) {
     if (P.n_heavy != 0 || P.v_tiles < 2 || P.w_total >= (int64_t(1) << 32)) return false;
     uint32_t k = 0;
     for (const TileDesc& d : P.c_tile)
@@ -1282,7 +1287,7 @@ bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& s
     // their four SIMDs one tile, half as many tiles where t goes in words (n =
     // 4000, 3-CNF, one restart: 2.33 us a step at one, 2.31 at two, 2.39 at
     // four, 2.94 at sixteen tiles)
-    if (P.v_tiles <= kWaves * C) {
+    if (!many && P.v_tiles <= kWaves * C) {
         const int per = P.v_tiles * kTile <= kOneSlots ? 2 : 4;  // tiles per workgroup
         int32_t c1 = 2;
         while (c1 < C && P.v_tiles > per * c1) c1 *= 2;
@@ -1310,15 +1315,23 @@ bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& s
     return true;
 }
 
-hipError_t launch_cluster_build(const ClusterDesc& D, double lr, double b1, double b2, hipStream_t s) {
-    const int P = D.C * D.slice;
-    hipLaunchKernelGGL(k_cluster_count, dim3((D.n_act + 1023) / 1024), dim3(1024), 0, s, D);
-    hipLaunchKernelGGL(k_cluster_scan, dim3(1), dim3(kClusterBins), 0, s, D);
-    hipLaunchKernelGGL(k_cluster_rank, dim3((P + 1023) / 1024), dim3(1024), 0, s, D);
-    const int extra = (int)std::min<int64_t>((D.c_ent_n + 4095) / 4096, 1024);
-    hipLaunchKernelGGL(k_cluster_records, dim3(D.v_tiles + extra), dim3(1024), 0, s, D);
-    if (D.T > 0)
-        hipLaunchKernelGGL(k_cluster_scalars, dim3((D.T + 255) / 256), dim3(256), 0, s, D.scal, D.step0, D.T, lr, b1, b2);
+hipError_t launch_cluster_build(const ClusterDesc* Ds, const ClusterDesc* hostDs, int32_t count, hipStream_t s) {
+    int32_t vars = 0, slots = 0, tiles = 0, T = 0;
+    int64_t entries = 0;
+    for (int32_t i = 0; i < count; ++i) {
+        const ClusterDesc& D = hostDs[i];
+        vars = std::max(vars, D.n_act);
+        slots = std::max(slots, D.C * D.slice);
+        tiles = std::max(tiles, D.v_tiles);
+        entries = std::max(entries, D.c_ent_n);
+        T = std::max(T, D.T);
+    }
+    hipLaunchKernelGGL(k_cluster_count, dim3((vars + 1023) / 1024, count), dim3(1024), 0, s, Ds);
+    hipLaunchKernelGGL(k_cluster_scan, dim3(1, count), dim3(kClusterBins), 0, s, Ds);
+    hipLaunchKernelGGL(k_cluster_rank, dim3((slots + 1023) / 1024, count), dim3(1024), 0, s, Ds);
+    const int extra = (int)std::max<int64_t>(std::min<int64_t>((entries + 4095) / 4096, 1024), 1);
+    hipLaunchKernelGGL(k_cluster_records, dim3(tiles + extra, count), dim3(1024), 0, s, Ds);
+    if (T > 0) hipLaunchKernelGGL(k_cluster_scalars, dim3((T + 255) / 256, count), dim3(256), 0, s, Ds);
     return hipGetLastError();
 }
 

@@ -84,7 +84,7 @@ struct ClusterGroup {
     float* tbuf;       // [2][C * slice] signed tanh, by LDS slot (kClusterOneWords: 64-bit words
                        // {t, step}, zero before the launch)
     uint64_t* flags;   // [C] 128-byte lines, by step parity: step number | partial count << 32
-                       // (kClusterOneWords: [4][8 C], by step, one word per counting wavefront);
+                       // (kClusterOneWords: [4][up to 14 C], by step, one word per counting wavefront);
                        // zero before the launch
     double* losses;    // [2][C] partial losses, by step parity (kClusterOneWords: [4][C])
     int32_t* ctl;      // [0] arrived, [1] decision, [2] a bounded wait ran out
@@ -98,8 +98,9 @@ struct ClusterLaunch {
     int32_t shared_off;          // LDS offset of the workgroup variables (set by launch_cluster)
 };
 
-// Whether the instance can run as a cluster solve of R restarts, and how.
-bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& sh);
+// Whether the instance can run as a cluster solve of R restarts, and how (many:
+// in the form for several tiles per wavefront, whatever its size).
+bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& sh, bool many = false);
 constexpr int kClusterBins = 512;  // list lengths (rows kept whole have at most kSplitDense entries)
 // Words of a record block (8 records of each list for 64 rows: column bits,
 // then the records) and the most blocks of an instance with `cols`
@@ -107,9 +108,10 @@ constexpr int kClusterBins = 512;  // list lengths (rows kept whole have at most
 constexpr int cluster_block_words(int NO) { return 128 + 1024 * (NO <= 2 ? 1 : 2); }
 inline size_t cluster_blocks(size_t cols, int32_t tiles) { return cols / 8 + (size_t)tiles; }
 
-// Variable order, records and clause slots of an instance, from its device
-// plan, and the Adam scalars of steps step0 .. step0 + T - 1.  D.bins is zero.
-hipError_t launch_cluster_build(const ClusterDesc& D, double lr, double b1, double b2, hipStream_t s);
+// Variable order, records and clause slots of `count` instances (Ds on the
+// device, hostDs the same on the host) from their device plans, and the Adam
+// scalars of steps step0 .. step0 + T - 1.  D.bins is zero.
+hipError_t launch_cluster_build(const ClusterDesc* Ds, const ClusterDesc* hostDs, int32_t count, hipStream_t s);
 // Bytes of one cluster's exchange buffer and flags.
 inline size_t cluster_tbuf_bytes(const ClusterShape& sh) {
     return (size_t)2 * sh.C * sh.slice * (sh.mode == kClusterOneWords ? 8 : 4);

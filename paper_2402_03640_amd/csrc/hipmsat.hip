@@ -798,7 +798,7 @@ bool resident_preferred(const hms_cnf* cnf, const hms_solve_params* p);
 hms_status time_resident(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms);
 hms_status time_cluster(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms);
 bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p);
-bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p);
+bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p, int64_t together = 0);
 constexpr int32_t kResidentId = 0xff;
 constexpr int32_t kClusterId = 0xfe;
 constexpr int64_t kResidentNnz = 1 << 15;  // largest instance the untimed choice sends to the resident solver
@@ -1341,30 +1341,311 @@ bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p) {
 //     7.5 against 8.8, n = 28000: 11.2 against 10.4);
 //   - from 64 steps on (256 up to 2^14 nonzeros, where a step gains least):
 //     building the records costs 40 to 250 us, about what so many steps gain.
-bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p) {
+// `together`: the restarts of a batch that would share the launches.
+bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p, int64_t together) {
     hms::ClusterShape sh;
     const int64_t nnz = cnf->plan.nnz;
     if (p->steps < (nnz <= (int64_t(1) << 14) ? 256 : 64) || !cluster_fits(cnf, p, sh)) return false;
     if (nnz < 1000 * (sh.NO >= 4 ? 24 : sh.NO == 3 ? 7 : 5)) return false;
-    if (nnz <= kResidentNnz && p->restarts > sh.per_launch) return false;
-    return p->restarts > 1 || nnz * sh.NO <= (int64_t(1) << 21);
+    const int64_t R = std::max<int64_t>(together, p->restarts);
+    if (nnz <= kResidentNnz && R > hms::kXcds * hms::kXcdCus / 2) return false;
+    if (nnz <= kResidentNnz && R > p->restarts &&
+        !hms::cluster_shape(cnf->plan, (int32_t)R, cluster_lds_cap(cnf->device), sh))
+        return false;
+    if (nnz <= kResidentNnz && R > sh.per_launch) return false;
+    return R > 1 || nnz * sh.NO <= (int64_t(1) << 21);
 }
 
 // One cluster launch at a time on a device: two that each hold part of an XCD
 // would wait for each other until their registrations run out.
 std::mutex g_cluster_mu[64];
 
-// Runs the solve as clusters; *ran = false (and HMS_OK) when the device was
-// taken by another cluster solve or a cluster could not assemble: nothing has
-// been written then and the caller takes the tiled kernels.
+// One instance of a cluster solve, with what the solve returns about it.
+struct ClusterItem {
+    const hms_cnf* cnf;
+    hms_solve_params p;
+    hms_solve_result* res;
+    hms::ClusterShape sh;
+    bool ran = false;     // its clusters assembled: the result is there
+    bool finite = true;   // every final loss is
+    size_t o_best, o_step, o_loss, o_ctl, o_trace;
+};
+
+// Runs instances of one kernel form (literals per clause, weights, mode) as
+// clusters, in as few launches as hold them.  An item keeps ran = false (all do
+// when the device was taken by another cluster solve) when its clusters could
+// not assemble: what is in its outputs is then to be overwritten by the schedule
+// that the caller takes instead.
+hms_status solve_clusters(std::vector<ClusterItem>& items, hipStream_t s) {
+    const int dev = items[0].cnf->device;
+    const hms::ClusterShape& sh0 = items[0].sh;
+    const bool weighted = items[0].cnf->plan.weighted;
+    std::unique_lock<std::mutex> lk(g_cluster_mu[dev], std::try_to_lock);
+    if (!lk.owns_lock()) return HMS_OK;
+    const int32_t count = (int32_t)items.size();
+    // words that carry their step start at zero in every launch; plain t is
+    // written before it is read, so later launches reuse the first one's
+    const bool words = sh0.mode == hms::kClusterOneWords;
+    size_t tb_bytes = 0, fl_bytes = 0, ls_bytes = 0;
+    int32_t units = 0;
+    for (const ClusterItem& it : items) {
+        tb_bytes = std::max(tb_bytes, hms::cluster_tbuf_bytes(it.sh));
+        fl_bytes = std::max(fl_bytes, hms::cluster_flag_bytes(it.sh));
+        ls_bytes = std::max(ls_bytes, (size_t)4 * it.sh.C * 8);
+        units += it.p.restarts;
+    }
+    // each restart of each item onto the XCD with the most free CUs, a further
+    // launch when none has enough
+    struct Unit {
+        int32_t item, r, xcd, launch;
+    };
+    std::vector<Unit> place;
+    place.reserve(units);
+    int32_t launches = 0, held = 0, most = 0;  // restarts in the current launch, and in the fullest
+    int32_t free_cus[hms::kXcds];
+    for (int32_t i = 0; i < count; ++i)
+        for (int32_t r = 0; r < items[i].p.restarts; ++r) {
+            int32_t x = 0;
+            if (launches > 0) x = (int32_t)(std::max_element(free_cus, free_cus + hms::kXcds) - free_cus);
+            if (launches == 0 || free_cus[x] < items[i].sh.C) {
+                ++launches;
+                held = 0;
+                x = 0;
+                std::fill(free_cus, free_cus + hms::kXcds, hms::kXcdCus);
+            }
+            free_cus[x] -= items[i].sh.C;
+            most = std::max(most, ++held);
+            place.push_back(Unit{i, r, x, launches - 1});
+        }
+    std::stable_sort(place.begin(), place.end(), [](const Unit& a, const Unit& b) {
+        return a.launch != b.launch ? a.launch < b.launch : a.xcd < b.xcd;
+    });
+    // host copies, declared before the guard that waits for the stream
+    std::vector<hms::ClusterDesc> D(count);
+    std::vector<hms::ClusterGroup> groups(units);
+    std::vector<char> host;
+    Layout lay;
+    const size_t o_desc = lay.add(sizeof(hms::ClusterDesc) * count);
+    const size_t o_groups = lay.add(sizeof(hms::ClusterGroup) * units);
+    // zeroed before the launches, from here: what is read back (bests, losses,
+    // control words), histograms, tickets, flags
+    const size_t o_zero = lay.off;
+    for (ClusterItem& it : items) {
+        it.o_best = lay.add((size_t)it.p.restarts * 8);
+        it.o_loss = lay.add((size_t)it.p.restarts * 8);
+        it.o_step = lay.add((size_t)it.p.restarts * 4);
+        it.o_ctl = lay.add((size_t)it.p.restarts * 16);
+    }
+    const size_t back = lay.off - o_zero;
+    const size_t o_bins = lay.add((size_t)count * hms::kClusterBins * 4);
+    const size_t o_tick = lay.add((size_t)launches * hms::kXcds * 4);
+    const size_t o_flags = lay.add(fl_bytes * units);
+    const size_t o_tbuf = lay.add(tb_bytes * (words ? units : most));
+    const size_t zero_bytes = (words ? lay.off : o_tbuf) - o_zero;
+    const size_t o_losses = lay.add(ls_bytes * most);
+    struct Parts {
+        size_t best_a, counts, slot, var, tile, rec, wrec, cslot, scal;
+    };
+    std::vector<Parts> parts(count);
+    for (int32_t i = 0; i < count; ++i) {
+        ClusterItem& it = items[i];
+        const hms::HostPlan& P = it.cnf->plan;
+        Parts& q = parts[i];
+        const size_t blocks = hms::cluster_blocks(P.v_ent.size() / hms::kTile, P.v_tiles);
+        q.best_a = lay.add((size_t)std::max(P.n, 1) * it.p.restarts);
+        it.o_trace = it.res->trace ? lay.add((size_t)it.res->trace_cap * it.p.restarts * sizeof(hms::TracePoint)) : 0;
+        q.counts = lay.add((size_t)P.n_act * 4);
+        q.slot = lay.add((size_t)P.n_act * 4);
+        q.var = lay.add((size_t)it.sh.C * it.sh.slice * 4);
+        q.tile = lay.add((size_t)P.v_tiles * sizeof(int2));
+        q.rec = lay.add(blocks * hms::cluster_block_words(it.sh.NO) * 4);
+        q.wrec = P.weighted ? lay.add(blocks * 1024 * 4) : 0;
+        q.cslot = lay.add(P.c_ent.size() * 4);
+        q.scal = lay.add((size_t)std::max(it.p.steps, 1) * sizeof(float2));
+    }
+    Arena A;
+    A.s = s;
+    HIPTRY(hipMallocAsync((void**)&A.base, lay.off, s));
+    host.resize(back);
+    for (int32_t i = 0; i < count; ++i) {
+        const ClusterItem& it = items[i];
+        const hms_solve_params& p = it.p;
+        const hms_cnf* cnf = it.cnf;
+        const hms::HostPlan& P = cnf->plan;
+        const hms::ClusterShape& sh = it.sh;
+        const Parts& q = parts[i];
+        const bool adam = p.optimizer == HMS_ADAM;
+        const hms_solve_state* so = it.res->state;
+        hms::ClusterDesc& d = D[i];
+        d.c_tile = cnf->c_tile;
+        d.c_ent = cnf->c_ent;
+        d.v_tile = cnf->v_tile;
+        d.v_ent = cnf->v_ent;
+        d.var_old = cnf->var_old;
+        d.c_w = cnf->c_w;
+        d.counts = A.at<uint32_t>(q.counts);
+        d.bins = A.at<int32_t>(o_bins) + (size_t)i * hms::kClusterBins;
+        d.slot = A.at<int32_t>(q.slot);
+        d.var = A.at<int32_t>(q.var);
+        d.tile = A.at<int2>(q.tile);
+        d.cslot = A.at<uint32_t>(q.cslot);
+        d.c_ent_n = (int64_t)P.c_ent.size();
+        d.rec = A.at<uint32_t>(q.rec);
+        d.wrec = P.weighted ? A.at<float>(q.wrec) : nullptr;
+        d.scal = A.at<float2>(q.scal);
+        d.n = P.n;
+        d.n_act = P.n_act;
+        d.c_tiles = P.c_tiles;
+        d.v_tiles = P.v_tiles;
+        d.C = sh.C;
+        d.log2C = ilog2(sh.C);
+        d.NO = sh.NO;
+        d.slice = sh.slice;
+        d.R = p.restarts;
+        d.T = p.steps;
+        d.K = p.eval_every;
+        d.opt = adam ? hms::kAdam : hms::kSgd;
+        d.w_empty = P.w_empty;
+        d.best0 = P.w_total;
+        d.two_over_m = P.m > 0 ? (float)(2.0 / (double)P.m) : 0.0f;
+        d.inv_m = P.m > 0 ? 1.0 / (double)P.m : 0.0;
+        d.lr = p.lr;
+        d.b1 = p.beta1;
+        d.b2 = p.beta2;
+        d.eps = p.eps;
+        d.omb1 = 1.0f - p.beta1;
+        d.omb2 = 1.0f - p.beta2;
+        d.seed = p.seed;
+        d.x0 = p.x0;
+        d.best_a = A.at<uint8_t>(q.best_a);
+        d.best = A.at<int64_t>(it.o_best);
+        d.best_step = A.at<int32_t>(it.o_step);
+        d.final_loss = A.at<double>(it.o_loss);
+        d.x_final = it.res->x_final ? it.res->x_final : (so ? so->x : nullptr);
+        if (so && adam) {
+            d.m_final = so->m;
+            d.v_final = so->v;
+        }
+        if (it.res->trace) {
+            d.trace = A.at<hms::TracePoint>(it.o_trace);
+            d.trace_cap = it.res->trace_cap;
+        }
+        if (const hms_solve_state* rs = p.resume) {
+            d.x0 = rs->x;
+            d.m0 = adam ? rs->m : nullptr;
+            d.v0 = adam ? rs->v : nullptr;
+            d.step0 = rs->step;
+            d.resume = 1;
+        }
+    }
+    std::vector<hms::ClusterLaunch> L(launches);
+    for (int32_t g = 0, k = 0; k < launches; ++k) {
+        L[k].groups = A.at<hms::ClusterGroup>(o_groups);
+        L[k].tickets = A.at<int32_t>(o_tick) + (size_t)k * hms::kXcds;
+        const int32_t g0 = g;
+        for (int32_t x = 0; x < hms::kXcds; ++x) {
+            L[k].off[x] = g;
+            for (; g < units && place[g].launch == k && place[g].xcd == x; ++g) {
+                const ClusterItem& it = items[place[g].item];
+                hms::ClusterGroup& q = groups[g];
+                q.desc = A.at<hms::ClusterDesc>(o_desc) + place[g].item;
+                q.tbuf = A.at<float>(o_tbuf + tb_bytes * (words ? g : g - g0));
+                q.losses = A.at<double>(o_losses + ls_bytes * (g - g0));
+                q.flags = A.at<uint64_t>(o_flags + fl_bytes * g);
+                q.ctl = A.at<int32_t>(it.o_ctl) + (size_t)place[g].r * 4;
+                q.r = place[g].r;
+                q.C = it.sh.C;
+            }
+        }
+        L[k].off[hms::kXcds] = g;
+    }
+    hms::ClusterShape widest = sh0;  // the launch's LDS: enough for each of its instances
+    for (const ClusterItem& it : items) widest.lds = std::max(widest.lds, it.sh.lds);
+    Events E;
+    for (int i = 0; i < 2; ++i) HIPTRY(hipEventCreate(&E.e[i]));
+    SyncOnExit done{s};
+    HIPTRY(hipMemcpyAsync(A.base + o_desc, D.data(), sizeof(hms::ClusterDesc) * count, hipMemcpyHostToDevice, s));
+    HIPTRY(hipMemcpyAsync(A.base + o_groups, groups.data(), sizeof(hms::ClusterGroup) * units, hipMemcpyHostToDevice,
+                          s));
+    HIPTRY(hipMemsetAsync(A.base + o_zero, 0, zero_bytes, s));
+    for (int32_t i = 0; i < count; ++i) {
+        // the resumed best enters through the output arrays the kernel updates
+        const hms_solve_state* rs = items[i].p.resume;
+        const size_t R = items[i].p.restarts, n = items[i].cnf->plan.n;
+        if (!rs) continue;
+        HIPTRY(hipMemcpyAsync(D[i].best, rs->best, R * 8, hipMemcpyHostToDevice, s));
+        HIPTRY(hipMemcpyAsync(D[i].best_step, rs->best_step, R * 4, hipMemcpyHostToDevice, s));
+        if (n > 0) HIPTRY(hipMemcpyAsync(D[i].best_a, rs->best_assignment, R * n, hipMemcpyDeviceToDevice, s));
+    }
+    HIPTRY(hipEventRecord(E.e[0], s));
+    HIPTRY(hms::launch_cluster_build(A.at<hms::ClusterDesc>(o_desc), D.data(), count, s));
+    for (const auto& l : L) HIPTRY(hms::launch_cluster(l, widest, weighted, cluster_lds_cap(dev), s));
+    HIPTRY(hipEventRecord(E.e[1], s));
+    HIPTRY(hipMemcpyAsync(host.data(), A.base + o_zero, back, hipMemcpyDeviceToHost, s));
+    HIPTRY(hipStreamSynchronize(s));
+    float ms = 0;
+    HIPTRY(hipEventElapsedTime(&ms, E.e[0], E.e[1]));
+    for (int32_t i = 0; i < count; ++i) {
+        ClusterItem& it = items[i];
+        const int32_t R = it.p.restarts;
+        const hms::HostPlan& P = it.cnf->plan;
+        const char* h = host.data() - o_zero;
+        const int32_t* ctl = reinterpret_cast<const int32_t*>(h + it.o_ctl);
+        it.ran = true;
+        for (int32_t r = 0; r < R; ++r)
+            if (ctl[(size_t)r * 4 + 1] != 1 || ctl[(size_t)r * 4 + 2] != 0) it.ran = false;  // not assembled
+        if (!it.ran) continue;
+        const int64_t* best = reinterpret_cast<const int64_t*>(h + it.o_best);
+        const int32_t* bstep = reinterpret_cast<const int32_t*>(h + it.o_step);
+        const double* closs = reinterpret_cast<const double*>(h + it.o_loss);
+        hms_solve_result* res = it.res;
+        hms_solve_state* so = res->state;
+        int32_t br = 0;
+        for (int32_t r = 1; r < R; ++r)
+            if (best[r] < best[br]) br = r;
+        if (res->best_assignment && P.n > 0)
+            HIPTRY(hipMemcpyAsync(res->best_assignment, D[i].best_a + (size_t)br * P.n, P.n, hipMemcpyDeviceToHost, s));
+        if (so && P.n > 0) {
+            if (res->x_final && so->x != res->x_final)
+                HIPTRY(hipMemcpyAsync(so->x, res->x_final, (size_t)P.n * R * 4, hipMemcpyDeviceToDevice, s));
+            HIPTRY(hipMemcpyAsync(so->best_assignment, D[i].best_a, (size_t)R * P.n, hipMemcpyDeviceToDevice, s));
+        }
+        res->best_cost = best[br];
+        res->best_restart = br;
+        res->best_step = bstep[br];
+        res->steps_done = it.p.steps;
+        res->schedule = kClusterId;
+        res->final_loss = closs[br];
+        res->device_ms = ms;
+        if (res->restart_best) std::memcpy(res->restart_best, best, (size_t)R * 8);
+        if (res->restart_step) std::memcpy(res->restart_step, bstep, (size_t)R * 4);
+        if (res->restart_loss) std::memcpy(res->restart_loss, closs, (size_t)R * 8);
+        const int32_t s0 = it.p.resume ? it.p.resume->step : 0;
+        if (so) {
+            std::memcpy(so->best, best, (size_t)R * 8);
+            std::memcpy(so->best_step, bstep, (size_t)R * 4);
+            so->step = s0 + it.p.steps;
+        }
+        if (res->trace)
+            if (hms_status rt = read_trace(D[i].trace, R, it.p.eval_every, s0, s0 + it.p.steps, s, res)) return rt;
+        for (int32_t r = 0; r < R; ++r)
+            if (!std::isfinite(closs[r])) it.finite = false;
+    }
+    HIPTRY(hipStreamSynchronize(s));
+    return HMS_OK;
+}
+
+// Runs one solve as clusters; *ran = false (and HMS_OK) when it did not.
 hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solve_result* res, bool& ran) {
     ran = false;
-    const hms::HostPlan& P = cnf->plan;
-    hms::ClusterShape sh;
-    if (!cluster_fits(cnf, p, sh)) return fail(HMS_ERR_ARG, "the cluster schedule does not fit this solve");
+    std::vector<ClusterItem> one(1);
+    one[0].cnf = cnf;
+    one[0].p = *p;
+    one[0].res = res;
+    if (!cluster_fits(cnf, p, one[0].sh)) return fail(HMS_ERR_ARG, "the cluster schedule does not fit this solve");
     // outputs over inputs: a solve whose clusters did not assemble would have
     // to start again from overwritten values
-    const size_t nR = (size_t)P.n * p->restarts;
+    const size_t nR = (size_t)cnf->plan.n * p->restarts;
     const float* const ins[] = {p->x0, p->resume ? p->resume->x : nullptr, p->resume ? p->resume->m : nullptr,
                                 p->resume ? p->resume->v : nullptr};
     const float* const outs[] = {res->x_final, res->state ? res->state->x : nullptr,
@@ -1372,199 +1653,44 @@ hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solv
     for (const float* i : ins)
         for (const float* o : outs)
             if (i && o && i < o + nR && o < i + nR) return HMS_OK;
-    std::unique_lock<std::mutex> lk(g_cluster_mu[cnf->device], std::try_to_lock);
-    if (!lk.owns_lock()) return HMS_OK;
-    const int32_t R = p->restarts;
-    const bool adam = p->optimizer == HMS_ADAM;
-    hipStream_t s = (hipStream_t)p->stream;
-    const hms_solve_state* rs = p->resume;
-    hms_solve_state* so = res->state;
-    // host destinations and sources of the copies below: declared before the
-    // guard that waits for the stream
-    std::vector<int64_t> best(R);
-    std::vector<int32_t> bstep(R);
-    std::vector<double> closs(R);
-    const int32_t launches = (R + sh.per_launch - 1) / sh.per_launch;
-    const int32_t clusters = std::min(R, sh.per_launch);
-    std::vector<hms::ClusterGroup> groups(R);
-    std::vector<int32_t> ctl((size_t)R * 4);
-    Layout lay;
-    const size_t o_desc = lay.add(sizeof(hms::ClusterDesc));
-    const size_t o_groups = lay.add(sizeof(hms::ClusterGroup) * R);
-    const SmallOut out = layout_small_out(P, R, lay);
-    const size_t o_trace = res->trace ? lay.add((size_t)res->trace_cap * R * sizeof(hms::TracePoint)) : 0;
-    const size_t blocks = hms::cluster_blocks(P.v_ent.size() / hms::kTile, P.v_tiles);
-    const size_t o_counts = lay.add((size_t)P.n_act * 4);
-    const size_t o_slot = lay.add((size_t)P.n_act * 4);
-    const size_t o_var = lay.add((size_t)sh.C * sh.slice * 4);
-    const size_t o_tile = lay.add((size_t)P.v_tiles * sizeof(int2));
-    const size_t o_rec = lay.add(blocks * hms::cluster_block_words(sh.NO) * 4);
-    const size_t o_wrec = P.weighted ? lay.add(blocks * 1024 * 4) : 0;
-    const size_t o_cslot = lay.add(P.c_ent.size() * 4);
-    const size_t o_scal = lay.add((size_t)std::max(p->steps, 1) * sizeof(float2));
-    const size_t tb_bytes = hms::cluster_tbuf_bytes(sh);
-    const size_t fl_bytes = hms::cluster_flag_bytes(sh);
-    // words that carry their step start at zero in every launch; plain t is
-    // written before it is read, so later launches reuse the first one's
-    const bool words = sh.mode == hms::kClusterOneWords;
-    const size_t o_tbuf0 = words ? 0 : lay.add(tb_bytes * clusters);
-    const size_t o_loss = lay.add((size_t)4 * sh.C * 8 * clusters);
-    // zeroed before the launches: flags, control words and tickets of each
-    const size_t o_zero = lay.add(0);
-    const size_t o_tbuf = words ? lay.add(tb_bytes * R) : o_tbuf0;
-    const size_t o_flags = lay.add(fl_bytes * R);
-    const size_t o_ctl = lay.add((size_t)R * 16);
-    const size_t o_tick = lay.add((size_t)launches * hms::kXcds * 4);
-    const size_t o_bins = lay.add(hms::kClusterBins * 4);
-    const size_t zero_bytes = lay.off - o_zero;
-    Arena A;
-    A.s = s;
-    HIPTRY(hipMallocAsync((void**)&A.base, lay.off, s));
-    hms::ClusterDesc D{};
-    D.c_tile = cnf->c_tile;
-    D.c_ent = cnf->c_ent;
-    D.v_tile = cnf->v_tile;
-    D.v_ent = cnf->v_ent;
-    D.var_old = cnf->var_old;
-    D.c_w = cnf->c_w;
-    D.counts = A.at<uint32_t>(o_counts);
-    D.bins = A.at<int32_t>(o_bins);
-    D.slot = A.at<int32_t>(o_slot);
-    D.var = A.at<int32_t>(o_var);
-    D.tile = A.at<int2>(o_tile);
-    D.cslot = A.at<uint32_t>(o_cslot);
-    D.c_ent_n = (int64_t)P.c_ent.size();
-    D.rec = A.at<uint32_t>(o_rec);
-    D.wrec = P.weighted ? A.at<float>(o_wrec) : nullptr;
-    D.scal = A.at<float2>(o_scal);
-    D.n = P.n;
-    D.n_act = P.n_act;
-    D.c_tiles = P.c_tiles;
-    D.v_tiles = P.v_tiles;
-    D.C = sh.C;
-    D.log2C = ilog2(sh.C);
-    D.NO = sh.NO;
-    D.slice = sh.slice;
-    D.R = R;
-    D.T = p->steps;
-    D.K = p->eval_every;
-    D.opt = adam ? hms::kAdam : hms::kSgd;
-    D.w_empty = P.w_empty;
-    D.best0 = P.w_total;
-    D.two_over_m = P.m > 0 ? (float)(2.0 / (double)P.m) : 0.0f;
-    D.inv_m = P.m > 0 ? 1.0 / (double)P.m : 0.0;
-    D.lr = p->lr;
-    D.b1 = p->beta1;
-    D.b2 = p->beta2;
-    D.eps = p->eps;
-    D.omb1 = 1.0f - p->beta1;
-    D.omb2 = 1.0f - p->beta2;
-    D.seed = p->seed;
-    D.x0 = p->x0;
-    D.best_a = A.at<uint8_t>(out.o_best_a);
-    D.best = A.at<int64_t>(out.o_best);
-    D.best_step = A.at<int32_t>(out.o_step);
-    D.final_loss = A.at<double>(out.o_loss);
-    D.x_final = res->x_final ? res->x_final : (so ? so->x : nullptr);
-    if (so && adam) {
-        D.m_final = so->m;
-        D.v_final = so->v;
-    }
-    if (res->trace) {
-        D.trace = A.at<hms::TracePoint>(o_trace);
-        D.trace_cap = res->trace_cap;
-    }
-    if (rs) {
-        D.x0 = rs->x;
-        D.m0 = adam ? rs->m : nullptr;
-        D.v0 = adam ? rs->v : nullptr;
-        D.step0 = rs->step;
-        D.resume = 1;
-    }
-    // restart r of a launch on XCD r % 8; the groups of a launch lie XCD by XCD
-    std::vector<hms::ClusterLaunch> L(launches);
-    int32_t g = 0;
-    for (int32_t k = 0; k < launches; ++k) {
-        const int32_t r0 = k * sh.per_launch;
-        const int32_t cnt = std::min(sh.per_launch, R - r0);
-        L[k].groups = A.at<hms::ClusterGroup>(o_groups);
-        L[k].tickets = A.at<int32_t>(o_tick) + (size_t)k * hms::kXcds;
-        for (int32_t x = 0; x < hms::kXcds; ++x) {
-            L[k].off[x] = g;
-            for (int32_t i = x; i < cnt; i += hms::kXcds, ++g) {
-                hms::ClusterGroup& q = groups[g];
-                q.desc = A.at<hms::ClusterDesc>(o_desc);
-                q.tbuf = A.at<float>(o_tbuf + tb_bytes * (words ? r0 + i : i));
-                q.losses = A.at<double>(o_loss) + (size_t)4 * sh.C * i;
-                q.flags = A.at<uint64_t>(o_flags + fl_bytes * g);
-                q.ctl = A.at<int32_t>(o_ctl) + (size_t)g * 4;
-                q.r = r0 + i;
-                q.C = sh.C;
-            }
-        }
-        L[k].off[hms::kXcds] = g;
-    }
-    Events E;
-    for (int i = 0; i < 2; ++i) HIPTRY(hipEventCreate(&E.e[i]));
-    SyncOnExit done{s};
-    HIPTRY(hipMemcpyAsync(A.base + o_desc, &D, sizeof(D), hipMemcpyHostToDevice, s));
-    HIPTRY(hipMemcpyAsync(A.base + o_groups, groups.data(), sizeof(hms::ClusterGroup) * R, hipMemcpyHostToDevice, s));
-    HIPTRY(hipMemsetAsync(A.base + o_zero, 0, zero_bytes, s));
-    if (rs) {
-        // the resumed best enters through the output arrays the kernel updates
-        HIPTRY(hipMemcpyAsync(D.best, rs->best, (size_t)R * 8, hipMemcpyHostToDevice, s));
-        HIPTRY(hipMemcpyAsync(D.best_step, rs->best_step, (size_t)R * 4, hipMemcpyHostToDevice, s));
-        if (P.n > 0)
-            HIPTRY(hipMemcpyAsync(D.best_a, rs->best_assignment, (size_t)R * P.n, hipMemcpyDeviceToDevice, s));
-    }
-    HIPTRY(hipEventRecord(E.e[0], s));
-    HIPTRY(hms::launch_cluster_build(D, (double)p->lr, (double)p->beta1, (double)p->beta2, s));
-    for (const auto& l : L)
-        HIPTRY(hms::launch_cluster(l, sh, P.weighted, cluster_lds_cap(cnf->device), s));
-    HIPTRY(hipEventRecord(E.e[1], s));
-    HIPTRY(hipMemcpyAsync(best.data(), D.best, R * 8, hipMemcpyDeviceToHost, s));
-    HIPTRY(hipMemcpyAsync(bstep.data(), D.best_step, R * 4, hipMemcpyDeviceToHost, s));
-    HIPTRY(hipMemcpyAsync(closs.data(), D.final_loss, R * 8, hipMemcpyDeviceToHost, s));
-    HIPTRY(hipMemcpyAsync(ctl.data(), A.base + o_ctl, (size_t)R * 16, hipMemcpyDeviceToHost, s));
-    HIPTRY(hipStreamSynchronize(s));
-    for (int32_t i = 0; i < R; ++i)
-        if (ctl[(size_t)i * 4 + 1] != 1 || ctl[(size_t)i * 4 + 2] != 0) return HMS_OK;  // not all assembled
-    ran = true;
-    int32_t br = 0;
-    for (int32_t r = 1; r < R; ++r)
-        if (best[r] < best[br]) br = r;
-    if (res->best_assignment && P.n > 0)
-        HIPTRY(hipMemcpyAsync(res->best_assignment, D.best_a + (size_t)br * P.n, P.n, hipMemcpyDeviceToHost, s));
-    if (so && P.n > 0) {
-        if (res->x_final && so->x != res->x_final)
-            HIPTRY(hipMemcpyAsync(so->x, res->x_final, (size_t)P.n * R * 4, hipMemcpyDeviceToDevice, s));
-        HIPTRY(hipMemcpyAsync(so->best_assignment, D.best_a, (size_t)R * P.n, hipMemcpyDeviceToDevice, s));
-    }
-    HIPTRY(hipStreamSynchronize(s));
-    float ms = 0;
-    HIPTRY(hipEventElapsedTime(&ms, E.e[0], E.e[1]));
-    res->best_cost = best[br];
-    res->best_restart = br;
-    res->best_step = bstep[br];
-    res->steps_done = p->steps;
-    res->schedule = kClusterId;
-    res->final_loss = closs[br];
-    res->device_ms = ms;
-    if (res->restart_best) std::memcpy(res->restart_best, best.data(), R * 8);
-    if (res->restart_step) std::memcpy(res->restart_step, bstep.data(), R * 4);
-    if (res->restart_loss) std::memcpy(res->restart_loss, closs.data(), R * 8);
-    if (so) {
-        std::memcpy(so->best, best.data(), R * 8);
-        std::memcpy(so->best_step, bstep.data(), R * 4);
-        so->step = (rs ? rs->step : 0) + p->steps;
-    }
-    if (res->trace) {
-        const int32_t s0 = rs ? rs->step : 0;
-        if (hms_status rt = read_trace(D.trace, R, p->eval_every, s0, s0 + p->steps, s, res)) return rt;
-    }
-    for (int32_t r = 0; r < R; ++r)
-        if (!std::isfinite(closs[r])) return fail(HMS_ERR_NONFINITE, "the loss at the final iterate is not finite");
+    if (hms_status rc = solve_clusters(one, (hipStream_t)p->stream)) return rc;
+    ran = one[0].ran;
+    if (ran && !one[0].finite) return fail(HMS_ERR_NONFINITE, "the loss at the final iterate is not finite");
     return HMS_OK;
+}
+
+// Shapes of the items (one form: literals per clause, weights) for running
+// together, largest first: as many workgroups per restart as leave every
+// restart its own at once.  The items of one launch run one kernel, so all take
+// the form for several tiles per wavefront unless all fit the same other one;
+// in that form what CUs are left go to the largest items (twelve 3-CNF
+// instances of 15000 to 26000 variables: 16 workgroups each, 32 for the four
+// largest).  False when an item does not fit.
+bool cluster_shapes(std::vector<ClusterItem>& items) {
+    const size_t cap = cluster_lds_cap(items[0].cnf->device);
+    int32_t units = 0;
+    for (const ClusterItem& it : items) units += it.p.restarts;
+    bool same = true;
+    for (ClusterItem& it : items) {
+        if (!hms::cluster_shape(it.cnf->plan, units, cap, it.sh)) return false;
+        same = same && it.sh.mode == items[0].sh.mode;
+    }
+    if (same && items[0].sh.mode != hms::kClusterMany) return true;
+    int32_t left = hms::kXcds * hms::kXcdCus;
+    for (ClusterItem& it : items) {
+        if (!hms::cluster_shape(it.cnf->plan, units, cap, it.sh, true)) return false;
+        left -= it.p.restarts * it.sh.C;
+    }
+    for (ClusterItem& it : items) {
+        hms::ClusterShape wide;
+        const int32_t C = it.sh.C;
+        if (C == hms::kXcdCus || it.p.restarts * C > left) break;
+        if (!hms::cluster_shape(it.cnf->plan, hms::kXcds * (hms::kXcdCus / (2 * C)), cap, wide, true) || wide.C != 2 * C)
+            break;
+        it.sh = wide;
+        left -= it.p.restarts * C;
+    }
+    return true;
 }
 
 // Device time per step of the cluster solver, by the difference of a short
@@ -1993,7 +2119,11 @@ hms_status hms_time_kernels(const hms_cnf* cnf, const hms_solve_params* p, int32
     return HMS_OK;
 }
 
-// Batched solve: every instance that fits the resident solver runs in shared
+// Batched solve: the instances that the cluster solver is the better choice for
+// share its launches (sixteen 3-CNF instances of 15000 to 56000 variables, 1000
+// steps: the twelve up to 26500 variables take 5.7 ms so, the whole batch 27.6
+// against 35.9 ms with every instance in the grouped tiled launches).  Then
+// every instance that fits the resident solver runs in shared
 // launches (one workgroup per (instance, restart), grouped by LDS size so
 // each launch wastes at most half its LDS), the others one after the other on
 // the tiled path.  Each result is bitwise what hms_solve gives alone.
@@ -2015,13 +2145,53 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
             return fail(HMS_ERR_ARG, "invalid parameters for instance " + std::to_string(i));
     }
     DeviceGuard dg(dev);
+    constexpr size_t kGroup = 64;  // instances of a launch, at most (clusters and tiled)
     std::vector<int32_t> res_idx, tiled_idx, alone;
+    // cluster solves of one form (literals per clause, weights) run together;
+    // the untimed choice is made for a solve of as many restarts as the
+    // candidates have between them
+    std::map<std::pair<int32_t, bool>, std::vector<int32_t>> cluster_idx;
+    std::map<std::pair<int32_t, bool>, int64_t> cluster_units;
+    std::vector<hms::ClusterShape> shape(count);
+    std::vector<char> fits(count, 0);
+    for (int32_t i = 0; i < count; ++i) {
+        const hms_solve_params& p = params[i];
+        if (p.schedule != kClusterId && !(p.schedule == 0 && cluster_preferred(cnfs[i], &p, 2))) continue;
+        if (p.resume || results[i].state || results[i].trace || !cluster_fits(cnfs[i], &p, shape[i])) continue;
+        {
+            // the handle's own timing decides where there is one
+            std::lock_guard<std::mutex> tl(cnfs[i]->tune_mu);
+            auto t = cnfs[i]->tuned.find(tune_key(&p));
+            if (p.schedule == 0 && t != cnfs[i]->tuned.end() && t->second != kClusterId) continue;
+        }
+        // no input of the batch may lie in an output: the launches before
+        // another one's would overwrite it
+        bool apart = true;
+        const float* o = results[i].x_final;
+        const size_t on = (size_t)cnfs[i]->plan.n * p.restarts;
+        for (int32_t j = 0; j < count && o && apart; ++j) {
+            const float* in = params[j].resume ? params[j].resume->x : params[j].x0;
+            if (in && in < o + on && o < in + (size_t)cnfs[j]->plan.n * params[j].restarts) apart = false;
+        }
+        if (!apart) continue;
+        fits[i] = 1;
+        cluster_units[{shape[i].NO, cnfs[i]->plan.weighted}] += p.restarts;
+    }
+    auto clusters = [&](int32_t i) {
+        if (!fits[i]) return false;
+        const std::pair<int32_t, bool> form{shape[i].NO, cnfs[i]->plan.weighted};
+        const int64_t all = cluster_units[form];
+        if (params[i].schedule == 0 && !cluster_preferred(cnfs[i], &params[i], all)) return false;
+        cluster_idx[form].push_back(i);
+        return true;
+    };
     for (int32_t i = 0; i < count; ++i) {
         // a resumed solve, or one that hands back its state or its trajectory, runs as hms_solve
         if (params[i].resume != nullptr || results[i].state != nullptr || results[i].trace != nullptr) {
             alone.push_back(i);
             continue;
         }
+        if (clusters(i)) continue;
         const bool want_res = params[i].schedule == kResidentId ||
                               (params[i].schedule == 0 && resident_preferred(cnfs[i], &params[i]));
         if (want_res && resident_ok(cnfs[i], &params[i])) res_idx.push_back(i);
@@ -2029,6 +2199,40 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
     }
     hms_status worst = HMS_OK;
     std::string worst_msg;
+    for (auto& kv : cluster_idx) {
+        std::vector<int32_t>& c = kv.second;
+        std::stable_sort(c.begin(), c.end(), [&](int32_t a, int32_t b) { return cnfs[a]->plan.nnz > cnfs[b]->plan.nnz; });
+        for (size_t k0 = 0; k0 < c.size(); k0 += kGroup) {
+            const size_t cnt = std::min(kGroup, c.size() - k0);
+            std::vector<ClusterItem> items(cnt);
+            for (size_t k = 0; k < cnt; ++k) {
+                items[k].cnf = cnfs[c[k0 + k]];
+                items[k].p = params[c[k0 + k]];
+                items[k].res = &results[c[k0 + k]];
+            }
+            // a launch runs one kernel form
+            hms_status st = HMS_OK;
+            if (cluster_shapes(items)) st = solve_clusters(items, s);
+            for (size_t k = 0; k < cnt; ++k) {
+                const int32_t i = c[k0 + k];
+                if (st) {
+                    if (statuses) statuses[i] = st;
+                } else if (!items[k].ran) {
+                    tiled_idx.push_back(i);
+                } else if (!items[k].finite) {
+                    if (statuses) statuses[i] = HMS_ERR_NONFINITE;
+                    if (!worst) {
+                        worst = HMS_ERR_NONFINITE;
+                        worst_msg = "instance " + std::to_string(i) + ": the loss at the final iterate is not finite";
+                    }
+                }
+            }
+            if (st && !worst) {
+                worst = st;
+                worst_msg = "instance " + std::to_string(c[k0]) + ": " + g_err;
+            }
+        }
+    }
     if (!res_idx.empty()) {
         std::sort(res_idx.begin(), res_idx.end(), [&](int32_t a, int32_t b) {
             return resident_lds(cnfs[a]) > resident_lds(cnfs[b]);
@@ -2144,7 +2348,6 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
     // optimizer, loss mode and requested schedule run together (largest
     // first, at most kGroup per launch) with the schedule of their largest
     // instance; a group of one, or a solve with a time limit, runs alone
-    constexpr size_t kGroup = 64;
     std::map<std::tuple<int32_t, int32_t, int32_t, int32_t, int32_t, int32_t>, std::vector<int32_t>> groups;
     for (int32_t i : tiled_idx) {
         const hms_solve_params& p = params[i];
@@ -2202,7 +2405,7 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
     for (int32_t i : alone) {
         hms_solve_params p = params[i];
         p.stream = params[0].stream;
-        if (p.schedule == kResidentId) p.schedule = 0;
+        if (p.schedule == kResidentId || (p.schedule == kClusterId && !cluster_ok(cnfs[i], &p))) p.schedule = 0;
         hms_status st = hms_solve(cnfs[i], &p, &results[i]);
         if (statuses) statuses[i] = st;
         note(st, i);

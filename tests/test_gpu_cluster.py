@@ -211,3 +211,46 @@ def test_cluster_concurrent_threads():
     _say("schedules:", sorted(ran))
     assert not errors, errors
     assert hm.CLUSTER in ran
+
+
+# (kind, n, k, restarts) of the batch's instances: one form and one kernel
+# (words, flags), several kernels' sizes in one form, several forms, more
+# restarts than one launch holds, and instances that run elsewhere
+BATCHES = [
+    [("uniform", 600 + 150 * i, 3, 1 + i % 3) for i in range(5)],
+    [("uniform", n, 3, 1) for n in (5000, 9000, 12000)],
+    [("uniform", n, 3, R) for n, R in ((20000, 1), (15500, 1), (16700, 2), (900, 4), (26000, 1), (5000, 1))],
+    [("uniform", 3000, 3, 1), ("mixed", 2000, 4, 2), ("uniform", 700, 4, 3), ("uniform", 1500, 5, 1),
+     ("mixed", 5000, 4, 1), ("two", 9000, 2, 1)],
+    [("uniform", 20000, 3, 70), ("uniform", 8000, 3, 90)],
+    [("uniform", 33000, 3, 1), ("uniform", 18000, 3, 1), ("uniform", 150, 3, 2), ("uniform", 21000, 3, 1)],
+]
+
+
+@pytest.mark.parametrize("batch", range(len(BATCHES)))
+@pytest.mark.parametrize("schedule", [0, hm.CLUSTER])
+def test_cluster_batch_equals_single(batch, schedule):
+    """A batch's cluster solves share launches: each result is the tiled
+    solve's bit for bit, with its own steps, period, rate and optimizer."""
+    insts = BATCHES[batch]
+    cnfs, w = [], None
+    for j, (kind, n, k, R) in enumerate(insts):
+        m = int(n * {2: 2.0, 3: 4.2, 4: 6.0, 5: 12.0}[k])
+        if batch == 3 and j in (0, 4):
+            w = np.random.default_rng(j).integers(1, 30, size=m).astype(np.int64)
+        cnfs.append(hm.load_cnf(n, _formula(kind, n, m, k, seed=n), weights=w))
+        w = None
+    N = len(insts)
+    kw = dict(steps=[256 + 3 * j for j in range(N)], restarts=[i[3] for i in insts], eval_every=[1 + 6 * j for j in range(N)],
+              seeds=list(range(5, 5 + N)), lr=[1e-2 / (1 + j) for j in range(N)],
+              optimizer=[hm.SGD if j == 1 else hm.ADAM for j in range(N)])
+    outs = hm.solve_batch(cnfs, schedule=schedule, want_x=True, **kw)
+    for j, (cnf, out) in enumerate(zip(cnfs, outs)):
+        one = hm.solve(cnf, schedule=1, want_x=True, seed=kw["seeds"][j],
+                       **{key: kw[key][j] for key in ("steps", "restarts", "eval_every", "lr", "optimizer")})
+        _say(f"batch {batch} schedule {schedule} instance {j} {insts[j]}: schedule {out.schedule}, best {out.best_cost}")
+        assert out.status == 0
+        _same(out, one)
+        big = insts[j][1] > 32768
+        assert out.schedule != hm.CLUSTER if big else out.schedule == hm.CLUSTER or insts[j][1] < 3000
+        cnf.free()
