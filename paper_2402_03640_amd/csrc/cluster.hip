@@ -78,6 +78,14 @@ __host__ __device__ __forceinline__ size_t t_bytes(int32_t C, int32_t slice) { r
 size_t lds_bytes(int32_t C, int32_t slice) {
     return up16(t_bytes(C, slice) + (size_t)slice * 12 + (size_t)(slice / 64) * 16) + sizeof(Shared);
 }
+// The same in the wide form: a bit per variable and for the two constants, own
+// t, x, m, v, own rounded bits.
+__host__ __device__ __forceinline__ size_t bits_bytes(int32_t C, int32_t slice) {
+    return up16(((size_t)C * slice / 64 + 1) * 8);
+}
+size_t wide_lds_bytes(int32_t C, int32_t slice) {
+    return up16(bits_bytes(C, slice) + (size_t)slice * 16 + (size_t)(slice / 64) * 16) + sizeof(Shared);
+}
 
 // A wave-uniform pointer, and a structure behind one, in scalar registers.
 template <typename T>
@@ -115,6 +123,10 @@ __device__ __forceinline__ T load_uniform(const T* p) {
 // (3-CNF, 12.9 occurrences per variable: 8.5 records walked instead of 13.3).
 // Every kernel builds one instance per row of its grid: Ds[blockIdx.y].
 
+// Wide form: where slot s is named and its t kept.  The low five bits are the
+// rotation that brings the slot's bit of its 32-bit word to the top.
+__device__ __forceinline__ uint32_t wide_pos(uint32_t s) { return (s & ~31u) | ((s + 1u) & 31u); }
+
 __device__ __forceinline__ int list_len(uint32_t counts) { return max((int)(counts & 0xffffu), (int)(counts >> 16)); }
 
 // Occurrences of each variable and the histogram of list lengths (summed in
@@ -146,21 +158,30 @@ __global__ __launch_bounds__(1024) void k_cluster_count(const ClusterDesc* Ds) {
 __global__ __launch_bounds__(kClusterBins) void k_cluster_scan(const ClusterDesc* Ds) {
     const ClusterDesc D = load_uniform(Ds + blockIdx.y);
     __shared__ int first[kClusterBins + 1];
-    __shared__ int blocks[kClusterMaxPos / kTile];
+    __shared__ int sums[kClusterBins];
+    __shared__ uint8_t blocks[kClusterMaxWide / kTile];
     const int tid = threadIdx.x;
-    first[tid] = D.bins[kClusterBins - 1 - tid];  // by descending length
-    __syncthreads();
-    if (tid == 0) {
-        int sum = 0;
-        for (int i = 0; i < kClusterBins; ++i) {
-            const int c = first[i];
-            first[i] = sum;
-            sum += c;
+    // running sum over the workgroup of one value per thread, own value included
+    auto running = [&](int own) {
+        sums[tid] = own;
+        __syncthreads();
+        for (int o = 1; o < kClusterBins; o <<= 1) {
+            const int left = tid >= o ? sums[tid - o] : 0;
+            __syncthreads();
+            sums[tid] += left;
+            __syncthreads();
         }
-        first[kClusterBins] = sum;
-    }
+        return sums[tid];
+    };
+    const int here = D.bins[kClusterBins - 1 - tid];  // by descending length
+    const int upto = running(here);
+    first[tid] = upto - here;
+    if (tid == kClusterBins - 1) first[kClusterBins] = upto;
     __syncthreads();
-    for (int t = tid; t < D.v_tiles; t += kClusterBins) {
+    // a run of tiles per thread
+    const int run = (D.v_tiles + kClusterBins - 1) / kClusterBins;
+    int mine = 0;
+    for (int t = tid * run; t < (tid + 1) * run && t < D.v_tiles; ++t) {
         // the length whose ranks hold the tile's first row: the last bin
         // that starts at or before it
         int lo = 0, hi = kClusterBins;
@@ -171,15 +192,13 @@ __global__ __launch_bounds__(kClusterBins) void k_cluster_scan(const ClusterDesc
         }
         const int len = kClusterBins - 1 - lo;
         D.tile[t].y = len;
-        blocks[t] = (len + 7) / 8;
+        blocks[t] = (uint8_t)((len + 7) / 8);
+        mine += blocks[t];
     }
-    __syncthreads();
-    if (tid == 0) {
-        int sum = 0;
-        for (int t = 0; t < D.v_tiles; ++t) {
-            D.tile[t].x = sum;
-            sum += blocks[t];
-        }
+    int sum = running(mine) - mine;
+    for (int t = tid * run; t < (tid + 1) * run && t < D.v_tiles; ++t) {
+        D.tile[t].x = sum;
+        sum += blocks[t];
     }
     D.bins[kClusterBins - 1 - tid] = first[tid];
 }
@@ -216,15 +235,20 @@ __global__ __launch_bounds__(1024) void k_cluster_rank(const ClusterDesc* Ds) {
 // record block holds 8 records of both lists: one word of bits per row and
 // list (own literal comes after other literal j in the clause, j = 2 .. NO, 8
 // bits each; the first two terms of a sum commute), then the records in quads
-// of 16 bytes per row, so every load of a wavefront covers whole lines.
+// of 16 bytes per row, so every load of a wavefront covers whole lines.  In the
+// wide form a literal is a 16-bit position, and a second word of bits per row
+// and list holds the signs (bit NO i + j for other literal j of record i).
 __global__ __launch_bounds__(1024) void k_cluster_records(const ClusterDesc* Ds) {
     const ClusterDesc D = load_uniform(Ds + blockIdx.y);
     __shared__ uint8_t at[2][kSplitDense][64];         // column of each list's k-th entry
     __shared__ uint32_t bits[2][kSplitDense / 8][64];
+    __shared__ uint32_t sign[2][kSplitDense / 8][64];  // wide form
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int NO = D.NO;
-    const int W = NO <= 2 ? 1 : 2;
+    const bool wide = D.wide != 0;
+    const int W = cluster_record_words(NO);
+    const int block_words = cluster_block_words(NO, wide);
     const uint32_t P = (uint32_t)D.C * (uint32_t)D.slice;
     const uint32_t pad = (uint32_t)D.c_tiles * kTile;
     if ((int)blockIdx.x >= D.v_tiles) {
@@ -233,7 +257,8 @@ __global__ __launch_bounds__(1024) void k_cluster_records(const ClusterDesc* Ds)
         for (int64_t i = (int64_t)(blockIdx.x - D.v_tiles) * 1024 + threadIdx.x; i < D.c_ent_n; i += stride) {
             const uint32_t l = D.c_ent[i];
             const uint32_t u = l & kIdx;
-            D.cslot[i] = (u == (uint32_t)D.n ? P : (uint32_t)D.slot[u]) | (l & kSign);
+            const uint32_t at = u == (uint32_t)D.n ? P : (uint32_t)D.slot[u];
+            D.cslot[i] = (wide ? wide_pos(at) : at) | (l & kSign);
         }
         return;
     }
@@ -244,8 +269,8 @@ __global__ __launch_bounds__(1024) void k_cluster_records(const ClusterDesc* Ds)
     const uint32_t* ent = D.v_ent + d.base + (v >= 0 ? v % kTile : 0);
     const uint32_t cnt = v >= 0 ? D.counts[v] : 0u;
     const int blocks = (ti.y + 7) / 8;
-    uint32_t* rp = D.rec + (size_t)ti.x * cluster_block_words(NO);
-    for (int i = wave; i < 2 * blocks; i += 16) bits[i & 1][i >> 1][lane] = 0;
+    uint32_t* rp = D.rec + (size_t)ti.x * block_words;
+    for (int i = wave; i < 2 * blocks; i += 16) bits[i & 1][i >> 1][lane] = sign[i & 1][i >> 1][lane] = 0;
     if (wave == 0) {
         int kp = 0, kn = 0;
 #pragma unroll 8
@@ -287,20 +312,26 @@ __global__ __launch_bounds__(1024) void k_cluster_records(const ClusterDesc* Ds)
         }
         if (!live) o[0] = P + 1u;
         const int blk = k >> 3, i = k & 7;
-        uint32_t* qp = rp + (size_t)blk * cluster_block_words(NO) + 128 + neg * 512 * W;
+        uint32_t* qp = rp + (size_t)blk * block_words + cluster_head_words(wide) + neg * 512 * W;
         for (int w = 0; w < W; ++w) {
             const int q = i * W + w;  // word of the row's 8 W
-            qp[(q >> 2) * 256 + lane * 4 + (q & 3)] = (o[2 * w] << 2) | (o[2 * w + 1] << 17) | ((sg >> (2 * w)) & 3u);
+            qp[(q >> 2) * 256 + lane * 4 + (q & 3)] =
+                wide ? wide_pos(o[2 * w]) | (wide_pos(o[2 * w + 1]) << 16)
+                     : (o[2 * w] << 2) | (o[2 * w + 1] << 17) | ((sg >> (2 * w)) & 3u);
         }
         uint32_t b = 0;
         for (int j = 2; j <= NO; ++j) b |= (own >= j ? 1u : 0u) << (i + 8 * (j - 2));
         if (b != 0) atomicOr(&bits[neg][blk][lane], b);
+        if (wide && sg != 0) atomicOr(&sign[neg][blk][lane], sg << (i * NO));
         if (D.wrec != nullptr)
             D.wrec[((size_t)(ti.x + blk) * 16 + neg * 8 + (i & 4)) * 64 + lane * 4 + (i & 3)] = wf;
     }
     __syncthreads();
-    for (int i = wave; i < 2 * blocks; i += 16)
-        rp[(size_t)(i >> 1) * cluster_block_words(NO) + (i & 1) * 64 + lane] = bits[i & 1][i >> 1][lane];
+    for (int i = wave; i < 2 * blocks; i += 16) {
+        uint32_t* hp = rp + (size_t)(i >> 1) * block_words + (i & 1) * 64 + lane;
+        hp[0] = bits[i & 1][i >> 1][lane];
+        if (wide) hp[128] = sign[i & 1][i >> 1][lane];
+    }
 }
 
 __global__ __launch_bounds__(256) void k_cluster_scalars(const ClusterDesc* Ds) {
@@ -318,19 +349,23 @@ __global__ __launch_bounds__(256) void k_cluster_scalars(const ClusterDesc* Ds) 
 __device__ __attribute__((noinline)) float signed_tanh_call(float x) { return signed_tanh(x); }
 
 // One record block of the list that counts (neg: x rounds to true).
-template <int NO, bool WT>
+template <int NO, bool WT, bool WIDE = false>
 struct RecordBlock {
-    static constexpr int W = NO <= 2 ? 1 : 2;
+    static constexpr int W = cluster_record_words(NO);
     uint32_t w[8 * W];
     float wf[WT ? 8 : 1];
-    uint32_t bits;
+    uint32_t bits, sign;
+    // the block's first `left` records, all or the first half
     __device__ __forceinline__ void load(const HMS_GLOBAL uint32_t* rec, const HMS_GLOBAL float* wrec, int block,
-                                         bool neg, int lane) {
-        const HMS_GLOBAL uint32_t* bp = rec + (size_t)block * cluster_block_words(NO);
+                                         int left, bool neg, int lane) {
+        const HMS_GLOBAL uint32_t* bp = rec + (size_t)block * cluster_block_words(NO, WIDE);
         bits = bp[(neg ? 64 : 0) + lane];
-        const HMS_GLOBAL u32x4* qp = (const HMS_GLOBAL u32x4*)(bp + 128) + ((neg ? 128 * W : 0) + lane);
+        if constexpr (WIDE) sign = bp[(neg ? 192 : 128) + lane];
+        const HMS_GLOBAL u32x4* qp =
+            (const HMS_GLOBAL u32x4*)(bp + cluster_head_words(WIDE)) + ((neg ? 128 * W : 0) + lane);
 #pragma unroll
         for (int k = 0; k < 2 * W; ++k) {
+            if (WIDE && k == W && left <= 4) break;
             const u32x4 v = qp[k * 64];
             w[4 * k] = v.x;
             w[4 * k + 1] = v.y;
@@ -341,6 +376,7 @@ struct RecordBlock {
             const HMS_GLOBAL f32x4* fp = (const HMS_GLOBAL f32x4*)(wrec + (size_t)block * 1024) + ((neg ? 128 : 0) + lane);
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
+                if (WIDE && k == 1 && left <= 4) break;
                 const f32x4 v = fp[k * 64];
                 wf[4 * k] = v.x;
                 wf[4 * k + 1] = v.y;
@@ -412,6 +448,74 @@ __device__ __forceinline__ void sum_block(const unsigned char* smem, const uint3
     }
 }
 
+// The same in the wide form.  The roundings of the other literals (a bit each,
+// in LDS) say which lanes' clauses are unsatisfied; those alone read the values
+// of t, from the L2.
+template <int N, int OFF, int NO, bool WT>
+__device__ __forceinline__ void sum_records(const unsigned char* smem, const __amdgpu_buffer_rsrc_t rs,
+                                            const RecordBlock<NO, WT, true>& b, const float to, const float tom,
+                                            double& Gm) {
+    constexpr int W = cluster_record_words(NO);
+    uint32_t t[N][NO], sat[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c)
+#pragma unroll
+        for (int j = 0; j < NO; ++j)
+            t[c][j] = *reinterpret_cast<const uint32_t*>(
+                smem + ((b.w[(OFF + c) * W + (j >> 1)] >> (j & 1 ? 19 : 3)) & 0x1ffcu));
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        uint32_t any = 0;  // top bit: some other literal is true
+#pragma unroll
+        for (int j = 0; j < NO; ++j) {
+            const uint32_t w = b.w[(OFF + c) * W + (j >> 1)];
+            any |= __builtin_amdgcn_alignbit(t[c][j], t[c][j], j & 1 ? w >> 16 : w) ^
+                   (b.sign << (31 - ((OFF + c) * NO + j)));
+        }
+        sat[c] = (uint32_t)((int)any >> 31);
+    }
+#pragma unroll
+    for (int c = 0; c < N; ++c)
+        if (sat[c] == 0) {
+#pragma unroll
+            for (int j = 0; j < NO; ++j) {
+                const uint32_t w = b.w[(OFF + c) * W + (j >> 1)];
+                t[c][j] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)((j & 1 ? w >> 14 : w << 2) & 0x3fffcu), 0, 16);
+            }
+        }
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        uint32_t z = __float_as_uint(to);
+        float f = fabsf(__uint_as_float(t[c][0]));
+#pragma unroll
+        for (int j = 2; j <= NO; ++j) {
+            uint32_t after;  // all ones where the own literal comes after literal j
+            asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(after) : "v"(b.bits), "n"(OFF + c + 8 * (j - 2)));
+            uint32_t take;
+            asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(take) : "v"(after), "v"(t[c][j - 1]), "v"(z));
+            asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(z) : "v"(after), "v"(z), "v"(t[c][j - 1]));
+            f = f + fabsf(__uint_as_float(take));
+        }
+        f = f + fabsf(__uint_as_float(z));
+        if constexpr (WT) f = f * b.wf[OFF + c];
+        uint32_t a = __float_as_uint(f * tom) & ~sat[c];
+        asm("" : "+v"(a));  // the mask stays on the 32-bit value
+        Gm = Gm + (double)__uint_as_float(a);
+    }
+}
+template <int NO, bool WT>
+__device__ __forceinline__ void sum_block(const unsigned char* smem, const __amdgpu_buffer_rsrc_t rs,
+                                          const RecordBlock<NO, WT, true>& b, const int left, const float to,
+                                          const float tom, double& Gm) {
+    if constexpr (NO == 2) {
+        if (left > 4) sum_records<8, 0>(smem, rs, b, to, tom, Gm);
+        else sum_records<4, 0>(smem, rs, b, to, tom, Gm);
+    } else {
+        sum_records<4, 0>(smem, rs, b, to, tom, Gm);
+        if (left > 4) sum_records<4, 4>(smem, rs, b, to, tom, Gm);
+    }
+}
+
 // The sum over the wavefront, in every lane.
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);   // row_shr:1
@@ -460,6 +564,45 @@ __device__ __forceinline__ unsigned long long count_clauses(const unsigned char*
             all &= b;
         }
         count_row<WT>(lane < (int)d.nreal && (all >> 31) != 0, f, c_w, (size_t)ct * kTile + lane, want_loss, cnt, l);
+    }
+    if constexpr (WT)
+        for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o);
+    if (want_loss) {
+        for (int o = 32; o >= 1; o >>= 1) l += __shfl_xor(l, o);
+        los += l;
+    }
+    return cnt;
+}
+
+// The same in the wide form (t only where the loss is wanted).
+template <bool WT>
+__device__ __forceinline__ unsigned long long count_clauses_wide(const unsigned char* smem,
+                                                                 const __amdgpu_buffer_rsrc_t rs,
+                                                                 const TileDesc* c_tile,
+                                                                 const HMS_GLOBAL uint32_t* cslot,
+                                                                 const HMS_GLOBAL int64_t* c_w, const int c_tiles,
+                                                                 const int ct0, const int stride, const int lane,
+                                                                 const bool want_loss, double& los) {
+    unsigned long long cnt = 0;
+    double l = 0.0;
+    for (int ct = ct0; ct < c_tiles; ct += stride) {
+        const TileDesc d = ldtile(c_tile + ct);
+        if (d.flags & 1u) continue;  // tautologies are never unsatisfied
+        uint32_t any = 0;
+#pragma unroll 5
+        for (uint32_t c = 0; c < d.len; ++c) {
+            const uint32_t en = cslot[(size_t)d.base + (size_t)c * kTile + lane];
+            const uint32_t b = *reinterpret_cast<const uint32_t*>(smem + ((en >> 3) & 0x0ffffffcu));
+            any |= __builtin_amdgcn_alignbit(b, b, en) ^ en;
+        }
+        float f = 0.0f;
+        if (want_loss)
+            for (uint32_t c = 0; c < d.len; ++c) {
+                const uint32_t en = cslot[(size_t)d.base + (size_t)c * kTile + lane];
+                const uint32_t t = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)((en << 2) | (uint32_t)((int)any >> 31)), 0, 16);
+                f = f + __uint_as_float(t ^ (en & kSign));
+            }
+        count_row<WT>(lane < (int)d.nreal && (any >> 31) == 0, f, c_w, (size_t)ct * kTile + lane, want_loss, cnt, l);
     }
     if constexpr (WT)
         for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o);
@@ -520,6 +663,7 @@ struct ClauseCache {
 // its one or two peers (one per lane), then copies its part of their slices
 // into LDS (16 / C wavefronts per peer, two whole slices each with 32
 // workgroups).
+template <bool WIDE = false>
 __device__ __forceinline__ void collect(const ClusterGroup& G, Shared& sh, unsigned char* smem, HMS_GLOBAL float* tb,
                                         const int member, const int C, const int log2C, const int slice,
                                         const int wave, const int lane, const int step, const bool eval,
@@ -547,6 +691,17 @@ __device__ __forceinline__ void collect(const ClusterGroup& G, Shared& sh, unsig
     if (last) return;
     // device-scope loads: from the L2, never from this CU's L1
     const int P = C * slice;
+    if constexpr (WIDE) {
+        // a word of roundings per tile (tb: where they are kept)
+        const HMS_GLOBAL uint64_t* from = (const HMS_GLOBAL uint64_t*)tb;
+        uint64_t* to = reinterpret_cast<uint64_t*>(smem);
+        const int st = slice / 64, nt = rounds * st;
+        for (int i = part * 64 + lane; i < nt; i += parts * 64) {
+            const int w = i < st ? peer0 * st + i : peer1 * st + (i - st);
+            to[w] = __hip_atomic_load(from + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return;
+    }
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)tb, 0, P * 4, 0x00020000);
     const int s4 = slice / 4;
     u32x4* dst = reinterpret_cast<u32x4*>(smem);
@@ -628,9 +783,23 @@ __device__ void enroll(const ClusterLaunch& A, Shared& sh) {
     sh.cnt[0] = sh.cnt[1] = sh.tot[0] = sh.tot[1] = sh.tot[2] = sh.tot[3] = 0;
 }
 
-template <int NO, bool WT>
+// Several variable tiles per wavefront, state in LDS.  3-CNF n = 20000, 64
+// restarts: 11.9 us a step, about 10 of them vector issue (records 4.8, tanh,
+// sech^2 and Adam 4.6).
+//
+// WIDE: for more variables than t fits LDS for (n past 32000), or than a 15-bit
+// field can name.  LDS holds the roundings, a bit each, which decide for every
+// record whether its clause is unsatisfied; t itself is gathered from the L2
+// only in the lanes (a tenth or so) where it is.  An iteration exchanges the
+// bits, not t.  Bound by the latency of those gathers and the stream of records
+// (with neither: 4.3 of 7.9 us a step at n = 33000, 5.4 of 11.4 at n = 55566).
+// A literal takes 16 bits (with 32 the records no longer stay in the L2: 10.8
+// and 13.6), and the second half of a row's last block is loaded only where it
+// is used (which does not pay with t in LDS: 12.5 against 11.9 us at n = 20000,
+// 64 restarts).
+template <int NO, bool WT, bool WIDE>
 __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
-    constexpr int W = NO <= 2 ? 1 : 2;
+    constexpr int W = cluster_record_words(NO);
     extern __shared__ __align__(16) unsigned char smem[];
     Shared& sh = *reinterpret_cast<Shared*>(smem + A.shared_off);
 
@@ -653,11 +822,16 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     const int n_act = D.n_act;  // variables past these are in no clause
     const int P = C * slice;
     const int ntl = (D.v_tiles - member + C - 1) >> log2C;  // own variable tiles
+    // t of all variables, or (WIDE) their roundings; own t is kept in lo then
     float* lt = reinterpret_cast<float*>(smem);
-    float* lx = reinterpret_cast<float*>(smem + t_bytes(C, slice));
+    uint64_t* lround = reinterpret_cast<uint64_t*>(smem);
+    float* lx = reinterpret_cast<float*>(smem + (WIDE ? bits_bytes(C, slice) : t_bytes(C, slice)));
     float* lm = lx + slice;
     float* lv = lm + slice;
-    uint64_t* pbits = reinterpret_cast<uint64_t*>(lv + slice);
+    float* lo = lv + slice;
+    uint64_t* pbits = reinterpret_cast<uint64_t*>(WIDE ? lo + slice : lo);
+    const int TP = WIDE ? P + 64 : P;  // places of one copy of t in the exchange buffer
+    HMS_GLOBAL uint64_t* rbuf = (HMS_GLOBAL uint64_t*)(G.tbuf + 2 * (size_t)TP);  // WIDE: [2][P / 64]
     uint64_t* bbits = pbits + slice / 64;
     uint8_t* best_a = D.best_a + (size_t)r * n;
 
@@ -666,8 +840,19 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
         const int v = D.var[i];
         int o = 0;
         const float x = v >= 0 ? start_x(D, r, v, o) : 0.0f;
-        lt[i] = signed_tanh(x);
+        const float t = signed_tanh(x);
         const int l = i - member * slice;
+        if constexpr (WIDE) {
+            // every workgroup writes the start of all variables, the same
+            // values: what it reads in step 0 is there once its own stores are
+            __hip_atomic_store((HMS_GLOBAL float*)G.tbuf + TP + wide_pos((uint32_t)i), t, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+            const uint64_t bits = __ballot(x > 0.0f);
+            if (lane == 0) lround[i / 64] = bits;
+            if (l >= 0 && l < slice) lo[l] = t;
+        } else {
+            lt[i] = t;
+        }
         if (l >= 0 && l < slice) {
             lx[l] = x;
             lm[l] = v >= 0 && D.m0 != nullptr ? D.m0[(size_t)o * D.R + r] : 0.0f;
@@ -675,9 +860,17 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
         }
     }
     if (tid == 0) {
-        lt[P] = -0.0f;     // a literal that is false
-        lt[P + 1] = 0.0f;  // a literal that is true
+        if constexpr (WIDE) {
+            lround[P / 64] = 2;  // slot P: a literal that is false, P + 1: one that is true
+            for (int c = 0; c < 2; ++c)
+                __hip_atomic_store((HMS_GLOBAL float*)G.tbuf + c * (size_t)TP + wide_pos((uint32_t)P), -0.0f,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        } else {
+            lt[P] = -0.0f;     // a literal that is false
+            lt[P + 1] = 0.0f;  // a literal that is true
+        }
     }
+    if constexpr (WIDE) __builtin_amdgcn_s_waitcnt(0);
     if (member == 0) keep_inactive(D, r, tid, best_a);
     __syncthreads();
     const int32_t* my_var = D.var + member * slice;  // own variables, by own slot
@@ -708,8 +901,8 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     // own tiles of this wavefront
     const int my_tiles = ntl > wave ? (ntl - 1 - wave) / kWaves + 1 : 0;
     auto own_tile = [&](int i) { return i * kWaves + wave; };
-    RecordBlock<NO, WT> nx;  // the next record block, loaded one block ahead
-    auto fetch = [&](RecordBlock<NO, WT>& b, int block, bool neg) { b.load(rec, wrec, block, neg, lane); };
+    RecordBlock<NO, WT, WIDE> nx;  // the next record block, loaded one block ahead
+    auto fetch = [&](RecordBlock<NO, WT, WIDE>& b, int block, int left, bool neg) { b.load(rec, wrec, block, left, neg, lane); };
     auto tile_info = [&](int i) {
         const uint32_t* p = reinterpret_cast<const uint32_t*>(tiles + (own_tile(i) * C + member));
         return make_int2((int)ldc(p), (int)ldc(p + 1));
@@ -717,7 +910,7 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     int2 tn = make_int2(0, 0);
     if (my_tiles > 0) {
         tn = tile_info(0);
-        fetch(nx, __builtin_amdgcn_readfirstlane(tn.x), lx[own_tile(0) * 64 + lane] > 0.0f);
+        fetch(nx, __builtin_amdgcn_readfirstlane(tn.x), __builtin_amdgcn_readfirstlane(tn.y), lx[own_tile(0) * 64 + lane] > 0.0f);
     }
 
     int kc = step0 % K;
@@ -727,15 +920,22 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
         if (++kc == K) kc = 0;
         const bool want_loss = last || (eval && D.trace != nullptr);
         const int par = step & 1;
-        HMS_GLOBAL float* tb = (HMS_GLOBAL float*)G.tbuf + (size_t)par * P;
+        HMS_GLOBAL float* tb = (HMS_GLOBAL float*)G.tbuf + (size_t)par * TP;
+        // this iterate's t (WIDE): written in the step before
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc((void*)(G.tbuf + (size_t)(par ^ 1) * TP), 0, TP * 4, 0x00020000);
         // ---- count and loss of this iterate ------------------------------------
         if (eval) {
             // the clause tiles are dealt out from the last wavefront on (the
             // variable tiles start at the first)
             double los = 0.0;
-            const unsigned long long cnt = count_clauses<WT>(smem, 0u, c_tile, cslot, c_w, c_tiles,
-                                                             (kWaves - 1 - wave) * C + member, kWaves * C, lane,
-                                                             want_loss, los);
+            unsigned long long cnt;
+            if constexpr (WIDE)
+                cnt = count_clauses_wide<WT>(smem, rs, c_tile, cslot, c_w, c_tiles, (kWaves - 1 - wave) * C + member,
+                                             kWaves * C, lane, want_loss, los);
+            else
+                cnt = count_clauses<WT>(smem, 0u, c_tile, cslot, c_w, c_tiles, (kWaves - 1 - wave) * C + member,
+                                        kWaves * C, lane, want_loss, los);
             if (lane == 0 && cnt != 0) atomicAdd(&sh.cnt[par], cnt);
             if (want_loss && lane == 0) sh.los[wave] = los;
         }
@@ -754,21 +954,22 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
                 const int tb0 = __builtin_amdgcn_readfirstlane(tn.x), len = __builtin_amdgcn_readfirstlane(tn.y);
                 const int l = q * 64 + lane;
                 const float xo = lx[l];
-                const float to = lt[member * slice + l];
+                const float to = WIDE ? lo[l] : lt[member * slice + l];
                 double Gm = 0.0;
                 // the next tile; the last one's next is fetched once its x is known
                 const bool more = i + 1 < my_tiles;
                 if (more) tn = tile_info(i + 1);
                 const float xn = lx[own_tile(more ? i + 1 : i) * 64 + lane];
                 for (int k = 0; k < len; k += 8) {
-                    RecordBlock<NO, WT> b = nx;
+                    RecordBlock<NO, WT, WIDE> b = nx;
 #pragma unroll
                     for (int j = 0; j < 8 * W; ++j) asm volatile("" : "+v"(b.w[j]));
                     asm volatile("" : "+v"(b.bits));
                     const int left = len - k;
-                    if (left > 8) fetch(nx, tb0 + (k >> 3) + 1, xo > 0.0f);
-                    else if (more) fetch(nx, __builtin_amdgcn_readfirstlane(tn.x), xn > 0.0f);
-                    sum_block(smem, 0u, b, left, to, tom, Gm);
+                    if (left > 8) fetch(nx, tb0 + (k >> 3) + 1, left - 8, xo > 0.0f);
+                    else if (more) fetch(nx, __builtin_amdgcn_readfirstlane(tn.x), __builtin_amdgcn_readfirstlane(tn.y), xn > 0.0f);
+                    if constexpr (WIDE) sum_block(smem, rs, b, left, to, tom, Gm);
+                    else sum_block(smem, 0u, b, left, to, tom, Gm);
                 }
                 // a positive literal in the loss adds -a, a negative one +a (0.0 - 0.0 keeps an empty sum +0)
                 const double Gs = xo > 0.0f ? Gm : 0.0 - Gm;
@@ -783,13 +984,21 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
                     lv[l] = vv;
                 }
                 lx[l] = x;
-                __hip_atomic_store(tb + member * slice + l, signed_tanh_call(x), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+                const float t = signed_tanh_call(x);
+                const uint32_t at = (uint32_t)(member * slice + l);
+                __hip_atomic_store(tb + (WIDE ? wide_pos(at) : at), t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if constexpr (WIDE) {
+                    lo[l] = t;
+                    const uint64_t up = __ballot(x > 0.0f);
+                    if (lane == 0)
+                        __hip_atomic_store(rbuf + (size_t)par * (P / 64) + member * (slice / 64) + q, up,
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
             }
             // the next step's first block, in flight over the exchange
             if (my_tiles > 0) {
                 tn = tile_info(0);
-                fetch(nx, __builtin_amdgcn_readfirstlane(tn.x), lx[own_tile(0) * 64 + lane] > 0.0f);
+                fetch(nx, __builtin_amdgcn_readfirstlane(tn.x), __builtin_amdgcn_readfirstlane(tn.y), lx[own_tile(0) * 64 + lane] > 0.0f);
             }
         }
         // ---- the step's flag: own stores have reached the L2 ------------------
@@ -811,7 +1020,11 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
             sh.tot[par ^ 1] = 0;
         }
         // ---- every workgroup's new t (and count) ------------------------------
-        collect(G, sh, smem, tb, member, C, log2C, slice, wave, lane, step, eval, last);
+        if constexpr (WIDE)
+            collect<true>(G, sh, smem, (HMS_GLOBAL float*)(rbuf + (size_t)par * (P / 64)), member, C, log2C, slice, wave,
+                          lane, step, eval, last);
+        else
+            collect(G, sh, smem, tb, member, C, log2C, slice, wave, lane, step, eval, last);
         __syncthreads();
         if (__builtin_amdgcn_readfirstlane(sh.dead)) break;
         if (eval) {
@@ -969,8 +1182,8 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster_one(ClusterLaunch A
         len = __builtin_amdgcn_readfirstlane((int)ldc(p + 1));
         const HMS_GLOBAL uint32_t* rec = (const HMS_GLOBAL uint32_t*)D.rec;
         const HMS_GLOBAL float* wrec = (const HMS_GLOBAL float*)D.wrec;
-        b0.load(rec, wrec, block0, x > 0.0f, lane);
-        if (len > 8) b1.load(rec, wrec, block0 + 1, x > 0.0f, lane);
+        b0.load(rec, wrec, block0, 8, x > 0.0f, lane);
+        if (len > 8) b1.load(rec, wrec, block0 + 1, 8, x > 0.0f, lane);
     }
     if constexpr (EX) {
         if (tid < kHalf) {
@@ -1090,7 +1303,7 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster_one(ClusterLaunch A
                 RecordBlock<NO, WT> b;
                 const ClusterDesc* d = launder(dp);
                 b.load((const HMS_GLOBAL uint32_t*)load_uniform(&d->rec), (const HMS_GLOBAL float*)load_uniform(&d->wrec),
-                       block0 + (k >> 3), neg, lane);
+                       block0 + (k >> 3), 8, neg, lane);
                 sum_block(smem, at, b, len - k, to, tom, Gm);
             }
             // a positive literal in the loss adds -a, a negative one +a (0.0 - 0.0 keeps an empty sum +0)
@@ -1111,8 +1324,8 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster_one(ClusterLaunch A
                 const ClusterDesc* d = launder(dp);
                 const HMS_GLOBAL uint32_t* rec = (const HMS_GLOBAL uint32_t*)load_uniform(&d->rec);
                 const HMS_GLOBAL float* wrec = (const HMS_GLOBAL float*)load_uniform(&d->wrec);
-                b0.load(rec, wrec, block0, neg, lane);
-                if (len > 8) b1.load(rec, wrec, block0 + 1, neg, lane);
+                b0.load(rec, wrec, block0, 8, neg, lane);
+                if (len > 8) b1.load(rec, wrec, block0 + 1, 8, neg, lane);
             }
             s2 = sech2f(x);
         }
@@ -1258,9 +1471,10 @@ hipError_t launch_as(Kernel kernel, ClusterLaunch L, size_t lds, size_t lds_cap,
 
 template <int NO, bool WT>
 hipError_t launch_mode(const ClusterLaunch& L, const ClusterShape& sh, size_t lds_cap, hipStream_t s) {
-    static std::atomic<uint64_t> set_on[3];  // bit d: the kernel's attribute is set on device d
+    static std::atomic<uint64_t> set_on[4];  // bit d: the kernel's attribute is set on device d
     switch (sh.mode) {
-        case kClusterMany: return launch_as(k_cluster<NO, WT>, L, sh.lds, lds_cap, s, set_on[0]);
+        case kClusterMany: return launch_as(k_cluster<NO, WT, false>, L, sh.lds, lds_cap, s, set_on[0]);
+        case kClusterWide: return launch_as(k_cluster<NO, WT, true>, L, sh.lds, lds_cap, s, set_on[3]);
         case kClusterOne: return launch_as(k_cluster_one<NO, WT, false>, L, sh.lds, lds_cap, s, set_on[1]);
         default: return launch_as(k_cluster_one<NO, WT, true>, L, sh.lds, lds_cap, s, set_on[2]);
     }
@@ -1303,12 +1517,22 @@ bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& s
             return true;
         }
     }
+    auto slice_at = [&](int32_t c) { return (P.v_tiles + c - 1) / c * kTile; };
+    const int32_t C0 = C;
     sh.mode = kClusterMany;
-    for (;; C *= 2) {
-        if (C > kXcdCus) return false;
-        sh.slice = (P.v_tiles + C - 1) / C * kTile;
+    for (; C <= kXcdCus; C *= 2) {
+        sh.slice = slice_at(C);
         sh.lds = lds_bytes(C, sh.slice);
         if (sh.lds <= lds_cap && (int64_t)C * sh.slice + 2 <= kClusterMaxPos) break;
+    }
+    if (C > kXcdCus) {
+        sh.mode = kClusterWide;
+        for (C = C0; C <= kXcdCus; C *= 2) {
+            sh.slice = slice_at(C);
+            sh.lds = wide_lds_bytes(C, sh.slice);
+            if (sh.lds <= lds_cap && (int64_t)C * sh.slice + 64 <= kClusterMaxWide) break;
+        }
+        if (C > kXcdCus) return false;
     }
     sh.C = C;
     sh.per_launch = kXcds * (kXcdCus / C);

@@ -19,12 +19,14 @@ constexpr int kXcdCus = 32;           // CUs per XCD: the most workgroups a clus
 constexpr int kClusterThreads = 1024;
 constexpr int kClusterMaxK = 5;       // longest clause
 constexpr int kClusterMaxPos = 32768; // LDS slots a 15-bit literal field can name
+constexpr int kClusterMaxWide = 65536; // positions a 16-bit literal field can name (wide form)
 constexpr int32_t kClusterMaxT = 1 << 20;
 
 // How a cluster's wavefronts hold their tiles: several each (state in LDS), or
 // at most one (state in registers), the latter exchanging t behind flags or,
-// for few variables, as words that carry their step.
-enum ClusterMode : int32_t { kClusterMany = 0, kClusterOne = 1, kClusterOneWords = 2 };
+// for few variables, as words that carry their step.  Wide: several each, with
+// only the roundings of all variables in LDS (more variables than t fits for).
+enum ClusterMode : int32_t { kClusterMany = 0, kClusterOne = 1, kClusterOneWords = 2, kClusterWide = 3 };
 
 // Shape of a cluster solve of an instance.
 struct ClusterShape {
@@ -74,7 +76,7 @@ struct ClusterDesc {
     float* m_final;
     float* v_final;
     TracePoint* trace;    // [trace_cap][R] or null
-    int32_t trace_cap, pad;
+    int32_t trace_cap, wide;
 };
 
 // One cluster of a launch: restart r of desc, its exchange buffers, and the
@@ -82,7 +84,8 @@ struct ClusterDesc {
 struct ClusterGroup {
     const ClusterDesc* desc;
     float* tbuf;       // [2][C * slice] signed tanh, by LDS slot (kClusterOneWords: 64-bit words
-                       // {t, step}, zero before the launch)
+                       // {t, step}, zero before the launch; kClusterWide: [2][C * slice + 64] by
+                       // position, then [2][C * slice / 64] words of roundings)
     uint64_t* flags;   // [C] 128-byte lines, by step parity: step number | partial count << 32
                        // (kClusterOneWords: [4][up to 14 C], by step, one word per counting wavefront);
                        // zero before the launch
@@ -105,7 +108,9 @@ constexpr int kClusterBins = 512;  // list lengths (rows kept whole have at most
 // Words of a record block (8 records of each list for 64 rows: column bits,
 // then the records) and the most blocks of an instance with `cols`
 // variable-side columns in `tiles` tiles.
-constexpr int cluster_block_words(int NO) { return 128 + 1024 * (NO <= 2 ? 1 : 2); }
+constexpr int cluster_record_words(int NO) { return NO <= 2 ? 1 : 2; }
+constexpr int cluster_head_words(bool wide) { return wide ? 256 : 128; }
+constexpr int cluster_block_words(int NO, bool wide) { return cluster_head_words(wide) + 1024 * cluster_record_words(NO); }
 inline size_t cluster_blocks(size_t cols, int32_t tiles) { return cols / 8 + (size_t)tiles; }
 
 // Variable order, records and clause slots of `count` instances (Ds on the
@@ -114,7 +119,9 @@ inline size_t cluster_blocks(size_t cols, int32_t tiles) { return cols / 8 + (si
 hipError_t launch_cluster_build(const ClusterDesc* Ds, const ClusterDesc* hostDs, int32_t count, hipStream_t s);
 // Bytes of one cluster's exchange buffer and flags.
 inline size_t cluster_tbuf_bytes(const ClusterShape& sh) {
-    return (size_t)2 * sh.C * sh.slice * (sh.mode == kClusterOneWords ? 8 : 4);
+    const size_t P = (size_t)sh.C * sh.slice;
+    if (sh.mode == kClusterWide) return 2 * (P + 64) * 4 + 2 * (P / 64) * 8;
+    return 2 * P * (sh.mode == kClusterOneWords ? 8 : 4);
 }
 inline size_t cluster_flag_bytes(const ClusterShape& sh) { return (size_t)sh.C * 512; }
 hipError_t launch_cluster(const ClusterLaunch& L, const ClusterShape& sh, bool weighted, size_t lds_cap,

@@ -1339,6 +1339,15 @@ bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p) {
 //     tiled kernels wins again past 2^21 record terms (nonzeros times other
 //     literals per clause; 3-CNF n = 28000: 4.6 against 7.1; 4-CNF n = 16000:
 //     7.5 against 8.8, n = 28000: 11.2 against 10.4);
+//   - in the wide form (past 32000 variables), which reads t from the L2, from
+//     two, three and four restarts on with at most three, four and five literals
+//     per clause, and past three only up to 16, where the tiled kernels share a
+//     formula's entries between enough restarts (3-CNF n = 33000: one restart
+//     7.9 against 7.5, two 7.9 against 9.6, 64 38 against 40; n = 60000: two 12.0
+//     against 14.9, 64 71 against 75; 4-CNF n = 34000: two 19.7 against 17.2,
+//     three 19.9 against 25.0, 16 28 against 32, 32 49 against 46; 5-CNF n =
+//     34000: two 21 against 19, four 21.7 against 22.7, 16 30 against 35, 32 55
+//     against 48);
 //   - from 64 steps on (256 up to 2^14 nonzeros, where a step gains least):
 //     building the records costs 40 to 250 us, about what so many steps gain.
 // `together`: the restarts of a batch that would share the launches.
@@ -1353,6 +1362,7 @@ bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p, int64_t to
         !hms::cluster_shape(cnf->plan, (int32_t)R, cluster_lds_cap(cnf->device), sh))
         return false;
     if (nnz <= kResidentNnz && R > sh.per_launch) return false;
+    if (sh.mode == hms::kClusterWide) return R >= sh.NO && (sh.NO == 2 || p->restarts <= 16);
     return R > 1 || nnz * sh.NO <= (int64_t(1) << 21);
 }
 
@@ -1458,7 +1468,7 @@ hms_status solve_clusters(std::vector<ClusterItem>& items, hipStream_t s) {
         q.slot = lay.add((size_t)P.n_act * 4);
         q.var = lay.add((size_t)it.sh.C * it.sh.slice * 4);
         q.tile = lay.add((size_t)P.v_tiles * sizeof(int2));
-        q.rec = lay.add(blocks * hms::cluster_block_words(it.sh.NO) * 4);
+        q.rec = lay.add(blocks * hms::cluster_block_words(it.sh.NO, it.sh.mode == hms::kClusterWide) * 4);
         q.wrec = P.weighted ? lay.add(blocks * 1024 * 4) : 0;
         q.cslot = lay.add(P.c_ent.size() * 4);
         q.scal = lay.add((size_t)std::max(it.p.steps, 1) * sizeof(float2));
@@ -1501,6 +1511,7 @@ hms_status solve_clusters(std::vector<ClusterItem>& items, hipStream_t s) {
         d.log2C = ilog2(sh.C);
         d.NO = sh.NO;
         d.slice = sh.slice;
+        d.wide = sh.mode == hms::kClusterWide ? 1 : 0;
         d.R = p.restarts;
         d.T = p.steps;
         d.K = p.eval_every;
@@ -1659,7 +1670,7 @@ hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solv
     return HMS_OK;
 }
 
-// Shapes of the items (one form: literals per clause, weights) for running
+// Shapes of the items (one form: literals per clause, weights, wide) for running
 // together, largest first: as many workgroups per restart as leave every
 // restart its own at once.  The items of one launch run one kernel, so all take
 // the form for several tiles per wavefront unless all fit the same other one;
@@ -1675,7 +1686,7 @@ bool cluster_shapes(std::vector<ClusterItem>& items) {
         if (!hms::cluster_shape(it.cnf->plan, units, cap, it.sh)) return false;
         same = same && it.sh.mode == items[0].sh.mode;
     }
-    if (same && items[0].sh.mode != hms::kClusterMany) return true;
+    if (same && (items[0].sh.mode == hms::kClusterOne || items[0].sh.mode == hms::kClusterOneWords)) return true;
     int32_t left = hms::kXcds * hms::kXcdCus;
     for (ClusterItem& it : items) {
         if (!hms::cluster_shape(it.cnf->plan, units, cap, it.sh, true)) return false;
@@ -2121,8 +2132,8 @@ hms_status hms_time_kernels(const hms_cnf* cnf, const hms_solve_params* p, int32
 
 // Batched solve: the instances that the cluster solver is the better choice for
 // share its launches (sixteen 3-CNF instances of 15000 to 56000 variables, 1000
-// steps: the twelve up to 26500 variables take 5.7 ms so, the whole batch 27.6
-// against 35.9 ms with every instance in the grouped tiled launches).  Then
+// steps: 17.9 ms so, 5.7 of them for the twelve up to 26500 variables, against
+// 35.9 ms with every instance in the grouped tiled launches).  Then
 // every instance that fits the resident solver runs in shared
 // launches (one workgroup per (instance, restart), grouped by LDS size so
 // each launch wastes at most half its LDS), the others one after the other on
@@ -2147,13 +2158,17 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
     DeviceGuard dg(dev);
     constexpr size_t kGroup = 64;  // instances of a launch, at most (clusters and tiled)
     std::vector<int32_t> res_idx, tiled_idx, alone;
-    // cluster solves of one form (literals per clause, weights) run together;
+    // cluster solves of one form (literals per clause, weights, wide) run together;
     // the untimed choice is made for a solve of as many restarts as the
     // candidates have between them
-    std::map<std::pair<int32_t, bool>, std::vector<int32_t>> cluster_idx;
-    std::map<std::pair<int32_t, bool>, int64_t> cluster_units;
+    using Form = std::tuple<int32_t, bool, bool>;
+    std::map<Form, std::vector<int32_t>> cluster_idx;
+    std::map<Form, int64_t> cluster_units;
     std::vector<hms::ClusterShape> shape(count);
     std::vector<char> fits(count, 0);
+    auto form = [&](int32_t i) {
+        return Form{shape[i].NO, cnfs[i]->plan.weighted, shape[i].mode == hms::kClusterWide};
+    };
     for (int32_t i = 0; i < count; ++i) {
         const hms_solve_params& p = params[i];
         if (p.schedule != kClusterId && !(p.schedule == 0 && cluster_preferred(cnfs[i], &p, 2))) continue;
@@ -2175,14 +2190,13 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
         }
         if (!apart) continue;
         fits[i] = 1;
-        cluster_units[{shape[i].NO, cnfs[i]->plan.weighted}] += p.restarts;
+        cluster_units[form(i)] += p.restarts;
     }
     auto clusters = [&](int32_t i) {
         if (!fits[i]) return false;
-        const std::pair<int32_t, bool> form{shape[i].NO, cnfs[i]->plan.weighted};
-        const int64_t all = cluster_units[form];
+        const int64_t all = cluster_units[form(i)];
         if (params[i].schedule == 0 && !cluster_preferred(cnfs[i], &params[i], all)) return false;
-        cluster_idx[form].push_back(i);
+        cluster_idx[form(i)].push_back(i);
         return true;
     };
     for (int32_t i = 0; i < count; ++i) {

@@ -64,7 +64,11 @@ CASES = [("uniform", 65, 300, 3, 1), ("uniform", 129, 520, 3, 9), ("uniform", 10
          ("uniform", 5000, 21500, 3, 2), ("two", 2000, 5000, 2, 3), ("ragged", 700, 3000, 5, 5),
          ("ragged3", 2500, 9000, 3, 4), ("sparse", 4000, 3000, 4, 2), ("uniform", 20000, 86000, 3, 64),
          ("uniform", 30000, 129000, 3, 18), ("uniform", 4096, 17600, 3, 1), ("uniform", 4097, 17600, 3, 1),
-         ("mixed", 2050, 8600, 4, 16), ("uniform", 8200, 35000, 3, 9)]
+         ("mixed", 2050, 8600, 4, 16), ("uniform", 8200, 35000, 3, 9),
+         # only the roundings in LDS: the first size past the 15-bit slots, ragged lists and clauses with
+         # fewer literals than the record holds, fewer workgroups per restart, the largest number of tiles
+         ("uniform", 32767, 120000, 3, 1), ("ragged", 40000, 170000, 5, 3), ("two", 50000, 90000, 2, 9),
+         ("mixed", 36000, 150000, 4, 17), ("uniform", 34000, 200000, 5, 2), ("uniform", 63488, 200000, 3, 1)]
 
 
 def _formula(kind, n, m, k, seed):
@@ -175,7 +179,7 @@ def test_cluster_choice_and_refusals():
             hm.solve(cnf, **dict(dict(steps=4, schedule=hm.CLUSTER), **kw))
     heavy = hm.load_cnf(3000, cnfgen.structured_cnf(3000, 15000, seed=4))  # split rows
     long = hm.load_cnf(500, cnfgen.uniform_kcnf(500, 300, 6, seed=4))      # six literals
-    wide = hm.load_cnf(40000, cnfgen.uniform_kcnf(40000, 50000, 3, seed=4))  # more variables than LDS holds
+    wide = hm.load_cnf(63489, cnfgen.uniform_kcnf(63489, 400000, 3, seed=4))  # more variables than the widest form
     big = hm.load_cnf(500, cnfgen.uniform_kcnf(500, 2000, 3, seed=4), weights=np.full(2000, 1 << 22, np.int64))
     for c in (heavy, long, wide, big):
         with pytest.raises(hm.HipMsatError):
@@ -223,7 +227,8 @@ BATCHES = [
     [("uniform", 3000, 3, 1), ("mixed", 2000, 4, 2), ("uniform", 700, 4, 3), ("uniform", 1500, 5, 1),
      ("mixed", 5000, 4, 1), ("two", 9000, 2, 1)],
     [("uniform", 20000, 3, 70), ("uniform", 8000, 3, 90)],
-    [("uniform", 33000, 3, 1), ("uniform", 18000, 3, 1), ("uniform", 150, 3, 2), ("uniform", 21000, 3, 1)],
+    [("uniform", 140000, 3, 1), ("uniform", 18000, 3, 1), ("uniform", 150, 3, 2), ("uniform", 21000, 3, 1),
+     ("uniform", 33000, 3, 2), ("uniform", 41000, 3, 1)],
 ]
 
 
@@ -251,6 +256,6 @@ def test_cluster_batch_equals_single(batch, schedule):
         _say(f"batch {batch} schedule {schedule} instance {j} {insts[j]}: schedule {out.schedule}, best {out.best_cost}")
         assert out.status == 0
         _same(out, one)
-        big = insts[j][1] > 32768
+        big = insts[j][1] > 63488
         assert out.schedule != hm.CLUSTER if big else out.schedule == hm.CLUSTER or insts[j][1] < 3000
         cnf.free()
