@@ -30,10 +30,12 @@
 #include <algorithm>
 #include <atomic>
 #include <cerrno>
+#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <exception>
+#include <mutex>
 #include <new>
 #include <numeric>
 #include <thread>
@@ -106,34 +108,111 @@ struct BuildSlot {
     }
 };
 
-// Runs fn(t) for t = 0..T-1, thread 0 on the caller; an exception in any
-// part is rethrown here after all have joined.
-template <typename F>
-void par(int T, const F& fn) {
-    if (T <= 1) {
-        fn(0);
-        return;
-    }
-    std::vector<std::exception_ptr> ex((size_t)T);
-    auto run = [&](int t) {
+// The threads of one build, started once (a build has some twenty-five parallel
+// phases; starting and joining fifteen threads in each took half of its time)
+// and joined with it.  Between phases they poll for a moment, then sleep.
+class Team {
+  public:
+    explicit Team(int parts) : parts_(std::max(parts, 1)) {
+        if (parts_ <= 1) return;
+        th_.reserve((size_t)parts_ - 1);
         try {
-            fn(t);
+            for (int t = 1; t < parts_; ++t) th_.emplace_back([this, t] { work(t); });
         } catch (...) {
-            ex[(size_t)t] = std::current_exception();
+            // could not start every thread: the caller runs the other parts
+        }
+    }
+    ~Team() {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            stop_ = true;
+            phase_.fetch_add(1, std::memory_order_release);
+        }
+        wake_.notify_all();
+        for (auto& t : th_) t.join();
+    }
+    Team(const Team&) = delete;
+    Team& operator=(const Team&) = delete;
+
+    int parts() const { return parts_; }
+
+    // fn(t) for t = 0 .. parts() - 1, part 0 on the caller; an exception in any
+    // part is rethrown here after all have ended.
+    template <typename F>
+    void run(const F& fn) {
+        if (parts_ <= 1) {
+            fn(0);
+            return;
+        }
+        std::vector<std::exception_ptr> ex((size_t)parts_);
+        Job job{&fn, [](const void* f, int t) { (*static_cast<const F*>(f))(t); }, ex.data()};
+        const int started = (int)th_.size();
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            job_ = &job;
+            left_.store(started, std::memory_order_relaxed);
+            phase_.fetch_add(1, std::memory_order_release);
+        }
+        wake_.notify_all();
+        for (int t = started + 1; t < parts_; ++t) job.part(t);
+        job.part(0);
+        for (int i = 0; i < kPolls && left_.load(std::memory_order_acquire) != 0; ++i) pause();
+        if (left_.load(std::memory_order_acquire) != 0) {
+            std::unique_lock<std::mutex> lk(mu_);
+            done_.wait(lk, [&] { return left_.load(std::memory_order_acquire) == 0; });
+        }
+        for (auto& e : ex)
+            if (e) std::rethrow_exception(e);
+    }
+
+  private:
+    static constexpr int kPolls = 2000;  // some tens of microseconds
+    struct Job {
+        const void* fn;
+        void (*call)(const void*, int);
+        std::exception_ptr* ex;
+        void part(int t) const {
+            try {
+                call(fn, t);
+            } catch (...) {
+                ex[t] = std::current_exception();
+            }
         }
     };
-    std::vector<std::thread> th;
-    th.reserve((size_t)T - 1);
-    try {
-        for (int t = 1; t < T; ++t) th.emplace_back(run, t);
-    } catch (...) {
-        // could not start every thread: run the rest here
-        for (int t = (int)th.size() + 1; t < T; ++t) run(t);
+    static void pause() {
+#if defined(__x86_64__)
+        __builtin_ia32_pause();
+#endif
     }
-    run(0);
-    for (auto& x : th) x.join();
-    for (auto& e : ex)
-        if (e) std::rethrow_exception(e);
+    void work(int t) {
+        for (uint64_t seen = 0;;) {
+            for (int i = 0; i < kPolls && phase_.load(std::memory_order_acquire) == seen; ++i) pause();
+            if (phase_.load(std::memory_order_acquire) == seen) {
+                std::unique_lock<std::mutex> lk(mu_);
+                wake_.wait(lk, [&] { return phase_.load(std::memory_order_acquire) != seen; });
+            }
+            ++seen;  // a phase ends only after every thread has taken part in it
+            if (stop_) return;
+            job_->part(t);
+            if (left_.fetch_sub(1, std::memory_order_acq_rel) == 1) {
+                std::lock_guard<std::mutex> lk(mu_);
+                done_.notify_one();
+            }
+        }
+    }
+    const int parts_;
+    std::vector<std::thread> th_;
+    std::mutex mu_;
+    std::condition_variable wake_, done_;
+    std::atomic<uint64_t> phase_{0};
+    std::atomic<int> left_{0};
+    const Job* job_ = nullptr;  // set before phase_ moves on
+    bool stop_ = false;
+};
+
+template <typename F>
+void par(Team& team, const F& fn) {
+    team.run(fn);
 }
 
 // Part t of T of [0, n): [lo, hi).
@@ -142,11 +221,12 @@ inline int64_t part_lo(int64_t n, int t, int T) { return (int64_t)((__int128)n *
 // Lay out rows (already ordered) into 64-row column-major tiles appended to
 // tiles / ent; tiles fill in parallel at bases fixed beforehand.
 template <typename LenFn, typename EntFn>
-int32_t tile_rows(int T, int32_t nrows, LenFn len_of, EntFn ent_of, uint32_t pad, uint32_t flags,
+int32_t tile_rows(Team& team, int32_t nrows, LenFn len_of, EntFn ent_of, uint32_t pad, uint32_t flags,
                   PVec<TileDesc>& tiles, PVec<uint32_t>& ent, std::string& err) {
+    const int T = team.parts();
     const int32_t nt = (nrows + kTile - 1) / kTile;
     PVec<uint32_t> tlen((size_t)nt, 0);
-    par(T, [&](int t) {
+    par(team, [&](int t) {
         for (int64_t k = part_lo(nt, t, T); k < part_lo(nt, t + 1, T); ++k) {
             uint32_t len = 0;
             const int32_t r1 = std::min<int32_t>(nrows, (int32_t)k * kTile + kTile);
@@ -166,10 +246,11 @@ int32_t tile_rows(int T, int32_t nrows, LenFn len_of, EntFn ent_of, uint32_t pad
                                  (uint32_t)std::min<int32_t>(kTile, nrows - k * kTile), flags});
         base += (uint64_t)tlen[(size_t)k] * kTile;
     }
-    ent.resize((size_t)base, pad);
-    par(T, [&](int t) {
+    ent.resize((size_t)base);  // filled below, padding included
+    par(team, [&](int t) {
         for (int64_t k = part_lo(nt, t, T); k < part_lo(nt, t + 1, T); ++k) {
             const TileDesc& d = tiles[t0 + (size_t)k];
+            std::fill_n(ent.begin() + d.base, (size_t)d.len * kTile, pad);
             for (uint32_t q = 0; q < d.nreal; ++q) {
                 const int32_t r = (int32_t)k * kTile + (int32_t)q;
                 const int32_t L = len_of(r);
@@ -190,10 +271,13 @@ struct Chunk {
     int64_t w_empty = 0;
 };
 
-void canonical_chunk(const int32_t* lits, int64_t b0, int64_t b1, int32_t j0, const int64_t* weights, Chunk& C) {
+void canonical_chunk(const int32_t* lits, int64_t b0, int64_t b1, int32_t j0, int64_t clauses, const int64_t* weights,
+                     Chunk& C) {
     constexpr int kShort = 16;  // clauses up to this length are deduplicated in registers
     PVec<uint64_t> key;  // longer ones: (variable, position) sorted
     PVec<uint64_t> emit; // (position, entry) of the emitted literals
+    C.flat.reserve((size_t)(b1 - b0));
+    C.rows.reserve((size_t)clauses);
     int64_t start = b0;
     int32_t j = j0;
     for (int64_t p = b0; p < b1; ++p) {
@@ -277,7 +361,8 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
         return kErrParse;
     }
     BuildSlot slot(nlits);
-    const int T = slot.threads;
+    Team team(slot.threads);
+    const int T = team.parts();
 
     // ---- chunks of whole clauses; checks and counts per chunk ---------------
     PVec<int64_t> cb((size_t)T + 1, nlits);
@@ -288,7 +373,7 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
         cb[(size_t)t] = q;
     }
     PVec<int64_t> zeros((size_t)T, 0), nonzero((size_t)T, 0), bad((size_t)T, -1);
-    par(T, [&](int t) {
+    par(team, [&](int t) {
         int64_t z = 0, nz = 0;  // counted in registers, stored once (no shared cache lines in the loop)
         for (int64_t p = cb[(size_t)t]; p < cb[(size_t)t + 1]; ++p) {
             const int32_t l = lits[p];
@@ -346,7 +431,10 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
     PVec<Row> rows;
     {
         PVec<Chunk> ch((size_t)T);
-        par(T, [&](int t) { canonical_chunk(lits, cb[(size_t)t], cb[(size_t)t + 1], j0[(size_t)t], weights, ch[(size_t)t]); });
+        par(team, [&](int t) {
+            canonical_chunk(lits, cb[(size_t)t], cb[(size_t)t + 1], j0[(size_t)t], zeros[(size_t)t], weights,
+                            ch[(size_t)t]);
+        });
         PVec<int64_t> foff((size_t)T + 1, 0), roff((size_t)T + 1, 0);
         for (int t = 0; t < T; ++t) {
             const Chunk& c = ch[(size_t)t];
@@ -359,7 +447,7 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
         }
         flat.resize((size_t)foff[(size_t)T]);
         rows.resize((size_t)roff[(size_t)T]);
-        par(T, [&](int t) {
+        par(team, [&](int t) {
             Chunk& c = ch[(size_t)t];
             if (!c.flat.empty()) std::memcpy(&flat[(size_t)foff[(size_t)t]], c.flat.data(), c.flat.size() * 4);
             for (size_t i = 0; i < c.rows.size(); ++i) {
@@ -377,11 +465,11 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
     if ((int64_t)T * n <= ((int64_t)1 << 26) && T > 1) {
         // per-thread histograms, then a sum over variable ranges
         std::vector<std::vector<int32_t>> h((size_t)T);
-        par(T, [&](int t) {
+        par(team, [&](int t) {
             h[(size_t)t].assign((size_t)n, 0);
             for (int64_t e = part_lo(P.nnz, t, T); e < part_lo(P.nnz, t + 1, T); ++e) h[(size_t)t][flat[(size_t)e] & kIdx]++;
         });
-        par(T, [&](int t) {
+        par(team, [&](int t) {
             for (int64_t i = part_lo(n, t, T); i < part_lo(n, t + 1, T); ++i) {
                 int32_t d = 0;
                 for (int u = 0; u < T; ++u) d += h[(size_t)u][(size_t)i];
@@ -420,17 +508,21 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
     // from here on the flat entries hold the new variable index, and each row
     // knows its smallest one
     const int64_t nr = (int64_t)rows.size();
-    par(T, [&](int t) {
+    par(team, [&](int t) {
         for (int64_t e = part_lo(P.nnz, t, T); e < part_lo(P.nnz, t + 1, T); ++e)
             flat[(size_t)e] = (uint32_t)P.var_new[flat[(size_t)e] & kIdx] | (flat[(size_t)e] & kSign);
     });
-    par(T, [&](int t) {
+    PVec<int32_t> longest((size_t)T, 0);
+    par(team, [&](int t) {
+        int32_t ml = 0;
         for (int64_t i = part_lo(nr, t, T); i < part_lo(nr, t + 1, T); ++i) {
             Row& r = rows[(size_t)i];
+            ml = std::max(ml, r.len);
             int32_t mv = INT32_MAX;
             for (int32_t c = 0; c < r.len; ++c) mv = std::min(mv, (int32_t)(flat[(size_t)r.off + c] & kIdx));
             r.minvar = mv;
         }
+        longest[(size_t)t] = ml;
     });
 
     // ---- clause rows: plain rows by length desc, then tautological rows; ---
@@ -442,14 +534,13 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
     // counts; then the rows and their entries are gathered into that order
     // once.
     {
-        int32_t maxl = 0;
-        for (const Row& r : rows) maxl = std::max(maxl, r.len);
+        const int32_t maxl = *std::max_element(longest.begin(), longest.end());
         int vbits = 1;
         while (vbits < 31 && ((int64_t)1 << vbits) < (int64_t)n) ++vbits;
         PVec<uint64_t> key((size_t)nr), key2((size_t)nr);
         PVec<int32_t> ord((size_t)nr), ord2((size_t)nr);
         uint64_t kmax = 0;
-        par(T, [&](int t) {
+        par(team, [&](int t) {
             for (int64_t i = part_lo(nr, t, T); i < part_lo(nr, t + 1, T); ++i) {
                 const Row& r = rows[(size_t)i];
                 // class: plain rows of length maxl - c for c <= maxl, then tautologies likewise
@@ -463,7 +554,7 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
         constexpr int kBins = 1 << kDigit;
         std::vector<std::vector<int64_t>> cnt((size_t)T);
         for (int shift = 0; shift < 64 && (kmax >> shift) != 0; shift += kDigit) {
-            par(T, [&](int t) {
+            par(team, [&](int t) {
                 std::vector<int64_t>& c = cnt[(size_t)t];
                 c.assign(kBins, 0);
                 for (int64_t i = part_lo(nr, t, T); i < part_lo(nr, t + 1, T); ++i)
@@ -476,7 +567,7 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
                     cnt[(size_t)t][d] = o;  // this thread's first slot for digit d
                     o += c;
                 }
-            par(T, [&](int t) {
+            par(team, [&](int t) {
                 std::vector<int64_t>& c = cnt[(size_t)t];
                 for (int64_t i = part_lo(nr, t, T); i < part_lo(nr, t + 1, T); ++i) {
                     const int64_t q = c[(key[(size_t)i] >> shift) & (kBins - 1)]++;
@@ -490,7 +581,7 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
         PVec<uint64_t>().swap(key);
         PVec<uint64_t>().swap(key2);
         PVec<int64_t> psum((size_t)T + 1, 0);
-        par(T, [&](int t) {
+        par(team, [&](int t) {
             int64_t s = 0;
             for (int64_t r = part_lo(nr, t, T); r < part_lo(nr, t + 1, T); ++r) s += rows[(size_t)ord[(size_t)r]].len;
             psum[(size_t)t + 1] = s;
@@ -498,7 +589,7 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
         for (int t = 0; t < T; ++t) psum[(size_t)t + 1] += psum[(size_t)t];
         PVec<Row> sorted((size_t)nr);
         PVec<uint32_t> flat2(flat.size());
-        par(T, [&](int t) {
+        par(team, [&](int t) {
             int64_t o = psum[(size_t)t];
             constexpr int64_t kAhead = 16;  // rows fetched ahead of the copy
             const int64_t r1 = part_lo(nr, t + 1, T);
@@ -523,10 +614,10 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
     int32_t n_tr = (int32_t)rows.size() - n_plain;
     const uint32_t cpad = (uint32_t)n;  // dummy variable whose relaxed value stays -0.0
     int32_t rc;
-    rc = tile_rows(T, n_plain, [&](int32_t r) { return rows[r].len; },
+    rc = tile_rows(team, n_plain, [&](int32_t r) { return rows[r].len; },
                    [&](int32_t r, int32_t c) { return flat[rows[r].off + c]; }, cpad, 0u, P.c_tile, P.c_ent, err);
     if (rc) return rc;
-    rc = tile_rows(T, n_tr, [&](int32_t r) { return rows[n_plain + r].len; },
+    rc = tile_rows(team, n_tr, [&](int32_t r) { return rows[n_plain + r].len; },
                    [&](int32_t r, int32_t c) { return flat[rows[n_plain + r].off + c]; }, cpad, 1u, P.c_tile,
                    P.c_ent, err);
     if (rc) return rc;
@@ -542,7 +633,7 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
     {
         const int32_t tp = (n_plain + kTile - 1) / kTile;
         if (weights) P.c_w.assign((size_t)P.c_tiles * kTile, 0);
-        par(T, [&](int t) {
+        par(team, [&](int t) {
             for (int64_t r = part_lo(nr, t, T); r < part_lo(nr, t + 1, T); ++r) {
                 const int32_t k = r < n_plain ? (int32_t)r : tp * kTile + (int32_t)(r - n_plain);
                 krow[(size_t)r] = k;
@@ -570,7 +661,7 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
             bstart[b + 1] = voff[std::min<int64_t>((int64_t)(b + 1) << kShift, n)];
         PVec<uint64_t> pairs((size_t)P.nnz);  // variable << 32 | (row | sign)
         std::vector<std::vector<int64_t>> cnt((size_t)T);
-        par(T, [&](int t) {
+        par(team, [&](int t) {
             cnt[(size_t)t].assign((size_t)nblk, 0);
             for (int64_t r = part_lo(nr, t, T); r < part_lo(nr, t + 1, T); ++r) {
                 const Row& R = rows[(size_t)r];
@@ -585,7 +676,7 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
                 o += c;
             }
         }
-        par(T, [&](int t) {
+        par(team, [&](int t) {
             std::vector<int64_t>& fill = cnt[(size_t)t];
             for (int64_t r = part_lo(nr, t, T); r < part_lo(nr, t + 1, T); ++r) {
                 const Row& R = rows[(size_t)r];
@@ -596,7 +687,7 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
                 }
             }
         });
-        par(T, [&](int t) {
+        par(team, [&](int t) {
             PVec<int64_t> fill;
             for (int64_t b = part_lo(nblk, t, T); b < part_lo(nblk, t + 1, T); ++b) {
                 const int64_t v0 = b << kShift, v1 = std::min<int64_t>((b + 1) << kShift, n);
@@ -630,13 +721,13 @@ int32_t build_plan_impl(int32_t n, const int32_t* lits, int64_t nlits, const int
     P.seg_row.resize((size_t)P.seg_rows);
     std::iota(P.seg_row.begin(), P.seg_row.end(), 0);
     const uint32_t vpad = (uint32_t)P.a_zero_row();
-    rc = tile_rows(T, P.seg_rows, [&](int32_t r) { return segs[r].len; },
+    rc = tile_rows(team, P.seg_rows, [&](int32_t r) { return segs[r].len; },
                    [&](int32_t r, int32_t c) { return occ[segs[r].off + (int64_t)c * segs[r].stride]; }, vpad, 0u,
                    P.v_tile, P.v_ent, err);
     if (rc) return rc;
     P.seg_tiles = (int32_t)P.v_tile.size();
     int32_t n_light = P.n_act - P.n_heavy;
-    rc = tile_rows(T, n_light, [&](int32_t r) { return P.degree[P.n_heavy + r]; },
+    rc = tile_rows(team, n_light, [&](int32_t r) { return P.degree[P.n_heavy + r]; },
                    [&](int32_t r, int32_t c) { return occ[voff[P.n_heavy + r] + c]; }, vpad, 0u,
                    P.v_tile, P.v_ent, err);
     if (rc) return rc;

@@ -6,6 +6,8 @@
 #include <cstddef>
 #include <cstdint>
 #include <string>
+#include <new>
+#include <utility>
 #include <vector>
 
 namespace hms {
@@ -13,7 +15,9 @@ namespace hms {
 // Host buffers of the plan build.  Blocks of 2 MiB or more are mapped apart
 // with transparent huge pages requested: the build is bound by the first-touch
 // page faults of its fresh buffers, and a 2 MiB page faults once where 4 KiB
-// pages fault 512 times.  Smaller blocks come from operator new.
+// pages fault 512 times.  Smaller blocks come from operator new.  An element
+// made without a value is left as the memory is: a buffer that is filled in
+// parallel is then first touched there, not zeroed by the calling thread.
 void* build_alloc(std::size_t bytes);
 void build_free(void* p, std::size_t bytes) noexcept;
 
@@ -25,6 +29,14 @@ struct BuildAlloc {
     BuildAlloc(const BuildAlloc<U>&) {}
     T* allocate(std::size_t n) { return static_cast<T*>(build_alloc(n * sizeof(T))); }
     void deallocate(T* p, std::size_t n) noexcept { build_free(p, n * sizeof(T)); }
+    template <class U>
+    void construct(U* p) {
+        ::new (static_cast<void*>(p)) U;
+    }
+    template <class U, class... A>
+    void construct(U* p, A&&... a) {
+        ::new (static_cast<void*>(p)) U(std::forward<A>(a)...);
+    }
     template <class U>
     bool operator==(const BuildAlloc<U>&) const { return true; }
     template <class U>
