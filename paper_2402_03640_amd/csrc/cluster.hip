@@ -343,6 +343,29 @@ __global__ __launch_bounds__(256) void k_cluster_scalars(const ClusterDesc* Ds) 
     D.scal[k] = make_float2(ss, ib2);
 }
 
+// The word at a byte of the dynamic LDS array: by LDS address, or by index.
+// The kernels declare no other LDS, so the array starts at 0 (enroll checks
+// that), and an index costs an addition of that 0 per access: n = 20000, 64
+// restarts 12.0 us a step by index, 11.6 by address (with the record blocks in
+// two buffers in turn instead of copied).  Where one tile's latency counts, not
+// the instructions, the index is the faster one (n = 1000: 2.78 against 2.85).
+struct LdsAddress {
+    __device__ __forceinline__ uint32_t operator()(uint32_t at) const {
+        return *(const __attribute__((address_space(3))) uint32_t*)at;
+    }
+};
+struct LdsIndex {
+    const unsigned char* smem;
+    __device__ __forceinline__ uint32_t operator()(uint32_t at) const {
+        return *reinterpret_cast<const uint32_t*>(smem + at);
+    }
+};
+// Before LdsAddress is used the array's address has to have escaped, or the
+// compiler may hold stores to it to be no concern of those loads.
+__device__ __forceinline__ void escape_lds(const unsigned char* smem) {
+    asm volatile("" : : "v"((const __attribute__((address_space(3))) unsigned char*)smem) : "memory");
+}
+
 // Out of line: the branch inside tanhf would make the compiler treat the whole
 // tile loop around it as divergent (vector branches and masks for its trip
 // counts).
@@ -389,8 +412,8 @@ struct RecordBlock {
 
 // Adds records OFF .. OFF + N - 1 of a block to the row's sum of magnitudes.
 // t sits at LDS byte `at` (a power of two past every offset, or 0).
-template <int N, int OFF, int NO, bool WT>
-__device__ __forceinline__ void sum_records(const unsigned char* smem, const uint32_t at, const RecordBlock<NO, WT>& b,
+template <int N, int OFF, class Lds, int NO, bool WT>
+__device__ __forceinline__ void sum_records(const Lds lds, const uint32_t at, const RecordBlock<NO, WT>& b,
                                             const float to, const float tom, double& Gm) {
     constexpr int W = RecordBlock<NO, WT>::W;
     float t[N][NO];
@@ -399,7 +422,7 @@ __device__ __forceinline__ void sum_records(const unsigned char* smem, const uin
 #pragma unroll
         for (int j = 0; j < NO; ++j) {
             const uint32_t w = b.w[(OFF + c) * W + (j >> 1)];
-            t[c][j] = *reinterpret_cast<const float*>(smem + (((j & 1 ? w >> 15 : w) & 0x1fffcu) | at));
+            t[c][j] = __uint_as_float(lds(((j & 1 ? w >> 15 : w) & 0x1fffcu) | at));
         }
 #pragma unroll
     for (int c = 0; c < N; ++c) {
@@ -432,19 +455,19 @@ __device__ __forceinline__ void sum_records(const unsigned char* smem, const uin
 
 // The first `left` records of a block (1 to 8; whole pairs, the rest is inert),
 // up to 16 gathers together.
-template <int NO, bool WT>
-__device__ __forceinline__ void sum_block(const unsigned char* smem, const uint32_t at, const RecordBlock<NO, WT>& b,
+template <class Lds, int NO, bool WT>
+__device__ __forceinline__ void sum_block(const Lds lds, const uint32_t at, const RecordBlock<NO, WT>& b,
                                           const int left, const float to, const float tom, double& Gm) {
     if constexpr (NO == 2) {
-        if (left > 6) sum_records<8, 0>(smem, at, b, to, tom, Gm);
-        else if (left > 4) sum_records<6, 0>(smem, at, b, to, tom, Gm);
-        else if (left > 2) sum_records<4, 0>(smem, at, b, to, tom, Gm);
-        else sum_records<2, 0>(smem, at, b, to, tom, Gm);
+        if (left > 6) sum_records<8, 0>(lds, at, b, to, tom, Gm);
+        else if (left > 4) sum_records<6, 0>(lds, at, b, to, tom, Gm);
+        else if (left > 2) sum_records<4, 0>(lds, at, b, to, tom, Gm);
+        else sum_records<2, 0>(lds, at, b, to, tom, Gm);
     } else {
-        if (left > 2) sum_records<4, 0>(smem, at, b, to, tom, Gm);
-        else sum_records<2, 0>(smem, at, b, to, tom, Gm);
-        if (left > 6) sum_records<4, 4>(smem, at, b, to, tom, Gm);
-        else if (left > 4) sum_records<2, 4>(smem, at, b, to, tom, Gm);
+        if (left > 2) sum_records<4, 0>(lds, at, b, to, tom, Gm);
+        else sum_records<2, 0>(lds, at, b, to, tom, Gm);
+        if (left > 6) sum_records<4, 4>(lds, at, b, to, tom, Gm);
+        else if (left > 4) sum_records<2, 4>(lds, at, b, to, tom, Gm);
     }
 }
 
@@ -452,7 +475,7 @@ __device__ __forceinline__ void sum_block(const unsigned char* smem, const uint3
 // in LDS) say which lanes' clauses are unsatisfied; those alone read the values
 // of t, from the L2.
 template <int N, int OFF, int NO, bool WT>
-__device__ __forceinline__ void sum_records(const unsigned char* smem, const __amdgpu_buffer_rsrc_t rs,
+__device__ __forceinline__ void sum_records(const __amdgpu_buffer_rsrc_t rs,
                                             const RecordBlock<NO, WT, true>& b, const float to, const float tom,
                                             double& Gm) {
     constexpr int W = cluster_record_words(NO);
@@ -461,8 +484,7 @@ __device__ __forceinline__ void sum_records(const unsigned char* smem, const __a
     for (int c = 0; c < N; ++c)
 #pragma unroll
         for (int j = 0; j < NO; ++j)
-            t[c][j] = *reinterpret_cast<const uint32_t*>(
-                smem + ((b.w[(OFF + c) * W + (j >> 1)] >> (j & 1 ? 19 : 3)) & 0x1ffcu));
+            t[c][j] = LdsAddress{}((b.w[(OFF + c) * W + (j >> 1)] >> (j & 1 ? 19 : 3)) & 0x1ffcu);
 #pragma unroll
     for (int c = 0; c < N; ++c) {
         uint32_t any = 0;  // top bit: some other literal is true
@@ -504,15 +526,15 @@ __device__ __forceinline__ void sum_records(const unsigned char* smem, const __a
     }
 }
 template <int NO, bool WT>
-__device__ __forceinline__ void sum_block(const unsigned char* smem, const __amdgpu_buffer_rsrc_t rs,
+__device__ __forceinline__ void sum_block(const __amdgpu_buffer_rsrc_t rs,
                                           const RecordBlock<NO, WT, true>& b, const int left, const float to,
                                           const float tom, double& Gm) {
     if constexpr (NO == 2) {
-        if (left > 4) sum_records<8, 0>(smem, rs, b, to, tom, Gm);
-        else sum_records<4, 0>(smem, rs, b, to, tom, Gm);
+        if (left > 4) sum_records<8, 0>(rs, b, to, tom, Gm);
+        else sum_records<4, 0>(rs, b, to, tom, Gm);
     } else {
-        sum_records<4, 0>(smem, rs, b, to, tom, Gm);
-        if (left > 4) sum_records<4, 4>(smem, rs, b, to, tom, Gm);
+        sum_records<4, 0>(rs, b, to, tom, Gm);
+        if (left > 4) sum_records<4, 4>(rs, b, to, tom, Gm);
     }
 }
 
@@ -543,8 +565,8 @@ __device__ __forceinline__ void count_row(const bool unsat, const float f, const
 
 // Unsatisfied weight of clause tiles ct0, ct0 + stride, ...; the loss terms are
 // added to los.  Both are the wavefront's sums.
-template <bool WT>
-__device__ __forceinline__ unsigned long long count_clauses(const unsigned char* smem, const uint32_t at,
+template <bool WT, class Lds>
+__device__ __forceinline__ unsigned long long count_clauses(const Lds lds, const uint32_t at,
                                                             const TileDesc* c_tile, const HMS_GLOBAL uint32_t* cslot,
                                                             const HMS_GLOBAL int64_t* c_w, const int c_tiles,
                                                             const int ct0, const int stride, const int lane,
@@ -559,7 +581,7 @@ __device__ __forceinline__ unsigned long long count_clauses(const unsigned char*
 #pragma unroll 5
         for (uint32_t c = 0; c < d.len; ++c) {
             const uint32_t en = cslot[(size_t)d.base + (size_t)c * kTile + lane];
-            const uint32_t b = *reinterpret_cast<const uint32_t*>(smem + (((en & kIdx) << 2) | at)) ^ (en & kSign);
+            const uint32_t b = lds(((en & kIdx) << 2) | at) ^ (en & kSign);
             f = f + __uint_as_float(b);
             all &= b;
         }
@@ -576,8 +598,7 @@ __device__ __forceinline__ unsigned long long count_clauses(const unsigned char*
 
 // The same in the wide form (t only where the loss is wanted).
 template <bool WT>
-__device__ __forceinline__ unsigned long long count_clauses_wide(const unsigned char* smem,
-                                                                 const __amdgpu_buffer_rsrc_t rs,
+__device__ __forceinline__ unsigned long long count_clauses_wide(const __amdgpu_buffer_rsrc_t rs,
                                                                  const TileDesc* c_tile,
                                                                  const HMS_GLOBAL uint32_t* cslot,
                                                                  const HMS_GLOBAL int64_t* c_w, const int c_tiles,
@@ -592,7 +613,7 @@ __device__ __forceinline__ unsigned long long count_clauses_wide(const unsigned 
 #pragma unroll 5
         for (uint32_t c = 0; c < d.len; ++c) {
             const uint32_t en = cslot[(size_t)d.base + (size_t)c * kTile + lane];
-            const uint32_t b = *reinterpret_cast<const uint32_t*>(smem + ((en >> 3) & 0x0ffffffcu));
+            const uint32_t b = LdsAddress{}((en >> 3) & 0x0ffffffcu);
             any |= __builtin_amdgcn_alignbit(b, b, en) ^ en;
         }
         float f = 0.0f;
@@ -632,7 +653,7 @@ struct ClauseCache {
             if (c < len) en[c] = cslot[(size_t)d.base + (size_t)c * kTile + lane];
     }
     template <bool WT>
-    __device__ __forceinline__ unsigned long long count(const unsigned char* smem, const uint32_t at,
+    __device__ __forceinline__ unsigned long long count(const LdsIndex lds, const uint32_t at,
                                                         const HMS_GLOBAL int64_t* c_w, const bool want_loss, double& los,
                                                         const int lane) const {
         los = 0.0;
@@ -643,7 +664,7 @@ struct ClauseCache {
 #pragma unroll
         for (int c = 0; c < kClusterMaxK; ++c)
             if (c < len)
-                b[c] = *reinterpret_cast<const uint32_t*>(smem + (((en[c] & kIdx) << 2) | at)) ^ (en[c] & kSign);
+                b[c] = lds(((en[c] & kIdx) << 2) | at) ^ (en[c] & kSign);
 #pragma unroll
         for (int c = 0; c < kClusterMaxK; ++c)
             if (c < len) {
@@ -748,7 +769,7 @@ __device__ __forceinline__ void keep_inactive(const ClusterDesc& D, const int r,
 // Registration of a workgroup (one thread): its place on its XCD, then the
 // wait until the whole cluster has arrived.  sh.group is null when there is
 // nothing to do: no cluster left for this ticket, or one that did not fill.
-__device__ void enroll(const ClusterLaunch& A, Shared& sh) {
+__device__ void enroll(const ClusterLaunch& A, const unsigned char* smem, Shared& sh) {
     const int x = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kXcds - 1);  // XCC_ID
     int tk = __hip_atomic_fetch_add(A.tickets + x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const ClusterGroup* g = nullptr;
@@ -759,6 +780,7 @@ __device__ void enroll(const ClusterLaunch& A, Shared& sh) {
         }
         tk -= A.groups[i].C;
     }
+    if ((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)smem != 0) g = nullptr;
     if (g != nullptr) {
         int32_t* ctl = g->ctl;
         const int before = __hip_atomic_fetch_add(ctl, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -784,8 +806,11 @@ __device__ void enroll(const ClusterLaunch& A, Shared& sh) {
 }
 
 // Several variable tiles per wavefront, state in LDS.  3-CNF n = 20000, 64
-// restarts: 11.9 us a step, about 10 of them vector issue (records 4.8, tanh,
-// sech^2 and Adam 4.6).
+// restarts: 11.6 us a step, bound by vector instructions (24500 of a CU's 27800
+// cycles a step; without the optimizer's 130 per tile 9.2 us, without copying
+// t 11.4, with the records always the same 11.8 where all takes 11.9).  A record
+// costs 17 of them.  Taking 16-bit slots out with one instruction each
+// (sub-dword addressing) saves one and gains nothing: it issues at half rate.
 //
 // WIDE: for more variables than t fits LDS for (n past 32000), or than a 15-bit
 // field can name.  LDS holds the roundings, a bit each, which decide for every
@@ -807,7 +832,8 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    if (tid == 0) enroll(A, sh);
+    escape_lds(smem);
+    if (tid == 0) enroll(A, smem, sh);
     __syncthreads();
     const ClusterGroup* gp = uniform(sh.group);
     if (gp == nullptr) return;
@@ -901,7 +927,8 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     // own tiles of this wavefront
     const int my_tiles = ntl > wave ? (ntl - 1 - wave) / kWaves + 1 : 0;
     auto own_tile = [&](int i) { return i * kWaves + wave; };
-    RecordBlock<NO, WT, WIDE> nx;  // the next record block, loaded one block ahead
+    RecordBlock<NO, WT, WIDE> ra, rb;  // record blocks in turn: one in use, the next one loading
+    bool turn = false;                 // rb is the one in use
     auto fetch = [&](RecordBlock<NO, WT, WIDE>& b, int block, int left, bool neg) { b.load(rec, wrec, block, left, neg, lane); };
     auto tile_info = [&](int i) {
         const uint32_t* p = reinterpret_cast<const uint32_t*>(tiles + (own_tile(i) * C + member));
@@ -910,7 +937,7 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     int2 tn = make_int2(0, 0);
     if (my_tiles > 0) {
         tn = tile_info(0);
-        fetch(nx, __builtin_amdgcn_readfirstlane(tn.x), __builtin_amdgcn_readfirstlane(tn.y), lx[own_tile(0) * 64 + lane] > 0.0f);
+        fetch(ra, __builtin_amdgcn_readfirstlane(tn.x), __builtin_amdgcn_readfirstlane(tn.y), lx[own_tile(0) * 64 + lane] > 0.0f);
     }
 
     int kc = step0 % K;
@@ -931,10 +958,10 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
             double los = 0.0;
             unsigned long long cnt;
             if constexpr (WIDE)
-                cnt = count_clauses_wide<WT>(smem, rs, c_tile, cslot, c_w, c_tiles, (kWaves - 1 - wave) * C + member,
+                cnt = count_clauses_wide<WT>(rs, c_tile, cslot, c_w, c_tiles, (kWaves - 1 - wave) * C + member,
                                              kWaves * C, lane, want_loss, los);
             else
-                cnt = count_clauses<WT>(smem, 0u, c_tile, cslot, c_w, c_tiles, (kWaves - 1 - wave) * C + member,
+                cnt = count_clauses<WT>(LdsAddress{}, 0u, c_tile, cslot, c_w, c_tiles, (kWaves - 1 - wave) * C + member,
                                         kWaves * C, lane, want_loss, los);
             if (lane == 0 && cnt != 0) atomicAdd(&sh.cnt[par], cnt);
             if (want_loss && lane == 0) sh.los[wave] = los;
@@ -961,15 +988,21 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
                 if (more) tn = tile_info(i + 1);
                 const float xn = lx[own_tile(more ? i + 1 : i) * 64 + lane];
                 for (int k = 0; k < len; k += 8) {
-                    RecordBlock<NO, WT, WIDE> b = nx;
-#pragma unroll
-                    for (int j = 0; j < 8 * W; ++j) asm volatile("" : "+v"(b.w[j]));
-                    asm volatile("" : "+v"(b.bits));
                     const int left = len - k;
-                    if (left > 8) fetch(nx, tb0 + (k >> 3) + 1, left - 8, xo > 0.0f);
-                    else if (more) fetch(nx, __builtin_amdgcn_readfirstlane(tn.x), __builtin_amdgcn_readfirstlane(tn.y), xn > 0.0f);
-                    if constexpr (WIDE) sum_block(smem, rs, b, left, to, tom, Gm);
-                    else sum_block(smem, 0u, b, left, to, tom, Gm);
+                    auto block = [&](RecordBlock<NO, WT, WIDE>& b, RecordBlock<NO, WT, WIDE>& nx) {
+                        // the block in use has arrived before the next one's loads go out: its wait
+                        // would be for both
+#pragma unroll
+                        for (int j = 0; j < 8 * W; ++j) asm volatile("" : "+v"(b.w[j]));
+                        asm volatile("" : "+v"(b.bits));
+                        if (left > 8) fetch(nx, tb0 + (k >> 3) + 1, left - 8, xo > 0.0f);
+                        else if (more) fetch(nx, __builtin_amdgcn_readfirstlane(tn.x), __builtin_amdgcn_readfirstlane(tn.y), xn > 0.0f);
+                        if constexpr (WIDE) sum_block(rs, b, left, to, tom, Gm);
+                        else sum_block(LdsAddress{}, 0u, b, left, to, tom, Gm);
+                    };
+                    if (turn) block(rb, ra);
+                    else block(ra, rb);
+                    turn = !turn;
                 }
                 // a positive literal in the loss adds -a, a negative one +a (0.0 - 0.0 keeps an empty sum +0)
                 const double Gs = xo > 0.0f ? Gm : 0.0 - Gm;
@@ -998,7 +1031,8 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
             // the next step's first block, in flight over the exchange
             if (my_tiles > 0) {
                 tn = tile_info(0);
-                fetch(nx, __builtin_amdgcn_readfirstlane(tn.x), __builtin_amdgcn_readfirstlane(tn.y), lx[own_tile(0) * 64 + lane] > 0.0f);
+                fetch(ra, __builtin_amdgcn_readfirstlane(tn.x), __builtin_amdgcn_readfirstlane(tn.y), lx[own_tile(0) * 64 + lane] > 0.0f);
+                turn = false;
             }
         }
         // ---- the step's flag: own stores have reached the L2 ------------------
@@ -1106,7 +1140,7 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster_one(ClusterLaunch A
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (tid == 0) enroll(A, sh);
+    if (tid == 0) enroll(A, smem, sh);
     __syncthreads();
     const ClusterGroup* gp = uniform(sh.group);
     if (gp == nullptr) return;
@@ -1268,11 +1302,11 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster_one(ClusterLaunch A
             double los = 0.0;
             unsigned long long cnt = 0;
             const int first = (kWaves - 1 - wave) * C + member;
-            if constexpr (EX) cnt = cache.count<WT>(smem, at, c_w, want_loss, los, lane);
+            if constexpr (EX) cnt = cache.count<WT>(LdsIndex{smem}, at, c_w, want_loss, los, lane);
             const ClusterDesc* d = launder(dp);
             const int c_tiles = load_uniform(&d->c_tiles);
             if (!EX || first + CW * C < c_tiles)
-                cnt += count_clauses<WT>(smem, at, load_uniform(&d->c_tile),
+                cnt += count_clauses<WT>(LdsIndex{smem}, at, load_uniform(&d->c_tile),
                                          (const HMS_GLOBAL uint32_t*)load_uniform(&d->cslot), c_w, c_tiles,
                                          EX ? first + CW * C : first, (EX ? CW : kWaves) * C, lane, want_loss, los);
             if (lane == 0) {
@@ -1297,14 +1331,14 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster_one(ClusterLaunch A
             if (opt != kSgd)
                 sc = make_float2(__uint_as_float(ldc(scal + 2 * step)), __uint_as_float(ldc(scal + 2 * step + 1)));
             double Gm = 0.0;
-            sum_block(smem, at, b0, len, to, tom, Gm);
-            if (len > 8) sum_block(smem, at, b1, len - 8, to, tom, Gm);
+            sum_block(LdsIndex{smem}, at, b0, len, to, tom, Gm);
+            if (len > 8) sum_block(LdsIndex{smem}, at, b1, len - 8, to, tom, Gm);
             for (int k = 16; k < len; k += 8) {
                 RecordBlock<NO, WT> b;
                 const ClusterDesc* d = launder(dp);
                 b.load((const HMS_GLOBAL uint32_t*)load_uniform(&d->rec), (const HMS_GLOBAL float*)load_uniform(&d->wrec),
                        block0 + (k >> 3), 8, neg, lane);
-                sum_block(smem, at, b, len - k, to, tom, Gm);
+                sum_block(LdsIndex{smem}, at, b, len - k, to, tom, Gm);
             }
             // a positive literal in the loss adds -a, a negative one +a (0.0 - 0.0 keeps an empty sum +0)
             const double Gs = was ? Gm : 0.0 - Gm;
