@@ -730,10 +730,13 @@ def main():
         # cluster solver: one launch holds the whole loop, with the state in LDS
         # and the formula in each XCD's L2.  The algorithmic bytes of a step
         # (index arrays once, state per restart) against its time: a rate to
-        # compare schedules by, not HBM traffic
+        # compare schedules by, not HBM traffic.  The time is the timed solves'
+        # (time_kernels counts every iterate of a one-launch schedule)
+        step_ms = sum(dev_ms) / len(dev_ms) / T
         achieved = (fb + bb) / (step_ms * 1e-3) / 1e9
-        roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
+        roof = {"bound": "vector instructions (state on chip)", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": None,
+                "note": "algorithmic bytes over time, not HBM traffic: the state never leaves the chip",
                 "kernel": "cluster (whole loop in one launch; figures per gradient step)",
                 "algorithmic_bytes_per_launch": fb + bb, "avg_launch_us": round(step_ms * 1e3, 3)}
     elif fwd_ms <= 0 or bwd_ms <= 0:
