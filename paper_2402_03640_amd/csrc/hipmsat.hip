@@ -1354,7 +1354,7 @@ bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p) {
 bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p, int64_t together) {
     hms::ClusterShape sh;
     const int64_t nnz = cnf->plan.nnz;
-    if (p->steps < (nnz <= (int64_t(1) << 14) ? 256 : 64) || !cluster_fits(cnf, p, sh)) return false;
+    if (nnz < 5000 || p->steps < (nnz <= (int64_t(1) << 14) ? 256 : 64) || !cluster_fits(cnf, p, sh)) return false;
     if (nnz < 1000 * (sh.NO >= 4 ? 24 : sh.NO == 3 ? 7 : 5)) return false;
     const int64_t R = std::max<int64_t>(together, p->restarts);
     if (nnz <= kResidentNnz && R > hms::kXcds * hms::kXcdCus / 2) return false;
@@ -2166,6 +2166,14 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
     std::map<Form, int64_t> cluster_units;
     std::vector<hms::ClusterShape> shape(count);
     std::vector<char> fits(count, 0);
+    std::vector<std::pair<const float*, const float*>> inputs;  // start points of the batch
+    for (int32_t i = 0; i < count; ++i) {
+        const size_t nR = (size_t)cnfs[i]->plan.n * params[i].restarts;
+        const hms_solve_state* rs = params[i].resume;
+        for (const float* in : {(const float*)params[i].x0, (const float*)(rs ? rs->x : nullptr),
+                                (const float*)(rs ? rs->m : nullptr), (const float*)(rs ? rs->v : nullptr)})
+            if (in) inputs.emplace_back(in, in + nR);
+    }
     auto form = [&](int32_t i) {
         return Form{shape[i].NO, cnfs[i]->plan.weighted, shape[i].mode == hms::kClusterWide};
     };
@@ -2181,13 +2189,11 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
         }
         // no input of the batch may lie in an output: the launches before
         // another one's would overwrite it
-        bool apart = true;
         const float* o = results[i].x_final;
         const size_t on = (size_t)cnfs[i]->plan.n * p.restarts;
-        for (int32_t j = 0; j < count && o && apart; ++j) {
-            const float* in = params[j].resume ? params[j].resume->x : params[j].x0;
-            if (in && in < o + on && o < in + (size_t)cnfs[j]->plan.n * params[j].restarts) apart = false;
-        }
+        bool apart = true;
+        if (o)
+            for (const auto& in : inputs) apart = apart && !(in.first < o + on && o < in.second);
         if (!apart) continue;
         fits[i] = 1;
         cluster_units[form(i)] += p.restarts;
