@@ -167,10 +167,10 @@ typedef struct {
                             (small instances skip the timing); 0 = take the resident solver
                             (255) when the state fits it and nnz <= 2^15 (2^16 with K = 1),
                             else a fixed tiled schedule for R.  Either way a solve of 64 steps
-                            or more that the cluster solver (254: a few workgroups of one XCD
-                            per restart, unsat-masked loss, clauses of at most five literals,
-                            at most about 32000 variables, no split rows) can run and is known
-                            to run faster takes it without timing */
+                            or more (256 up to 2^14 nonzeros) that the cluster solver (254: a
+                            few workgroups of one XCD per restart, unsat-masked loss, clauses of
+                            at most five literals, at most 63488 variables, no split rows) can
+                            run and is known to run faster takes it without timing */
     double time_limit_s; /* > 0: stop at a K-step boundary once exceeded (not reproducible) */
     const float* x0;     /* DEVICE [n][R] initial values, or NULL for SplitMix64 U(-1,1) */
     void* stream;        /* hipStream_t */

@@ -1,6 +1,6 @@
 // Cluster solver: the whole Algorithm 1 loop of one (instance, restart) runs
 // in C workgroups on the CUs of one XCD, with the relaxed values of every
-// variable in each workgroup's LDS.  Used where the state of an instance fits
+// variable (in the wide form: their roundings) in each workgroup's LDS.  Used where the state of an instance fits
 // LDS but one workgroup is too slow and the tiled kernels are bound by launch
 // latency or by the fabric traffic of their gathers.
 #pragma once
