@@ -45,12 +45,10 @@ namespace hms {
 
 namespace {
 
-constexpr int kWaves = kClusterThreads / 64;
+constexpr int kWaves = kClusterWaves;
 constexpr int kFlagStride = 16;          // u64 per flag: one 128-byte line
 constexpr uint64_t kRegisterTicks = 2000000;  // wall-clock ticks (100 MHz) a cluster waits to fill: 20 ms
 constexpr int kSpinLimit = 1 << 21;      // polls of one flag, about a second
-constexpr int kOneSlots = 4096;           // LDS slots up to which t is exchanged as {t, step} words
-constexpr uint32_t kAltByte = 0x20000;   // second copy of t in LDS (a bit past every record offset)
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -59,8 +57,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // load counts as an LDS access as well, and every wait for a gather would then
 // wait for the record loads in flight.
 #define HMS_GLOBAL __attribute__((address_space(1)))
-
-__host__ __device__ __forceinline__ size_t up16(size_t b) { return (b + 15) & ~size_t(15); }
 
 // Workgroup variables, after the arrays (no static LDS: the records' byte
 // offsets are then LDS addresses as they stand).
@@ -71,21 +67,7 @@ struct Shared {
     double los[kWaves];
     unsigned long long wcnt[kWaves];
 };
-
-// LDS of a workgroup: t of all variables and two constants, own x, m, v, own
-// rounded bits (current and best).
-__host__ __device__ __forceinline__ size_t t_bytes(int32_t C, int32_t slice) { return up16(((size_t)C * slice + 2) * 4); }
-size_t lds_bytes(int32_t C, int32_t slice) {
-    return up16(t_bytes(C, slice) + (size_t)slice * 12 + (size_t)(slice / 64) * 16) + sizeof(Shared);
-}
-// The same in the wide form: a bit per variable and for the two constants, own
-// t, x, m, v, own rounded bits.
-__host__ __device__ __forceinline__ size_t bits_bytes(int32_t C, int32_t slice) {
-    return up16(((size_t)C * slice / 64 + 1) * 8);
-}
-size_t wide_lds_bytes(int32_t C, int32_t slice) {
-    return up16(bits_bytes(C, slice) + (size_t)slice * 16 + (size_t)(slice / 64) * 16) + sizeof(Shared);
-}
+static_assert(sizeof(Shared) == kClusterSharedBytes, "the LDS sizes count these");
 
 // A wave-uniform pointer, and a structure behind one, in scalar registers.
 template <typename T>
@@ -812,8 +794,7 @@ __device__ void enroll(const ClusterLaunch& A, const unsigned char* smem, Shared
 // costs 17 of them.  Taking 16-bit slots out with one instruction each
 // (sub-dword addressing) saves one and gains nothing: it issues at half rate.
 //
-// WIDE: for more variables than t fits LDS for (n past 32000), or than a 15-bit
-// field can name.  LDS holds the roundings, a bit each, which decide for every
+// WIDE: for more variables than t fits LDS for (n past 31744).  LDS holds the roundings, a bit each, which decide for every
 // record whether its clause is unsatisfied; t itself is gathered from the L2
 // only in the lanes (a tenth or so) where it is.  An iteration exchanges the
 // bits, not t.  Bound by the latency of those gathers and the stream of records
@@ -851,7 +832,7 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     // t of all variables, or (WIDE) their roundings; own t is kept in lo then
     float* lt = reinterpret_cast<float*>(smem);
     uint64_t* lround = reinterpret_cast<uint64_t*>(smem);
-    float* lx = reinterpret_cast<float*>(smem + (WIDE ? bits_bytes(C, slice) : t_bytes(C, slice)));
+    float* lx = reinterpret_cast<float*>(smem + (WIDE ? cluster_bits_bytes(C, slice) : cluster_t_bytes(C, slice)));
     float* lm = lx + slice;
     float* lv = lm + slice;
     float* lo = lv + slice;
@@ -1516,61 +1497,20 @@ hipError_t launch_mode(const ClusterLaunch& L, const ClusterShape& sh, size_t ld
 
 }  // namespace
 
-size_t one_lds_bytes(int32_t C, int32_t slice, bool ex) {
-    return (ex ? kAltByte : 0) + t_bytes(C, slice) + sizeof(Shared);
-}
-
-bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& sh, bool many) {
+bool cluster_size(const HostPlan& P, ClusterSize& Z) {
     if (P.n_heavy != 0 || P.v_tiles < 2 || P.w_total >= (int64_t(1) << 32)) return false;
     uint32_t k = 0;
     for (const TileDesc& d : P.c_tile)
         if (!(d.flags & 1u)) k = std::max(k, d.len);
     if (k > (uint32_t)kClusterMaxK) return false;
-    sh.NO = std::max(2, (int32_t)k - 1);
-    // as many workgroups per restart as leave every restart its own at once
-    int32_t C = kXcdCus;
-    while (C > 2 && (int64_t)kXcds * (kXcdCus / C) < R) C /= 2;
-    while (C > 2 && C > P.v_tiles) C /= 2;
-    // at most one tile per wavefront: the fewest workgroups that leave each of
-    // their four SIMDs one tile, half as many tiles where t goes in words (n =
-    // 4000, 3-CNF, one restart: 2.33 us a step at one, 2.31 at two, 2.39 at
-    // four, 2.94 at sixteen tiles)
-    if (!many && P.v_tiles <= kWaves * C) {
-        const int per = P.v_tiles * kTile <= kOneSlots ? 2 : 4;  // tiles per workgroup
-        int32_t c1 = 2;
-        while (c1 < C && P.v_tiles > per * c1) c1 *= 2;
-        const int32_t slice = (P.v_tiles + c1 - 1) / c1 * kTile;
-        const bool words = c1 * slice <= kOneSlots && slice / kTile <= kWaves / 2;
-        const size_t lds = one_lds_bytes(c1, slice, words);
-        if (lds <= lds_cap && c1 * slice + 2 <= kClusterMaxPos) {
-            sh.C = c1;
-            sh.slice = slice;
-            sh.lds = lds;
-            sh.mode = words ? kClusterOneWords : kClusterOne;
-            sh.per_launch = kXcds * (kXcdCus / c1);
-            return true;
-        }
-    }
-    auto slice_at = [&](int32_t c) { return (P.v_tiles + c - 1) / c * kTile; };
-    const int32_t C0 = C;
-    sh.mode = kClusterMany;
-    for (; C <= kXcdCus; C *= 2) {
-        sh.slice = slice_at(C);
-        sh.lds = lds_bytes(C, sh.slice);
-        if (sh.lds <= lds_cap && (int64_t)C * sh.slice + 2 <= kClusterMaxPos) break;
-    }
-    if (C > kXcdCus) {
-        sh.mode = kClusterWide;
-        for (C = C0; C <= kXcdCus; C *= 2) {
-            sh.slice = slice_at(C);
-            sh.lds = wide_lds_bytes(C, sh.slice);
-            if (sh.lds <= lds_cap && (int64_t)C * sh.slice + 64 <= kClusterMaxWide) break;
-        }
-        if (C > kXcdCus) return false;
-    }
-    sh.C = C;
-    sh.per_launch = kXcds * (kXcdCus / C);
+    Z.v_tiles = P.v_tiles;
+    Z.NO = std::max(2, (int32_t)k - 1);
     return true;
+}
+
+bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& sh) {
+    ClusterSize Z;
+    return cluster_size(P, Z) && cluster_shape_of(Z, R, lds_cap, sh);
 }
 
 hipError_t launch_cluster_build(const ClusterDesc* Ds, const ClusterDesc* hostDs, int32_t count, hipStream_t s) {

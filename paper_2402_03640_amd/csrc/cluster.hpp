@@ -9,35 +9,14 @@
 
 #include <cstdint>
 
+#include "cluster_shape.hpp"
 #include "kernels.hpp"
 #include "plan.hpp"
 
 namespace hms {
 
-constexpr int kXcds = 8;              // XCDs of the GPU, each with its own L2
-constexpr int kXcdCus = 32;           // CUs per XCD: the most workgroups a cluster can have
-constexpr int kClusterThreads = 1024;
 constexpr int kClusterMaxK = 5;       // longest clause
-constexpr int kClusterMaxPos = 32768; // LDS slots a 15-bit literal field can name
-constexpr int kClusterMaxWide = 65536; // positions a 16-bit literal field can name (wide form)
 constexpr int32_t kClusterMaxT = 1 << 20;
-
-// How a cluster's wavefronts hold their tiles: several each (state in LDS), or
-// at most one (state in registers), the latter exchanging t behind flags or,
-// for few variables, as words that carry their step.  Wide: several each, with
-// only the roundings of all variables in LDS (more variables than t fits for).
-enum ClusterMode : int32_t { kClusterMany = 0, kClusterOne = 1, kClusterOneWords = 2, kClusterWide = 3 };
-
-// Shape of a cluster solve of an instance.
-struct ClusterShape {
-    int32_t mode = kClusterMany;
-    int32_t C = 0;         // workgroups per restart (a power of two)
-    int32_t NO = 0;        // other literals per occurrence record (2, 3 or 4)
-    int32_t slice = 0;     // variables per workgroup, padded to whole tiles
-    int32_t live_tiles = 0;  // clause tiles before the tautological ones
-    size_t lds = 0;        // dynamic LDS per workgroup
-    int32_t per_launch = 0;  // restarts one launch holds
-};
 
 // One instance of a cluster launch (device-visible).
 struct ClusterDesc {
@@ -101,9 +80,10 @@ struct ClusterLaunch {
     int32_t shared_off;          // LDS offset of the workgroup variables (set by launch_cluster)
 };
 
-// Whether the instance can run as a cluster solve of R restarts, and how (many:
-// in the form for several tiles per wavefront, whatever its size).
-bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& sh, bool many = false);
+// Whether the instance can run as a cluster solve at all, and the sizes that its
+// shape depends on; then the shape for R restarts.
+bool cluster_size(const HostPlan& P, ClusterSize& Z);
+bool cluster_shape(const HostPlan& P, int32_t R, size_t lds_cap, ClusterShape& sh);
 constexpr int kClusterBins = 512;  // list lengths (rows kept whole have at most kSplitDense entries)
 // Words of a record block (8 records of each list for 64 rows: column bits,
 // then the records) and the most blocks of an instance with `cols`

@@ -1338,8 +1338,12 @@ bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p) {
 //   - with one restart only one XCD works, and the others' share of the
 //     tiled kernels wins again past 2^21 record terms (nonzeros times other
 //     literals per clause; 3-CNF n = 28000: 4.6 against 7.1; 4-CNF n = 16000:
-//     7.5 against 8.8, n = 28000: 11.2 against 10.4);
-//   - in the wide form (past 32000 variables), which reads t from the L2, from
+//     7.5 against 8.8, n = 28000: 11.2 against 10.4), and past 30720 variables,
+//     where t fits LDS with 16 workgroups only, with four and five literals per
+//     clause (n = 31000, m = 5 n: 4-CNF 10.6 against 9.3, 5-CNF 12.4 against
+//     10.0; with three restarts 10.6 against 14.7 and 12.4 against 15.7; 3-CNF
+//     with one 6.7 against 8.9);
+//   - in the wide form (past 31744 variables), which reads t from the L2, from
 //     two, three and four restarts on with at most three, four and five literals
 //     per clause, and past three only up to 16, where the tiled kernels share a
 //     formula's entries between enough restarts (3-CNF n = 33000: one restart
@@ -1363,7 +1367,9 @@ bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p, int64_t to
         return false;
     if (nnz <= kResidentNnz && R > sh.per_launch) return false;
     if (sh.mode == hms::kClusterWide) return R >= sh.NO && (sh.NO == 2 || p->restarts <= 16);
-    return R > 1 || nnz * sh.NO <= (int64_t(1) << 21);
+    if (R > 1) return true;
+    const bool few = sh.mode == hms::kClusterMany && sh.C < hms::kXcdCus;
+    return nnz * sh.NO <= (int64_t(1) << 21) && (sh.NO == 2 || !few);
 }
 
 // One cluster launch at a time on a device: two that each hold part of an XCD
@@ -1383,13 +1389,15 @@ struct ClusterItem {
 
 // Runs instances of one kernel form (literals per clause, weights, mode) as
 // clusters, in as few launches as hold them.  An item keeps ran = false (all do
-// when the device was taken by another cluster solve) when its clusters could
-// not assemble: what is in its outputs is then to be overwritten by the schedule
-// that the caller takes instead.
+// when the device was taken by another cluster solve, or the forms differ) when
+// its clusters could not assemble: what is in its outputs is then to be
+// overwritten by the schedule that the caller takes instead.
 hms_status solve_clusters(std::vector<ClusterItem>& items, hipStream_t s) {
     const int dev = items[0].cnf->device;
     const hms::ClusterShape& sh0 = items[0].sh;
     const bool weighted = items[0].cnf->plan.weighted;
+    for (const ClusterItem& it : items)
+        if (it.sh.mode != sh0.mode || it.sh.NO != sh0.NO || it.cnf->plan.weighted != weighted) return HMS_OK;
     std::unique_lock<std::mutex> lk(g_cluster_mu[dev], std::try_to_lock);
     if (!lk.owns_lock()) return HMS_OK;
     const int32_t count = (int32_t)items.size();
@@ -1670,37 +1678,18 @@ hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solv
     return HMS_OK;
 }
 
-// Shapes of the items (one form: literals per clause, weights, wide) for running
-// together, largest first: as many workgroups per restart as leave every
-// restart its own at once.  The items of one launch run one kernel, so all take
-// the form for several tiles per wavefront unless all fit the same other one;
-// in that form what CUs are left go to the largest items (twelve 3-CNF
-// instances of 15000 to 26000 variables: 16 workgroups each, 32 for the four
-// largest).  False when an item does not fit.
+// Shapes of the items for running together (cluster_group); false when one does
+// not fit or their kernels differ.
 bool cluster_shapes(std::vector<ClusterItem>& items) {
-    const size_t cap = cluster_lds_cap(items[0].cnf->device);
-    int32_t units = 0;
-    for (const ClusterItem& it : items) units += it.p.restarts;
-    bool same = true;
-    for (ClusterItem& it : items) {
-        if (!hms::cluster_shape(it.cnf->plan, units, cap, it.sh)) return false;
-        same = same && it.sh.mode == items[0].sh.mode;
+    std::vector<hms::ClusterSize> Z(items.size());
+    std::vector<int32_t> R(items.size());
+    std::vector<hms::ClusterShape> sh;
+    for (size_t i = 0; i < items.size(); ++i) {
+        if (!hms::cluster_size(items[i].cnf->plan, Z[i])) return false;
+        R[i] = items[i].p.restarts;
     }
-    if (same && (items[0].sh.mode == hms::kClusterOne || items[0].sh.mode == hms::kClusterOneWords)) return true;
-    int32_t left = hms::kXcds * hms::kXcdCus;
-    for (ClusterItem& it : items) {
-        if (!hms::cluster_shape(it.cnf->plan, units, cap, it.sh, true)) return false;
-        left -= it.p.restarts * it.sh.C;
-    }
-    for (ClusterItem& it : items) {
-        hms::ClusterShape wide;
-        const int32_t C = it.sh.C;
-        if (C == hms::kXcdCus || it.p.restarts * C > left) break;
-        if (!hms::cluster_shape(it.cnf->plan, hms::kXcds * (hms::kXcdCus / (2 * C)), cap, wide, true) || wide.C != 2 * C)
-            break;
-        it.sh = wide;
-        left -= it.p.restarts * C;
-    }
+    if (!hms::cluster_group(Z, R, cluster_lds_cap(items[0].cnf->device), sh)) return false;
+    for (size_t i = 0; i < items.size(); ++i) items[i].sh = sh[i];
     return true;
 }
 
