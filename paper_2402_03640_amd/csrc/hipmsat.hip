@@ -20,6 +20,12 @@
 #include "plan.hpp"
 #include "small.hpp"
 
+// A timed choice: the fastest schedule, and the fastest but for the cluster
+// solver, which takes over where clusters cannot run a solve.
+struct Tuned {
+    int32_t best = 0, other = 0;
+};
+
 struct hms_cnf {
     hms::HostPlan plan;
     int device = -1;
@@ -36,7 +42,7 @@ struct hms_cnf {
     // autotuned schedule per (restarts, optimizer, loss mode); results do not
     // depend on the schedule, only the speed does
     mutable std::mutex tune_mu;
-    mutable std::map<uint64_t, int32_t> tuned;
+    mutable std::map<uint64_t, Tuned> tuned;
 };
 
 namespace {
@@ -820,7 +826,7 @@ int ilog2(int64_t v) {
 // Process-wide cache by size class (restarts, optimizer, loss mode, log2 nnz,
 // log2 n): a new instance of a size already tuned reuses that choice.
 std::mutex g_tune_mu;
-std::map<uint64_t, int32_t> g_tuned;
+std::map<uint64_t, Tuned> g_tuned;
 
 uint64_t class_key(const hms_cnf* cnf, const hms_solve_params* p) {
     return tune_key(p) ^ ((uint64_t)ilog2(cnf->plan.nnz + 1) << 48) ^ ((uint64_t)ilog2(cnf->plan.n + 1) << 56);
@@ -949,10 +955,13 @@ hms_status time_split(const hms_cnf* cnf, const hms_solve_params* p0, int32_t co
 
 // Autotuner: for every table entry, the forward and the backward pass each
 // take their fastest rows per unit (timed apart), then whole steps of each
-// entry's pair are timed against each other (and the resident solver).
-hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, int32_t& best, double& best_ms) {
-    best = 0;
+// entry's pair are timed against each other (and the resident solver).  Without
+// `clusters` (they cannot run now) the cluster solver is not timed: it stays the
+// choice where it is known to be the faster one.
+hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, Tuned& pick, double& best_ms,
+                bool clusters = true) {
     best_ms = 1e300;
+    double other_ms = 1e300;
     struct Pick {
         double f = 1e300, b = 1e300;
         int Uf = 0, Ub = 0;
@@ -976,7 +985,7 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, in
     std::vector<int32_t> cands;
     for (auto& kv : picks) cands.push_back(kv.first | (kv.second.Uf << 8) | (kv.second.Ub << 16));
     if (resident_ok(cnf, p)) cands.push_back(kResidentId);
-    if (cluster_ok(cnf, p)) cands.push_back(kClusterId);
+    if (clusters && cluster_ok(cnf, p)) cands.push_back(kClusterId);
     auto time_code = [&](int32_t code, double& ms) {
         if (code == kClusterId) return time_cluster(cnf, p, iters, ms);
         return code == kResidentId ? time_resident(cnf, p, iters, ms) : time_steps(cnf, p, code, iters, ms);
@@ -1004,58 +1013,68 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, in
             timed[k].first = std::min(timed[k].first, ms);
         }
     }
-    for (const auto& tc : timed)
+    auto canonical = [](int32_t c) {
+        return c != kResidentId && c != kClusterId && ((c >> 16) & 0xff) == ((c >> 8) & 0xff) ? c & 0xffff : c;
+    };
+    for (const auto& tc : timed) {
         if (tc.first < best_ms) {
             best_ms = tc.first;
-            best = tc.second;
+            pick.best = canonical(tc.second);
         }
-    if (best != kResidentId && best != kClusterId && ((best >> 16) & 0xff) == ((best >> 8) & 0xff)) best &= 0xffff;  // canonical id
+        if (tc.second != kClusterId && tc.first < other_ms) {
+            other_ms = tc.first;
+            pick.other = canonical(tc.second);
+        }
+    }
+    if (!clusters && cluster_preferred(cnf, p)) pick.best = kClusterId;
     {
         std::lock_guard<std::mutex> lk(cnf->tune_mu);
-        cnf->tuned[tune_key(p)] = best;
+        cnf->tuned[tune_key(p)] = pick;
     }
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tuned[class_key(cnf, p)] = best;
+    g_tuned[class_key(cnf, p)] = pick;
     return HMS_OK;
 }
 
-// Schedule to run when the caller asked for the automatic choice.
-hms_status resolve_schedule(const hms_cnf* cnf, const hms_solve_params* p, int32_t& code) {
+// Schedule to run when the caller asked for the automatic choice; without
+// `clusters`, what it is when the cluster solver cannot take the solve.
+hms_status resolve_schedule(const hms_cnf* cnf, const hms_solve_params* p, int32_t& code, bool clusters = true) {
     code = p->schedule;
     if (code != 0) return HMS_OK;
     // the resident and the cluster solver cannot honour a time limit or a
     // cancel flag: a solve that asks for one takes the tiled choice below
     // instead (as one whose size class was tuned on an instance that fits them
     // when it does not)
-    auto runs = [&](int32_t c) {
-        return c == kResidentId ? resident_ok(cnf, p) : c == kClusterId ? cluster_ok(cnf, p) : true;
+    auto take = [&](const Tuned& t) {
+        const int32_t c = t.best == kClusterId && !(clusters && cluster_ok(cnf, p)) ? t.other : t.best;
+        if (c == 0 || (c == kResidentId && !resident_ok(cnf, p))) return false;
+        code = c;
+        return true;
     };
     {
         std::lock_guard<std::mutex> lk(cnf->tune_mu);
         auto it = cnf->tuned.find(tune_key(p));
-        if (it != cnf->tuned.end() && runs(it->second)) {
-            code = it->second;
-            return HMS_OK;
-        }
+        if (it != cnf->tuned.end() && take(it->second)) return HMS_OK;
     }
-    if (cluster_preferred(cnf, p)) {  // no timing needed: ahead of every other schedule where it runs
+    if (clusters && cluster_preferred(cnf, p)) {  // no timing needed: ahead of every other schedule where it runs
         code = kClusterId;
         return HMS_OK;
     }
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(class_key(cnf, p));
-        if (it != g_tuned.end() && runs(it->second)) {
-            code = it->second;
-            return HMS_OK;
-        }
+        if (it != g_tuned.end() && take(it->second)) return HMS_OK;
     }
     if (!p->autotune || (double)cnf->plan.nnz * p->restarts < (double)(1 << 18)) {
         if (resident_preferred(cnf, p)) code = kResidentId;  // small: launch latency dominates
         return HMS_OK;
     }
     double ms = 0;
-    return tune(cnf, p, 6, code, ms);
+    Tuned t;
+    hms_status rc = tune(cnf, p, 6, t, ms, clusters);
+    if (rc) return rc;
+    code = t.best == kClusterId && !clusters ? t.other : t.best;
+    return HMS_OK;
 }
 
 // ---- resident path (one workgroup per restart, state in LDS) ---------------
@@ -1923,30 +1942,31 @@ hms_status solve_tiled_group(const hms_cnf* const* cnfs, const hms_solve_params*
     return HMS_OK;
 }
 
-}  // namespace
-
-extern "C" {
-
-hms_status hms_solve(const hms_cnf* cnf, const hms_solve_params* p, hms_solve_result* res) {
-    g_err.clear();
-    if (check_cnf(cnf) || !p || !res) return fail(HMS_ERR_ARG, "null argument");
+// One solve (hms_solve); without `clusters` the cluster solver is not tried.
+hms_status solve_one(const hms_cnf* cnf, const hms_solve_params* p, hms_solve_result* res, bool clusters) {
     if (hms_status rc = check_resume(cnf, p, res)) return rc;
     DeviceGuard dg(cnf->device);
     hms_solve_params pr = *p;
-    hms_status rc0 = resolve_schedule(cnf, p, pr.schedule);
+    hms_status rc0 = resolve_schedule(cnf, p, pr.schedule, clusters);
     if (rc0) return rc0;
+    if (pr.schedule == kClusterId) {
+        bool ran = false;
+        if (clusters) rc0 = solve_cluster(cnf, &pr, res, ran);
+        if (rc0 || ran) return rc0;
+        // what the automatic choice is without clusters (no timing for a caller who asked for them by id)
+        pr.schedule = 0;
+        if (p->schedule == kClusterId) pr.autotune = 0;
+        int32_t code = 0;
+        rc0 = resolve_schedule(cnf, &pr, code, false);
+        if (rc0) return rc0;
+        pr.schedule = code;
+    }
     p = &pr;
     if (p->schedule == kResidentId) {
         if (!resident_ok(cnf, p)) return fail(HMS_ERR_ARG, "the resident schedule does not fit this instance");
         if (p->restarts < 1 || p->steps < 0 || p->eval_every < 1)
             return fail(HMS_ERR_ARG, "restarts >= 1, steps >= 0 and eval_every >= 1 required");
         return solve_resident(cnf, p, res);
-    }
-    if (p->schedule == kClusterId) {
-        bool ran = false;
-        rc0 = solve_cluster(cnf, p, res, ran);
-        if (rc0 || ran) return rc0;
-        pr.schedule = 0;  // the untimed tiled choice
     }
     SolveSetup Z;
     rc0 = setup_solve(cnf, p, Z);
@@ -2058,6 +2078,16 @@ hms_status hms_solve(const hms_cnf* cnf, const hms_solve_params* p, hms_solve_re
     }
     if (cancelled && rr == HMS_OK) return fail(HMS_ERR_CANCELLED, "cancelled by the caller; the best so far is filled");
     return rr;
+}
+
+}  // namespace
+
+extern "C" {
+
+hms_status hms_solve(const hms_cnf* cnf, const hms_solve_params* p, hms_solve_result* res) {
+    g_err.clear();
+    if (check_cnf(cnf) || !p || !res) return fail(HMS_ERR_ARG, "null argument");
+    return solve_one(cnf, p, res, true);
 }
 
 hms_status hms_time_kernels(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, double* fwd_ms,
@@ -2174,7 +2204,7 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
             // the handle's own timing decides where there is one
             std::lock_guard<std::mutex> tl(cnfs[i]->tune_mu);
             auto t = cnfs[i]->tuned.find(tune_key(&p));
-            if (p.schedule == 0 && t != cnfs[i]->tuned.end() && t->second != kClusterId) continue;
+            if (p.schedule == 0 && t != cnfs[i]->tuned.end() && t->second.best != kClusterId) continue;
         }
         // no input of the batch may lie in an output: the launches before
         // another one's would overwrite it
@@ -2187,6 +2217,13 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
         fits[i] = 1;
         cluster_units[form(i)] += p.restarts;
     }
+    std::vector<char> fell(count, 0);  // clusters were tried and did not run
+    auto elsewhere = [&](int32_t i) {
+        const bool automatic = params[i].schedule == 0 || params[i].schedule == kClusterId;
+        const bool want_res = params[i].schedule == kResidentId || (automatic && resident_preferred(cnfs[i], &params[i]));
+        if (want_res && resident_ok(cnfs[i], &params[i])) res_idx.push_back(i);
+        else tiled_idx.push_back(i);
+    };
     auto clusters = [&](int32_t i) {
         if (!fits[i]) return false;
         const int64_t all = cluster_units[form(i)];
@@ -2200,11 +2237,7 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
             alone.push_back(i);
             continue;
         }
-        if (clusters(i)) continue;
-        const bool want_res = params[i].schedule == kResidentId ||
-                              (params[i].schedule == 0 && resident_preferred(cnfs[i], &params[i]));
-        if (want_res && resident_ok(cnfs[i], &params[i])) res_idx.push_back(i);
-        else tiled_idx.push_back(i);
+        if (!clusters(i)) elsewhere(i);
     }
     hms_status worst = HMS_OK;
     std::string worst_msg;
@@ -2227,7 +2260,8 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
                 if (st) {
                     if (statuses) statuses[i] = st;
                 } else if (!items[k].ran) {
-                    tiled_idx.push_back(i);
+                    fell[i] = 1;
+                    elsewhere(i);
                 } else if (!items[k].finite) {
                     if (statuses) statuses[i] = HMS_ERR_NONFINITE;
                     if (!worst) {
@@ -2364,7 +2398,7 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
             alone.push_back(i);
             continue;
         }
-        const int32_t sch = p.schedule == kResidentId ? 0 : p.schedule;
+        const int32_t sch = p.schedule == kResidentId || p.schedule == kClusterId ? 0 : p.schedule;
         groups[std::make_tuple(p.restarts, p.steps, p.eval_every, p.optimizer, p.loss_mode, sch)].push_back(i);
     }
     auto note = [&](hms_status st, int32_t i) {
@@ -2384,10 +2418,10 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
             }
             hms_solve_params p = params[g[k0]];
             p.stream = params[0].stream;
-            if (p.schedule == kResidentId) p.schedule = 0;
+            if (p.schedule == kResidentId || p.schedule == kClusterId) p.schedule = 0;
             int32_t code = 0;
-            hms_status st = resolve_schedule(cnfs[g[k0]], &p, code);
-            if (!st && (code == kResidentId || code == kClusterId)) code = 0;
+            hms_status st = resolve_schedule(cnfs[g[k0]], &p, code, false);
+            if (!st && code == kResidentId) code = 0;
             // one explicit schedule for the whole group (the automatic choice
             // depends on the instance)
             Shape sh0;
@@ -2415,7 +2449,8 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
         hms_solve_params p = params[i];
         p.stream = params[0].stream;
         if (p.schedule == kResidentId || (p.schedule == kClusterId && !cluster_ok(cnfs[i], &p))) p.schedule = 0;
-        hms_status st = hms_solve(cnfs[i], &p, &results[i]);
+        g_err.clear();
+        hms_status st = solve_one(cnfs[i], &p, &results[i], !fell[i]);
         if (statuses) statuses[i] = st;
         note(st, i);
     }
@@ -2442,11 +2477,11 @@ hms_status hms_tune(const hms_cnf* cnf, const hms_solve_params* params, int32_t 
     g_err.clear();
     if (check_cnf(cnf) || !params || iters < 1) return fail(HMS_ERR_ARG, "null argument or iters < 1");
     DeviceGuard dg(cnf->device);
-    int32_t best = 0;
+    Tuned best;
     double ms = 0;
     hms_status rc = tune(cnf, params, iters, best, ms);
     if (rc) return rc;
-    if (schedule) *schedule = best;
+    if (schedule) *schedule = best.best;
     if (step_ms) *step_ms = ms;
     return HMS_OK;
 }

@@ -76,3 +76,142 @@ def test_form_change_batch(batch, schedule):
         assert out.status == 0 and out.schedule == hm.CLUSTER
         _same(out, one)
         cnf.free()
+
+
+def _solve_into(cnf, x, **kw):
+    """hm.solve with x_T written over the start point `x` (a [n][R] tensor)."""
+    import ctypes as C
+
+    from paper_2402_03640_amd import _lib
+    d = dict(steps=300, restarts=x.shape[1], eval_every=10, seed=0, optimizer=hm.ADAM, lr=1e-2, beta1=0.9, beta2=0.999,
+             eps=1e-8, loss_mode=hm.LOSS_UNSAT, schedule=0, use_graph=True, time_limit_s=0.0, x0=x, stream=None,
+             autotune=False)
+    d.update(kw)
+    p = _lib._params(cnf, **d)
+    res = _lib.SolveResult()
+    best = np.zeros(d["restarts"], dtype=np.int64)
+    res.restart_best = best.ctypes.data
+    res.x_final = x.data_ptr()
+    _lib._check(_lib.lib().hms_solve(cnf.handle, C.byref(p), C.byref(res)))
+    return res.schedule, best
+
+
+def test_outputs_over_inputs_take_what_is_next_best():
+    """A start point that receives x_T rules clusters out: small instances run
+    on the resident solver, larger ones on the schedule that was timed."""
+    for n, tuned in ((1000, False), (6000, True)):
+        cnf = _cnf(n, ratio=4.2)
+        x0 = torch.from_numpy(cnfgen.random_x(n, 2, seed=3)).cuda()
+        kw = dict(steps=300, restarts=2, eval_every=10, lr=1e-2)
+        ref = hm.solve(cnf, x0=x0, want_x=True, schedule=1, **kw)
+        other = hm.RESIDENT
+        if tuned:
+            assert hm.tune(cnf, restarts=2)[0] == hm.CLUSTER
+            other = hm.solve(cnf, time_limit_s=100.0, x0=x0, **kw).schedule
+            assert other not in (hm.CLUSTER, hm.RESIDENT)
+        assert hm.solve(cnf, x0=x0, autotune=False, **kw).schedule == hm.CLUSTER
+        x = x0.clone()
+        schedule, best = _solve_into(cnf, x)
+        _say(f"n={n}: schedule {schedule} over the start point")
+        assert schedule == other
+        np.testing.assert_array_equal(best, ref.restart_best)
+        np.testing.assert_array_equal(_bits(x), _bits(ref.x_final))
+        cnf.free()
+
+
+def test_time_limited_solve_leaves_the_timed_choice():
+    """A solve that clusters cannot take (a time limit) uses the schedule timed
+    next to them; it does not time again and put it in their place."""
+    cnf = _cnf(8000, ratio=4.2)
+    kw = dict(steps=300, restarts=9, eval_every=10)
+    assert hm.tune(cnf, restarts=9)[0] == hm.CLUSTER
+    a = hm.solve(cnf, time_limit_s=100.0, **kw)
+    assert a.schedule != hm.CLUSTER
+    assert hm.solve(cnf, **kw).schedule == hm.CLUSTER
+    assert hm.solve(cnf, time_limit_s=100.0, **kw).schedule == a.schedule
+
+
+def _beside(work, run):
+    """run() while another thread repeats work(stream); stops it afterwards."""
+    import threading
+    import time
+    errors, stop, turns = [], threading.Event(), []
+
+    def loop():
+        try:
+            torch.cuda.set_device(0)
+            st = torch.cuda.Stream()
+            while not stop.is_set():
+                work(st)
+                turns.append(1)
+        except BaseException as e:  # reported below, on the test's thread
+            errors.append(repr(e))
+
+    th = threading.Thread(target=loop)
+    th.start()
+    time.sleep(0.1)
+    try:
+        return run()
+    finally:
+        stop.set()
+        th.join()
+        _say("turns of the other thread:", len(turns))
+        assert not errors, errors
+
+
+def test_small_instances_beside_a_cluster_solve():
+    """While another thread's solve holds the clusters, small instances take
+    the resident solver, alone and in a batch."""
+    big = _cnf(20000, ratio=4.2)
+    small = [_cnf(1000 + 300 * j, ratio=4.2) for j in range(3)]
+    kw = dict(steps=300, restarts=2, eval_every=10, lr=1e-2, want_x=True)
+    ref = [hm.solve(c, schedule=1, seed=j, **kw) for j, c in enumerate(small)]
+    ran = []
+
+    def work(st):
+        assert hm.solve(big, steps=15000, restarts=8, eval_every=50, autotune=False, stream=st).schedule == hm.CLUSTER
+
+    def run():
+        st = torch.cuda.Stream()
+        for _ in range(4):
+            outs = [hm.solve(c, seed=j, stream=st, autotune=False, **kw) for j, c in enumerate(small)]
+            outs += hm.solve_batch(small, seeds=[0, 1, 2], stream=st, **kw)
+            for j, out in enumerate(outs):
+                ran.append(out.schedule)
+                _same(out, ref[j % 3])
+
+    _beside(work, run)
+    _say("schedules:", sorted(ran))
+    assert set(ran) <= {hm.CLUSTER, hm.RESIDENT} and hm.RESIDENT in ran
+
+
+def test_clusters_that_do_not_fill():
+    """Other work holds CUs of every XCD for longer than a cluster waits to
+    fill: the registration is voided and the solve runs elsewhere."""
+    other = _cnf(2500, ratio=4.2, seed=1)
+    inst = [_cnf(2500, ratio=4.2, seed=2), _cnf(9000, ratio=4.2, seed=3)]
+    kw = dict(steps=300, restarts=1, eval_every=10, lr=1e-2)
+    ref = [hm.solve(c, schedule=1, seed=j, **kw) for j, c in enumerate(inst)]
+    streams = [torch.cuda.Stream() for _ in range(4)]
+
+    def solves(st):
+        return [hm.solve(c, schedule=hm.CLUSTER, seed=j, stream=st, **kw) for j, c in enumerate(inst)]
+
+    def hold(stream, steps=60000):  # 64 workgroups, eight on each XCD; too much LDS for a cluster's beside them
+        r = hm.solve(other, steps=steps, restarts=64, eval_every=50, schedule=hm.RESIDENT, stream=stream)
+        assert r.schedule == hm.RESIDENT
+
+    for st in streams:
+        assert [o.schedule for o in solves(st)] == [hm.CLUSTER] * 2
+    hold(streams[0], 10)
+    # a stream that shares a hardware queue with the other work runs behind it, the others beside it
+    turns = _beside(hold, lambda: [solves(st) for st in streams])
+    _say("schedules:", [[o.schedule for o in outs] for outs in turns])
+    for outs in turns:
+        for out, one in zip(outs, ref):
+            np.testing.assert_array_equal(out.restart_best, one.restart_best)
+            np.testing.assert_array_equal(out.restart_step, one.restart_step)
+            np.testing.assert_array_equal(out.best_assignment, one.best_assignment)
+            np.testing.assert_allclose(out.restart_loss, one.restart_loss, rtol=1e-12, atol=0)
+    voided = [outs for outs in turns if all(o.schedule != hm.CLUSTER for o in outs)]
+    assert voided and all(outs[0].schedule == hm.RESIDENT and outs[1].schedule != hm.RESIDENT for outs in voided)
