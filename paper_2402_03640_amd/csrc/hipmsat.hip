@@ -24,6 +24,7 @@
 // solver, which takes over where clusters cannot run a solve.
 struct Tuned {
     int32_t best = 0, other = 0;
+    int32_t from = 0;  // the cluster solver is the fastest from so many steps on
 };
 
 struct hms_cnf {
@@ -802,7 +803,9 @@ struct Events {
 bool resident_ok(const hms_cnf* cnf, const hms_solve_params* p);
 bool resident_preferred(const hms_cnf* cnf, const hms_solve_params* p);
 hms_status time_resident(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms);
-hms_status time_cluster(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms);
+hms_status time_cluster(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms,
+                        double* build_ms = nullptr);
+int32_t cluster_least_steps(const hms_cnf* cnf);
 bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p);
 bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p, int64_t together = 0);
 constexpr int32_t kResidentId = 0xff;
@@ -961,7 +964,7 @@ hms_status time_split(const hms_cnf* cnf, const hms_solve_params* p0, int32_t co
 hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, Tuned& pick, double& best_ms,
                 bool clusters = true) {
     best_ms = 1e300;
-    double other_ms = 1e300;
+    double other_ms = 1e300, cluster_ms = 1e300, build_ms = 1e300;
     struct Pick {
         double f = 1e300, b = 1e300;
         int Uf = 0, Ub = 0;
@@ -987,7 +990,12 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, Tu
     if (resident_ok(cnf, p)) cands.push_back(kResidentId);
     if (clusters && cluster_ok(cnf, p)) cands.push_back(kClusterId);
     auto time_code = [&](int32_t code, double& ms) {
-        if (code == kClusterId) return time_cluster(cnf, p, iters, ms);
+        if (code == kClusterId) {
+            double b = 0;
+            hms_status rc = time_cluster(cnf, p, iters, ms, &b);
+            build_ms = std::min(build_ms, b);
+            return rc;
+        }
         return code == kResidentId ? time_resident(cnf, p, iters, ms) : time_steps(cnf, p, code, iters, ms);
     };
     std::vector<std::pair<double, int32_t>> timed;
@@ -1021,12 +1029,24 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, Tu
             best_ms = tc.first;
             pick.best = canonical(tc.second);
         }
-        if (tc.second != kClusterId && tc.first < other_ms) {
+        if (tc.second == kClusterId) {
+            cluster_ms = tc.first;
+        } else if (tc.first < other_ms) {
             other_ms = tc.first;
             pick.other = canonical(tc.second);
         }
     }
-    if (!clusters && cluster_preferred(cnf, p)) pick.best = kClusterId;
+    if (pick.best == kClusterId) {
+        // each solve builds its records first, which so many steps gain; the
+        // other schedules' set-up takes the host some 45 us longer (n = 60000,
+        // 8 restarts, us a call: two steps 277 against 210 tiled, ten 375 against
+        // 388; n = 20000, one restart: two 167 against 162, ten 195 against 228)
+        const double gain = std::max(other_ms - cluster_ms, 1e-6);
+        pick.from = (int32_t)std::min(std::max((build_ms - 0.045) / gain, 0.0), 1e6);
+    } else if (!clusters && cluster_preferred(cnf, p)) {
+        pick.best = kClusterId;
+        pick.from = cluster_least_steps(cnf);
+    }
     {
         std::lock_guard<std::mutex> lk(cnf->tune_mu);
         cnf->tuned[tune_key(p)] = pick;
@@ -1046,7 +1066,8 @@ hms_status resolve_schedule(const hms_cnf* cnf, const hms_solve_params* p, int32
     // instead (as one whose size class was tuned on an instance that fits them
     // when it does not)
     auto take = [&](const Tuned& t) {
-        const int32_t c = t.best == kClusterId && !(clusters && cluster_ok(cnf, p)) ? t.other : t.best;
+        const bool now = clusters && p->steps >= t.from && cluster_ok(cnf, p);
+        const int32_t c = t.best == kClusterId && !now ? t.other : t.best;
         if (c == 0 || (c == kResidentId && !resident_ok(cnf, p))) return false;
         code = c;
         return true;
@@ -1073,7 +1094,7 @@ hms_status resolve_schedule(const hms_cnf* cnf, const hms_solve_params* p, int32
     Tuned t;
     hms_status rc = tune(cnf, p, 6, t, ms, clusters);
     if (rc) return rc;
-    code = t.best == kClusterId && !clusters ? t.other : t.best;
+    code = t.best == kClusterId && (!clusters || p->steps < t.from) ? t.other : t.best;
     return HMS_OK;
 }
 
@@ -1374,10 +1395,12 @@ bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p) {
 //   - from 64 steps on (256 up to 2^14 nonzeros, where a step gains least):
 //     building the records costs 40 to 250 us, about what so many steps gain.
 // `together`: the restarts of a batch that would share the launches.
+int32_t cluster_least_steps(const hms_cnf* cnf) { return cnf->plan.nnz <= (int64_t(1) << 14) ? 256 : 64; }
+
 bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p, int64_t together) {
     hms::ClusterShape sh;
     const int64_t nnz = cnf->plan.nnz;
-    if (nnz < 5000 || p->steps < (nnz <= (int64_t(1) << 14) ? 256 : 64) || !cluster_fits(cnf, p, sh)) return false;
+    if (nnz < 5000 || p->steps < cluster_least_steps(cnf) || !cluster_fits(cnf, p, sh)) return false;
     if (nnz < 1000 * (sh.NO >= 4 ? 24 : sh.NO == 3 ? 7 : 5)) return false;
     const int64_t R = std::max<int64_t>(together, p->restarts);
     if (nnz <= kResidentNnz && R > hms::kXcds * hms::kXcdCus / 2) return false;
@@ -1713,9 +1736,10 @@ bool cluster_shapes(std::vector<ClusterItem>& items) {
 }
 
 // Device time per step of the cluster solver, by the difference of a short
-// and a three times longer solve (as time_resident); a device taken by
+// and a three times longer solve (as time_resident), and what comes before the
+// steps; a device taken by
 // another cluster solve leaves it untimed (never the fastest).
-hms_status time_cluster(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms) {
+hms_status time_cluster(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms, double* build_ms) {
     hms_solve_params p = *p0;
     p.eval_every = std::max(p0->eval_every, 1);
     p.x0 = nullptr;
@@ -1735,6 +1759,7 @@ hms_status time_cluster(const hms_cnf* cnf, const hms_solve_params* p0, int32_t 
         t[k] = r.device_ms;
     }
     ms = std::max(t[2] - t[1], 0.0) / (2.0 * S);
+    if (build_ms) *build_ms = std::max(t[1] - S * ms, 0.0);
     return HMS_OK;
 }
 
