@@ -803,7 +803,7 @@ struct Events {
 bool resident_ok(const hms_cnf* cnf, const hms_solve_params* p);
 bool resident_preferred(const hms_cnf* cnf, const hms_solve_params* p);
 hms_status time_resident(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms);
-hms_status time_cluster(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms,
+hms_status time_cluster(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, bool& ran, double& ms,
                         double* build_ms = nullptr);
 int32_t cluster_least_steps(const hms_cnf* cnf);
 bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p);
@@ -965,6 +965,7 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, Tu
                 bool clusters = true) {
     best_ms = 1e300;
     double other_ms = 1e300, cluster_ms = 1e300, build_ms = 1e300;
+    bool ran = true;  // the clusters could be timed
     struct Pick {
         double f = 1e300, b = 1e300;
         int Uf = 0, Ub = 0;
@@ -992,7 +993,10 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, Tu
     auto time_code = [&](int32_t code, double& ms) {
         if (code == kClusterId) {
             double b = 0;
-            hms_status rc = time_cluster(cnf, p, iters, ms, &b);
+            bool now = false;
+            hms_status rc = time_cluster(cnf, p, iters, now, ms, &b);
+            if (!now) ms = 1e300;
+            ran = ran && now;
             build_ms = std::min(build_ms, b);
             return rc;
         }
@@ -1047,6 +1051,7 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, Tu
         pick.best = kClusterId;
         pick.from = cluster_least_steps(cnf);
     }
+    if (!ran) return HMS_OK;  // a choice without the clusters is not kept for later solves
     {
         std::lock_guard<std::mutex> lk(cnf->tune_mu);
         cnf->tuned[tune_key(p)] = pick;
@@ -1431,17 +1436,19 @@ struct ClusterItem {
 
 // Runs instances of one kernel form (literals per clause, weights, mode) as
 // clusters, in as few launches as hold them.  An item keeps ran = false (all do
-// when the device was taken by another cluster solve, or the forms differ) when
-// its clusters could not assemble: what is in its outputs is then to be
-// overwritten by the schedule that the caller takes instead.
-hms_status solve_clusters(std::vector<ClusterItem>& items, hipStream_t s) {
+// when the device was taken by another cluster solve and the caller does not
+// wait for it, or the forms differ) when its clusters could not assemble: what
+// is in its outputs is then to be overwritten by the schedule that the caller
+// takes instead.
+hms_status solve_clusters(std::vector<ClusterItem>& items, hipStream_t s, bool wait = false) {
     const int dev = items[0].cnf->device;
     const hms::ClusterShape& sh0 = items[0].sh;
     const bool weighted = items[0].cnf->plan.weighted;
     for (const ClusterItem& it : items)
         if (it.sh.mode != sh0.mode || it.sh.NO != sh0.NO || it.cnf->plan.weighted != weighted) return HMS_OK;
-    std::unique_lock<std::mutex> lk(g_cluster_mu[dev], std::try_to_lock);
-    if (!lk.owns_lock()) return HMS_OK;
+    std::unique_lock<std::mutex> lk(g_cluster_mu[dev], std::defer_lock);
+    if (wait) lk.lock();
+    else if (!lk.try_lock()) return HMS_OK;
     const int32_t count = (int32_t)items.size();
     // words that carry their step start at zero in every launch; plain t is
     // written before it is read, so later launches reuse the first one's
@@ -1697,7 +1704,8 @@ hms_status solve_clusters(std::vector<ClusterItem>& items, hipStream_t s) {
 }
 
 // Runs one solve as clusters; *ran = false (and HMS_OK) when it did not.
-hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solve_result* res, bool& ran) {
+hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solve_result* res, bool& ran,
+                         bool wait = false) {
     ran = false;
     std::vector<ClusterItem> one(1);
     one[0].cnf = cnf;
@@ -1714,7 +1722,7 @@ hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solv
     for (const float* i : ins)
         for (const float* o : outs)
             if (i && o && i < o + nR && o < i + nR) return HMS_OK;
-    if (hms_status rc = solve_clusters(one, (hipStream_t)p->stream)) return rc;
+    if (hms_status rc = solve_clusters(one, (hipStream_t)p->stream, wait)) return rc;
     ran = one[0].ran;
     if (ran && !one[0].finite) return fail(HMS_ERR_NONFINITE, "the loss at the final iterate is not finite");
     return HMS_OK;
@@ -1737,25 +1745,22 @@ bool cluster_shapes(std::vector<ClusterItem>& items) {
 
 // Device time per step of the cluster solver, by the difference of a short
 // and a three times longer solve (as time_resident), and what comes before the
-// steps; a device taken by
-// another cluster solve leaves it untimed (never the fastest).
-hms_status time_cluster(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, double& ms, double* build_ms) {
+// steps.  Waits for other cluster solves to end; `ran` false when the clusters
+// did not assemble beside other work all the same.
+hms_status time_cluster(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, bool& ran, double& ms,
+                        double* build_ms) {
     hms_solve_params p = *p0;
     p.eval_every = std::max(p0->eval_every, 1);
     p.x0 = nullptr;
     p.resume = nullptr;
-    const int32_t S = std::max(iters, 16) * 4;
+    const int32_t S = std::min(std::max(iters, 16), hms::kClusterMaxT / 12) * 4;  // 3 S steps are within the limit
     double t[3] = {0, 0, 0};
+    ms = 0;
     for (int k = 0; k < 3; ++k) {
         p.steps = k == 2 ? 3 * S : S;
         hms_solve_result r{};
-        bool ran = false;
-        hms_status rc = solve_cluster(cnf, &p, &r, ran);
-        if (rc) return rc;
-        if (!ran) {
-            ms = 1e30;
-            return HMS_OK;
-        }
+        hms_status rc = solve_cluster(cnf, &p, &r, ran, true);
+        if (rc || !ran) return rc;
         t[k] = r.device_ms;
     }
     ms = std::max(t[2] - t[1], 0.0) / (2.0 * S);
@@ -2137,8 +2142,10 @@ hms_status hms_time_kernels(const hms_cnf* cnf, const hms_solve_params* p, int32
     }
     if (p->schedule == kClusterId) {
         double ms = 0;
-        hms_status rc = time_cluster(cnf, p, iters, ms);
+        bool ran = false;
+        hms_status rc = time_cluster(cnf, p, iters, ran, ms);
         if (rc) return rc;
+        if (!ran) return fail(HMS_ERR_DEVICE, "the clusters did not assemble beside other work on the device");
         if (fwd_ms) *fwd_ms = 0.0;
         if (bwd_ms) *bwd_ms = 0.0;
         if (step_ms) *step_ms = ms;

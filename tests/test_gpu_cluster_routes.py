@@ -231,3 +231,29 @@ def test_few_steps_on_a_timed_handle():
         assert a.schedule == other and b.schedule == hm.CLUSTER
         _same(a, b)
         assert hm.solve(c, steps=100, **kw).schedule == hm.CLUSTER
+
+
+def test_timing_beside_another_cluster_solve():
+    """Timing waits for the clusters that another thread holds: the time is a
+    step's, and clusters stay the timed choice."""
+    big, cnf = _cnf(20000, ratio=4.2), _cnf(7000, ratio=4.2)
+    alone = hm.time_kernels(cnf, restarts=5, iters=20, schedule=hm.CLUSTER)[2]
+
+    def work(st):
+        hm.solve(big, steps=3000, restarts=8, eval_every=50, autotune=False, stream=st)
+
+    def run():
+        st = torch.cuda.Stream()
+        times = [hm.time_kernels(cnf, restarts=5, iters=20, schedule=hm.CLUSTER, stream=st)[2] for _ in range(5)]
+        return times, hm.tune(cnf, restarts=5, stream=st)[0]
+
+    times, code = _beside(work, run)
+    _say("ms per step:", alone, times, "timed choice", code)
+    assert all(0 < t < 1 for t in times)  # 1 ms: some hundred times a step's time
+    assert code == hm.CLUSTER
+
+
+def test_timing_many_iterations():
+    """More iterations than a cluster solve has steps for are timed over fewer."""
+    cnf = _cnf(130, ratio=4.2)
+    assert 0 < hm.time_kernels(cnf, iters=100000, schedule=hm.CLUSTER)[2] < 1
