@@ -327,9 +327,10 @@ hms_status hms_evaluate(const hms_cnf* cnf, const uint8_t* assignment, int64_t* 
  *   - grad = dL/dx with mu held constant (Algorithm 1 backpropagation step).
  * x: DEVICE [n][R] FP32, caller order, read only.  loss: HOST [R] doubles,
  * unsat: HOST [R] int64, grad: DEVICE [n][R] FP32 (caller-owned; each may be
- * NULL).  Instances of at most 2^16 nonzeros that fit one workgroup's LDS take
- * one launch; otherwise the call allocates its own device workspace and
- * releases it in stream order.  grad may be x.  Synchronises `stream` when a host output is requested.
+ * NULL).  Instances of at most 2^16 nonzeros and 2^14 clauses and variables that
+ * fit one workgroup's LDS take one launch for up to 12 * 2^16 values of x (6 *
+ * 2^16 past 512 points); otherwise the call allocates its own device workspace
+ * and releases it in stream order.  grad may be x.  Synchronises `stream` when a host output is requested.
  * Errors: HMS_ERR_ARG (null instance or x, R < 1, bad loss mode),
  * HMS_ERR_DEVICE, HMS_ERR_NOMEM, HMS_ERR_TOO_LARGE.
  */

@@ -2594,9 +2594,11 @@ hms_status eval_relaxed_impl(const hms_cnf* cnf, const float* x, int32_t R, int3
         if (unsat) std::memcpy(unsat, d_unsat, (size_t)R * 8);
         return HMS_OK;
     };
-    // small instances: one launch, one workgroup per point, nothing allocated
+    // small instances: one launch, one workgroup per point.  Decided by the
+    // instance, the points and their overlap alone: with and without allocation
+    // the loss is then added in the same order
     const bool partly = want_g && grad != x && grad < x + (size_t)P.n * R && x < grad + (size_t)P.n * R;
-    if (!partly && (fixed || host.p || !(loss || unsat)) && hms::eval_small_ok(P, lds_limit(cnf->device))) {
+    if (!partly && hms::eval_small_ok(P, R, lds_limit(cnf->device))) {
         hms::EvalSmall E{};
         E.c_tile = cnf->c_tile;
         E.c_ent = cnf->c_ent;
@@ -2618,11 +2620,26 @@ hms_status eval_relaxed_impl(const hms_cnf* cnf, const float* x, int32_t R, int3
         E.inv_m = P.m > 0 ? 1.0 / (double)P.m : 0.0;
         E.w_empty = P.w_empty;
         E.x = x;
+        Arena A;  // more results than the pinned memory holds, or none to be had: copied back
+        A.s = s;
+        const bool copy = !fixed && !host.p && (loss || unsat);
+        if (copy) {
+            HIPTRY(hipMallocAsync((void**)&A.base, (size_t)R * 16, s));
+            d_loss = A.at<double>(0);
+            d_unsat = A.at<int64_t>((size_t)R * 8);
+        }
         E.loss = d_loss;
         E.unsat = d_unsat;
         E.grad = want_g ? grad : nullptr;
+        SyncOnExit outs_done{s, copy};
         HIPTRY(hms::launch_eval_small(E, P, lds_limit(cnf->device), s));
-        return host.p ? finish() : HMS_OK;
+        if (host.p) return finish();
+        if (copy) {
+            if (loss) HIPTRY(hipMemcpyAsync(loss, d_loss, (size_t)R * 8, hipMemcpyDeviceToHost, s));
+            if (unsat) HIPTRY(hipMemcpyAsync(unsat, d_unsat, (size_t)R * 8, hipMemcpyDeviceToHost, s));
+            HIPTRY(hipStreamSynchronize(s));
+        }
+        return HMS_OK;
     }
     Arena A;
     A.s = s;

@@ -591,8 +591,11 @@ size_t eval_small_lds(const HostPlan& P) {
 
 }  // namespace
 
-bool eval_small_ok(const HostPlan& P, size_t lds_cap) {
-    return P.nnz <= (1 << 16) && P.n_heavy_wide == 0 && eval_small_lds(P) <= lds_cap;
+bool eval_small_ok(const HostPlan& P, int32_t R, size_t lds_cap) {
+    const int32_t tiles = std::max(P.c_tiles, P.v_tiles);
+    const int64_t points = (int64_t)std::max(P.n, 1) * R;
+    return P.nnz <= (1 << 16) && tiles <= 256 && points <= (R <= 512 ? 12 : 6) * int64_t(1 << 16) &&
+           P.n_heavy_wide == 0 && eval_small_lds(P) <= lds_cap;
 }
 
 size_t small_lds_bytes(const HostPlan& P) {

@@ -74,10 +74,18 @@ struct EvalSmall {
     int64_t* unsat;       // [R]
     float* grad;
 };
-// Instances it takes: those that fit its LDS, up to 2^16 nonzeros (one
-// workgroup then takes at most about what the launches of the tiled
-// evaluation do) and no variable wider than the 64-slot combine.
-bool eval_small_ok(const HostPlan& P, size_t lds_cap);
+// Whether it takes R points of an instance.  Each workgroup walks the whole
+// formula (3-CNF, a few points, us of device time and launches against the tiled
+// passes: n = 1500 13 against 20, n = 3000 20 against 20, n = 5000 30 against 17)
+// and touches a line of x and of the gradient per variable and point, so the
+// tiled passes take over past 2^16 nonzeros, 256 tiles, or 12 * 2^16 values of x
+// up to 512 points (n = 1500: 512 points 33 against 27 and the launches'
+// workspace, 640 points 45 against 32; n = 3000: 256 points 36 against 27, 320
+// points 58 against 33) and 6 * 2^16 beyond, whose results are copied back (n =
+// 50: 2048 points 10 against 18; n = 200: 2048 points 26 against 21; n = 400: 1024
+// points 19 against 23, 1536 points 27 against 24).  No variable may be wider than
+// the 64-slot combine.
+bool eval_small_ok(const HostPlan& P, int32_t R, size_t lds_cap);
 hipError_t launch_eval_small(const EvalSmall& E, const HostPlan& P, size_t lds_cap, hipStream_t s);
 
 // LDS bytes the resident solver needs for an instance's state (per workgroup).

@@ -105,3 +105,33 @@ def test_results_with_more_points_than_the_pinned_memory():
         np.testing.assert_allclose(l1[0], loss[r], rtol=1e-13)
         np.testing.assert_array_equal(g1.cpu().numpy().view(np.uint32).ravel(),
                                       g[:, r].contiguous().cpu().numpy().view(np.uint32))
+
+
+# more points than the pinned memory holds (512); the last sizes of the one-launch route and the first past it (6 or,
+# up to 512 points, 12 times 2^16 values of x; 256 tiles of clauses); no clause at all
+NOALLOC = [(40, 170, 512), (40, 170, 513), (128, 200, 3072), (128, 200, 3073), (640, 2700, 614), (640, 2700, 615),
+           (1536, 6450, 512), (1537, 6450, 512), (3900, 16384, 3), (3900, 16385, 3), (40, 0, 515)]
+
+
+@pytest.mark.parametrize("n,m,R", NOALLOC)
+@pytest.mark.parametrize("mode", [hm.LOSS_UNSAT, hm.LOSS_ALL])
+def test_noalloc_equals_eval_bitwise(n, m, R, mode):
+    """With and without allocation: the same loss, gradient and counts, bit for
+    bit, with results in pinned memory or copied; each output may be left out."""
+    cnf = hm.load_cnf(n, cnfgen.uniform_kcnf(n, m, 3, seed=n + m) if m else np.zeros(0, np.int32))
+    x = torch.from_numpy(cnfgen.random_x(n, R, seed=4, lo=-2, hi=2)).cuda()
+    loss, g, u = hm.eval_relaxed(cnf, x, loss_mode=mode)
+    dl = torch.full((R,), -1.0, dtype=torch.float64, device="cuda")
+    du = torch.full((R,), -1, dtype=torch.int64, device="cuda")
+    dg = torch.full((n, R), 9.0, device="cuda")
+    hm.eval_relaxed_noalloc(cnf, x, loss_out=dl, grad_out=dg, unsat_out=du, loss_mode=mode)
+    np.testing.assert_array_equal(dl.cpu().numpy().view(np.uint64), loss.view(np.uint64))
+    np.testing.assert_array_equal(du.cpu().numpy(), u)
+    np.testing.assert_array_equal(dg.cpu().numpy().view(np.uint32), g.cpu().numpy().view(np.uint32))
+    l2, none, u2 = hm.eval_relaxed(cnf, x, loss_mode=mode, want_grad=False)
+    assert none is None
+    np.testing.assert_array_equal(l2.view(np.uint64), loss.view(np.uint64))
+    np.testing.assert_array_equal(u2, u)
+    dg.fill_(9.0)
+    hm.eval_relaxed_noalloc(cnf, x, grad_out=dg, loss_mode=mode)
+    np.testing.assert_array_equal(dg.cpu().numpy().view(np.uint32), g.cpu().numpy().view(np.uint32))
