@@ -353,6 +353,13 @@ __device__ __forceinline__ void escape_lds(const unsigned char* smem) {
 // counts).
 __device__ __attribute__((noinline)) float signed_tanh_call(float x) { return signed_tanh(x); }
 
+// Waits until this wavefront's stores have reached the L2.  As an instruction
+// with a memory effect: the builtin has none, and would let the compiler move a
+// relaxed store across it.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); }
+// What others published before the flag just read is loaded after it.
+__device__ __forceinline__ void flag_seen() { asm volatile("" : : : "memory"); }
+
 // One record block of the list that counts (neg: x rounds to true).
 template <int NO, bool WT, bool WIDE = false>
 struct RecordBlock {
@@ -689,6 +696,7 @@ __device__ __forceinline__ void collect(const ClusterGroup& G, Shared& sh, unsig
         }
         if (__ballot(!ok) == 0) break;
     }
+    flag_seen();
     if (__ballot(!ok) != 0) sh.dead = 1;
     if (eval && part == 0 && lane < rounds) atomicAdd(&sh.tot[par], (unsigned long long)(f >> 32));
     if (last) return;
@@ -826,7 +834,6 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
     const int slice = D.slice;
     const int r = G.r;
     const int n = D.n;
-    const int n_act = D.n_act;  // variables past these are in no clause
     const int P = C * slice;
     const int ntl = (D.v_tiles - member + C - 1) >> log2C;  // own variable tiles
     // t of all variables, or (WIDE) their roundings; own t is kept in lo then
@@ -877,7 +884,7 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
             lt[P + 1] = 0.0f;  // a literal that is true
         }
     }
-    if constexpr (WIDE) __builtin_amdgcn_s_waitcnt(0);
+    if constexpr (WIDE) stores_done();
     if (member == 0) keep_inactive(D, r, tid, best_a);
     __syncthreads();
     const int32_t* my_var = D.var + member * slice;  // own variables, by own slot
@@ -1020,14 +1027,14 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster(ClusterLaunch A) {
         // flags and losses alternate between two places: a workgroup that is
         // done may publish the next step while another still reads this one,
         // but not the one after, which needs the other's next flag
-        __builtin_amdgcn_s_waitcnt(0);
+        stores_done();
         __syncthreads();
         if (tid == 0) {
             if (want_loss) {
                 double ls = 0.0;
                 for (int w = 0; w < kWaves; ++w) ls = ls + sh.los[w];
                 __hip_atomic_store(G.losses + par * C + member, ls, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                __builtin_amdgcn_s_waitcnt(0);
+                stores_done();
             }
             const uint64_t f = (uint64_t)(uint32_t)(step + 1) | ((uint64_t)sh.cnt[par] << 32);
             __hip_atomic_store((HMS_GLOBAL uint64_t*)G.flags + (size_t)member * kFlagStride + par, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1356,7 +1363,7 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster_one(ClusterLaunch A
                         if (w == 0 || w * C + member < c_tiles) ls = ls + sh.los[kWaves - 1 - w];
                     __hip_atomic_store(losses + (step & 3) * C + member, ls, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
-                    __builtin_amdgcn_s_waitcnt(0);
+                    stores_done();
                     for (int w = 0; w < CW; ++w)
                         if (w == 0 || w * C + member < c_tiles)
                             __hip_atomic_store(counts + ((step & 3) * C + member) * CW + w,
@@ -1410,14 +1417,14 @@ __global__ __launch_bounds__(kClusterThreads) void k_cluster_one(ClusterLaunch A
             }
         } else {
             // own stores have reached the L2, then the flag
-            __builtin_amdgcn_s_waitcnt(0);
+            stores_done();
             __syncthreads();
             if (tid == 0) {
                 if (want_loss) {
                     double ls = 0.0;
                     for (int w = 0; w < kWaves; ++w) ls = ls + sh.los[w];
                     __hip_atomic_store(load_uniform(&launder(gp)->losses) + par * C + member, ls, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    __builtin_amdgcn_s_waitcnt(0);
+                    stores_done();
                 }
                 __hip_atomic_store((HMS_GLOBAL uint64_t*)G.flags + (size_t)member * kFlagStride + par,
                                    (uint64_t)epoch | ((uint64_t)sh.cnt[par] << 32), __ATOMIC_RELAXED,
