@@ -2127,7 +2127,9 @@ hms_status hms_time_kernels(const hms_cnf* cnf, const hms_solve_params* p, int32
     DeviceGuard dg(cnf->device);
     hms_solve_params pr = *p;
     pr.resume = nullptr;  // timing starts from the seed or x0
-    hms_status rc0 = resolve_schedule(cnf, p, pr.schedule);
+    // the automatic choice is one with a forward and a backward pass to time
+    // wherever it was one without clusters; by id, a cluster step is timed whole
+    hms_status rc0 = resolve_schedule(cnf, p, pr.schedule, false);
     if (rc0) return rc0;
     p = &pr;
     if (p->schedule == kResidentId) {

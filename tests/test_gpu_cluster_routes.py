@@ -257,3 +257,22 @@ def test_timing_many_iterations():
     """More iterations than a cluster solve has steps for are timed over fewer."""
     cnf = _cnf(130, ratio=4.2)
     assert 0 < hm.time_kernels(cnf, iters=100000, schedule=hm.CLUSTER)[2] < 1
+
+
+def test_kernel_times_of_the_automatic_schedule():
+    """hms_time_kernels with schedule 0 times the forward and the backward
+    kernels, whatever the step count and also on a handle timed to clusters."""
+    import ctypes as C
+
+    from paper_2402_03640_amd import _lib
+    cnf = _cnf(20000, ratio=4.2)
+    f, b, st = C.c_double(), C.c_double(), C.c_double()
+    p = _lib._params(cnf, 1000, 4, 50, 0, hm.ADAM, 1e-4, 0.9, 0.999, 1e-8, hm.LOSS_UNSAT, 0, False, 0.0, None, None,
+                     False)
+    for tuned in (False, True):
+        if tuned:
+            assert hm.tune(cnf, restarts=4)[0] == hm.CLUSTER
+        _lib._check(_lib.lib().hms_time_kernels(cnf.handle, C.byref(p), 20, C.byref(f), C.byref(b), C.byref(st)))
+        _say("ms:", f.value, b.value, st.value)
+        assert f.value > 0 and b.value > 0 and st.value > 0
+    assert hm.time_kernels(cnf, restarts=4, schedule=hm.CLUSTER)[:2] == (0.0, 0.0)
