@@ -130,7 +130,9 @@ struct SyncOnExit {
 // with four lanes per row up to 2^14 active variables (entry 39: one of them
 // works, so a wavefront takes 16 rows and a small instance's rows spread over
 // four times the wavefronts), else two (entry 38).
-int auto_schedule(int32_t R, int loss_mode, int64_t nnz = 0, int32_t n_act = 0) {
+int auto_schedule(int32_t R, int loss_mode, const hms::HostPlan& P) {
+    const int64_t nnz = P.nnz;
+    const int32_t n_act = P.n_act;
     if (R <= 1) {
         // the slot schedules from 2^17 nonzeros with the unsat-masked loss:
         // two clause tiles per forward wavefront past 2^22, one below
@@ -141,18 +143,35 @@ int auto_schedule(int32_t R, int loss_mode, int64_t nnz = 0, int32_t n_act = 0) 
         // while the rows are few, two beyond
         return n_act <= (1 << 14) ? 39 : 38;
     }
-    // several restarts, forward + backward us timed over every entry on 3-CNF
-    // n = 20000 m = 86000 and 5-CNF n = 12000 m = 204000 (unmasked): up to eight
-    // the long backward batches at four lanes per row (8 restarts 10.6 and 23.5,
-    // entry 5: 10.4 and 24.8); then four restarts per lane, 16 or 32 restarts
-    // per group (16: 13.1 and 28.0, entry 4 13.4 and 29.6; 32: 16.6 and 35.1,
-    // entry 10 21.3 and 50; 64: 25.6 and 53.8, entry 15 27.4 and 60.6), two
-    // per lane (32: 18.5 and 40.2), else one restart per lane, 16 per group
-    // (32: 19.8 and 40.4)
-    if (R <= 8) return 39;
+    // several restarts, us per step timed on 3-CNF of 12000 to 100000 variables,
+    // mixed n = 30000, 4-CNF n = 25000, 5-CNF n = 12000 m = 204000 and structured
+    // formulas of 20000 to 500000 variables (up to 8.7 million nonzeros):
+    //   - multiples of four past eight: four restarts per lane, 16 or 32 per group
+    //     (64 restarts, n = 20000: 25.6 against 27.4 with entry 15);
+    //   - three and four: the long backward batches at four lanes per row (0.89 to
+    //     0.97 of entry 3 on all of them); two: the same up to 2^21 nonzeros (n = 20000
+    //     8.7 against 9.0, structured n = 250000 53 against 47);
+    //   - five to eight: the same up to 2^19 nonzeros, 2^20 with at most 16000 variables
+    //     or a split row (n = 20000 12.8 against 13.5, structured n = 60000 34 against
+    //     36; n = 50000 22.2 against 20.6, structured n = 500000 300 against 198);
+    //   - up to 32, and even: two per lane up to 24000 variables (n = 20000 20.6 against
+    //     22.2, mixed n = 30000 26.2 against 25.2); odd: 16 per group up to 16000 (n =
+    //     12000 18.1 against 19.4, n = 20000 23.7 against 22.2); else 32 per group;
+    //   - beyond, up to 2^19 nonzeros: even and up to 24000 variables, two per lane (34
+    //     restarts, n = 20000 29.0 against 31.8), else 32 per group (33 restarts, mixed n =
+    //     30000 39.9 against 40.8); else 64 per group (structured n = 250000, 33
+    //     restarts 392 against 433, 99 restarts 911 against 993)
+    if (R <= 2) return nnz > (1 << 21) ? 2 : 39;
+    if (R <= 4) return 39;
+    if (R <= 8) return nnz > (P.n_heavy > 0 || n_act <= 16000 ? 1 << 20 : 1 << 19) ? 5 : 39;
     if (R % 4 == 0) return R <= 16 ? 33 : 34;
     if (R <= 16) return 4;
-    return R % 2 == 0 ? 35 : 6;
+    if (R <= 32) {
+        if (R % 2 == 0) return n_act <= 24000 ? 35 : 10;
+        return n_act <= 16000 ? 6 : 10;
+    }
+    if (nnz > (1 << 19)) return 14;
+    return R % 2 == 0 && n_act <= 24000 ? 35 : 10;
 }
 
 struct Shape {
@@ -175,7 +194,7 @@ hms_status make_shape(const hms::HostPlan& P, int32_t R, int32_t req, int loss_m
     int U = (req >> 8) & 0xff;
     int Ub = (req >> 16) & 0xff;
     if (req < 0 || (req >> 24) != 0 || idx > hms::kNumSchedules) return fail(HMS_ERR_ARG, "unknown schedule id");
-    sh.sched = idx == 0 ? auto_schedule(R, loss_mode, P.nnz, P.n_act) : idx;
+    sh.sched = idx == 0 ? auto_schedule(R, loss_mode, P) : idx;
     if (hms::kSchedules[sh.sched].mask && (loss_mode != HMS_LOSS_UNSAT || !allow_mask))
         sh.sched = hms::kSchedules[sh.sched].twin;
     // slot schedules: one restart, the unsat-masked loss, and a plan with the
@@ -196,9 +215,13 @@ hms_status make_shape(const hms::HostPlan& P, int32_t R, int32_t req, int loss_m
         // the automatic choice gives a forward wavefront more rows once the
         // wavefronts pass what the chip holds: each writes its count and
         // loss partials, 16 bytes per restart (64 restarts at n = 20000: 4 rows
-        // per unit wrote 22 MB of them, the counting forward 18.3 us)
+        // per unit wrote 22 MB of them, the counting forward 18.3 us); with 64
+        // lanes per row in evaluations alone, which always count (solves that
+        // count every 50th step, 4-CNF n = 25000, 66 restarts: forward 44 us with
+        // 8 rows, 47 with 32)
         const int64_t groups = (R + sh.P * sh.V - 1) / (sh.P * sh.V);
-        if (idx == 0 && c.nt == 1 && !sh.mask)
+        const bool evaluation = !allow_slot;
+        if (idx == 0 && c.nt == 1 && !sh.mask && (sh.P < 64 || evaluation))
             while (U < hms::kTile && (int64_t)P.c_tiles * (hms::kTile / U) * groups > 8192) U *= 2;
     }
     if (Ub == 0) Ub = U;
@@ -1013,7 +1036,7 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, Tu
     // timed twice more and keep their best time, so that one noisy
     // measurement does not decide between near-equal choices
     std::sort(timed.begin(), timed.end());
-    const int untimed = auto_schedule(p->restarts, p->loss_mode, cnf->plan.nnz, cnf->plan.n_act);
+    const int untimed = auto_schedule(p->restarts, p->loss_mode, cnf->plan);
     for (size_t k = 0; k < timed.size(); ++k) {
         if (k >= 3 && (timed[k].second == kResidentId || timed[k].second == kClusterId ||
                        (timed[k].second & 0xff) != untimed))

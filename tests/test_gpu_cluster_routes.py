@@ -276,3 +276,20 @@ def test_kernel_times_of_the_automatic_schedule():
         _say("ms:", f.value, b.value, st.value)
         assert f.value > 0 and b.value > 0 and st.value > 0
     assert hm.time_kernels(cnf, restarts=4, schedule=hm.CLUSTER)[:2] == (0.0, 0.0)
+
+
+# (variables, clauses, literals, restarts, entry of the schedule table): the
+# untimed choice on either side of its size limits
+UNTIMED = [(20000, 86000, 3, 8, 39), (50000, 215000, 3, 8, 5), (20000, 86000, 3, 18, 35), (26000, 110000, 3, 18, 10),
+           (12000, 50000, 3, 17, 6), (20000, 86000, 3, 17, 10), (20000, 86000, 3, 34, 35), (26000, 110000, 3, 34, 10),
+           (50000, 215000, 3, 33, 14), (50000, 215000, 3, 36, 34)]
+
+
+@pytest.mark.parametrize("n,m,k,R,entry", UNTIMED)
+def test_untimed_schedule_of_several_restarts(n, m, k, R, entry):
+    cnf = hm.load_cnf(n, cnfgen.uniform_kcnf(n, m, k, seed=1))
+    kw = dict(steps=3, restarts=R, eval_every=2, lr=1e-2, want_x=True)
+    a, b = hm.solve(cnf, autotune=False, **kw), hm.solve(cnf, schedule=1, **kw)
+    assert a.schedule & 0xFF == entry
+    _same(a, b)
+    cnf.free()
