@@ -64,9 +64,13 @@ constexpr size_t cluster_one_lds(int32_t C, int32_t slice, bool words) {
     return (words ? kAltByte : 0) + cluster_t_bytes(C, slice) + kClusterSharedBytes;
 }
 
-// Shape for R restarts together (many: in a form for several tiles per
-// wavefront, whatever the size); false when there is none.
-inline bool cluster_shape_of(const ClusterSize& Z, int32_t R, size_t lds_cap, ClusterShape& sh, bool many = false) {
+// Which shapes are looked at: any (a single instance), or those of the two forms
+// for several tiles per wavefront.
+enum ClusterForm : int32_t { kFormAny = 0, kFormMany = 1, kFormWide = 2 };
+
+// Shape for R restarts together; false when there is none.
+inline bool cluster_shape_of(const ClusterSize& Z, int32_t R, size_t lds_cap, ClusterShape& sh,
+                             ClusterForm form = kFormAny) {
     sh.NO = Z.NO;
     // as many workgroups per restart as leave every restart its own at once
     int32_t C = kXcdCus;
@@ -76,7 +80,7 @@ inline bool cluster_shape_of(const ClusterSize& Z, int32_t R, size_t lds_cap, Cl
     // their four SIMDs one tile, half as many tiles where t goes in words (n =
     // 4000, 3-CNF, one restart: 2.33 us a step at one, 2.31 at two, 2.39 at
     // four, 2.94 at sixteen tiles)
-    if (!many && Z.v_tiles <= kClusterWaves * C) {
+    if (form == kFormAny && Z.v_tiles <= kClusterWaves * C) {
         const int per = Z.v_tiles * kTile <= kOneSlots ? 2 : 4;  // tiles per workgroup
         int32_t c1 = 2;
         while (c1 < C && Z.v_tiles > per * c1) c1 *= 2;
@@ -98,22 +102,18 @@ inline bool cluster_shape_of(const ClusterSize& Z, int32_t R, size_t lds_cap, Cl
         if (wide) return P + 64 <= kClusterMaxWide && cluster_wide_lds(c, slice_at(c)) <= lds_cap;
         return P + 2 <= kClusterMaxPos && cluster_many_lds(c, slice_at(c)) <= lds_cap;
     };
-    // wide only where t fits LDS for no number of workgroups: which of the two it
-    // is then depends on the instance alone, not on R, so instances grouped by
-    // their own form still agree once their restarts are counted together.  481 to
-    // 496 tiles fit with 16 workgroups only (n = 31000, us a step in that form
-    // against wide: 3-CNF 6.6 against 6.9, nine restarts 6.6 against 10.0; 4-CNF
-    // 10.6 against 12.5; 5-CNF 12.5 against 14)
+    // wide where t fits LDS neither with so many workgroups nor with more.  481 to
+    // 496 tiles fit with 16 only and so change form past eight restarts (n = 31000,
+    // us a step with 16 in that form and wide with 32: 3-CNF 6.6 and 6.9, counted
+    // every step 17.1 and 12.7; nine restarts, both with 16, 6.6 and 10.0)
     const int32_t C0 = C;
-    bool wide = false;
+    bool wide = form == kFormWide;
     while (C <= kXcdCus && !fits(C, wide)) C *= 2;
-    if (C > kXcdCus)
-        for (C = C0; C >= 2 && !fits(C, wide);) C /= 2;
-    if (C < 2) {
+    if (C > kXcdCus && form == kFormAny) {
         wide = true;
         for (C = C0; C <= kXcdCus && !fits(C, wide);) C *= 2;
-        if (C > kXcdCus) return false;
     }
+    if (C > kXcdCus) return false;
     sh.mode = wide ? kClusterWide : kClusterMany;
     sh.slice = slice_at(C);
     sh.lds = wide ? cluster_wide_lds(C, sh.slice) : cluster_many_lds(C, sh.slice);
@@ -124,36 +124,37 @@ inline bool cluster_shape_of(const ClusterSize& Z, int32_t R, size_t lds_cap, Cl
 
 // Shapes of instances whose solves run together, largest first, R[i] restarts
 // of instance i: as many workgroups per restart as leave every restart its own
-// at once.  One launch runs one kernel, so all take the form for several tiles
-// per wavefront unless all fit the same other one; in that form what CUs are
-// left go to the largest instances (twelve 3-CNF instances of 15000 to 26000
-// variables: 16 workgroups each, 32 for the four largest).  False when an
-// instance does not fit or their kernels differ.
-inline bool cluster_group(const std::vector<ClusterSize>& Z, const std::vector<int32_t>& R, size_t lds_cap,
+// at once.  One launch runs one kernel.  `wide`: which form each instance has by
+// itself (the form may change with the number of restarts, so it is fixed here
+// for all of them); those that are not wide take the form for several tiles per
+// wavefront unless all fit the same other one.  What CUs are left in that form go
+// to the largest instances (twelve 3-CNF instances of 15000 to 26000 variables: 16
+// workgroups each, 32 for the four largest).  False when an instance does not fit
+// the form or their kernels differ.
+inline bool cluster_group(const std::vector<ClusterSize>& Z, const std::vector<int32_t>& R, bool wide, size_t lds_cap,
                           std::vector<ClusterShape>& sh) {
     const size_t count = Z.size();
     sh.assign(count, ClusterShape());
     int32_t units = 0;
     for (int32_t r : R) units += r;
-    bool same = true;
-    for (size_t i = 0; i < count; ++i) {
-        if (!cluster_shape_of(Z[i], units, lds_cap, sh[i])) return false;
-        if (sh[i].NO != sh[0].NO) return false;
-        same = same && sh[i].mode == sh[0].mode;
-    }
-    if (same && (sh[0].mode == kClusterOne || sh[0].mode == kClusterOneWords)) return true;
+    for (size_t i = 0; i < count; ++i)
+        if (Z[i].NO != Z[0].NO) return false;
+    bool one = !wide;  // all at most one tile per wavefront, with one exchange
+    for (size_t i = 0; i < count && one; ++i)
+        one = cluster_shape_of(Z[i], units, lds_cap, sh[i]) && sh[i].mode == sh[0].mode &&
+              (sh[i].mode == kClusterOne || sh[i].mode == kClusterOneWords);
+    if (one) return true;
+    const ClusterForm form = wide ? kFormWide : kFormMany;
     int32_t left = kXcds * kXcdCus;
     for (size_t i = 0; i < count; ++i) {
-        if (!cluster_shape_of(Z[i], units, lds_cap, sh[i], true) || sh[i].mode != sh[0].mode) return false;
+        if (!cluster_shape_of(Z[i], units, lds_cap, sh[i], form)) return false;
         left -= R[i] * sh[i].C;
     }
     for (size_t i = 0; i < count; ++i) {
         ClusterShape more;
         const int32_t C = sh[i].C;
         if (C == kXcdCus || R[i] * C > left) break;
-        if (!cluster_shape_of(Z[i], kXcds * (kXcdCus / (2 * C)), lds_cap, more, true) || more.C != 2 * C ||
-            more.mode != sh[i].mode)
-            break;
+        if (!cluster_shape_of(Z[i], kXcds * (kXcdCus / (2 * C)), lds_cap, more, form) || more.C != 2 * C) break;
         sh[i] = more;
         left -= R[i] * C;
     }

@@ -1406,12 +1406,9 @@ bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p) {
 //   - with one restart only one XCD works, and the others' share of the
 //     tiled kernels wins again past 2^21 record terms (nonzeros times other
 //     literals per clause; 3-CNF n = 28000: 4.6 against 7.1; 4-CNF n = 16000:
-//     7.5 against 8.8, n = 28000: 11.2 against 10.4), and past 30720 variables,
-//     where t fits LDS with 16 workgroups only, with four and five literals per
-//     clause (n = 31000, m = 5 n: 4-CNF 10.6 against 9.3, 5-CNF 12.4 against
-//     10.0; with three restarts 10.6 against 14.7 and 12.4 against 15.7; 3-CNF
-//     with one 6.7 against 8.9);
-//   - in the wide form (past 31744 variables), which reads t from the L2, from
+//     7.5 against 8.8, n = 28000: 11.2 against 10.4));
+//   - in the wide form (past 30720 variables with up to eight restarts, 31744 with
+//     more), which reads t from the L2, from
 //     two, three and four restarts on with at most three, four and five literals
 //     per clause, and past three only up to 16, where the tiled kernels share a
 //     formula's entries between enough restarts (3-CNF n = 33000: one restart
@@ -1438,8 +1435,7 @@ bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p, int64_t to
     if (nnz <= kResidentNnz && R > sh.per_launch) return false;
     if (sh.mode == hms::kClusterWide) return R >= sh.NO && (sh.NO == 2 || p->restarts <= 16);
     if (R > 1) return true;
-    const bool few = sh.mode == hms::kClusterMany && sh.C < hms::kXcdCus;
-    return nnz * sh.NO <= (int64_t(1) << 21) && (sh.NO == 2 || !few);
+    return nnz * sh.NO <= (int64_t(1) << 21);
 }
 
 // One cluster launch at a time on a device: two that each hold part of an XCD
@@ -1751,9 +1747,9 @@ hms_status solve_cluster(const hms_cnf* cnf, const hms_solve_params* p, hms_solv
     return HMS_OK;
 }
 
-// Shapes of the items for running together (cluster_group); false when one does
-// not fit or their kernels differ.
-bool cluster_shapes(std::vector<ClusterItem>& items) {
+// Shapes of the items for running together in one form (cluster_group); false
+// when one does not fit it or their kernels differ.
+bool cluster_shapes(std::vector<ClusterItem>& items, bool wide) {
     std::vector<hms::ClusterSize> Z(items.size());
     std::vector<int32_t> R(items.size());
     std::vector<hms::ClusterShape> sh;
@@ -1761,7 +1757,7 @@ bool cluster_shapes(std::vector<ClusterItem>& items) {
         if (!hms::cluster_size(items[i].cnf->plan, Z[i])) return false;
         R[i] = items[i].p.restarts;
     }
-    if (!hms::cluster_group(Z, R, cluster_lds_cap(items[0].cnf->device), sh)) return false;
+    if (!hms::cluster_group(Z, R, wide, cluster_lds_cap(items[0].cnf->device), sh)) return false;
     for (size_t i = 0; i < items.size(); ++i) items[i].sh = sh[i];
     return true;
 }
@@ -2311,7 +2307,7 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
             }
             // a launch runs one kernel form
             hms_status st = HMS_OK;
-            if (cluster_shapes(items)) st = solve_clusters(items, s);
+            if (cluster_shapes(items, std::get<2>(kv.first))) st = solve_clusters(items, s);
             for (size_t k = 0; k < cnt; ++k) {
                 const int32_t i = c[k0 + k];
                 if (st) {

@@ -31,15 +31,21 @@ void check_shape(const ClusterShape& s, int tiles, int NO, int R) {
     if (s.lds != need || s.NO != NO) wrong("LDS of another form", tiles, NO, R);
 }
 
-// One launch: one kernel, shapes in order, every restart its own workgroups or less room than that.
-bool check_group(const std::vector<ClusterSize>& Z, const std::vector<int32_t>& R) {
+bool is_wide(int tiles, int NO, int R) {
+    ClusterShape s;
+    return cluster_shape_of(ClusterSize{tiles, NO}, R, kCap, s) && s.mode == kClusterWide;
+}
+
+// One launch: one kernel, every shape a valid one.
+bool check_group(const std::vector<ClusterSize>& Z, const std::vector<int32_t>& R, bool wide) {
     std::vector<ClusterShape> sh;
     int units = 0;
     for (int32_t r : R) units += r;
-    if (!cluster_group(Z, R, kCap, sh)) return false;
+    if (!cluster_group(Z, R, wide, kCap, sh)) return false;
     for (size_t i = 0; i < Z.size(); ++i) {
         check_shape(sh[i], Z[i].v_tiles, Z[i].NO, units);
         if (sh[i].mode != sh[0].mode || sh[i].NO != sh[0].NO) wrong("two kernels in one launch", Z[i].v_tiles, Z[i].NO, units);
+        if ((sh[i].mode == kClusterWide) != wide) wrong("not the group's form", Z[i].v_tiles, Z[i].NO, units);
     }
     return true;
 }
@@ -48,7 +54,6 @@ bool check_group(const std::vector<ClusterSize>& Z, const std::vector<int32_t>& 
 
 int main() {
     long shapes = 0, groups = 0;
-    std::vector<int> wide(kMaxTiles + 1, -1);  // whether an instance's roundings alone are in LDS
     std::vector<int> least(kMaxTiles + 1, 0);  // fewest restarts it runs with
     for (int NO = 2; NO <= 4; ++NO)
         for (int tiles = 2; tiles <= kMaxTiles; ++tiles) {
@@ -63,9 +68,6 @@ int main() {
                 if (!least[tiles]) least[tiles] = R;
                 check_shape(s, tiles, NO, R);
                 ++shapes;
-                const int w = s.mode == kClusterWide;
-                if (wide[tiles] < 0) wide[tiles] = w;
-                if (wide[tiles] != w) wrong("the form depends on the restarts", tiles, NO, R);
             }
         }
     // equal instances, one or several restarts each
@@ -74,7 +76,8 @@ int main() {
             for (int count = 2; count <= 64; ++count)
                 for (int r : {1, 2, 5, 9}) {
                     if (!least[tiles] || least[tiles] > r) continue;
-                    if (!check_group(std::vector<ClusterSize>(count, ClusterSize{tiles, NO}), std::vector<int32_t>(count, r)))
+                    if (!check_group(std::vector<ClusterSize>(count, ClusterSize{tiles, NO}), std::vector<int32_t>(count, r),
+                                     is_wide(tiles, NO, r)))
                         wrong("equal instances refused", tiles, NO, r);
                     ++groups;
                 }
@@ -88,23 +91,23 @@ int main() {
         std::vector<int32_t> R;
         while ((int)Z.size() < count) {
             const int tiles = lo + rnd(hi - lo + 1), r = 1 + rnd(rnd(2) ? 3 : 20);
-            if (wide[tiles] != w || least[tiles] > r) continue;
+            if (!least[tiles] || least[tiles] > r || is_wide(tiles, NO, r) != (w != 0)) continue;
             Z.push_back(ClusterSize{tiles, NO});
             R.push_back(r);
         }
         std::stable_sort(Z.begin(), Z.end(), [](const ClusterSize& a, const ClusterSize& b) { return a.v_tiles > b.v_tiles; });
-        if (!check_group(Z, R)) wrong("instances of one form refused", Z[0].v_tiles, NO, count);
+        if (!check_group(Z, R, w != 0)) wrong("instances of one form refused", Z[0].v_tiles, NO, count);
         ++groups;
     }
-    // of two forms: never one launch
+    // sizes in no order, with either form asked for: one kernel, or none
     for (int a = 2; a <= kMaxTiles; ++a)
         for (int b = 470; b <= 520; ++b)
-            for (int r : {1, 2, 9}) {
-                if (wide[a] < 0 || wide[b] < 0 || least[a] > r || least[b] > r) continue;
-                const bool ok = check_group({ClusterSize{std::max(a, b), 2}, ClusterSize{std::min(a, b), 2}}, {r, r});
-                if (ok != (wide[a] == wide[b])) wrong("two forms in one launch", a, b, r);
-                ++groups;
-            }
+            for (int r : {1, 2, 9})
+                for (bool w : {false, true}) {
+                    check_group({ClusterSize{std::max(a, b), 2}, ClusterSize{std::min(a, b), 2}}, {r, r}, w);
+                    ++groups;
+                }
+    if (check_group({ClusterSize{100, 2}, ClusterSize{100, 3}}, {1, 1}, false)) wrong("two record sizes in one launch", 100, 2, 1);
     std::printf("ok %ld shapes %ld groups\n", shapes, groups);
     return 0;
 }

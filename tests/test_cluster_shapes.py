@@ -1,6 +1,5 @@
 """Shapes of cluster solves (host arithmetic): within LDS and the literal fields at
-every size, in a form (t or only its roundings in LDS) that depends on the
-instance alone, and one kernel per launch whatever a batch brings together."""
+every size, and one kernel per launch whatever a batch brings together."""
 import os
 import shutil
 import subprocess
