@@ -1389,9 +1389,12 @@ bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p) {
     return cluster_fits(cnf, p, sh);
 }
 
+// Least number of steps that the untimed choice takes clusters for.
+int32_t cluster_least_steps(const hms_cnf* cnf) { return cnf->plan.nnz <= (int64_t(1) << 14) ? 256 : 64; }
+
 // Without timing, the cluster solver is taken wherever it runs and was the
 // faster one, us per step on uniform 3-, 4-, 5-CNF and mixed formulas of 150 to
-// 28000 variables, 1 to 256 restarts, against the resident or the tuned tiled
+// 60000 variables, 1 to 1024 restarts, against the resident or the tuned tiled
 // schedule:
 //   - from 5, 7 and 24 thousand nonzeros up with at most three, four and five
 //     literals per clause: below, the resident solver's single workgroup needs
@@ -1406,22 +1409,39 @@ bool cluster_ok(const hms_cnf* cnf, const hms_solve_params* p) {
 //   - with one restart only one XCD works, and the others' share of the
 //     tiled kernels wins again past 2^21 record terms (nonzeros times other
 //     literals per clause; 3-CNF n = 28000: 4.6 against 7.1; 4-CNF n = 16000:
-//     7.5 against 8.8, n = 28000: 11.2 against 10.4));
+//     7.5 against 8.8, n = 28000: 11.2 against 10.4);
+//   - counted every step or every other, where a count costs clusters more than
+//     the tiled kernels (each restart's workgroups walk all clauses), without limit
+//     only up to 2^18, 160 thousand and 220 thousand nonzeros with at most three,
+//     four and five literals per clause.  Past them, us a step counted every step and
+//     every other: three literals up to 96 restarts, counted every step past 320
+//     thousand nonzeros 1.6e7 nonzeros times restarts (n = 24000, 96 restarts 58
+//     against 66, 128 restarts 78 and 62 against 74 and 63; n = 28000, 64 restarts 54
+//     and 36 against 52 and 44, 128 restarts 107 and 72 against 82 and 74); four, all
+//     restarts in one launch with a workgroup for so many steps' 60 thousand nonzeros
+//     (n = 20000, 32 restarts 29 against 35, 64 restarts 56 and 37 against 46 and 39,
+//     96 restarts 110 and 74 against 66 and 60; n = 28000, 32 restarts 40 and 27 against
+//     37 and 33); five, 128 restarts, or 256 (n = 22000, 128 restarts 75 and 60
+//     against 84 and 73, 256 restarts 149 and 119 against 135 and 121);
 //   - in the wide form (past 30720 variables with up to eight restarts, 31744 with
-//     more), which reads t from the L2, from
-//     two, three and four restarts on with at most three, four and five literals
-//     per clause, and past three only up to 16, where the tiled kernels share a
-//     formula's entries between enough restarts (3-CNF n = 33000: one restart
-//     7.9 against 7.5, two 7.9 against 9.6, 64 38 against 40; n = 60000: two 12.0
-//     against 14.9, 64 71 against 75; 4-CNF n = 34000: two 19.7 against 17.2,
-//     three 19.9 against 25.0, 16 28 against 32, 32 49 against 46; 5-CNF n =
-//     34000: two 21 against 19, four 21.7 against 22.7, 16 30 against 35, 32 55
-//     against 48);
+//     more), which reads t from the L2, from two, three and four restarts on with at
+//     most three, four and five literals per clause (counted every 50th step and
+//     every step: 3-CNF n = 33000 one restart 8.8 and 13.4 against 10.1 and 15.2, n =
+//     60000 one 13.3 and 21.3 against 12.2 and 16.6, two 13.2 and 21.4 against 16.4 and
+//     21.6; 4-CNF n = 34000 two 15.3 against 14.5, three 15.6 against 17.3; 5-CNF n =
+//     34000 three 16.8 against 16.4, eight 17.3 against 19.5), and up to 16 restarts,
+//     where the tiled kernels share a formula's entries between enough of them (4-CNF
+//     n = 34000: 16 20.0 and 35 against 25.9 and 35.5, 32 33.7 against 32.0); with
+//     three literals also up to 32 counted every fourth step or less (n = 60000: 45.7
+//     against 47.1, every other 55 against 48), every other up to 500 thousand nonzeros
+//     (n = 33000: 31.0 against 32.2), and up to 64 every 16th or less, to 600 thousand
+//     (n = 45000: 56 against 61, n = 33000: 96 restarts 74.5 against 71.4; n = 60000: 40
+//     restarts 75 against 72);
 //   - from 64 steps on (256 up to 2^14 nonzeros, where a step gains least):
 //     building the records costs 40 to 250 us, about what so many steps gain.
-// `together`: the restarts of a batch that would share the launches.
-int32_t cluster_least_steps(const hms_cnf* cnf) { return cnf->plan.nnz <= (int64_t(1) << 14) ? 256 : 64; }
-
+// `together`: the restarts of a batch that would share the launches (clusters were
+// the faster ones on batches of 2 to 48 one-restart instances of all these sizes
+// at every period; the limits on restarts are those of one instance).
 bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p, int64_t together) {
     hms::ClusterShape sh;
     const int64_t nnz = cnf->plan.nnz;
@@ -1433,9 +1453,18 @@ bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p, int64_t to
         !hms::cluster_shape(cnf->plan, (int32_t)R, cluster_lds_cap(cnf->device), sh))
         return false;
     if (nnz <= kResidentNnz && R > sh.per_launch) return false;
-    if (sh.mode == hms::kClusterWide) return R >= sh.NO && (sh.NO == 2 || p->restarts <= 16);
-    if (R > 1) return true;
-    return nnz * sh.NO <= (int64_t(1) << 21);
+    const int32_t own = p->restarts, K = p->eval_every;
+    if (sh.mode == hms::kClusterWide) {
+        int32_t most = 16;
+        if (sh.NO == 2 && K >= (nnz <= 500000 ? 2 : 4)) most = K < 16 || nnz > 600000 ? 32 : 64;
+        return R >= sh.NO && own <= most;
+    }
+    if (K <= 2 && nnz > (sh.NO == 2 ? 1 << 18 : sh.NO == 3 ? 160000 : 220000)) {
+        if (sh.NO == 2 && own > (K == 2 || nnz <= 320000 ? 96 : 16000000 / nnz)) return false;
+        if (sh.NO == 3 && (own > sh.per_launch || nnz > 60000 * (int64_t)(K * sh.C))) return false;
+        if (sh.NO == 4 && own > 128 * K) return false;
+    }
+    return R > 1 || nnz * sh.NO <= (int64_t(1) << 21);
 }
 
 // One cluster launch at a time on a device: two that each hold part of an XCD
