@@ -47,7 +47,6 @@ namespace {
 
 constexpr int kWaves = kClusterWaves;
 constexpr int kFlagStride = 16;          // u64 per flag: one 128-byte line
-constexpr uint64_t kRegisterTicks = 2000000;  // wall-clock ticks (100 MHz) a cluster waits to fill: 20 ms
 constexpr int kSpinLimit = 1 << 21;      // polls of one flag, about a second
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -781,7 +780,7 @@ __device__ void enroll(const ClusterLaunch& A, const unsigned char* smem, Shared
         const uint64_t t0 = wall_clock64();
         int go = 0;
         while ((go = __hip_atomic_load(ctl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
-            if (wall_clock64() - t0 > kRegisterTicks) {
+            if (wall_clock64() - t0 > A.wait_ticks) {
                 expect = 0;
                 __hip_atomic_compare_exchange_strong(ctl + 1, &expect, 2, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT);

@@ -77,9 +77,16 @@ struct ClusterLaunch {
     const ClusterGroup* groups;  // device; clusters of XCD x are [off[x], off[x + 1])
     int32_t* tickets;            // device [kXcds], zero
     int32_t off[kXcds + 1];
+    uint64_t wait_ticks;         // wall-clock ticks (100 MHz) that a cluster waits to fill
     int32_t shared_off;          // LDS offset of the workgroup variables (set by launch_cluster)
 };
 
+// How long the clusters of a launch of T steps wait to fill beside other work: as
+// long as the solve takes, about, and no longer than 20 ms (a solve of 300 steps
+// beside work that keeps CUs for longer took 24 ms, 20 of them this wait).
+inline uint64_t cluster_wait_ticks(int32_t T) {
+    return (uint64_t)std::min<int64_t>(std::max<int64_t>((int64_t)T * 500, 200000), 2000000);
+}
 // Whether the instance can run as a cluster solve at all, and the sizes that its
 // shape depends on; then the shape for R restarts.
 bool cluster_size(const HostPlan& P, ClusterSize& Z);

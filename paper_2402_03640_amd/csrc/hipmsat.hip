@@ -1654,8 +1654,11 @@ hms_status solve_clusters(std::vector<ClusterItem>& items, hipStream_t s, bool w
             d.resume = 1;
         }
     }
+    int32_t steps = 0;
+    for (const ClusterItem& it : items) steps = std::max(steps, it.p.steps);
     std::vector<hms::ClusterLaunch> L(launches);
     for (int32_t g = 0, k = 0; k < launches; ++k) {
+        L[k].wait_ticks = hms::cluster_wait_ticks(steps);
         L[k].groups = A.at<hms::ClusterGroup>(o_groups);
         L[k].tickets = A.at<int32_t>(o_tick) + (size_t)k * hms::kXcds;
         const int32_t g0 = g;

@@ -2,6 +2,7 @@
 the sizes where the form changes, and what takes over where clusters cannot
 run.  Every result is the tiled solve's, bit for bit."""
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -134,7 +135,6 @@ def test_time_limited_solve_leaves_the_timed_choice():
 def _beside(work, run):
     """run() while another thread repeats work(stream); stops it afterwards."""
     import threading
-    import time
     errors, stop, turns = [], threading.Event(), []
 
     def loop():
@@ -194,8 +194,13 @@ def test_clusters_that_do_not_fill():
     ref = [hm.solve(c, schedule=1, seed=j, **kw) for j, c in enumerate(inst)]
     streams = [torch.cuda.Stream() for _ in range(4)]
 
+    seconds = []
+
     def solves(st):
-        return [hm.solve(c, schedule=hm.CLUSTER, seed=j, stream=st, **kw) for j, c in enumerate(inst)]
+        t0 = time.perf_counter()
+        outs = [hm.solve(c, schedule=hm.CLUSTER, seed=j, stream=st, **kw) for j, c in enumerate(inst)]
+        seconds.append(time.perf_counter() - t0)
+        return outs
 
     def hold(stream, steps=60000):  # 64 workgroups, eight on each XCD; too much LDS for a cluster's beside them
         r = hm.solve(other, steps=steps, restarts=64, eval_every=50, schedule=hm.RESIDENT, stream=stream)
@@ -213,6 +218,9 @@ def test_clusters_that_do_not_fill():
             np.testing.assert_array_equal(out.restart_step, one.restart_step)
             np.testing.assert_array_equal(out.best_assignment, one.best_assignment)
             np.testing.assert_allclose(out.restart_loss, one.restart_loss, rtol=1e-12, atol=0)
+    # each of the two waits no longer than the solve would take (2 ms here), well under a whole 20 ms
+    _say("seconds:", seconds)
+    assert min(seconds[-4:]) < 0.03
     voided = [outs for outs in turns if all(o.schedule != hm.CLUSTER for o in outs)]
     assert voided and all(outs[0].schedule == hm.RESIDENT and outs[1].schedule != hm.RESIDENT for outs in voided)
 
