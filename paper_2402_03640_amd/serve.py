@@ -29,6 +29,8 @@ from . import _lib
 
 # instances at most this large (n + m) are grouped for the resident solver
 SMALL_ROWS = 12000
+# most variables of an instance that the cluster solver runs, and its longest clause
+CLUSTER_VARS, CLUSTER_LITS = 65024, 5
 # instances with more literals run as jobs of their own: one of them keeps the
 # device busy alone, and a job's plans are built one after the other, so a
 # request grouped with a large one would wait for its build and its solve
@@ -38,13 +40,19 @@ GROUP_MAX_LITS = 1 << 21
 def footprint_bytes(n: int, m: int, n_lits: int, restarts: int = 1, weighted: bool = False) -> int:
     """Device bytes of one solve: plan (both sparse layouts, tiles, offsets,
     clause weights) plus per-restart state (x, m, v, t, adjoint, best bytes,
-    heavy partials)."""
+    heavy partials), or plus what the cluster solver builds for a solve it takes
+    (occurrence records, clause entries by slot, exchange buffers), if more."""
     L = max(n_lits, 0)
     # clause-side and variable-side entries and the map between them
     struct = 4 * (3 * L + m + n + 2) + 16 * (m + n) // 64 + 4 * n + 8 * L // 64 + (8 * (m + 64) if weighted else 0)
     state = restarts * (16 * (n + 1) + 4 * (m + 64) + (n + 1) + 8 * L // 64) + 4096
     if restarts == 1:
         state += 4 * L + 4 * L // 8  # occurrence slots of the slot schedule
+    if n <= CLUSTER_VARS and L <= CLUSTER_LITS * m:
+        # record blocks of 8 columns and 64 rows (256 words of bits, 2048 of records, weights beside)
+        block = 4 * (256 + 2048) + (4096 if weighted else 0)
+        cluster = (L // 512 + n // 64 + 1) * block + 4 * L + 20 * n + restarts * (n + 65536 + min(16 * n, 1 << 19))
+        state = max(state, cluster)
     return int(1.25 * (struct + state)) + (1 << 16)
 
 
