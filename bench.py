@@ -45,7 +45,8 @@ def kernel_bytes(n, m, L, R, weighted=False):
 
 def kernels_sha():
     h = hashlib.sha256()
-    for f in ("kernels.hip", "kernels.hpp", "plan.cpp", "plan.hpp", "cluster.hip", "cluster.hpp"):
+    for f in ("kernels.hip", "kernels.hpp", "plan.cpp", "plan.hpp", "cluster.hip", "cluster.hpp",
+              "cluster_shape.hpp"):
         with open(os.path.join(ROOT, "paper_2402_03640_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -159,8 +159,9 @@ typedef struct {
     uint64_t seed;       /* restart r starts from the SplitMix64 stream seeded seed + r */
     float lr, beta1, beta2, eps; /* Adam: PyTorch defaults 0.9 / 0.999 / 1e-8 */
     int32_t loss_mode;   /* HMS_LOSS_UNSAT or HMS_LOSS_ALL */
-    int32_t schedule;    /* 0 = automatic; else table index | rows-per-unit << 8
-                            | backward rows-per-unit << 16 (0 = the same; see hms_tune) */
+    int32_t schedule;    /* 0 = automatic; 255 the resident, 254 the cluster solver; else table
+                            index | rows-per-unit << 8 | backward rows-per-unit << 16 (0 = the
+                            same; see hms_tune) */
     int32_t use_graph;   /* 1 = replay the step body as a HIP graph, 0 = direct launches */
     int32_t autotune;    /* 1 = with schedule 0, time the candidate schedules once per handle,
                             restart count, optimizer and loss mode, and keep the fastest
@@ -169,8 +170,11 @@ typedef struct {
                             else a fixed tiled schedule for R.  Either way a solve of 64 steps
                             or more (256 up to 2^14 nonzeros) that the cluster solver (254: a
                             few workgroups of one XCD per restart, unsat-masked loss, clauses of
-                            at most five literals, at most 63488 variables, no split rows) can
-                            run and is known to run faster takes it without timing */
+                            at most five literals, no split rows, at most 63488 variables in
+                            clauses, 64512 from 9 and 65024 from 17 restarts on) can run and is
+                            known to run faster takes it without timing; where its clusters
+                            cannot assemble beside other work, or an output lies over an
+                            input, the solve runs on what it would take without clusters */
     double time_limit_s; /* > 0: stop at a K-step boundary once exceeded (not reproducible) */
     const float* x0;     /* DEVICE [n][R] initial values, or NULL for SplitMix64 U(-1,1) */
     void* stream;        /* hipStream_t */
@@ -247,7 +251,11 @@ hms_status hms_solve(const hms_cnf* cnf, const hms_solve_params* params, hms_sol
  * params->stream with HIP events `iters` back-to-back launches of the forward
  * kernel (scores, mask, adjoint), then of the backward kernels (transposed sums
  * and fused optimizer step), then of whole steps.  Outputs are the average
- * milliseconds per launch (any may be NULL).  The relaxed state keeps moving
+ * milliseconds per launch (any may be NULL).  Schedule 0 is the choice that a
+ * solve has without clusters; a solver whose whole loop is one launch (255, 254)
+ * has a step time only (0 for the others), with a count every eval_every;
+ * 254 waits for other cluster solves on
+ * the device, and is HMS_ERR_DEVICE where its clusters do not assemble.  The relaxed state keeps moving
  * during the measurement; nothing is returned from it.
  */
 hms_status hms_time_kernels(const hms_cnf* cnf, const hms_solve_params* params, int32_t iters,
@@ -279,8 +287,10 @@ hms_status hms_solve_batch(const hms_cnf* const* cnfs, const hms_solve_params* p
  * params->restarts restarts, times the forward and the backward pass at each
  * rows-per-unit value (`iters` launches each, HIP events on params->stream)
  * and pairs the fastest of each; then times whole steps of those pairs and
- * of the resident solver, and records the fastest for this handle (and its
- * size class); later solves with schedule 0 use it.  The choice changes speed only: results are bitwise the same under
+ * of the resident and the cluster solver, and records the fastest for this
+ * handle (and its size class), next to the fastest but for the cluster solver;
+ * later solves with schedule 0 use it (clusters: from so many steps on that make
+ * up for building their records).  The choice changes speed only: results are bitwise the same under
  * every schedule.  Outputs the chosen schedule id and its time per step.
  */
 hms_status hms_tune(const hms_cnf* cnf, const hms_solve_params* params, int32_t iters, int32_t* schedule,

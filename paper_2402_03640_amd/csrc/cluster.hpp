@@ -1,8 +1,9 @@
 // Cluster solver: the whole Algorithm 1 loop of one (instance, restart) runs
 // in C workgroups on the CUs of one XCD, with the relaxed values of every
-// variable (in the wide form: their roundings) in each workgroup's LDS.  Used where the state of an instance fits
-// LDS but one workgroup is too slow and the tiled kernels are bound by launch
-// latency or by the fabric traffic of their gathers.
+// variable (in the wide form: their roundings) in each workgroup's LDS.  Used
+// where the state of an instance fits LDS but one workgroup is too slow and the
+// tiled kernels are bound by launch latency or by the fabric traffic of their
+// gathers.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -66,7 +67,7 @@ struct ClusterGroup {
                        // {t, step}, zero before the launch; kClusterWide: [2][C * slice + 64] by
                        // position, then [2][C * slice / 64] words of roundings)
     uint64_t* flags;   // [C] 128-byte lines, by step parity: step number | partial count << 32
-                       // (kClusterOneWords: [4][up to 14 C], by step, one word per counting wavefront);
+                       // (kClusterOneWords: [4][up to 15 C], by step, one word per counting wavefront);
                        // zero before the launch
     double* losses;    // [2][C] partial losses, by step parity (kClusterOneWords: [4][C])
     int32_t* ctl;      // [0] arrived, [1] decision, [2] a bounded wait ran out

@@ -1854,12 +1854,12 @@ hms_status read_result(const hms_cnf* cnf, const SolveSetup& Z, int32_t done, fl
         HIPTRY(hms::launch_extract(P.n, sh.B, br, cnf->var_old, S.best_a, S.out_assign, s));
         HIPTRY(hipMemcpyAsync(res->best_assignment, S.out_assign, P.n, hipMemcpyDeviceToHost, s));
     }
-    if (res->x_final) HIPTRY(hms::launch_scatter(P.n, P.n, sh.B, cnf->var_old, S.x, res->x_final, s));
+    if (res->x_final) HIPTRY(hms::launch_scatter(P.n, sh.B, cnf->var_old, S.x, res->x_final, s));
     if (so) {
-        HIPTRY(hms::launch_scatter(P.n, P.n, sh.B, cnf->var_old, S.x, so->x, s));
+        HIPTRY(hms::launch_scatter(P.n, sh.B, cnf->var_old, S.x, so->x, s));
         if (S.m) {
-            HIPTRY(hms::launch_scatter(P.n, P.n, sh.B, cnf->var_old, S.m, so->m, s));
-            HIPTRY(hms::launch_scatter(P.n, P.n, sh.B, cnf->var_old, S.v, so->v, s));
+            HIPTRY(hms::launch_scatter(P.n, sh.B, cnf->var_old, S.m, so->m, s));
+            HIPTRY(hms::launch_scatter(P.n, sh.B, cnf->var_old, S.v, so->v, s));
         }
         HIPTRY(hms::launch_scatter_bytes(P.n, sh.B, cnf->var_old, S.best_a, so->best_assignment, s));
     }

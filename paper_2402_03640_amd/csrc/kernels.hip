@@ -1202,15 +1202,13 @@ __global__ __launch_bounds__(256) void k_scatter_bytes(int32_t n, Blocking B, co
     dst[(size_t)r * n + var_old[i]] = src[boff(B, B.rows_x, i, r)];
 }
 
-__global__ __launch_bounds__(256) void k_scatter(int32_t n, int32_t n_act, Blocking B, const int32_t* var_old,
-                                                  const float* src, float* dst, const float* scale) {
+__global__ __launch_bounds__(256) void k_scatter(int32_t n, Blocking B, const int32_t* var_old, const float* src,
+                                                  float* dst) {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (int64_t)n * B.R) return;
     const int32_t i = (int32_t)(idx / B.R);
     const int32_t r = (int32_t)(idx % B.R);
-    float v = i < n_act ? src[boff(B, B.rows_x, i, r)] : 0.0f;
-    if (scale != nullptr) v = scale[r] * v;
-    dst[(size_t)var_old[i] * B.R + r] = v;
+    dst[(size_t)var_old[i] * B.R + r] = src[boff(B, B.rows_x, i, r)];
 }
 
 template <int P, int V, int UR, int MASK, int CB = kChunkB>
@@ -1481,12 +1479,11 @@ hipError_t launch_scatter_bytes(int32_t n, const Blocking& B, const int32_t* var
     return hipGetLastError();
 }
 
-hipError_t launch_scatter(int32_t n, int32_t n_act, const Blocking& B, const int32_t* var_old, const float* src,
-                          float* dst, hipStream_t s, const float* scale) {
+hipError_t launch_scatter(int32_t n, const Blocking& B, const int32_t* var_old, const float* src, float* dst,
+                          hipStream_t s) {
     const int64_t total = (int64_t)n * B.R;
     if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scatter, dim3((int)((total + 255) / 256)), dim3(256), 0, s, n, n_act, B, var_old, src,
-                       dst, scale);
+    hipLaunchKernelGGL(k_scatter, dim3((int)((total + 255) / 256)), dim3(256), 0, s, n, B, var_old, src, dst);
     return hipGetLastError();
 }
 

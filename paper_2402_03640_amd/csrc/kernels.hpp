@@ -241,8 +241,8 @@ hipError_t launch_extract(int32_t n, const Blocking& B, int32_t r, const int32_t
 // best rounded iterate in caller order, one row per restart).
 hipError_t launch_scatter_bytes(int32_t n, const Blocking& B, const int32_t* var_old, const uint8_t* src,
                                 uint8_t* dst, hipStream_t s);
-// dst[var_old[i]][r] = scale[r] * src(i, r) (scale may be null: 1), 0 for inactive variables.
-hipError_t launch_scatter(int32_t n, int32_t n_act, const Blocking& B, const int32_t* var_old, const float* src,
-                          float* dst, hipStream_t s, const float* scale = nullptr);
+// dst[var_old[i]][r] = src(i, r).
+hipError_t launch_scatter(int32_t n, const Blocking& B, const int32_t* var_old, const float* src, float* dst,
+                          hipStream_t s);
 
 }  // namespace hms
