@@ -187,14 +187,15 @@ struct Shape {
 // work unit U (0 = the default for that entry), bits 16..23 = rows per work
 // unit of the backward pass (0 = U).  The bitset variants apply to
 // the unsat-masked loss; elsewhere they fall back to their unmasked twin (same
-// arithmetic).
+// arithmetic).  `automatic`: the table entry to take for an automatic choice in
+// place of the rule's.
 hms_status make_shape(const hms::HostPlan& P, int32_t R, int32_t req, int loss_mode, Shape& sh,
-                      bool allow_mask = true, bool allow_slot = true) {
+                      bool allow_mask = true, bool allow_slot = true, int automatic = 0) {
     const int idx = req & 0xff;
     int U = (req >> 8) & 0xff;
     int Ub = (req >> 16) & 0xff;
     if (req < 0 || (req >> 24) != 0 || idx > hms::kNumSchedules) return fail(HMS_ERR_ARG, "unknown schedule id");
-    sh.sched = idx == 0 ? auto_schedule(R, loss_mode, P) : idx;
+    sh.sched = idx != 0 ? idx : automatic != 0 ? automatic : auto_schedule(R, loss_mode, P);
     if (hms::kSchedules[sh.sched].mask && (loss_mode != HMS_LOSS_UNSAT || !allow_mask))
         sh.sched = hms::kSchedules[sh.sched].twin;
     // slot schedules: one restart, the unsat-masked loss, and a plan with the
@@ -2631,6 +2632,22 @@ hms_status eval_relaxed_impl(const hms_cnf* cnf, const float* x, int32_t R, int3
     Layout lay;
     size_t off[kOffN];
     layout_state(P, sh, false, want_g, false, lay, off);
+    if (lay.off > kScratchBytes && R > 32 && R % 4 != 0) {
+        // smaller groups pad the restarts less (34 to 48 instead of 64): taken where
+        // only they fit the fixed workspace, with and without allocation, so that both
+        // add the loss in the same order
+        Shape less;
+        Layout lay2;
+        size_t off2[kOffN];
+        rc = make_shape(P, R, 0, loss_mode, less, true, false, R % 2 == 0 ? 35 : 6);
+        if (rc) return rc;
+        layout_state(P, less, false, want_g, false, lay2, off2);
+        if (lay2.off <= kScratchBytes) {
+            sh = less;
+            lay = lay2;
+            std::copy(off2, off2 + kOffN, off);
+        }
+    }
     if (fixed && lay.off > cap)
         return fail(HMS_ERR_TOO_LARGE, "this evaluation needs " + std::to_string(lay.off) +
                                            " bytes of workspace, more than the " + std::to_string(cap) +

@@ -110,7 +110,9 @@ def test_results_with_more_points_than_the_pinned_memory():
 # more points than the pinned memory holds (512); the last sizes of the one-launch route and the first past it (6 or,
 # up to 512 points, 12 times 2^16 values of x; 256 tiles of clauses); no clause at all
 NOALLOC = [(40, 170, 512), (40, 170, 513), (128, 200, 3072), (128, 200, 3073), (640, 2700, 614), (640, 2700, 615),
-           (1536, 6450, 512), (1537, 6450, 512), (3900, 16384, 3), (3900, 16385, 3), (40, 0, 515)]
+           (1536, 6450, 512), (1537, 6450, 512), (3900, 16384, 3), (3900, 16385, 3), (40, 0, 515),
+           # the fixed workspace holds them only with fewer restarts per group
+           (40000, 176000, 34), (40000, 176000, 33)]
 
 
 @pytest.mark.parametrize("n,m,R", NOALLOC)
