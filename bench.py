@@ -72,6 +72,21 @@ def traffic_record(config, schedule, kernel_key):
     return None if not k else round(k["hbm_bytes_per_launch"])
 
 
+def cluster_record(config, restarts):
+    """Vector instructions and busy cycles of a CU per gradient step from the
+    committed counter run of the cluster solver (profiles/cluster_counters.json),
+    if it was taken on the current kernel sources; None otherwise."""
+    try:
+        with open(os.path.join(ROOT, "profiles", "cluster_counters.json")) as fh:
+            rec = json.load(fh)
+    except (OSError, ValueError):
+        return None
+    c = rec.get("configs", {}).get(config)
+    if rec.get("kernels_sha") != kernels_sha() or not c or c["restarts"] != restarts:
+        return None
+    return c
+
+
 def counters_summary(dirs):
     """Summarise rocprofv3 counter runs of ``--kernels-only``.
 
@@ -729,17 +744,22 @@ def main():
     log(f"[bench] kernels: fwd {fwd_ms*1e3:.2f} us, bwd {bwd_ms*1e3:.2f} us, step {step_ms*1e3:.2f} us")
     if code == hm.CLUSTER:
         # cluster solver: one launch holds the whole loop, with the state in LDS
-        # and the formula in each XCD's L2.  The algorithmic bytes of a step
-        # (index arrays once, state per restart) against its time: a rate to
-        # compare schedules by, not HBM traffic.  The time is the timed solves'
+        # and the formula in each XCD's L2, so HBM bytes do not bound it.  What
+        # does with every CU in use is the issue of vector instructions, one per
+        # CU and cycle: their count and the CU's busy cycles per step come from
+        # the committed counter run, the time from the timed solves
         # (time_kernels counts every iterate of a one-launch schedule)
         step_ms = sum(dev_ms) / len(dev_ms) / T
-        achieved = (fb + bb) / (step_ms * 1e-3) / 1e9
-        roof = {"bound": "vector instructions (state on chip)", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
-                "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": None,
-                "note": "algorithmic bytes over time, not HBM traffic: the state never leaves the chip",
+        roof = {"bound": "on chip (not counted)", "unit": "vector instructions per ns and CU in use", "traffic": None,
+                "achieved": None, "peak": None, "frac": None,
                 "kernel": "cluster (whole loop in one launch; figures per gradient step)",
                 "algorithmic_bytes_per_launch": fb + bb, "avg_launch_us": round(step_ms * 1e3, 3)}
+        cnt = cluster_record(wl["name"], R)
+        if cnt:
+            roof["bound"] = cnt["bound"]
+            roof["achieved"] = round(cnt["valu_per_cu_step"] / (step_ms * 1e6), 3)
+            roof["frac"] = round(cnt["valu_per_cu_step"] / cnt["busy_cycles_per_cu_step"], 4)
+            roof["peak"] = round(cnt["busy_cycles_per_cu_step"] / (step_ms * 1e6), 3)
     elif fwd_ms <= 0 or bwd_ms <= 0:
         # resident schedule: the whole loop is one launch with the state in LDS;
         # per-kernel HBM bytes do not describe it
@@ -764,9 +784,9 @@ def main():
     copy_gbps = copy_bandwidth()
     log(f"[bench] device copy (project kernel): {copy_gbps:.0f} GB/s (read + write)")
     floors = None
-    if roof is not None:
+    if roof is not None and code != hm.CLUSTER:
         roof["frac_of_copy"] = round(roof["achieved"] / copy_gbps, 4)
-        if wl["uniform"] and code != hm.CLUSTER:
+        if wl["uniform"]:
             floors = pattern_floors(n, m, L, R, copy_gbps)
             roof["pattern_floor_us"] = floors[key]["floor_us"]
             roof["frac_of_pattern_floor"] = round(floors[key]["floor_us"] / roof["avg_launch_us"], 4)
