@@ -795,13 +795,14 @@ __device__ void enroll(const ClusterLaunch& A, const unsigned char* smem, Shared
 }
 
 // Several variable tiles per wavefront, state in LDS.  3-CNF n = 20000, 64
-// restarts: 11.6 us a step, bound by vector instructions (24500 of a CU's 27800
+// restarts: 11.7 us a step, bound by vector instructions (24460 in a CU's 27600
 // cycles a step; without the optimizer's 130 per tile 9.2 us, without copying
 // t 11.4, with the records always the same 11.8 where all takes 11.9).  A record
 // costs 17 of them.  Taking 16-bit slots out with one instruction each
 // (sub-dword addressing) saves one and gains nothing: it issues at half rate.
 //
-// WIDE: for more variables than t fits LDS for (n past 31744).  LDS holds the roundings, a bit each, which decide for every
+// WIDE: for more variables than t fits LDS for (past 30720 with 32 workgroups,
+// 31744 with 16).  LDS holds the roundings, a bit each, which decide for every
 // record whether its clause is unsatisfied; t itself is gathered from the L2
 // only in the lanes (a tenth or so) where it is.  An iteration exchanges the
 // bits, not t.  Bound by the latency of those gathers and the stream of records
