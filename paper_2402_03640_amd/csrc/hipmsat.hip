@@ -21,10 +21,12 @@
 #include "small.hpp"
 
 // A timed choice: the fastest schedule, and the fastest but for the cluster
-// solver, which takes over where clusters cannot run a solve.
+// solver and of the tiled ones alone, which take over where the first cannot run
+// a solve.
 struct Tuned {
-    int32_t best = 0, other = 0;
+    int32_t best = 0, other = 0, tiled = 0;
     int32_t from = 0;  // the cluster solver is the fastest from so many steps on
+    double best_ms = 1e300, tiled_ms = 1e300;
 };
 
 struct hms_cnf {
@@ -984,10 +986,13 @@ hms_status time_split(const hms_cnf* cnf, const hms_solve_params* p0, int32_t co
 // take their fastest rows per unit (timed apart), then whole steps of each
 // entry's pair are timed against each other (and the resident solver).  Without
 // `clusters` (they cannot run now) the cluster solver is not timed: it stays the
-// choice where it is known to be the faster one.
-hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, Tuned& pick, double& best_ms,
-                bool clusters = true) {
-    best_ms = 1e300;
+// choice where it is known to be the faster one.  A time limit or a cancel flag
+// is the solve's own and not the choice's: everything is timed without them.
+hms_status tune(const hms_cnf* cnf, const hms_solve_params* p0, int32_t iters, Tuned& pick, bool clusters = true) {
+    hms_solve_params pr = *p0;
+    pr.time_limit_s = 0;
+    pr.cancel = nullptr;
+    const hms_solve_params* p = &pr;
     double other_ms = 1e300, cluster_ms = 1e300, build_ms = 1e300;
     bool ran = true;  // the clusters could be timed
     struct Pick {
@@ -1053,9 +1058,13 @@ hms_status tune(const hms_cnf* cnf, const hms_solve_params* p, int32_t iters, Tu
         return c != kResidentId && c != kClusterId && ((c >> 16) & 0xff) == ((c >> 8) & 0xff) ? c & 0xffff : c;
     };
     for (const auto& tc : timed) {
-        if (tc.first < best_ms) {
-            best_ms = tc.first;
+        if (tc.first < pick.best_ms) {
+            pick.best_ms = tc.first;
             pick.best = canonical(tc.second);
+        }
+        if (tc.second != kClusterId && tc.second != kResidentId && tc.first < pick.tiled_ms) {
+            pick.tiled_ms = tc.first;
+            pick.tiled = canonical(tc.second);
         }
         if (tc.second == kClusterId) {
             cluster_ms = tc.first;
@@ -1091,20 +1100,21 @@ hms_status resolve_schedule(const hms_cnf* cnf, const hms_solve_params* p, int32
     code = p->schedule;
     if (code != 0) return HMS_OK;
     // the resident and the cluster solver cannot honour a time limit or a
-    // cancel flag: a solve that asks for one takes the tiled choice below
-    // instead (as one whose size class was tuned on an instance that fits them
-    // when it does not)
+    // cancel flag: a solve that asks for one takes the tiled choice instead (as
+    // one whose size class was tuned on an instance that fits them when it does
+    // not)
     auto take = [&](const Tuned& t) {
         const bool now = clusters && p->steps >= t.from && cluster_ok(cnf, p);
-        const int32_t c = t.best == kClusterId && !now ? t.other : t.best;
-        if (c == 0 || (c == kResidentId && !resident_ok(cnf, p))) return false;
-        code = c;
-        return true;
+        code = t.best == kClusterId && !now ? t.other : t.best;
+        if (code == kResidentId && !resident_ok(cnf, p)) code = t.tiled;
     };
     {
         std::lock_guard<std::mutex> lk(cnf->tune_mu);
         auto it = cnf->tuned.find(tune_key(p));
-        if (it != cnf->tuned.end() && take(it->second)) return HMS_OK;
+        if (it != cnf->tuned.end()) {
+            take(it->second);
+            return HMS_OK;
+        }
     }
     if (clusters && cluster_preferred(cnf, p)) {  // no timing needed: ahead of every other schedule where it runs
         code = kClusterId;
@@ -1113,17 +1123,19 @@ hms_status resolve_schedule(const hms_cnf* cnf, const hms_solve_params* p, int32
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(class_key(cnf, p));
-        if (it != g_tuned.end() && take(it->second)) return HMS_OK;
+        if (it != g_tuned.end()) {
+            take(it->second);
+            return HMS_OK;
+        }
     }
     if (!p->autotune || (double)cnf->plan.nnz * p->restarts < (double)(1 << 18)) {
         if (resident_preferred(cnf, p)) code = kResidentId;  // small: launch latency dominates
         return HMS_OK;
     }
-    double ms = 0;
     Tuned t;
-    hms_status rc = tune(cnf, p, 6, t, ms, clusters);
+    hms_status rc = tune(cnf, p, 6, t, clusters);
     if (rc) return rc;
-    code = t.best == kClusterId && (!clusters || p->steps < t.from) ? t.other : t.best;
+    take(t);
     return HMS_OK;
 }
 
@@ -2563,12 +2575,14 @@ hms_status hms_tune(const hms_cnf* cnf, const hms_solve_params* params, int32_t 
     g_err.clear();
     if (check_cnf(cnf) || !params || iters < 1) return fail(HMS_ERR_ARG, "null argument or iters < 1");
     DeviceGuard dg(cnf->device);
-    Tuned best;
-    double ms = 0;
-    hms_status rc = tune(cnf, params, iters, best, ms);
+    Tuned t;
+    hms_status rc = tune(cnf, params, iters, t);
     if (rc) return rc;
-    if (schedule) *schedule = best.best;
-    if (step_ms) *step_ms = ms;
+    // a schedule that these parameters can be solved with
+    const bool watched = params->time_limit_s > 0 || params->cancel != nullptr;
+    const bool tiled = watched && (t.best == kClusterId || t.best == kResidentId);
+    if (schedule) *schedule = tiled ? t.tiled : t.best;
+    if (step_ms) *step_ms = tiled ? t.tiled_ms : t.best_ms;
     return HMS_OK;
 }
 

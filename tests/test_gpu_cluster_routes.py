@@ -318,3 +318,23 @@ def test_untimed_choice_by_counting_period(n, k, ratio, R, K, clusters):
     out = hm.solve(cnf, steps=64, restarts=R, eval_every=K, optimizer=hm.SGD, autotune=False)
     assert (out.schedule == hm.CLUSTER) == clusters
     cnf.free()
+
+
+def test_watched_solves_and_the_timed_choice():
+    """A time limit or a cancel flag keeps a solve off the one-launch solvers, but
+    not later solves of the handle: not when it is the first and times the
+    schedules, nor where the resident solver is next to clusters."""
+    cnf = _cnf(8000, ratio=4.2, seed=9)
+    kw = dict(steps=300, restarts=7, eval_every=10)
+    first = hm.solve(cnf, cancel=hm.CancelFlag(), **kw)
+    assert first.schedule not in (hm.CLUSTER, hm.RESIDENT)
+    assert hm.solve(cnf, **kw).schedule == hm.CLUSTER
+    assert hm.solve(cnf, time_limit_s=100.0, **kw).schedule == first.schedule
+    small = _cnf(2400, ratio=4.2, seed=9)
+    kw = dict(steps=300, restarts=13, eval_every=1)
+    best = hm.tune(small, restarts=13)[0]
+    first = hm.solve(small, time_limit_s=100.0, **kw)
+    assert first.schedule not in (hm.CLUSTER, hm.RESIDENT)
+    assert hm.solve(small, **kw).schedule == best
+    assert hm.solve(small, time_limit_s=100.0, **kw).schedule == first.schedule
+    assert best in (hm.CLUSTER, hm.RESIDENT)
