@@ -18,6 +18,7 @@ namespace hms {
 
 constexpr int kClusterMaxK = 5;       // longest clause
 constexpr int32_t kClusterMaxT = 1 << 20;
+constexpr int32_t kClusterMaxR = 1 << 20;  // restarts: the host holds a record of each
 
 // One instance of a cluster launch (device-visible).
 struct ClusterDesc {

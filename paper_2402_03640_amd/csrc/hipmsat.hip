@@ -1393,7 +1393,7 @@ bool cluster_fits(const hms_cnf* cnf, const hms_solve_params* p, hms::ClusterSha
         !std::isfinite(p->beta2) || !std::isfinite(p->eps))
         return false;
     return p->loss_mode == HMS_LOSS_UNSAT && p->time_limit_s <= 0 && p->cancel == nullptr && p->restarts >= 1 &&
-           p->steps >= 0 && p->eval_every >= 1 && p->steps <= hms::kClusterMaxT && cluster_device(cnf->device) &&
+           p->restarts <= hms::kClusterMaxR && p->steps >= 0 && p->eval_every >= 1 && p->steps <= hms::kClusterMaxT && cluster_device(cnf->device) &&
            hms::cluster_shape(cnf->plan, p->restarts, cluster_lds_cap(cnf->device), sh);
 }
 
@@ -1498,9 +1498,9 @@ struct ClusterItem {
 // Runs instances of one kernel form (literals per clause, weights, mode) as
 // clusters, in as few launches as hold them.  An item keeps ran = false (all do
 // when the device was taken by another cluster solve and the caller does not
-// wait for it, or the forms differ) when its clusters could not assemble: what
-// is in its outputs is then to be overwritten by the schedule that the caller
-// takes instead.
+// wait for it, memory is short, or the forms differ) when its clusters could not
+// assemble: what is in its outputs is then to be overwritten by the schedule
+// that the caller takes instead.
 hms_status solve_clusters(std::vector<ClusterItem>& items, hipStream_t s, bool wait = false) {
     const int dev = items[0].cnf->device;
     const hms::ClusterShape& sh0 = items[0].sh;
@@ -1593,7 +1593,11 @@ hms_status solve_clusters(std::vector<ClusterItem>& items, hipStream_t s, bool w
     }
     Arena A;
     A.s = s;
-    HIPTRY(hipMallocAsync((void**)&A.base, lay.off, s));
+    if (const hipError_t e = hipMallocAsync((void**)&A.base, lay.off, s)) {
+        if (e != hipErrorOutOfMemory) HIPTRY(e);
+        (void)hipGetLastError();  // no room for the records: another schedule may need less
+        return HMS_OK;
+    }
     host.resize(back);
     for (int32_t i = 0; i < count; ++i) {
         const ClusterItem& it = items[i];

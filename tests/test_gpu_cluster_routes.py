@@ -338,3 +338,20 @@ def test_watched_solves_and_the_timed_choice():
     assert hm.solve(small, **kw).schedule == best
     assert hm.solve(small, time_limit_s=100.0, **kw).schedule == first.schedule
     assert best in (hm.CLUSTER, hm.RESIDENT)
+
+
+def test_more_restarts_than_memory_is_an_error():
+    """A restart count that nothing can hold is refused at once, not listed on the
+    host first."""
+    import ctypes as C
+
+    from paper_2402_03640_amd import _lib
+    cnf = _cnf(9000, ratio=4.2)
+    p = _lib._params(cnf, 300, 1 << 30, 50, 0, hm.SGD, 1e-2, 0.9, 0.999, 1e-8, hm.LOSS_UNSAT, 0, False, 0.0, None, None,
+                     False)
+    res = _lib.SolveResult()
+    t0 = time.perf_counter()
+    with pytest.raises(hm.HipMsatError):
+        _lib._check(_lib.lib().hms_solve(cnf.handle, C.byref(p), C.byref(res)))
+    assert time.perf_counter() - t0 < 10
+    assert hm.solve(cnf, steps=300, eval_every=50, optimizer=hm.SGD, autotune=False).schedule == hm.CLUSTER
