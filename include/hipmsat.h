@@ -266,10 +266,12 @@ hms_status hms_time_kernels(const hms_cnf* cnf, const hms_solve_params* params, 
  * cnfs[i] with params[i] into results[i] (statuses[i], may be NULL, receives each
  * instance's status).  Instances that request the cluster solver, or leave the
  * schedule automatic where it is the better choice, share launches as clusters
- * when they have the same longest clause and all or none weights; those that
- * request the resident solver, or leave
- * the schedule automatic and fit it with at most 2^15 nonzeros (2^16 when
- * eval_every is 1), share launches, one workgroup per (instance, restart).  The others are grouped by restarts,
+ * when they have the same longest clause, all or none weights and the same form
+ * (the values of all variables in LDS, or past some 31000 variables their
+ * roundings alone); those that request the resident solver, or leave the schedule
+ * automatic and fit it with at most 2^15 nonzeros (2^16 when eval_every is 1),
+ * share launches, one workgroup per (instance, restart).  Instances whose
+ * clusters do not run go on to these or to the others, which are grouped by restarts,
  * steps, eval_every, optimizer, loss mode and requested schedule: each step of
  * a group is one launch per kernel over all its instances (a work queue of
  * (instance, work unit) items, replayed as a HIP graph), with the schedule of

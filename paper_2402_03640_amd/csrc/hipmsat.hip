@@ -1418,7 +1418,13 @@ int32_t cluster_least_steps(const hms_cnf* cnf) { return cnf->plan.nnz <= (int64
 //     5.3 against 7.9 / 7.8, 25800: 9.4 / 8.7 against 7.7 / 7.7);
 //   - as long as the resident solver is the other choice, only with all
 //     restarts in one launch (256 restarts: 2.7 against 4.7 at 5805 nonzeros,
-//     6.1 against 9.5 at 20640);
+//     6.1 against 9.5 at 20640; counted every step, where it is the choice up to
+//     2^16 nonzeros, 4-CNF n = 3000: 200 restarts 16.5 against 23.5, 128 restarts
+//     16.4 against 11.9), and counted every step with more than 64, which leave a
+//     restart two workgroups, not with 13 to 16 tiles and few nonzeros (100
+//     restarts, resident against clusters: mixed n = 1000 3.7 against 4.5, n = 1150
+//     6.9 against 4.3; 3-CNF n = 700 level, n = 1000 a sixth less, n = 1200 6.9
+//     against 4.5);
 //   - with one restart only one XCD works, and the others' share of the
 //     tiled kernels wins again past 2^21 record terms (nonzeros times other
 //     literals per clause; 3-CNF n = 28000: 4.6 against 7.1; 4-CNF n = 16000:
@@ -1461,12 +1467,13 @@ bool cluster_preferred(const hms_cnf* cnf, const hms_solve_params* p, int64_t to
     if (nnz < 5000 || p->steps < cluster_least_steps(cnf) || !cluster_fits(cnf, p, sh)) return false;
     if (nnz < 1000 * (sh.NO >= 4 ? 24 : sh.NO == 3 ? 7 : 5)) return false;
     const int64_t R = std::max<int64_t>(together, p->restarts);
-    if (nnz <= kResidentNnz && R > hms::kXcds * hms::kXcdCus / 2) return false;
-    if (nnz <= kResidentNnz && R > p->restarts &&
-        !hms::cluster_shape(cnf->plan, (int32_t)R, cluster_lds_cap(cnf->device), sh))
-        return false;
-    if (nnz <= kResidentNnz && R > sh.per_launch) return false;
     const int32_t own = p->restarts, K = p->eval_every;
+    if (nnz <= kResidentNnz || resident_preferred(cnf, p)) {
+        if (R > hms::kXcds * hms::kXcdCus / 2) return false;
+        if (R > own && !hms::cluster_shape(cnf->plan, (int32_t)R, cluster_lds_cap(cnf->device), sh)) return false;
+        if (R > sh.per_launch) return false;
+        if (K == 1 && R > 64 && nnz <= 13500 && cnf->plan.v_tiles > 12) return false;
+    }
     if (sh.mode == hms::kClusterWide) {
         int32_t most = 16;
         if (sh.NO == 2 && K >= (nnz <= 500000 ? 2 : 4)) most = K < 16 || nnz > 600000 ? 32 : 64;

@@ -308,14 +308,17 @@ def test_untimed_schedule_of_several_restarts(n, m, k, R, entry):
 PERIODS = [(28000, 3, 4.3, 44, 1, True), (28000, 3, 4.3, 64, 1, False), (28000, 3, 4.3, 64, 2, True),
            (20000, 3, 4.3, 256, 1, True), (20000, 4, 5.0, 32, 1, True), (20000, 4, 5.0, 64, 1, False),
            (20000, 4, 5.0, 64, 2, True), (22000, 5, 4.0, 129, 1, False), (34000, 3, 4.2, 17, 1, False),
-           (34000, 3, 4.2, 17, 4, True), (34000, 3, 4.2, 33, 4, False), (34000, 3, 4.2, 33, 16, True)]
+           (34000, 3, 4.2, 17, 4, True), (34000, 3, 4.2, 33, 4, False), (34000, 3, 4.2, 33, 16, True),
+           (3000, 4, 5.0, 128, 1, True), (3000, 4, 5.0, 129, 1, False), (3000, 4, 5.0, 129, 4, True),
+           (1000, 3, 4.3, 64, 1, True), (1000, 3, 4.3, 65, 1, False), (1000, 3, 4.3, 65, 2, True),
+           (1200, 3, 4.3, 65, 1, True)]
 
 
 @pytest.mark.parametrize("n,k,ratio,R,K,clusters", PERIODS)
 def test_untimed_choice_by_counting_period(n, k, ratio, R, K, clusters):
     cnf = hm.load_cnf(n, cnfgen.uniform_kcnf(n, int(n * ratio), k, seed=1))
     assert cnf.info["n_heavy"] == 0
-    out = hm.solve(cnf, steps=64, restarts=R, eval_every=K, optimizer=hm.SGD, autotune=False)
+    out = hm.solve(cnf, steps=256, restarts=R, eval_every=K, optimizer=hm.SGD, autotune=False)
     assert (out.schedule == hm.CLUSTER) == clusters
     cnf.free()
 
