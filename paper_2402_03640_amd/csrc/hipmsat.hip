@@ -294,8 +294,9 @@ int32_t reduce_chunks(int64_t n_units, int32_t R) {
 
 int32_t umask_words(const hms::HostPlan& P) { return P.c_tiles * 2 + 1; }
 
+// `adjoint`: false where the caller's memory takes the clause adjoints.
 void layout_state(const hms::HostPlan& P, const Shape& sh, bool moments, bool grad, bool best, Layout& L,
-                  size_t off[kOffN]) {
+                  size_t off[kOffN], bool adjoint = true) {
     const int32_t R = sh.B.R;
     const size_t Rp = (size_t)sh.B.RG * sh.B.G;  // padded restart count of the blocked layout
     const size_t nR = (size_t)sh.B.rows_x * Rp;
@@ -303,7 +304,7 @@ void layout_state(const hms::HostPlan& P, const Shape& sh, bool moments, bool gr
     off[kOffM] = moments ? L.add(nR * 4) : 0;
     off[kOffV] = moments ? L.add(nR * 4) : 0;
     off[kOffT] = L.add(nR * 4);
-    off[kOffA] = L.add((size_t)sh.B.rows_a * Rp * 4);
+    off[kOffA] = adjoint ? L.add((size_t)sh.B.rows_a * Rp * 4) : 0;
     off[kOffG] = grad ? L.add(nR * 4) : 0;
     off[kOffSeg] = L.add((size_t)sh.B.rows_seg * Rp * 8);
     off[kOffCnt] = L.add((size_t)std::max<int64_t>(sh.n_tc, 1) * R * 8);
@@ -2836,7 +2837,7 @@ hms_status hms_forward(const hms_cnf* cnf, const float* x, int32_t R, int32_t lo
     if (rc) return rc;
     Layout lay;
     size_t off[kOffN];
-    layout_state(P, sh, false, false, false, lay, off);
+    layout_state(P, sh, false, false, false, lay, off, adjoint == nullptr);
     Arena A;
     A.s = s;
     HIPTRY(hipMallocAsync((void**)&A.base, lay.off, s));
@@ -2866,13 +2867,15 @@ hms_status hms_backward(const hms_cnf* cnf, const float* x, int32_t R, int32_t l
     Shape sh;
     hms_status rc = adjoint_shape(cnf, R, loss_mode, sh);
     if (rc) return rc;
+    // gradients that would overwrite points still to be read go by way of the workspace
+    const bool partly = grad_x != x && grad_x < x + (size_t)P.n * R && x < grad_x + (size_t)P.n * R;
     Layout lay;
     size_t off[kOffN];
-    layout_state(P, sh, false, true, false, lay, off);
+    layout_state(P, sh, false, partly, false, lay, off, adjoint == nullptr);
     Arena A;
     A.s = s;
     HIPTRY(hipMallocAsync((void**)&A.base, lay.off, s));
-    State S = bind_state(A, off, false, true, false);
+    State S = bind_state(A, off, false, partly, false);
     if (adjoint) S.a = const_cast<float*>(static_cast<const float*>(adjoint));
     Launch L = make_launch(cnf, sh, S, hms::kGrad, loss_mode, 0.f, 0.9f, 0.999f, 1e-8f);
     if (!adjoint) {  // recompute the scores
@@ -2882,8 +2885,6 @@ hms_status hms_backward(const hms_cnf* cnf, const float* x, int32_t R, int32_t l
         HIPTRY(hms::launch_points(ia, s));
         HIPTRY(hms::launch_fwd(sh.sched, false, L.fa, sh.fwd_blocks, s));
     }
-    // gradients that would overwrite points still to be read go by way of the workspace
-    const bool partly = grad_x != x && grad_x < x + (size_t)P.n * R && x < grad_x + (size_t)P.n * R;
     float* g = partly ? S.g : grad_x;
     HIPTRY(hms::launch_grad_zero(P.n, P.n_act, R, cnf->var_old, grad_loss, g, s));
     set_grad(L.ba, x, grad_loss, g);
